@@ -239,8 +239,9 @@ int ssm_block_multistep(const ssmv_dims *dims, const ssmv_cache *cache, const ss
 /* Prefill: all L prompt tokens of every sequence through the layer (Section 2.1 Eq. 1 with the
  * discretisation of Section 2.2, evaluated chunk by chunk on the matrix cores), so that decoding can
  * start from the cache.  Computes the conv roll and every y_t, advances the LIVE slot in place by
- * the L tokens, leaves the newest conv_width-1 raw inputs in the ring, and (in a second, tiny launch)
- * sets pos[b] += L and conv_head[b] += L.  The cache must hold no pending tokens and no uncommitted
+ * the L tokens, leaves the newest conv_width-1 raw inputs in the ring, and (in a further launch)
+ * sets pos[b] += L and conv_head[b] += L.  A long prompt of few sequences and heads is cut into segments
+ * that run side by side; rows of y_out then carry intermediate values while the call is running.  The cache must hold no pending tokens and no uncommitted
  * verify (pend[b] = last_k[b] = 0), else err_flag is set.  Scalar a_mode, headdim and dstate in
  * {32, 64, 128} (SSMV_EUNSUPPORTED otherwise); L >= 1, the same for all sequences.
  * Arithmetic: fp32 tensors multiply in fp32; bf16 tensors multiply on the bf16 matrix cores with

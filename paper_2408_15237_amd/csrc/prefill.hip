@@ -20,7 +20,7 @@
 // The global loads of chunk c+1 are issued (as raw bits, unconditionally, from clamped addresses) right after the
 // barrier that ends the staging of chunk c and are decoded into LDS after chunk c's arithmetic: one chunk of
 // latency hiding for a kernel that would otherwise wait for memory once per chunk.
-#include "ssmv_internal.h"
+#include "prefill_split.h"
 
 namespace ssmv {
 
@@ -307,15 +307,56 @@ __global__ __launch_bounds__(256) void prefill_kernel(const PrefillParams p)
 }
 
 // pos += L, conv_head += L; a prefill on a cache with pending tokens or an uncommitted verify is a sequencing error
-__global__ void prefill_finish_kernel(int batch, int Ls, const int32_t *seq_len, int ring_len, int64_t *pos, int32_t *conv_head,
-                                      const int32_t *pend, const int32_t *last_k, int32_t *err_flag)
+__device__ __forceinline__ void finish_sequence(const PrefillParams &p, int b)
+{
+    const int L = p.seq_len ? min(max(p.seq_len[b], 0), p.L) : p.L;
+    if (p.pend[b] != 0 || p.last_k[b] != 0) *p.err_flag = 1;
+    p.pos[b] += L;
+    p.conv_head_rw[b] = (p.conv_head_rw[b] + L) & (p.ring_len - 1);
+}
+
+__global__ void prefill_finish_kernel(const PrefillParams p)
 {
     const int b = blockIdx.x * blockDim.x + threadIdx.x;
-    if (b >= batch) return;
-    const int L = seq_len ? min(max(seq_len[b], 0), Ls) : Ls;
-    if (pend[b] != 0 || last_k[b] != 0) *err_flag = 1;
-    pos[b] += L;
-    conv_head[b] = (conv_head[b] + L) & (ring_len - 1);
+    if (b < p.batch) finish_sequence(p, b);
+}
+
+// Between the two passes of a segmented prompt: (u, d) of the segments -> the states ahead of them, in place, one thread per
+// 16 bytes of a state (an element only ever meets itself).  grid = (P N / 1024, H, batch).  The loads of up to eight
+// segments are under way together: as a chain of load, multiply-add and store per segment it would be that many round
+// trips to memory long.
+template <int ES>
+__global__ __launch_bounds__(256) void prefill_combine_kernel(const PrefillParams p)
+{
+    const int hd = blockIdx.y, b = blockIdx.z, i = blockIdx.x * 256 + threadIdx.x;
+    if (blockIdx.x == 0 && hd == 0 && threadIdx.x == 0) finish_sequence(p, b);
+    const int L = p.seq_len ? min(max(p.seq_len[b], 0), p.L) : p.L;
+    if (L == 0) return;
+    const int n = (L + kPrefillChunk - 1) / kPrefillChunk, ns = segments_of(p.seg_chunks, n), HP = p.H * p.P;
+    if (ns < 3) return;                                  // one segment: done; two: the state ahead of the second is in its place already
+    char *y_b = static_cast<char *>(p.y) + (size_t)b * p.L * HP * ES;
+    auto area = [&](int s, int piece) { return y_b + seg_piece<ES>(piece, p.P, segment_begin(p.seg_chunks, n, s) * kPrefillChunk, HP, hd); };
+    constexpr int U = 8;
+    v4f_t h = *reinterpret_cast<const v4f_t *>(area(ns - 1, i));       // the state behind segment 0
+    for (int s0 = 1; s0 < ns - 1; s0 += U) {
+        v4f_t u[U];
+        float d[U];
+#pragma unroll
+        for (int j = 0; j < U; ++j) {
+            const int s = min(s0 + j, ns - 2);
+            u[j] = *reinterpret_cast<const v4f_t *>(area(s, i));
+            d[j] = *reinterpret_cast<const float *>(area(s, p.P * p.N / 4));
+        }
+#pragma unroll
+        for (int j = 0; j < U; ++j) {
+            if (s0 + j < ns - 1) {
+                *reinterpret_cast<v4f_t *>(area(s0 + j, i)) = h;
+                const float a = __builtin_amdgcn_exp2f(d[j]);
+                h.x = fmaf(a, h.x, u[j].x); h.y = fmaf(a, h.y, u[j].y); h.z = fmaf(a, h.z, u[j].z); h.w = fmaf(a, h.w, u[j].w);
+            }
+        }
+    }
+    *reinterpret_cast<v4f_t *>(area(ns - 1, i)) = h;
 }
 
 template <int P, int N>
@@ -346,22 +387,74 @@ bool prefill_shape_supported(int P, int N)
     return (P == 32 || P == 64 || P == 128) && (N == 32 || N == 64 || N == 128);
 }
 
-int launch_prefill(const PrefillParams &p, hipStream_t stream)
+// Whether and how a prompt is cut.  The unit is one chunk of a workgroup that has its compute unit to itself (1.8 us with
+// bf16 tensors, 128 x 64): with q workgroups on the fullest compute unit a chunk takes 1.5 of that when the unit is full (r
+// workgroups fit; measured 1.48 at 128 x 64, r = 2, and 1.58 at 64 x 64, r = 4), and linearly less below.  A segment's share of
+// the state alone costs 0.6 of a chunk with outputs, the two further launches 5.  More workgroups than fit at once would run
+// as a second round, which always lost (320 heads x 1500 tokens at 128 x 64: 150 us cut in three, 118 us uncut): not cut.
+// 15 % of expected gain are asked for.  Measured with bf16 tensors, uncut and cut (us; one sequence unless said):
+//   128 x 64, 32 heads:  700 tokens 47 -> 32, 1500: 93 -> 40, 3000: 180 -> 48;  5 sequences, 3000: 182 -> 125
+//   64 x 128, 80 heads:  1500 tokens 115 -> 70, 3000: 221 -> 91;   64 x 64, 4 x 80 heads, 1500: 123 -> 81
+static void choose_segments(PrefillParams &p)
 {
-    int rc;
-    if (p.io == SSMV_BF16) {
-        rc = launch_prefill_bf16(p, stream);
-    } else {
-        switch (p.P) {
-            case 32: rc = launch_p<32>(p, stream); break;
-            case 64: rc = launch_p<64>(p, stream); break;
-            case 128: rc = launch_p<128>(p, stream); break;
-            default: return (int)hipErrorInvalidConfiguration;
-        }
+    p.seg_chunks = p.seg_count = p.seg_pass = 0;
+    if (p.io != SSMV_BF16) return;
+    constexpr int kCUs = 256;
+    const int es = p.io == SSMV_BF16 ? 2 : 4;
+    const int r = prefill_bf16_resident(p.P, p.N);
+    const long pairs = (long)p.batch * p.H;
+    const int n = (p.L + kPrefillChunk - 1) / kPrefillChunk;
+    // the last segment may end with a chunk of one token, and has to hold a state in its rows
+    const int shortest = (4 * p.N / es + kPrefillChunk - 1 + kPrefillChunk - 1) / kPrefillChunk;
+    auto chunk_time = [&](long wgs) { return r > 1 ? 1.0 + 0.5 * ((wgs + kCUs - 1) / kCUs - 1) / (r - 1) : 1.0; };
+    double best = 0.85 * n * chunk_time(pairs);
+    for (int l = shortest; 2 * l < n; ++l) {
+        const int ns = segments_of(l, n), first = n - (ns - 1) * l;
+        const long wgs = pairs * (ns - 1);
+        if (wgs > (long)kCUs * r) continue;
+        const double t = ((first > 0.6 * l ? first : 0.6 * l) + l) * chunk_time(wgs) + 5;
+        if (t < best) { best = t; p.seg_chunks = l; p.seg_count = ns; }
     }
+    if (!p.seg_count) return;
+    // y carries states between the launches: not if it overlaps anything that is still to be read
+    const char *y0 = static_cast<const char *>(p.y), *y1 = y0 + (size_t)p.batch * p.L * p.H * p.P * es;
+    auto overlaps = [&](const void *t, size_t bytes) {
+        const char *a = static_cast<const char *>(t);
+        return a && a < y1 && y0 < a + bytes;
+    };
+    const size_t tok = (size_t)p.batch * p.L, ch = (size_t)p.H * p.P;
+    if (overlaps(p.x_raw, tok * ch * es) || overlaps(p.z, tok * ch * es) || overlaps(p.dt, tok * p.H * es) ||
+        overlaps(p.Bm, tok * p.G * p.N * es) || overlaps(p.Cm, tok * p.G * p.N * es) || overlaps(p.wgt, ch * SSMV_CONV_WIDTH * es) ||
+        overlaps(p.bias, ch * es) || overlaps(p.A, p.H * sizeof(float)) || overlaps(p.D, p.H * sizeof(float)) ||
+        overlaps(p.dt_bias, p.H * sizeof(float)) || overlaps(p.seq_len, p.batch * sizeof(int32_t)))
+        p.seg_chunks = p.seg_count = 0;
+}
+
+static int launch_pass(const PrefillParams &p, hipStream_t stream)
+{
+    if (p.io == SSMV_BF16) return launch_prefill_bf16(p, stream);
+    switch (p.P) {
+        case 32: return launch_p<32>(p, stream);
+        case 64: return launch_p<64>(p, stream);
+        case 128: return launch_p<128>(p, stream);
+        default: return (int)hipErrorInvalidConfiguration;
+    }
+}
+
+int launch_prefill(const PrefillParams &p_in, hipStream_t stream)
+{
+    PrefillParams p = p_in;
+    choose_segments(p);
+    int rc = launch_pass(p, stream);
     if (rc != 0) return rc;
-    hipLaunchKernelGGL(prefill_finish_kernel, dim3((p.batch + 63) / 64), dim3(64), 0, stream, p.batch, p.L, p.seq_len, p.ring_len, p.pos,
-                       p.conv_head_rw, p.pend, p.last_k, p.err_flag);
+    if (p.seg_count) {
+        const dim3 grid(p.P * p.N / 1024, p.H, p.batch);
+        hipLaunchKernelGGL(prefill_combine_kernel<2>, grid, dim3(256), 0, stream, p);
+        if ((rc = (int)hipGetLastError()) != 0) return rc;
+        p.seg_pass = 1;
+        return launch_pass(p, stream);
+    }
+    hipLaunchKernelGGL(prefill_finish_kernel, dim3((p.batch + 63) / 64), dim3(64), 0, stream, p);
     return (int)hipGetLastError();
 }
 

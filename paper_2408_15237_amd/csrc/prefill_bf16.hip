@@ -33,7 +33,7 @@
 // LDS rows that the kernel writes itself are padded by 16 bytes: a row stride that is an odd multiple of 16 bytes
 // spreads 16-byte reads of consecutive rows over all banks; the rows of B and C, which the direct loads fill without
 // gaps, have their 16-byte pieces XOR-swizzled instead (by the choice of the global address each lane fetches).
-#include "ssmv_internal.h"
+#include "prefill_split.h"
 
 namespace ssmv {
 
@@ -43,7 +43,7 @@ typedef __bf16 bf2 __attribute__((ext_vector_type(2)));
 
 namespace {
 
-constexpr int kQ = 32;      // tokens per chunk
+constexpr int kQ = kPrefillChunk;
 constexpr float kLog2e = 1.4426950408889634f;
 
 // waves per 32-channel tile: a large state under a narrow head is split over n
@@ -144,7 +144,10 @@ __device__ long long *pf_trace_buf_ = nullptr;
 // A state of N = 128 under a narrow head (P <= 64) is split over two waves per 32-channel tile, each with half of n: the
 // second adds its share of h C^T through LDS, both update their own half of the state, and the workgroup has twice the
 // threads for the staging.
-template <int P, int N>
+// SEG: the workgroup owns one segment of the prompt instead of all of it (prefill_split.h); in the first pass of such a
+// prompt every segment but the first one only needs its share of the state: no C, no Q x Q product, no outputs, and one
+// barrier less per chunk.
+template <int P, int N, bool SEG>
 __global__ __launch_bounds__(2 * P * prefill_nsplit(P, N)) __attribute__((amdgpu_waves_per_eu((N >= 128 && prefill_nsplit(P, N) == 1) ? 1 : 2)))
 void prefill_bf16_kernel(const PrefillParams p)
 {
@@ -181,20 +184,33 @@ void prefill_bf16_kernel(const PrefillParams p)
     float *sW = reinterpret_cast<float *>(lds + Ld::oW) + wave * Q;
     const int H = p.H, G = p.G;
     const unsigned item = xcd_contiguous(blockIdx.x, gridDim.x);       // the heads of a sequence on one XCD: B and C come out of its L2
-    const int hd = item % H, b = item / H;
+    const int hd = item % H, b = SEG ? (item / H) % p.batch : item / H;
     const int Ls = p.L;                                 // token stride of the arrays
     const int L = p.seq_len ? min(max(p.seq_len[b], 0), Ls) : Ls;     // this sequence's prompt length
     if (L == 0) return;                                 // nothing to feed: state, ring and outputs stay as they are
+    Segment seg = {0, (L + Q - 1) / Q, 0, true, true, true};
+    if constexpr (SEG) {
+        seg = segment_of(p, L, item / (H * p.batch));
+        if (!seg.work) return;
+    }
+    const int c_beg = SEG ? seg.c0 : 0, c_end = seg.c1; // the chunks of this workgroup
+    const bool emit = !SEG || seg.emit;                 // whether it writes outputs
     const int HP = H * P, GN = G * N;
     const int g = hd / (H / G);
     const int cur = (int)((unsigned)p.cur_slot[b] % 3u);
     const int mask = p.ring_len - 1;
-    const int conv_head = p.conv_head[b] & mask;
+    // (the last pass of a segmented prompt runs behind the launch that has moved conv_head on already)
+    const int conv_head = (p.conv_head[b] - (SEG && p.seg_pass == 1 ? L : 0)) & mask;
     const float A2_h = p.A[hd] * kLog2e, D_h = p.D[hd];
     const float dtb_h = p.dt_bias ? p.dt_bias[hd] : 0.f;
     const bool gated = p.z != nullptr, silu = p.conv_act == SSMV_ACT_SILU;
     float *state = p.state + (size_t)cur * p.slot_stride + ((size_t)b * H + hd) * P * N;
 
+    char *y_b = reinterpret_cast<char *>(p.y) + (size_t)b * Ls * HP * 2;
+    // a segment's state between the passes: the lane's float4 number q of tile tn in the rows of y from token `t` on
+    auto seg_at = [&](int tn, int q, int t) {
+        return reinterpret_cast<float4 *>(y_b + seg_piece<2>(((wave_u * TNL + tn) * 4 + q) * 64 + lane, P, t, HP, hd));
+    };
     // state -> accumulator registers, transposed tiles [n][p]: register 4 q + e of tile tn holds
     // h[p = 32 pt + li][n = 32 (TNL nh + tn) + 16 (q/2) + 8 lh + 4 (q%2) + e]
     f16v hacc[TNL];
@@ -205,7 +221,9 @@ void prefill_bf16_kernel(const PrefillParams p)
     for (int tn = 0; tn < TNL; ++tn)
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-            const float4 v = *reinterpret_cast<const float4 *>(state_at(tn, q));
+            float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (!SEG || c_beg == 0) v = *reinterpret_cast<const float4 *>(state_at(tn, q));
+            else if (p.seg_pass == 1) v = *seg_at(tn, q, seg.area);
             hacc[tn][4 * q + 0] = v.x; hacc[tn][4 * q + 1] = v.y; hacc[tn][4 * q + 2] = v.z; hacc[tn][4 * q + 3] = v.w;
         }
     // Every wave computes G^T whole (rows s, columns t = li) and finishes the 16 / (waves) of its registers that are its
@@ -232,7 +250,6 @@ void prefill_bf16_kernel(const PrefillParams p)
     // its end carry dt = 0 and thereby weight 0 everywhere (their rows of X, B, C are the last token's: finite).
     const uint16_t *x_b = reinterpret_cast<const uint16_t *>(p.x_raw) + (size_t)b * Ls * HP;
     const char *z_b = reinterpret_cast<const char *>(p.z) + (size_t)b * Ls * HP * 2;
-    char *y_b = reinterpret_cast<char *>(p.y) + (size_t)b * Ls * HP * 2;
     const uint16_t *B_b = reinterpret_cast<const uint16_t *>(p.Bm) + (size_t)b * Ls * GN + (size_t)g * N;
     const uint16_t *C_b = reinterpret_cast<const uint16_t *>(p.Cm) + (size_t)b * Ls * GN + (size_t)g * N;
     const uint16_t *dt_b = reinterpret_cast<const uint16_t *>(p.dt) + (size_t)b * Ls * H + hd;
@@ -242,8 +259,10 @@ void prefill_bf16_kernel(const PrefillParams p)
     // the W-1 raw inputs ahead of the prompt (newest last)
     uint32_t hist[W - 1];                               // as bits
 #pragma unroll
-    for (int j = 0; j < W - 1; ++j)
-        hist[j] = reinterpret_cast<const uint16_t *>(p.ring)[((size_t)b * p.ring_len + ((conv_head + 1 - (W - 1) + j) & mask)) * HP + ch];
+    for (int j = 0; j < W - 1; ++j) {
+        if (SEG && c_beg > 0) hist[j] = raw_bits(c_beg * Q - (W - 1) + j);
+        else hist[j] = reinterpret_cast<const uint16_t *>(p.ring)[((size_t)b * p.ring_len + ((conv_head + 1 - (W - 1) + j) & mask)) * HP + ch];
+    }
 
     constexpr int UI = (4 * N + NT - 1) / NT;           // (n, eight tokens) units of the transposed B per thread and chunk
     // The chunk's raw x, B and C rows go from global memory straight into LDS, 1 KB per wave and instruction (lane l's 16
@@ -273,12 +292,13 @@ void prefill_bf16_kernel(const PrefillParams p)
                 const int row = idx * (64 / PIECES) + lane / PIECES, pp = lane % PIECES;
                 const size_t o = off(tok(row), GN, (pp ^ Ld::swz(row)) * 8);
                 load_to_lds16(B_b + o, dB + idx * 1024);
-                load_to_lds16(C_b + o, dC + idx * 1024);
+                if (emit) load_to_lds16(C_b + o, dC + idx * 1024);
             }
         }
     };
     // Per chunk, of this lane's token t = li: log2 e * cum_t and exp(cum_t); and exp(cum_Q) (the same in every lane).
     float cum_t, at_t, aq;
+    float cum_all = 0.f;                                // SEG: log2 of the segment's decay
     auto consume = [&](int c, uint32_t dt_bits) {
         const int t0 = c * Q, s0 = sg * QS;
         const char *sB = lds + Ld::oB + (c & (Ld::BCC - 1)) * Ld::BCS;
@@ -293,6 +313,7 @@ void prefill_bf16_kernel(const PrefillParams p)
             cum_t = v;
             at_t = __builtin_amdgcn_exp2f(v);
             aq = __builtin_amdgcn_exp2f(cq);
+            if constexpr (SEG) cum_all += cq;
             if (lh == 0) {
                 sCum[li] = v;
                 sDt[li] = d;
@@ -309,7 +330,7 @@ void prefill_bf16_kernel(const PrefillParams p)
             if (s0 != 0) {
 #pragma unroll
                 for (int j = 0; j < W - 1; ++j) xb[j] = xin[(s0 - (W - 1) + j) * P];
-            } else if (c == 0) {
+            } else if (c == c_beg) {
 #pragma unroll
                 for (int j = 0; j < W - 1; ++j) xb[j] = hist[j];
             } else {
@@ -396,118 +417,119 @@ void prefill_bf16_kernel(const PrefillParams p)
             if (t0 + tt < L) Vec::store_raw(y_b, off(t0 + tt, HP, hd * P + pt * 32 + piece * 8), v);
         }
     };
-    const int n_chunks = (L + Q - 1) / Q;
     const int prow = pt * 32 + li;                      // this lane's channel (inside the head) as an operand row
     float *sZ = reinterpret_cast<float *>(lds + Ld::oZ) + pt * 1024;
     uint32_t dt_bits;
-    issue_x_loads(0, dt_bits);
-    issue_bc_loads(0);
+    issue_x_loads(c_beg, dt_bits);
+    issue_bc_loads(c_beg);
     wait_direct_loads();
     __syncthreads();
-    for (int c = 0; c < n_chunks; ++c) {
+    for (int c = c_beg; c < c_end; ++c) {
         const int t0 = c * Q;
         const char *sB = lds + Ld::oB + (c & (Ld::BCC - 1)) * Ld::BCS, *sC = lds + Ld::oC + (c & (Ld::BCC - 1)) * Ld::BCS;
         consume(c, dt_bits);
         __syncthreads();
         // the stores ahead of the loads on the wide tiles (2 % there; the other way round on the narrow ones)
         constexpr bool kStoresFirst = P >= 128 && N >= 64;
-        if (kStoresFirst && c > 0 && nh == 0) {
+        if (kStoresFirst && c > c_beg && nh == 0 && emit) {
             flush_outputs(c - 1);
             __builtin_amdgcn_sched_barrier(0);
         }
-        if (c + 1 < n_chunks) {                         // under way for the whole chunk
+        if (c + 1 < c_end) {                            // under way for the whole chunk
             issue_x_loads(c + 1, dt_bits);
             if (Ld::BCC == 2) issue_bc_loads(c + 1);
         }
-        if (!kStoresFirst && c > 0 && nh == 0) flush_outputs(c - 1);
+        if (!kStoresFirst && c > c_beg && nh == 0 && emit) flush_outputs(c - 1);
         __builtin_amdgcn_sched_barrier(0);              // the loads and stores stay here, a chunk of arithmetic ahead of the next wait
 
         const int t = li;                               // this lane's token within the chunk
         const bool live = t0 + t < L;
         using QV = XVec<SSMV_BF16, 4>;                  // four adjacent channels
         typename QV::Raw zraw[4];
-        if (gated && nh == 0) {                         // requested ahead of the matrix products
+        if (gated && nh == 0 && emit) {                 // requested ahead of the matrix products
             const int tc = live ? t0 + t : L - 1;
 #pragma unroll
             for (int q = 0; q < 4; ++q) zraw[q] = QV::load(z_b, off(tc, HP, hd * P + pt * 32 + 8 * q + 4 * lh));
         }
-        // C of this lane's token, all of it: the B operand of G^T and of h C^T
-        uint4 cop[N / 16];
-#pragma unroll
-        for (int st = 0; st < N / 16; ++st) cop[st] = *reinterpret_cast<const uint4 *>(sC + t * (N * 2) + (((2 * st + lh) ^ Ld::swz(t)) * 16));
-        // ---- G^T = B C^T, then this wave's share of M^T: masked, decayed, scaled, D on the diagonal; to LDS ----
-        {
-            f16v gacc = {0};
-#pragma unroll
-            for (int st = 0; st < N / 16; ++st)
-                gacc = mfma(as_bf8(*reinterpret_cast<const uint4 *>(sB + li * (N * 2) + (((2 * st + lh) ^ Ld::swz(li)) * 16))), as_bf8(cop[st]), gacc);
-            // registers 4 q .. 4 q + 3 of G^T -> M^T for tokens s = 8 q + 4 lh + [0, 4); r = the quad's index within the wave's share
-            auto finish = [&](int q, int r, float g0, float g1, float g2, float g3) {
-                const int s0 = 8 * q + 4 * lh;
-                const float4 cs = *reinterpret_cast<const float4 *>(sCum + s0), ds = *reinterpret_cast<const float4 *>(sDt + s0);
-                const float csv[4] = {cs.x, cs.y, cs.z, cs.w}, dsv[4] = {ds.x, ds.y, ds.z, ds.w}, g4[4] = {g0, g1, g2, g3};
-                float m[4];
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const float dec = __builtin_amdgcn_exp2f(cum_t - csv[e]) * dsv[e];      // may overflow where s > t: selected away
-                    m[e] = keep[4 * r + e] ? fmaf(g4[e], dec, dadd[4 * r + e]) : 0.f;
-                }
-                *reinterpret_cast<uint2 *>(sMh + t * XS + s0 * 2) = make_uint2(pack_bf16x2(m[0], m[1]), pack_bf16x2(m[2], m[3]));
-            };
-            // the wave's quads: a uniform branch, so that no register is indexed by a variable
-            if constexpr (RW == 4) {
-#pragma unroll
-                for (int r = 0; r < 4; ++r) finish(r, r, gacc[4 * r], gacc[4 * r + 1], gacc[4 * r + 2], gacc[4 * r + 3]);
-            } else if constexpr (RW == 2) {
-                if (wave_u == 0) {
-                    finish(0, 0, gacc[0], gacc[1], gacc[2], gacc[3]);
-                    finish(1, 1, gacc[4], gacc[5], gacc[6], gacc[7]);
-                } else {
-                    finish(2, 0, gacc[8], gacc[9], gacc[10], gacc[11]);
-                    finish(3, 1, gacc[12], gacc[13], gacc[14], gacc[15]);
-                }
-            } else {
-                switch (wave_u) {
-                    case 0: finish(0, 0, gacc[0], gacc[1], gacc[2], gacc[3]); break;
-                    case 1: finish(1, 0, gacc[4], gacc[5], gacc[6], gacc[7]); break;
-                    case 2: finish(2, 0, gacc[8], gacc[9], gacc[10], gacc[11]); break;
-                    default: finish(3, 0, gacc[12], gacc[13], gacc[14], gacc[15]); break;
-                }
-            }
-        }
-        // ---- Y^T = h C^T, scaled by exp(cum_t): the state registers are the A operand ----
         f16v yacc = {0};
+        if (emit) {
+            // C of this lane's token, all of it: the B operand of G^T and of h C^T
+            uint4 cop[N / 16];
 #pragma unroll
-        for (int tn = 0; tn < TNL; ++tn)
+            for (int st = 0; st < N / 16; ++st) cop[st] = *reinterpret_cast<const uint4 *>(sC + t * (N * 2) + (((2 * st + lh) ^ Ld::swz(t)) * 16));
+            // ---- G^T = B C^T, then this wave's share of M^T: masked, decayed, scaled, D on the diagonal; to LDS ----
+            {
+                f16v gacc = {0};
 #pragma unroll
-            for (int st = 0; st < 2; ++st) {
-                uint32_t ah[4];                          // heads only: these products end in outputs, not in the state
+                for (int st = 0; st < N / 16; ++st)
+                    gacc = mfma(as_bf8(*reinterpret_cast<const uint4 *>(sB + li * (N * 2) + (((2 * st + lh) ^ Ld::swz(li)) * 16))), as_bf8(cop[st]), gacc);
+                // registers 4 q .. 4 q + 3 of G^T -> M^T for tokens s = 8 q + 4 lh + [0, 4); r = the quad's index within the wave's share
+                auto finish = [&](int q, int r, float g0, float g1, float g2, float g3) {
+                    const int s0 = 8 * q + 4 * lh;
+                    const float4 cs = *reinterpret_cast<const float4 *>(sCum + s0), ds = *reinterpret_cast<const float4 *>(sDt + s0);
+                    const float csv[4] = {cs.x, cs.y, cs.z, cs.w}, dsv[4] = {ds.x, ds.y, ds.z, ds.w}, g4[4] = {g0, g1, g2, g3};
+                    float m[4];
 #pragma unroll
-                for (int d = 0; d < 4; ++d) {
-                    ah[d] = pack_bf16x2(hacc[tn][8 * st + 2 * d], hacc[tn][8 * st + 2 * d + 1]);
+                    for (int e = 0; e < 4; ++e) {
+                        const float dec = __builtin_amdgcn_exp2f(cum_t - csv[e]) * dsv[e];      // may overflow where s > t: selected away
+                        m[e] = keep[4 * r + e] ? fmaf(g4[e], dec, dadd[4 * r + e]) : 0.f;
+                    }
+                    *reinterpret_cast<uint2 *>(sMh + t * XS + s0 * 2) = make_uint2(pack_bf16x2(m[0], m[1]), pack_bf16x2(m[2], m[3]));
+                };
+                // the wave's quads: a uniform branch, so that no register is indexed by a variable
+                if constexpr (RW == 4) {
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) finish(r, r, gacc[4 * r], gacc[4 * r + 1], gacc[4 * r + 2], gacc[4 * r + 3]);
+                } else if constexpr (RW == 2) {
+                    if (wave_u == 0) {
+                        finish(0, 0, gacc[0], gacc[1], gacc[2], gacc[3]);
+                        finish(1, 1, gacc[4], gacc[5], gacc[6], gacc[7]);
+                    } else {
+                        finish(2, 0, gacc[8], gacc[9], gacc[10], gacc[11]);
+                        finish(3, 1, gacc[12], gacc[13], gacc[14], gacc[15]);
+                    }
+                } else {
+                    switch (wave_u) {
+                        case 0: finish(0, 0, gacc[0], gacc[1], gacc[2], gacc[3]); break;
+                        case 1: finish(1, 0, gacc[4], gacc[5], gacc[6], gacc[7]); break;
+                        case 2: finish(2, 0, gacc[8], gacc[9], gacc[10], gacc[11]); break;
+                        default: finish(3, 0, gacc[12], gacc[13], gacc[14], gacc[15]); break;
+                    }
                 }
-                // C for the wave's own tiles: with a split state read again at the wave's offset (a choice between
-                // registers by a variable would put the array into scratch memory)
-                uint4 c4;
-                if constexpr (NSPL == 2) c4 = *reinterpret_cast<const uint4 *>(sC + t * (N * 2) + (((2 * (2 * (TNL * nh + tn) + st) + lh) ^ Ld::swz(t)) * 16));
-                else c4 = cop[2 * tn + st];
-                const bf8 cb = as_bf8(c4);
-                yacc = mfma(as_bf8(ah[0], ah[1], ah[2], ah[3]), cb, yacc);
             }
-        if constexpr (NSPL == 2) {
-            if (nh == 1) {                              // the second half of n: hand the sum to the tile's first wave
+            // ---- Y^T = h C^T, scaled by exp(cum_t): the state registers are the A operand ----
 #pragma unroll
-                for (int q = 0; q < 4; ++q)
-                    *reinterpret_cast<float4 *>(sZ + q * 256 + lane * 4) = make_float4(yacc[4 * q], yacc[4 * q + 1], yacc[4 * q + 2], yacc[4 * q + 3]);
+            for (int tn = 0; tn < TNL; ++tn)
+#pragma unroll
+                for (int st = 0; st < 2; ++st) {
+                    uint32_t ah[4];                          // heads only: these products end in outputs, not in the state
+#pragma unroll
+                    for (int d = 0; d < 4; ++d) {
+                        ah[d] = pack_bf16x2(hacc[tn][8 * st + 2 * d], hacc[tn][8 * st + 2 * d + 1]);
+                    }
+                    // C for the wave's own tiles: with a split state read again at the wave's offset (a choice between
+                    // registers by a variable would put the array into scratch memory)
+                    uint4 c4;
+                    if constexpr (NSPL == 2) c4 = *reinterpret_cast<const uint4 *>(sC + t * (N * 2) + (((2 * (2 * (TNL * nh + tn) + st) + lh) ^ Ld::swz(t)) * 16));
+                    else c4 = cop[2 * tn + st];
+                    const bf8 cb = as_bf8(c4);
+                    yacc = mfma(as_bf8(ah[0], ah[1], ah[2], ah[3]), cb, yacc);
+                }
+            if constexpr (NSPL == 2) {
+                if (nh == 1) {                              // the second half of n: hand the sum to the tile's first wave
+#pragma unroll
+                    for (int q = 0; q < 4; ++q)
+                        *reinterpret_cast<float4 *>(sZ + q * 256 + lane * 4) = make_float4(yacc[4 * q], yacc[4 * q + 1], yacc[4 * q + 2], yacc[4 * q + 3]);
+                }
             }
         }
         // ---- Y^T += X^T M^T;  h^T <- exp(cum_Q) h^T + (diag(w) B)^T X: X is the A operand of one, the B operand of the other ----
         uint4 xop[2];
 #pragma unroll
         for (int st = 0; st < 2; ++st) xop[st] = *reinterpret_cast<const uint4 *>(sX + prow * XS + (16 * st + 8 * lh) * 2);
-        __syncthreads();     // M^T is complete; nobody reads this chunk's B and C rows any more
-        if (Ld::BCC == 1 && c + 1 < n_chunks) issue_bc_loads(c + 1);
-        if (nh == 0) {
+        if (emit) __syncthreads();     // M^T is complete; nobody reads this chunk's B and C rows any more
+        if (Ld::BCC == 1 && c + 1 < c_end) issue_bc_loads(c + 1);
+        if (nh == 0 && emit) {
             if constexpr (NSPL == 2) {
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
@@ -535,25 +557,38 @@ void prefill_bf16_kernel(const PrefillParams p)
             }
         }
         // ---- gate, store ----
-        if (nh == 0) {
+        if (nh == 0 && emit) {
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            float yv[4] = {yacc[4 * q + 0], yacc[4 * q + 1], yacc[4 * q + 2], yacc[4 * q + 3]};
-            if (gated) {
-                float zf[4];
-                QV::decode(zraw[q], zf);
+            for (int q = 0; q < 4; ++q) {
+                float yv[4] = {yacc[4 * q + 0], yacc[4 * q + 1], yacc[4 * q + 2], yacc[4 * q + 3]};
+                if (gated) {
+                    float zf[4];
+                    QV::decode(zraw[q], zf);
 #pragma unroll
-                for (int e = 0; e < 4; ++e) yv[e] *= silu_fast(zf[e]);
+                    for (int e = 0; e < 4; ++e) yv[e] *= silu_fast(zf[e]);
+                }
+                *reinterpret_cast<uint2 *>(sY + t * Ld::YS + (8 * q + 4 * lh) * 2) = QV::encode(yv);
             }
-            *reinterpret_cast<uint2 *>(sY + t * Ld::YS + (8 * q + 4 * lh) * 2) = QV::encode(yv);
-        }
         }
         __builtin_amdgcn_wave_barrier();                // the tile waits in the wave's LDS patch: flush_outputs
         wait_direct_loads();                            // this wave's share of the next chunk's inputs has landed ...
         __syncthreads();     // ... and so has everybody's; the next chunk overwrites X, B^T, M
     }
 
-    if (nh == 0) flush_outputs(n_chunks - 1);
+    if (nh == 0 && emit) flush_outputs(c_end - 1);
+    if constexpr (SEG) {
+        if (!seg.last) {
+            if (p.seg_pass == 1) return;                // the next segment has its state already
+            // a segment's state on its way to the combining launch
+#pragma unroll
+            for (int tn = 0; tn < TNL; ++tn)
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    *seg_at(tn, q, seg.area) = make_float4(hacc[tn][4 * q + 0], hacc[tn][4 * q + 1], hacc[tn][4 * q + 2], hacc[tn][4 * q + 3]);
+            if (c_beg > 0 && tid == 0) *reinterpret_cast<float *>(y_b + seg_piece<2>(P * N / 4, P, seg.area, HP, hd)) = cum_all;
+            return;
+        }
+    }
     // ---- state back in place; the newest W-1 raw inputs into the ring behind conv_head -----------------------
 #pragma unroll
     for (int tn = 0; tn < TNL; ++tn)
@@ -573,14 +608,14 @@ void prefill_bf16_kernel(const PrefillParams p)
 #endif
 }
 
-template <int P, int N>
+template <int P, int N, bool SEG>
 static int launch_pn(const PrefillParams &p, hipStream_t stream)
 {
     const size_t lds = PfLds<P, N>::total;
-    const dim3 grid(p.H * p.batch), block(2 * P * PfLds<P, N>::NSPL);
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&prefill_bf16_kernel<P, N>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    const dim3 grid((unsigned)(p.H * p.batch) * (SEG ? p.seg_count - 1 : 1)), block(2 * P * PfLds<P, N>::NSPL);
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&prefill_bf16_kernel<P, N, SEG>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return (int)e;
-    hipLaunchKernelGGL((prefill_bf16_kernel<P, N>), grid, block, lds, stream, p);
+    hipLaunchKernelGGL((prefill_bf16_kernel<P, N, SEG>), grid, block, lds, stream, p);
     return (int)hipGetLastError();
 }
 
@@ -588,18 +623,33 @@ template <int P>
 static int launch_p(const PrefillParams &p, hipStream_t stream)
 {
     switch (p.N) {
-        case 32: return launch_pn<P, 32>(p, stream);
-        case 64: return launch_pn<P, 64>(p, stream);
-        case 128: return launch_pn<P, 128>(p, stream);
+        case 32: return p.seg_count ? launch_pn<P, 32, true>(p, stream) : launch_pn<P, 32, false>(p, stream);
+        case 64: return p.seg_count ? launch_pn<P, 64, true>(p, stream) : launch_pn<P, 64, false>(p, stream);
+        case 128: return p.seg_count ? launch_pn<P, 128, true>(p, stream) : launch_pn<P, 128, false>(p, stream);
         default: return (int)hipErrorInvalidConfiguration;
     }
+}
+
+template <int P, int N>
+static constexpr int resident()
+{
+    // 160 KB of LDS; three waves per SIMD by their registers, one with the 128 x 128 tile
+    constexpr int by_lds = 160 * 1024 / PfLds<P, N>::total, by_waves = (P >= 128 && N >= 128 ? 4 : 12) / PfLds<P, N>::NW;
+    return by_lds < by_waves ? by_lds : by_waves;
+}
+int prefill_bf16_resident(int P, int N)
+{
+    auto pick = [&](int n32, int n64, int n128) { return N == 32 ? n32 : N == 64 ? n64 : n128; };
+    if (P == 32) return pick(resident<32, 32>(), resident<32, 64>(), resident<32, 128>());
+    if (P == 64) return pick(resident<64, 32>(), resident<64, 64>(), resident<64, 128>());
+    return pick(resident<128, 32>(), resident<128, 64>(), resident<128, 128>());
 }
 
 #ifdef SSMV_TRACE
 int set_trace_prefill(long long *buf) { return (int)hipMemcpyToSymbol(HIP_SYMBOL(pf_trace_buf_), &buf, sizeof(buf)); }
 #endif
 
-// the main kernel only; the caller appends the bookkeeping launch
+// one pass over the prompt; the caller appends the combining or the bookkeeping launch
 int launch_prefill_bf16(const PrefillParams &p, hipStream_t stream)
 {
     switch (p.P) {

@@ -1,0 +1,61 @@
+// A prompt cut into segments.  One workgroup per (sequence, head) walks the chunks of a prompt one after the other, so a
+// launch with fewer (sequence, head) pairs than the chip holds workgroups leaves most of it idle however long the prompt
+// is.  Eq. 1 is linear in the state: a segment of the prompt maps the state h before it to  2^d h + u,  with d the segment's
+// summed decay exponent and u its state when it starts from zero.  So such a prompt takes three launches:
+//   pass 0   segment 0 starts from the live slot and does everything; segments 1 .. n-2 form (u, d) only, side by side;
+//   combine  the states ahead of segments 1 .. n-1, one after the other but each element on its own (prefill.hip); also moves
+//            pos and conv_head on, which no launch of pass 0 is still reading;
+//   pass 1   segments 1 .. n-1 start from those states and write their outputs; the last one leaves the state in the live
+//            slot and the ring.
+// The library owns no memory, so (u, d) and the states travel in rows of y that nobody has written yet: a segment's own, and
+// for segment 0 (which does write its own in pass 0) the last segment's, whose u nobody needs.  A state is P N floats, that
+// is 4 N / sizeof(element) rows of a head's share of y, which bounds a segment's length from below.  The host takes this path
+// only if y overlaps none of the inputs.
+#pragma once
+
+#include "ssmv_internal.h"
+
+namespace ssmv {
+
+constexpr int kPrefillChunk = 32;      // tokens per chunk
+
+struct Segment {
+    int c0, c1;          // its chunks
+    int area;            // first token of the rows of y that hold its state between the launches
+    bool work;           // there is something to do in this pass
+    bool emit;           // it writes outputs in this pass
+    bool last;           // it ends the prompt
+};
+
+// a prompt of n chunks: every segment has seg_chunks chunks, but the first one has what is left
+__host__ __device__ inline int segments_of(int seg_chunks, int n_chunks) { return 1 + (n_chunks - 1) / seg_chunks; }
+__host__ __device__ inline int segment_begin(int seg_chunks, int n_chunks, int s)
+{
+    return s == 0 ? 0 : n_chunks - (segments_of(seg_chunks, n_chunks) - s) * seg_chunks;
+}
+
+// what workgroup number `slot` (0 .. seg_count - 2) of a (sequence, head) does in this pass; L >= 1
+__device__ __forceinline__ Segment segment_of(const PrefillParams &p, int L, int slot)
+{
+    const int n = (L + kPrefillChunk - 1) / kPrefillChunk, ns = segments_of(p.seg_chunks, n);
+    const int s = slot + p.seg_pass;
+    Segment g;
+    g.last = s == ns - 1;
+    g.work = p.seg_pass ? s < ns : (s == 0 || s < ns - 1);
+    g.emit = p.seg_pass || s == 0;
+    g.c0 = segment_begin(p.seg_chunks, n, s);
+    g.c1 = segment_begin(p.seg_chunks, n, s + 1);
+    g.area = (s == 0 ? segment_begin(p.seg_chunks, n, ns - 1) : g.c0) * kPrefillChunk;
+    return g;
+}
+
+// byte offset, from the sequence's first row of y, of 16-byte piece i of a state kept in head hd's rows from token t on;
+// ES = bytes of an element of y.  Piece P N / 4, behind the state, holds d.
+template <int ES>
+__device__ __forceinline__ size_t seg_piece(int i, int P, int t, int HP, int hd)
+{
+    const int ppr = P * ES / 16;                         // pieces per row
+    return ((size_t)(t + i / ppr) * HP + (size_t)hd * P) * ES + (size_t)(i % ppr) * 16;
+}
+
+}  // namespace ssmv

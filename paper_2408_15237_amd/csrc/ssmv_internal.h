@@ -85,6 +85,10 @@ struct PrefillParams {
     int32_t *conv_head_rw;
     const int32_t *pend, *last_k;
     int32_t *err_flag;
+    // a prompt cut into segments (prefill_split.h)
+    int seg_chunks;          // chunks of a segment (the first one of a prompt takes the rest), 0: not cut
+    int seg_count;           // segments of the longest prompt
+    int seg_pass;            // 0: first pass, 1: last pass
 };
 
 struct CacheInts {
@@ -151,6 +155,7 @@ bool verify_shape_supported(int N, int R, bool diag);
 int launch_conv(const ConvParams &p, hipStream_t stream);
 int launch_prefill(const PrefillParams &p, hipStream_t stream);
 int launch_prefill_bf16(const PrefillParams &p, hipStream_t stream);      // bf16 tensors: the main kernel only
+int prefill_bf16_resident(int P, int N);                                  // its workgroups that fit a compute unit side by side
 bool prefill_shape_supported(int P, int N);
 int launch_commit(const CommitParams &p, hipStream_t stream);
 int launch_reset(const ResetParams &p, hipStream_t stream);

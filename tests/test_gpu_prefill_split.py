@@ -1,0 +1,107 @@
+"""GPU parity of prompts that are cut into segments (csrc/prefill_split.h): few (sequence, head) pairs and a prompt long
+enough, so that the launch would leave most of the chip idle.  Every tile shape; lengths at the edges of chunks and
+segments; sequences of one call that are cut into many segments, two, one, or none at all."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2408_15237_amd as ssmv
+from workload import Workload, generate, round_to_io
+
+from _harness import HipLayer, TOL, rel_err, to_dev, to_host
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = [(P, N) for P in (32, 64, 128) for N in (32, 64, 128)]
+
+
+def _inputs(io, P, N, H, G, batch, L, act="none", seed=11):
+    dec = Workload("split", "scalar", batch=batch, nheads=H, headdim=P, dstate=N, k=4, rounds=2, io=io, accept="uniform", ngroups=G,
+                   conv_act=act, seed=seed)
+    data = generate(dec)
+    rng = np.random.default_rng(seed + 1)
+    draw = lambda *s: round_to_io(np.asarray(rng.standard_normal(s), dtype=np.float32), io)
+    tok = dict(x=draw(batch, L, H * P), dt=round_to_io(rng.standard_normal((batch, L, H)) - 4.0, io), z=draw(batch, L, H * P),
+               B=round_to_io(rng.standard_normal((batch, L, G, N)) / np.sqrt(N), io), C=round_to_io(rng.standard_normal((batch, L, G, N)) / np.sqrt(N), io))
+    bias = rng.uniform(-0.5, 0.5, size=H).astype(np.float32)
+    return dec, data, data.layers[0], tok, bias, draw(batch, 3, H * P)
+
+
+def _prefill(hip, tok, bias, io, L, y, z, lens=None):
+    ssmv.ssm_prefill_block(hip.dims, hip.cache.c, x_raw=to_dev(tok["x"], io), conv_wgt=hip.conv_w, conv_bias=hip.conv_b, dt=to_dev(tok["dt"], io),
+                           dt_bias=torch.from_numpy(bias).to("cuda"), dt_softplus=True, Bm=to_dev(tok["B"], io), Cm=to_dev(tok["C"], io), z=z,
+                           A=hip.A, D=hip.D, L=L, y_out=y, seq_len=None if lens is None else torch.from_numpy(lens).to("cuda"))
+
+
+@pytest.mark.parametrize("io", ["bf16", "f32"])
+@pytest.mark.parametrize("P,N", SHAPES)
+def test_segments_of_ragged_prompts_then_decoding(P, N, io):
+    H, G, L = 4, 2, 1200
+    lens = np.array([L, 0, 1, 33, L - 31, 32 * 20, 32 * 12 + 1], dtype=np.int32)
+    batch = len(lens)
+    dec, data, lp, tok, bias, conv_init = _inputs(io, P, N, H, G, batch, L, act="silu" if P == 64 else "none")
+    hip = HipLayer(dec, lp, conv_init=conv_init)
+    y = torch.full((batch, L, H * P), 7.0, dtype=torch.bfloat16 if io == "bf16" else torch.float32, device="cuda")
+    _prefill(hip, tok, bias, io, L, y, to_dev(tok["z"], io), lens)
+    y_h, h_g, ints = to_host(y), to_host(_materialize(hip, bias)), hip.cache.ints()
+    oras = []
+    for b, n in enumerate(int(v) for v in lens):
+        ora = oracle.EagerOracle("scalar", lp.A, lp.D, lp.conv_w, lp.conv_b, lp.h0[b:b + 1], io, dec.conv_act, G, dt_bias=bias, dt_softplus=True,
+                                 conv_init=conv_init[b:b + 1])
+        if n:
+            y_ref, _, _ = ora.verify(tok["x"][b:b + 1, :n], tok["dt"][b:b + 1, :n], tok["B"][b:b + 1, :n], tok["C"][b:b + 1, :n], z=tok["z"][b:b + 1, :n])
+            ora.commit([n])
+            assert rel_err(y_h[b, :n], y_ref[0]) <= TOL[io], "sequence %d" % b
+        assert np.all(y_h[b, n:] == 7.0), "sequence %d: outputs behind its length were written" % b
+        assert rel_err(h_g[b:b + 1], ora.h) <= TOL[io], "sequence %d: state" % b
+        oras.append(ora)
+    assert ints["pos"].tolist() == lens.tolist() and ints["err_flag"] == 0 and ints["pend"].tolist() == [0] * batch
+    assert ints["conv_head"].tolist() == [(2 + int(n)) & (dec.ring_len - 1) for n in lens]
+    rd = data.rounds[0]                                       # the ring and the state continue the prompt
+    y_g = torch.empty_like(to_dev(rd.x_raw, io))
+    dt = round_to_io(np.random.default_rng(5).standard_normal((batch, dec.k, H)) - 4.0, io)
+    ssmv.ssm_block_multistep(hip.dims, hip.cache.c, x_raw=to_dev(rd.x_raw, io), conv_wgt=hip.conv_w, conv_bias=hip.conv_b, dt=to_dev(dt, io),
+                             dt_bias=torch.from_numpy(bias).to("cuda"), dt_softplus=True, Bm=to_dev(rd.B[0], io), Cm=to_dev(rd.C[0], io), A=hip.A,
+                             D=hip.D, k=dec.k, y_out=y_g)
+    for b in range(batch):
+        y_r, _, _ = oras[b].verify(rd.x_raw[b:b + 1], dt[b:b + 1], rd.B[0][b:b + 1], rd.C[0][b:b + 1])
+        assert rel_err(to_host(y_g)[b:b + 1], y_r) <= TOL[io], "decode, sequence %d" % b
+
+
+def _materialize(hip, bias):
+    wl = hip.wl
+    h = torch.empty((wl.batch, wl.nheads, wl.headdim, wl.dstate), dtype=torch.float32, device="cuda")
+    ssmv.ssmv_materialize_block(hip.dims, hip.cache.c, hip.A, torch.from_numpy(bias).to("cuda"), True, h)
+    return h
+
+
+@pytest.mark.parametrize("io", ["bf16", "f32"])
+@pytest.mark.parametrize("L", [1024, 1025, 1535])
+def test_outputs_over_the_gate_input(L, io):
+    """z and y in one buffer: segments would keep states in rows of y that the gate has yet to be read from."""
+    P, N, H, batch = 64, 64, 2, 2
+    dec, data, lp, tok, bias, conv_init = _inputs(io, P, N, H, 1, batch, L, seed=21)
+    a, b = HipLayer(dec, lp, conv_init=conv_init), HipLayer(dec, lp, conv_init=conv_init)
+    z = to_dev(tok["z"], io)
+    y = torch.empty_like(z)
+    _prefill(a, tok, bias, io, L, y, z)
+    over = z.clone()
+    _prefill(b, tok, bias, io, L, over, over)
+    tol = TOL[io]
+    assert rel_err(to_host(over), to_host(y)) <= tol
+    assert rel_err(to_host(_materialize(b, bias)), to_host(_materialize(a, bias))) <= (1e-4 if io == "bf16" else 1e-5)
+
+
+@pytest.mark.parametrize("io", ["bf16", "f32"])
+def test_strong_decay_across_segments(io):
+    """Decay of up to e^-30 per token: the summed exponent of a segment is far below the smallest float's."""
+    P, N, H, batch, L = 128, 64, 2, 2, 1100
+    dec, data, lp, tok, bias, conv_init = _inputs(io, P, N, H, 1, batch, L, seed=31)
+    lp.A[:] = lp.A * 60.0
+    hip, ora = HipLayer(dec, lp), oracle.EagerOracle("scalar", lp.A, lp.D, lp.conv_w, lp.conv_b, lp.h0, io, "none", 1, dt_bias=bias, dt_softplus=True)
+    y = torch.empty_like(to_dev(tok["x"], io))
+    _prefill(hip, tok, bias, io, L, y, None)
+    y_ref, _, _ = ora.verify(tok["x"], tok["dt"], tok["B"], tok["C"])
+    ora.commit(np.full(batch, L))
+    assert rel_err(to_host(y), y_ref) <= TOL[io] and rel_err(to_host(_materialize(hip, bias)), ora.h) <= TOL[io]
