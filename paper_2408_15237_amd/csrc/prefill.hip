@@ -28,7 +28,7 @@ typedef float f16v __attribute__((ext_vector_type(16)));
 typedef float f4v __attribute__((ext_vector_type(4)));
 typedef float v4f_t __attribute__((ext_vector_type(4)));
 
-constexpr int kQ = 32;     // tokens per chunk
+constexpr int kQ = kPrefillChunk;
 
 template <int P, int N>
 __host__ __device__ constexpr size_t prefill_lds_floats()
@@ -36,7 +36,9 @@ __host__ __device__ constexpr size_t prefill_lds_floats()
     return (size_t)P * (N + 1) + (size_t)kQ * P + 2 * (size_t)kQ * (N + 1) + (size_t)kQ * (kQ + 1) + 4 * kQ;
 }
 
-template <int P, int N, int IO>
+// SEG: the workgroup owns one segment of the prompt instead of all of it (prefill_split.h); in the first pass every segment
+// but the first one forms its share of the state only: no Q x Q product, no outputs, one barrier less per chunk.
+template <int P, int N, int IO, bool SEG>
 __global__ __launch_bounds__(256) void prefill_kernel(const PrefillParams p)
 {
     constexpr int Q = kQ;
@@ -64,24 +66,36 @@ __global__ __launch_bounds__(256) void prefill_kernel(const PrefillParams p)
     const int li = lane & 31, lk = lane >> 5;           // MFMA: row/column index and k index of this lane
     const int H = p.H, G = p.G;
     const unsigned item = xcd_contiguous(blockIdx.x, gridDim.x);       // the heads of a sequence on one XCD: B and C come out of its L2
-    const int hd = item % H, b = item / H;
+    const int hd = item % H, b = SEG ? (item / H) % p.batch : item / H;
     const int Ls = p.L;                                 // token stride of the arrays
     const int L = p.seq_len ? min(max(p.seq_len[b], 0), Ls) : Ls;     // this sequence's prompt length
     if (L == 0) return;                                 // nothing to feed: state, ring and outputs stay as they are
+    Segment seg = {0, (L + Q - 1) / Q, 0, true, true, true};
+    if constexpr (SEG) {
+        seg = segment_of(p, L, item / (H * p.batch));
+        if (!seg.work) return;
+    }
+    const int c_beg = SEG ? seg.c0 : 0, c_end = seg.c1; // the chunks of this workgroup
+    const bool emit = !SEG || seg.emit;                 // whether it writes outputs
     const int HP = H * P, GN = G * N;
     const int g = hd / (H / G);
     const int cur = (int)((unsigned)p.cur_slot[b] % 3u);
     const int mask = p.ring_len - 1;
-    const int conv_head = p.conv_head[b] & mask;
+    // (the last pass of a segmented prompt runs behind the launch that has moved conv_head on already)
+    const int conv_head = (p.conv_head[b] - (SEG && p.seg_pass == 1 ? L : 0)) & mask;
     const float A_h = p.A[hd], D_h = p.D[hd];
     const float dtb_h = p.dt_bias ? p.dt_bias[hd] : 0.f;
     const bool gated = p.z != nullptr;
     float *state = p.state + (size_t)cur * p.slot_stride + ((size_t)b * H + hd) * P * N;
 
-    // state -> LDS
+    constexpr size_t ES = IO == SSMV_BF16 ? 2 : 4;
+    char *y_b = reinterpret_cast<char *>(p.y) + (size_t)b * Ls * HP * ES;
+    // state -> LDS: the live slot's, what the combining launch left in the segment's rows of y, or zeros
     for (int idx = tid; idx < P * N / 4; idx += 256) {
         const int row = (idx * 4) / N, col = (idx * 4) % N;
-        const float4 v = *reinterpret_cast<const float4 *>(state + state_off4(p.tiled, row, col, N));
+        float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (!SEG || c_beg == 0) v = *reinterpret_cast<const float4 *>(state + state_off4(p.tiled, row, col, N));
+        else if (p.seg_pass == 1) v = *reinterpret_cast<const float4 *>(y_b + seg_piece<ES>(idx, P, seg.area, HP, hd));
         float *d = sH + row * NP + col;
         d[0] = v.x; d[1] = v.y; d[2] = v.z; d[3] = v.w;
     }
@@ -98,10 +112,8 @@ __global__ __launch_bounds__(256) void prefill_kernel(const PrefillParams p)
     // Addresses: a base pointer per sequence that is uniform over the workgroup plus a 32-bit element offset from the
     // 24-bit multiplier (the host refuses prompts whose tensors would not fit), so that no load needs 64-bit or
     // quarter-rate integer arithmetic.
-    constexpr size_t ES = IO == SSMV_BF16 ? 2 : 4;
     const char *x_b = reinterpret_cast<const char *>(p.x_raw) + (size_t)b * Ls * HP * ES;
     const char *z_b = reinterpret_cast<const char *>(p.z) + (size_t)b * Ls * HP * ES;
-    char *y_b = reinterpret_cast<char *>(p.y) + (size_t)b * Ls * HP * ES;
     const char *B_b = reinterpret_cast<const char *>(p.Bm) + ((size_t)b * Ls * GN + (size_t)g * N) * ES;
     const char *C_b = reinterpret_cast<const char *>(p.Cm) + ((size_t)b * Ls * GN + (size_t)g * N) * ES;
     const char *dt_b = reinterpret_cast<const char *>(p.dt) + ((size_t)b * Ls * H + hd) * ES;
@@ -114,7 +126,8 @@ __global__ __launch_bounds__(256) void prefill_kernel(const PrefillParams p)
     float hist[W - 1];
 #pragma unroll
     for (int j = 0; j < W - 1; ++j)
-        hist[j] = load_io(p.ring, ((size_t)b * p.ring_len + ((conv_head + 1 - (W - 1) + j) & mask)) * HP + ch, IO);
+        hist[j] = SEG && c_beg > 0 ? Vec::decode1(raw_bits(c_beg * Q - (W - 1) + j))
+                                   : load_io(p.ring, ((size_t)b * p.ring_len + ((conv_head + 1 - (W - 1) + j) & mask)) * HP + ch, IO);
     constexpr int BI = (Q * (N / EV) + 255) / 256;      // 16-byte B (and C) vectors per thread and chunk
     struct Fetch { uint32_t x[QS + W - 1]; uint4 bv[BI], cv[BI]; uint32_t dt; };
     auto prefetch = [&](int c, Fetch &f) {
@@ -133,12 +146,13 @@ __global__ __launch_bounds__(256) void prefill_kernel(const PrefillParams p)
         const int tq = t0 + (tid & (Q - 1));
         f.dt = Vec::load_raw1(dt_b, off(tq < L ? tq : L - 1, H, 0));
     };
+    float cum_all = 0.f;                                // SEG, threads 0 .. Q - 1: log of the segment's decay
     auto consume = [&](int c, const Fetch &f) {
         const int t0 = c * Q, s0 = sg * QS;
         float tap[W - 1];
 #pragma unroll
         for (int j = 0; j < W - 1; ++j) {
-            const int tg = t0 + s0 - (W - 1) + j;       // < 0 only in the first chunk: -(W-1)+j, i.e. hist[j]
+            const int tg = t0 + s0 - (W - 1) + j;       // < 0 only in the prompt's first chunk: -(W-1)+j, i.e. hist[j]
             tap[j] = tg < 0 ? hist[j] : Vec::decode1(f.x[j]);
         }
         float t1 = tap[0], t2 = tap[1], t3 = tap[2];
@@ -184,6 +198,7 @@ __global__ __launch_bounds__(256) void prefill_kernel(const PrefillParams p)
                 if (tid >= off) v += u;
             }
             const float cq = __shfl(v, Q - 1, 64);
+            if constexpr (SEG) cum_all += cq;
             sDt[tid] = d;
             sCum[tid] = v;
             sAt[tid] = expf(v);
@@ -191,18 +206,17 @@ __global__ __launch_bounds__(256) void prefill_kernel(const PrefillParams p)
         }
     };
 
-    const int n_chunks = (L + Q - 1) / Q;
     Fetch fetch;
-    prefetch(0, fetch);
-    for (int c = 0; c < n_chunks; ++c) {
+    prefetch(c_beg, fetch);
+    for (int c = c_beg; c < c_end; ++c) {
         const int t0 = c * Q;
         consume(c, fetch);
         __syncthreads();
-        if (c + 1 < n_chunks) prefetch(c + 1, fetch);
+        if (c + 1 < c_end) prefetch(c + 1, fetch);
         __builtin_amdgcn_sched_barrier(0);              // the loads stay here, a whole chunk of arithmetic ahead of their use
 
         // ---- G = C B^T, one 16x16 quadrant per wave, masked and scaled into M; Y <- diag(exp(cum)) C h^T -----------
-        {
+        if (emit) {
             const int qi = wave >> 1, qj = wave & 1;        // rows t in [16 qi, +16), columns s in [16 qj, +16)
             const int l16 = lane & 15, k4 = lane >> 4;
             const int srow = qj * 16 + l16;
@@ -230,7 +244,7 @@ __global__ __launch_bounds__(256) void prefill_kernel(const PrefillParams p)
         // then holds, for its token, runs of four adjacent channels, which leave as 8- or 16-byte stores and meet the
         // gate inputs and the skip term in the same shape, with no trip through LDS.
         f16v yacc = {0};
-        if (wave < TP) {
+        if (emit && wave < TP) {
             const float at = sAt[li];
             const float *hrow = sH + (wave * 32 + li) * NP;
 #pragma unroll
@@ -239,10 +253,10 @@ __global__ __launch_bounds__(256) void prefill_kernel(const PrefillParams p)
                 yacc = __builtin_amdgcn_mfma_f32_32x32x2f32(hrow[n], sC[li * NP + n] * at, yacc, 0, 0, 0);
             }
         }
-        __syncthreads();     // M is complete; nobody reads the old state any more
+        if (emit) __syncthreads();     // M is complete; nobody reads the old state any more
 
         // ---- Y^T += X^T M^T, + D X, gate, store ---------------------------------------------------------
-        if (wave < TP) {
+        if (emit && wave < TP) {
             const int t = li;                                   // this lane's token within the chunk
             const bool live = t0 + t < L;
             const int tc = live ? t0 + t : L - 1;
@@ -294,6 +308,18 @@ __global__ __launch_bounds__(256) void prefill_kernel(const PrefillParams p)
         __syncthreads();     // the next chunk overwrites X, B, C, M and reads the new state
     }
 
+    if constexpr (SEG) {
+        if (!seg.last) {
+            if (p.seg_pass == 1) return;                // the next segment has its state already
+            // a segment's state on its way to the combining launch
+            for (int idx = tid; idx < P * N / 4; idx += 256) {
+                const float *s = sH + (idx * 4) / N * NP + (idx * 4) % N;
+                *reinterpret_cast<float4 *>(y_b + seg_piece<ES>(idx, P, seg.area, HP, hd)) = make_float4(s[0], s[1], s[2], s[3]);
+            }
+            if (c_beg > 0 && tid == 0) *reinterpret_cast<float *>(y_b + seg_piece<ES>(P * N / 4, P, seg.area, HP, hd)) = cum_all * 1.4426950408889634f;
+            return;
+        }
+    }
     // ---- state back in place; the newest W-1 raw inputs into the ring behind conv_head -----------------------
     for (int idx = tid; idx < P * N / 4; idx += 256) {
         const int row = (idx * 4) / N, col = (idx * 4) % N;
@@ -359,15 +385,15 @@ __global__ __launch_bounds__(256) void prefill_combine_kernel(const PrefillParam
     *reinterpret_cast<v4f_t *>(area(ns - 1, i)) = h;
 }
 
-template <int P, int N>
+// fp32 tensors only: bf16 tensors take the bf16 matrix cores (prefill_bf16.hip)
+template <int P, int N, bool SEG>
 static int launch_pn(const PrefillParams &p, hipStream_t stream)
 {
     const size_t lds = prefill_lds_floats<P, N>() * sizeof(float);
-    const dim3 grid(p.H * p.batch), block(256);
-    // fp32 tensors only: bf16 tensors take the bf16 matrix cores (prefill_bf16.hip)
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&prefill_kernel<P, N, SSMV_F32>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    const dim3 grid((unsigned)(p.H * p.batch) * (SEG ? p.seg_count - 1 : 1)), block(256);
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&prefill_kernel<P, N, SSMV_F32, SEG>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return (int)e;
-    hipLaunchKernelGGL((prefill_kernel<P, N, SSMV_F32>), grid, block, lds, stream, p);
+    hipLaunchKernelGGL((prefill_kernel<P, N, SSMV_F32, SEG>), grid, block, lds, stream, p);
     return (int)hipGetLastError();
 }
 
@@ -375,11 +401,19 @@ template <int P>
 static int launch_p(const PrefillParams &p, hipStream_t stream)
 {
     switch (p.N) {
-        case 32: return launch_pn<P, 32>(p, stream);
-        case 64: return launch_pn<P, 64>(p, stream);
-        case 128: return launch_pn<P, 128>(p, stream);
+        case 32: return p.seg_count ? launch_pn<P, 32, true>(p, stream) : launch_pn<P, 32, false>(p, stream);
+        case 64: return p.seg_count ? launch_pn<P, 64, true>(p, stream) : launch_pn<P, 64, false>(p, stream);
+        case 128: return p.seg_count ? launch_pn<P, 128, true>(p, stream) : launch_pn<P, 128, false>(p, stream);
         default: return (int)hipErrorInvalidConfiguration;
     }
+}
+
+// workgroups that fit a compute unit side by side: one wave per SIMD each, two or three of them by their registers
+static int resident_f32(int P, int N)
+{
+    const size_t lds = ((size_t)P * (N + 1) + (size_t)kQ * P + 2 * (size_t)kQ * (N + 1) + (size_t)kQ * (kQ + 1) + 4 * kQ) * sizeof(float);
+    const int by_lds = (int)(160 * 1024 / lds), by_registers = P * N <= 2048 ? 3 : 2;
+    return by_lds < by_registers ? by_lds : by_registers;
 }
 
 bool prefill_shape_supported(int P, int N)
@@ -395,13 +429,15 @@ bool prefill_shape_supported(int P, int N)
 // 15 % of expected gain are asked for.  Measured with bf16 tensors, uncut and cut (us; one sequence unless said):
 //   128 x 64, 32 heads:  700 tokens 47 -> 32, 1500: 93 -> 40, 3000: 180 -> 48;  5 sequences, 3000: 182 -> 125
 //   64 x 128, 80 heads:  1500 tokens 115 -> 70, 3000: 221 -> 91;   64 x 64, 4 x 80 heads, 1500: 123 -> 81
+// fp32 tensors (a chunk takes 6.6 us there, a state takes half as many rows of y):
+//   128 x 64, 32 heads:  400 tokens 88 -> 47, 1500: 299 -> 68, 3000: 592 -> 108;   64 x 128, 80 heads, 1500: 351 -> 152
 static void choose_segments(PrefillParams &p)
 {
     p.seg_chunks = p.seg_count = p.seg_pass = 0;
-    if (p.io != SSMV_BF16) return;
     constexpr int kCUs = 256;
     const int es = p.io == SSMV_BF16 ? 2 : 4;
-    const int r = prefill_bf16_resident(p.P, p.N);
+    const int r = es == 2 ? prefill_bf16_resident(p.P, p.N) : resident_f32(p.P, p.N);
+    const double share = es == 2 ? 0.6 : 0.5, launches = es == 2 ? 5.0 : 1.5;
     const long pairs = (long)p.batch * p.H;
     const int n = (p.L + kPrefillChunk - 1) / kPrefillChunk;
     // the last segment may end with a chunk of one token, and has to hold a state in its rows
@@ -412,7 +448,7 @@ static void choose_segments(PrefillParams &p)
         const int ns = segments_of(l, n), first = n - (ns - 1) * l;
         const long wgs = pairs * (ns - 1);
         if (wgs > (long)kCUs * r) continue;
-        const double t = ((first > 0.6 * l ? first : 0.6 * l) + l) * chunk_time(wgs) + 5;
+        const double t = ((first > share * l ? first : share * l) + l) * chunk_time(wgs) + launches;
         if (t < best) { best = t; p.seg_chunks = l; p.seg_count = ns; }
     }
     if (!p.seg_count) return;
@@ -449,7 +485,8 @@ int launch_prefill(const PrefillParams &p_in, hipStream_t stream)
     if (rc != 0) return rc;
     if (p.seg_count) {
         const dim3 grid(p.P * p.N / 1024, p.H, p.batch);
-        hipLaunchKernelGGL(prefill_combine_kernel<2>, grid, dim3(256), 0, stream, p);
+        if (p.io == SSMV_BF16) hipLaunchKernelGGL(prefill_combine_kernel<2>, grid, dim3(256), 0, stream, p);
+        else hipLaunchKernelGGL(prefill_combine_kernel<4>, grid, dim3(256), 0, stream, p);
         if ((rc = (int)hipGetLastError()) != 0) return rc;
         p.seg_pass = 1;
         return launch_pass(p, stream);
