@@ -23,7 +23,8 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-u
 # verify_mfma.hip: the first 14 dwords of kernel arguments (seven pointers its first scalar loads go through) are handed to
 # the waves in scalar registers at their start (gfx950 kernel-argument preload; where the firmware does not do it the
 # compiler's prologue loads them)
-EXTRA_FLAGS = {"verify_mfma.hip": ["-mllvm", "-amdgpu-kernarg-preload-count=14"]}
+EXTRA_FLAGS = {"verify_mfma.hip": ["-mllvm", "-amdgpu-kernarg-preload-count=14"],
+               "verify_diag.hip": ["-mllvm", "-amdgpu-kernarg-preload-count=10"]}       # five pointers, in the same way
 
 
 def _hipcc() -> str:

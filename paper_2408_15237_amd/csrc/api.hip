@@ -168,6 +168,7 @@ int choose_shape(const ssmv_dims *d, int lds_tokens, int k, bool gated, VerifySh
     if (waves != 1 && waves != 2 && waves != 4) return fail(SSMV_EINVAL, "waves_per_group %d not in {1,2,4}", waves);
     out->rows_per_lane = R;
     out->waves = waves;
+    out->forced = !autoR || !autoW;
     *rows_wg = waves * rpi * R;
     *tiles = (dom + *rows_wg - 1) / *rows_wg;
     if (*tiles > 65535 * 32) return fail(SSMV_EUNSUPPORTED, "too many row tiles (%d)", *tiles);

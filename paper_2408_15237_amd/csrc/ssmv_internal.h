@@ -123,6 +123,7 @@ struct ResetParams {
 struct VerifyShape {
     int rows_per_lane;   // R
     int waves;           // waves per workgroup
+    bool forced;         // asked for with ssmv_set_tuning
 };
 
 // lanes that share one state row, and rows one wave covers per 16-byte load instruction

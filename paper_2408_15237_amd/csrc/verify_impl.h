@@ -22,6 +22,7 @@
 //   * y_t[row] = sum_n C_t[n] h[row][n] is EPL FMAs in-lane, then a reduction over the LPR lanes
 //     of the row with DPP row operations; the row's first lane adds it to D*x in LDS with a
 //     no-return LDS add, and the workgroup writes y with 16-byte stores at the end.
+//   * Diagonal A: the rounds of a decoder run on verify_diag.hip; here it serves ssmv_materialize and chosen launch shapes.
 //   * The state is read and the snapshots are written with non-temporal accesses: each byte is touched
 //     once per round and a decoder streams the model's weights through the caches before the next one.
 //     (Mixing a temporal and a non-temporal access to one address under an `if` lets the optimiser merge
