@@ -138,13 +138,31 @@ int launch_commit(const CommitParams &p, hipStream_t stream)
 }
 
 // ---- FirstConflict ----------------------------------------------------------------------------------
+// Eight tokens of a sequence are requested at once: compared one by one, each agreement costs another round trip to memory
+// (launches back to back in a graph, operands in the L2, full agreement: k = 8 1.80 -> 1.58 us, the floor of a launch; k = 16 3.00 -> 1.73).
+constexpr int kConflictStep = 8;
 __global__ __launch_bounds__(256) void first_conflict_kernel(const int32_t *draft, const int32_t *target, int batch, int k,
                                                              int32_t *accepted)
 {
     const int b = blockIdx.x * blockDim.x + threadIdx.x;
     if (b >= batch) return;
+    const int32_t *d = draft + (size_t)b * k, *t = target + (size_t)b * k;
     int n = 0;
-    while (n < k && draft[(size_t)b * k + n] == target[(size_t)b * k + n]) ++n;
+    for (int first = 0; first < k && n == first; first += kConflictStep) {
+        int32_t dv[kConflictStep], tv[kConflictStep];
+#pragma unroll
+        for (int i = 0; i < kConflictStep; ++i) {
+            const int j = min(first + i, k - 1);
+            dv[i] = d[j];
+            tv[i] = t[j];
+        }
+        bool agree = true;
+#pragma unroll
+        for (int i = 0; i < kConflictStep; ++i) {
+            agree = agree && first + i < k && dv[i] == tv[i];
+            n += agree;
+        }
+    }
     accepted[b] = n;
 }
 
