@@ -21,3 +21,28 @@ def test_first_conflict_at_every_position(k):
     out = torch.full((batch,), -1, dtype=torch.int32, device="cuda")
     ssmv.ssmv_first_conflict(torch.from_numpy(draft).to("cuda"), torch.from_numpy(target).to("cuda"), batch, k, out)
     assert np.array_equal(out.cpu().numpy(), oracle.first_conflict(draft, target)) and out.tolist() == list(range(k + 1))
+
+
+@pytest.mark.parametrize("io", ["bf16", "f32"])
+@pytest.mark.parametrize("rows,groups,vecs", [(1, 1, 1), (3, 5, 7), (9, 3, 63), (5, 2, 64), (5, 2, 65), (3, 3, 80), (7, 1, 128), (2, 3, 129), (3, 1, 256),
+                                              (2, 2, 257), (3, 1, 512), (2, 1, 513), (1, 2, 1024), (2050, 9, 3), (4097, 5, 80), (4099, 3, 129)])
+def test_gated_rmsnorm_vector_counts(rows, groups, vecs, io):
+    """Group sizes around one, two and four vectors per thread of 64, 128 and 256 threads; a last workgroup with fewer groups
+    or rows than it has room for; in place as well."""
+    dt, ev = (torch.bfloat16, 8) if io == "bf16" else (torch.float32, 4)
+    group = vecs * ev
+    ch = groups * group
+    g = torch.Generator(device="cuda").manual_seed(rows * 1000 + vecs)
+    y, z = (torch.randn(rows, ch, generator=g, device="cuda").to(dt) for _ in range(2))
+    w = 1 + 0.1 * torch.randn(ch, generator=g, device="cuda")
+    for zz in (None, z):
+        v = y.double() if zz is None else y.double() * z.double() * torch.sigmoid(z.double())
+        v = v.view(rows, groups, group)
+        ref = (v * torch.rsqrt((v * v).mean(-1, keepdim=True) + 1e-5)).view(rows, ch) * w.double()
+        out, guard = torch.zeros_like(y), y.clone()
+        ssmv.ssmv_gated_rmsnorm(guard, zz, w, rows, ch, group, 1e-5, io, out)
+        # one rounding to the I/O type (2^-9), or a few fp32 roundings and the hardware's exp2, rcp and rsq (an ulp each)
+        tol = 2.0 ** -8 if io == "bf16" else 4e-6
+        assert ((out.double() - ref).abs() <= tol * ref.abs() + 1e-30).all()
+        ssmv.ssmv_gated_rmsnorm(guard, zz, w, rows, ch, group, 1e-5, io, guard)
+        assert torch.equal(guard, out)
