@@ -46,3 +46,33 @@ def test_gated_rmsnorm_vector_counts(rows, groups, vecs, io):
         assert ((out.double() - ref).abs() <= tol * ref.abs() + 1e-30).all()
         ssmv.ssmv_gated_rmsnorm(guard, zz, w, rows, ch, group, 1e-5, io, guard)
         assert torch.equal(guard, out)
+
+
+@pytest.mark.parametrize("mode,H,P,N,io,kmax", [("diag", 1, 1, 16, "bf16", 1), ("diag", 3, 1, 16, "f32", 1), ("diag", 37, 1, 32, "bf16", 4), ("scalar", 3, 5, 16, "bf16", 1),
+                                                ("scalar", 3, 64, 32, "bf16", 4), ("scalar", 2, 192, 128, "bf16", 5), ("scalar", 5, 64, 64, "f32", 16)])
+def test_reset_of_a_used_cache(mode, H, P, N, io, kmax):
+    """Everything a cache holds is overwritten, with and without a given start; nothing is written past its buffers."""
+    batch, dt = 3, torch.bfloat16 if io == "bf16" else torch.float32
+    d = ssmv.make_dims(batch, H, P, N, kmax=kmax, io=io, a_mode=mode)
+    g = torch.Generator(device="cuda").manual_seed(1)
+    h0, conv = torch.randn(batch, H, P, N, generator=g, device="cuda"), torch.randn(batch, 3, H * P, generator=g, device="cuda").to(dt)
+    A = -torch.rand(*((H, N) if mode == "diag" else (H,)), generator=g, device="cuda")
+    n_ring = batch * d.ring_len * H * P
+    for h, c in ((h0, conv), (None, None), (h0, None), (None, conv)):
+        cache = ssmv.LayerCache.allocate(d)
+        for b in cache.buffers.values():
+            b.fill_(0x0101010101010101)
+        ssmv.ssmv_cache_reset(d, cache.c, h, c)
+        out = torch.full_like(h0, 7.0)
+        ssmv.ssmv_materialize(d, cache.c, A, out)
+        assert torch.equal(out, h0 if h is not None else torch.zeros_like(h0))
+        ring = cache.buffers["conv_ring"].view(dt)
+        want = torch.zeros(batch, d.ring_len, H * P, dtype=dt, device="cuda")
+        if c is not None:
+            want[:, :3] = conv
+        assert torch.equal(ring[:n_ring].view_as(want), want)
+        assert (cache.buffers["conv_ring"].view(torch.uint8)[n_ring * dt.itemsize:] == 1).all()
+        assert (cache.buffers["state"].view(torch.uint8)[h0.numel() * 4:] == 1).all()
+        i = cache.ints()
+        assert [i[n].tolist() for n in ("cur_slot", "pend", "conv_head", "last_k", "pos")] == [[0] * 3, [0] * 3, [2] * 3, [0] * 3, [0] * 3]
+        assert i["win_par"] == 0 and i["err_flag"] == 0
