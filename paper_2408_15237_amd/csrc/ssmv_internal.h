@@ -147,6 +147,8 @@ __host__ __device__ inline size_t state_off4(bool tiled, int p, int n, int N)
 // launchers implemented in verify_scalar.hip / verify_diag.hip; return hipError_t as int
 int launch_verify_scalar(const VerifyParams &p, VerifyShape shape, hipStream_t stream);
 int launch_verify_diag(const VerifyParams &p, VerifyShape shape, hipStream_t stream);
+// ssmv_materialize of scalar mode (materialize.hip)
+int launch_materialize(const VerifyParams &p, hipStream_t stream);
 size_t verify_lds_bytes(const VerifyParams &p, bool diag);
 // the matrix-core form of the scalar-mode kernel (verify_mfma.hip): bf16 I/O, tiled state, at most 16 tokens per launch
 int launch_verify_mfma(const VerifyParams &p, hipStream_t stream);

@@ -5,6 +5,7 @@ namespace ssmv {
 
 int launch_verify_scalar(const VerifyParams &p, VerifyShape shape, hipStream_t stream)
 {
+    if (p.h_out && !shape.forced) return launch_materialize(p, stream);
     return launch_verify_any<false>(p, shape, stream);
 }
 

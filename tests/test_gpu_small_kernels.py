@@ -76,3 +76,38 @@ def test_reset_of_a_used_cache(mode, H, P, N, io, kmax):
         i = cache.ints()
         assert [i[n].tolist() for n in ("cur_slot", "pend", "conv_head", "last_k", "pos")] == [[0] * 3, [0] * 3, [2] * 3, [0] * 3, [0] * 3]
         assert i["win_par"] == 0 and i["err_flag"] == 0
+
+
+@pytest.mark.parametrize("P,N,G,io,mode,kmax", [(64, 32, 1, "bf16", "both", 8), (64, 128, 2, "bf16", "defer", 4), (192, 64, 1, "bf16", "hj_only", 8), (128, 64, 2, "bf16", "defer", 2),
+                                                (20, 16, 1, "f32", "both", 16), (70, 256, 2, "f32", "hj_only", 16), (5, 128, 1, "bf16", "hj_only", 16), (64, 64, 1, "f32", "defer", 4),
+                                                (128, 32, 4, "f32", "both", 5)])
+def test_materialize_folds_the_pending_tokens(P, N, G, io, mode, kmax):
+    """Against the vector verify kernel's replay (an explicitly chosen launch shape takes it), at every pending count that comes
+    up, with the step-size transform, and with one head whose decay underflows."""
+    H, batch = 4, 6
+    dt = torch.bfloat16 if io == "bf16" else torch.float32
+    d = ssmv.make_dims(batch, H, P, N, ngroups=G, kmax=kmax, io=io, snapshot_mode=mode)
+    g = torch.Generator(device="cuda").manual_seed(2)
+    rn = lambda *s: torch.randn(*s, generator=g, device="cuda")
+    A, D, w, bias, dtb = -torch.exp(rn(H)), rn(H), rn(H * P, 4).to(dt), rn(H * P).to(dt), 0.3 * rn(H)
+    A[1] = -1e4
+    cache = ssmv.LayerCache.allocate(d)
+    ssmv.ssmv_cache_reset(d, cache.c, rn(batch, H, P, N), rn(batch, 3, H * P).to(dt))
+    seen = set()
+    for rnd in range(8):
+        y = torch.empty(batch, kmax, H * P, dtype=dt, device="cuda")
+        ssmv.ssm_block_multistep(d, cache.c, x_raw=rn(batch, kmax, H * P).to(dt), conv_wgt=w, conv_bias=bias, dt=(rn(batch, kmax, H) - 3).to(dt), dt_bias=dtb,
+                                 dt_softplus=True, Bm=(rn(batch, kmax, G, N) / N ** 0.5).to(dt), Cm=rn(batch, kmax, G, N).to(dt), A=A, D=D, k=kmax, y_out=y)
+        ssmv.ssm_commit_rollback(d, cache.c, torch.randint(0, kmax + 1, (batch,), generator=g, device="cuda").int())
+        seen |= set(cache.ints()["pend"].tolist())
+        out, ref = torch.full((batch, H, P, N), 7.0, device="cuda"), torch.full((batch, H, P, N), 9.0, device="cuda")
+        ssmv.ssmv_materialize_block(d, cache.c, A, dtb, True, out)
+        ssmv.ssmv_set_tuning(1, 1)
+        try:
+            ssmv.ssmv_materialize_block(d, cache.c, A, dtb, True, ref)
+        finally:
+            ssmv.ssmv_set_tuning(0, 0)
+        # fp32 on both sides: a few dozen roundings of 2^-24 against the head's rms
+        rms = ref.pow(2).mean((2, 3), keepdim=True).sqrt()
+        assert ((out - ref).abs() / (ref.abs() + rms + 1e-30)).max() <= 4e-6
+    assert len(seen) >= 3 and max(seen) >= min(kmax - 1, 3)
