@@ -140,8 +140,11 @@ int choose_shape(const ssmv_dims *d, int lds_tokens, int k, bool gated, VerifySh
         return verify_lds_bytes(q, diag) <= 64 * 1024;
     };
     if (autoR || autoW) {
-        // Largest tile that still leaves >= 1024 workgroups (4 per compute unit) and does not
-        // exceed the domain; otherwise the smallest tile, to spread a small problem over the chip.
+        // Largest tile that still leaves >= 512 workgroups (two per compute unit) and does not exceed the domain; otherwise
+        // the smallest tile, to spread a small problem over the chip.  What a workgroup spends on staging its tokens does not
+        // depend on its rows, so few rows per workgroup cost more than a chip filled less evenly (fp32, 80 heads x 64 x 128, four
+        // layers of a round: 6 sequences, 960 workgroups of 32 rows 46 us, 1920 of 16 rows 60; 2 sequences, 640 of 16 36.9,
+        // 1280 of 8 38.4, 2560 of 4 38.7; bf16, 80 heads x 32 x 64, 12 sequences, 960 of 32 40.9, 1920 of 16 54.7).
         int bestR = -1, bestW = -1;
         long best_rows = -1;
         for (int r = 8; r >= 1; r /= 2) {
@@ -155,7 +158,7 @@ int choose_shape(const ssmv_dims *d, int lds_tokens, int k, bool gated, VerifySh
                 const long groups = domains * t;
                 const bool wasteful = rw > dom && rw > rpi;     // tile larger than the domain
                 long score;                                                    // ties: more waves, fewer rows per lane
-                if (groups >= 1024 && !wasteful) score = 1000000L + 16L * rw + w;   // big tiles first
+                if (groups >= 512 && !wasteful) score = 1000000L + 16L * rw + w;   // big tiles first
                 else score = wasteful ? -16L * rw + w : 500000L - 16L * rw + w;     // else the more groups the better
                 if (score > best_rows) { best_rows = score; bestR = r; bestW = w; }
             }
