@@ -65,14 +65,14 @@ __global__ __launch_bounds__(256) void prefill_kernel(const PrefillParams p)
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int li = lane & 31, lk = lane >> 5;           // MFMA: row/column index and k index of this lane
     const int H = p.H, G = p.G;
-    const unsigned item = xcd_contiguous(blockIdx.x, gridDim.x);       // the heads of a sequence on one XCD: B and C come out of its L2
-    const int hd = item % H, b = SEG ? (item / H) % p.batch : item / H;
+    const PrefillItem item = prefill_item(p);
+    const int hd = item.hd, b = item.b;
     const int Ls = p.L;                                 // token stride of the arrays
-    const int L = p.seq_len ? min(max(p.seq_len[b], 0), Ls) : Ls;     // this sequence's prompt length
+    const int L = item.L;                               // this sequence's prompt length
     if (L == 0) return;                                 // nothing to feed: state, ring and outputs stay as they are
     Segment seg = {0, (L + Q - 1) / Q, 0, true, true, true};
     if constexpr (SEG) {
-        seg = segment_of(p, L, item / (H * p.batch));
+        seg = segment_of(p, L, item.slot);
         if (!seg.work) return;
     }
     const int c_beg = SEG ? seg.c0 : 0, c_end = seg.c1; // the chunks of this workgroup

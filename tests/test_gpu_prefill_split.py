@@ -105,3 +105,27 @@ def test_strong_decay_across_segments(io):
     y_ref, _, _ = ora.verify(tok["x"], tok["dt"], tok["B"], tok["C"])
     ora.commit(np.full(batch, L))
     assert rel_err(to_host(y), y_ref) <= TOL[io] and rel_err(to_host(_materialize(hip, bias)), ora.h) <= TOL[io]
+
+
+@pytest.mark.parametrize("io", ["bf16", "f32"])
+@pytest.mark.parametrize("batch", [1, 2, 63, 64, 65, 130])
+def test_every_sequence_of_a_ragged_batch_is_taken_once(batch, io):
+    """Workgroups take the sequences in order of length (up to 64 of them) or as they come: equal lengths, empty prompts, more
+    sequences than lanes."""
+    P, N, H, L = 32, 32, 3, 70
+    dec, data, lp, tok, bias, conv_init = _inputs(io, P, N, H, 1, batch, L, seed=batch)
+    rng = np.random.default_rng(batch)
+    lens = rng.choice([0, 1, 5, 32, 33, 69, 70], size=batch).astype(np.int32)
+    hip = HipLayer(dec, lp, conv_init=conv_init)
+    y = torch.full((batch, L, H * P), 7.0, dtype=torch.bfloat16 if io == "bf16" else torch.float32, device="cuda")
+    _prefill(hip, tok, bias, io, L, y, to_dev(tok["z"], io), lens)
+    y_h, h_g = to_host(y), to_host(_materialize(hip, bias))
+    for b, n in enumerate(int(v) for v in lens):
+        ora = oracle.EagerOracle("scalar", lp.A, lp.D, lp.conv_w, lp.conv_b, lp.h0[b:b + 1], io, dec.conv_act, 1, dt_bias=bias, dt_softplus=True,
+                                 conv_init=conv_init[b:b + 1])
+        if n:
+            y_ref, _, _ = ora.verify(tok["x"][b:b + 1, :n], tok["dt"][b:b + 1, :n], tok["B"][b:b + 1, :n], tok["C"][b:b + 1, :n], z=tok["z"][b:b + 1, :n])
+            ora.commit([n])
+            assert rel_err(y_h[b, :n], y_ref[0]) <= TOL[io], "sequence %d" % b
+        assert np.all(y_h[b, n:] == 7.0) and rel_err(h_g[b:b + 1], ora.h) <= TOL[io], "sequence %d" % b
+    assert hip.cache.ints()["pos"].tolist() == lens.tolist()
