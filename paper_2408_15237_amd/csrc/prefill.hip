@@ -11,12 +11,17 @@
 //   h     <- exp(cum_Q) h  +  (diag(w) X)^T B,  w_s = exp(cum_Q - cum_s) dt_s      [P x N]   contraction over Q
 // which is Eq. 1 unrolled over the chunk and regrouped (the "chunked" or "state-space dual" evaluation of the
 // scan; the paper's own prefill uses the hardware-aware scan of its reference [Mamba]).  One workgroup of four
-// waves owns one (sequence, head); the state stays in LDS across the chunks, the chunk's X, B, C in LDS as fp32.
+// waves owns one (sequence, head).  The state stays in the accumulator registers across the chunks, transposed (rows = n,
+// columns = channel): a lane's register of a tile is then directly the A operand of C h^T (its two k slots are rows n and n + 4)
+// and the update accumulates in place; the chunk's X, B, C are in LDS as fp32, X is read once for both of its products.
+// (With the state in LDS, read for C h^T and read and written back for the update, a chunk took 256 instead of about 90 LDS
+// instructions per wave.  16 x 512 tokens of 32 heads x 128 x 128: 488 -> 237 us; 8 x 512 of 80 x 64 x 128: 293 -> 236; 32 x 512 of 32 x
+// 128 x 64: 321 -> 302.  The products alone, 80 of 64 cycles each per wave and chunk at 128 x 64, would take 0.6 of that time.)
 // v_mfma_f32_32x32x2_f32 operands: A[i = lane%32][k = lane/32], B[k = lane/32][j = lane%32]; result register v of
 // a lane is D[8*(v/4) + 4*(lane/32) + v%4][lane%32]; v_mfma_f32_16x16x4_f32 (used for the Q x Q product, one
 // quadrant per wave): A[i = lane%16][k = lane/16], B[k = lane/16][j = lane%16], D[4*(lane/16) + v][lane%16].  Rows of
-// the LDS arrays that are read with the lane as the ROW index are padded by one float, so that the lanes hit
-// different banks.
+// the LDS arrays that are read with the lane as the ROW index are padded, by one float (M) or by four (B, C: 16-byte reads),
+// so that the lanes hit different banks.
 // The global loads of chunk c+1 are issued (as raw bits, unconditionally, from clamped addresses) right after the
 // barrier that ends the staging of chunk c and are decoded into LDS after chunk c's arithmetic: one chunk of
 // latency hiding for a kernel that would otherwise wait for memory once per chunk.
@@ -30,21 +35,26 @@ typedef float v4f_t __attribute__((ext_vector_type(4)));
 
 constexpr int kQ = kPrefillChunk;
 
+// How the four waves share a head: wave w owns the 32 channels [32 (w % TP), +32) and, of the state's 32-wide tiles along n, the
+// TNL from TNL (w / TP) on (narrow heads split n; where there are fewer tiles than waves the last ones only stage).
 template <int P, int N>
-__host__ __device__ constexpr size_t prefill_lds_floats()
-{
-    return (size_t)P * (N + 1) + (size_t)kQ * P + 2 * (size_t)kQ * (N + 1) + (size_t)kQ * (kQ + 1) + 4 * kQ;
-}
+struct F32Shape {
+    static constexpr int TP = P / 32, TN = N / 32, SPL = 4 / TP;
+    static constexpr int TNL = TN > SPL ? TN / SPL : 1;
+    static constexpr int NSPL = TN / TNL;                // waves per channel tile that own state
+    static constexpr int NP = N + 4, QP = kQ + 1;        // row strides of B, C and of M: 16-byte rows, all banks
+    static constexpr int floats = kQ * P + 2 * kQ * NP + kQ * QP + 3 + 4 * kQ + (NSPL - 1) * TP * 1024;
+};
 
 // SEG: the workgroup owns one segment of the prompt instead of all of it (prefill_split.h); in the first pass every segment
 // but the first one forms its share of the state only: no Q x Q product, no outputs, one barrier less per chunk.
 template <int P, int N, int IO, bool SEG>
-__global__ __launch_bounds__(256) void prefill_kernel(const PrefillParams p)
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void prefill_kernel(const PrefillParams p)
 {
     constexpr int Q = kQ;
     constexpr int W = SSMV_CONV_WIDTH;
-    constexpr int NP = N + 1, QP = Q + 1;
-    constexpr int TP = P / 32, TN = N / 32;
+    using Sh = F32Shape<P, N>;
+    constexpr int NP = Sh::NP, QP = Sh::QP, TP = Sh::TP, TNL = Sh::TNL, NSPL = Sh::NSPL;
     constexpr int XG = 256 / P;          // thread groups along the tokens of a chunk
     constexpr int QS = Q / XG;           // consecutive tokens one thread convolves per chunk
     using Vec = IoVec<IO>;
@@ -52,18 +62,20 @@ __global__ __launch_bounds__(256) void prefill_kernel(const PrefillParams p)
     static_assert(P % 32 == 0 && P <= 128 && N % 32 == 0, "tile shapes");
 
     extern __shared__ float4 lds_raw[];
-    float *sH = reinterpret_cast<float *>(lds_raw);     // [P][N+1]  state
-    float *sX = sH + P * NP;                            // [Q][P]    conv output of the chunk (rounded to the I/O type)
-    float *sB = sX + Q * P;                             // [Q][N+1]
-    float *sC = sB + Q * NP;                            // [Q][N+1]
-    float *sM = sC + Q * NP;                            // [Q][Q+1]
-    float *sDt = sM + Q * QP;                           // [Q]
+    float *sX = reinterpret_cast<float *>(lds_raw);     // [Q][P]    conv output of the chunk (rounded to the I/O type)
+    float *sB = sX + Q * P;                             // [Q][N+4]
+    float *sC = sB + Q * NP;                            // [Q][N+4]
+    float *sDt = sC + Q * NP;                           // [Q]
     float *sCum = sDt + Q;                              // [Q]  inclusive prefix of dt*A
     float *sAt = sCum + Q;                              // [Q]  exp(cum_t): decay from the chunk's start to after token t
     float *sW = sAt + Q;                                // [Q]  exp(cum_Q - cum_s) dt_s: weight of token s in the chunk's state update
+    float *sM = sW + Q;                                 // [Q][Q+1]
+    float *sZ = sM + ((Q * QP + 3) & ~3);               // [NSPL-1][TP][16][64]  C h^T over the later shares of n
 
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int li = lane & 31, lk = lane >> 5;           // MFMA: row/column index and k index of this lane
+    const int pt = wave % TP, nh = wave / TP;           // the wave's channel tile, and its share of n
+    const bool owns = nh < NSPL;
     const int H = p.H, G = p.G;
     const PrefillItem item = prefill_item(p);
     const int hd = item.hd, b = item.b;
@@ -90,14 +102,23 @@ __global__ __launch_bounds__(256) void prefill_kernel(const PrefillParams p)
 
     constexpr size_t ES = IO == SSMV_BF16 ? 2 : 4;
     char *y_b = reinterpret_cast<char *>(p.y) + (size_t)b * Ls * HP * ES;
-    // state -> LDS: the live slot's, what the combining launch left in the segment's rows of y, or zeros
-    for (int idx = tid; idx < P * N / 4; idx += 256) {
-        const int row = (idx * 4) / N, col = (idx * 4) % N;
-        float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (!SEG || c_beg == 0) v = *reinterpret_cast<const float4 *>(state + state_off4(p.tiled, row, col, N));
-        else if (p.seg_pass == 1) v = *reinterpret_cast<const float4 *>(y_b + seg_piece<ES>(idx, P, seg.area, HP, hd));
-        float *d = sH + row * NP + col;
-        d[0] = v.x; d[1] = v.y; d[2] = v.z; d[3] = v.w;
+    // state -> registers, transposed tiles [n][p]: register 4 q + e of tile tn holds h[p = 32 pt + li][n = 32 (TNL nh + tn) + 8 q + 4 lk + e].
+    // From the live slot, from what the combining launch left in the segment's rows of y, or zeros
+    f16v hacc[TNL];
+    auto state_at = [&](int tn, int q) { return state + state_off4(p.tiled, pt * 32 + li, 32 * (TNL * nh + tn) + 8 * q + 4 * lk, N); };
+    auto seg_at = [&](int tn, int q) {
+        return reinterpret_cast<float4 *>(y_b + seg_piece<ES>((((nh * TP + pt) * TNL + tn) * 4 + q) * 64 + lane, P, seg.area, HP, hd));
+    };
+    if (owns) {
+#pragma unroll
+        for (int tn = 0; tn < TNL; ++tn)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+                if (!SEG || c_beg == 0) v = *reinterpret_cast<const float4 *>(state_at(tn, q));
+                else if (p.seg_pass == 1) v = *seg_at(tn, q);
+                hacc[tn][4 * q + 0] = v.x; hacc[tn][4 * q + 1] = v.y; hacc[tn][4 * q + 2] = v.z; hacc[tn][4 * q + 3] = v.w;
+            }
     }
     // this thread's conv channel: weights and bias stay in registers for the whole prompt
     const int pc = tid % P, sg = tid / P;
@@ -181,9 +202,9 @@ __global__ __launch_bounds__(256) void prefill_kernel(const PrefillParams p)
                 Vec::decode(f.bv[i], bv);
                 Vec::decode(f.cv[i], cv);
 #pragma unroll
-                for (int e = 0; e < EV; ++e) {
-                    sB[s_ * NP + n + e] = live ? bv[e] : 0.f;
-                    sC[s_ * NP + n + e] = live ? cv[e] : 0.f;
+                for (int e = 0; e < EV; e += 4) {
+                    *reinterpret_cast<v4f_t *>(sB + s_ * NP + n + e) = live ? v4f_t{bv[e], bv[e + 1], bv[e + 2], bv[e + 3]} : v4f_t{0.f, 0.f, 0.f, 0.f};
+                    *reinterpret_cast<v4f_t *>(sC + s_ * NP + n + e) = live ? v4f_t{cv[e], cv[e + 1], cv[e + 2], cv[e + 3]} : v4f_t{0.f, 0.f, 0.f, 0.f};
                 }
             }
         }
@@ -244,19 +265,30 @@ __global__ __launch_bounds__(256) void prefill_kernel(const PrefillParams p)
         // then holds, for its token, runs of four adjacent channels, which leave as 8- or 16-byte stores and meet the
         // gate inputs and the skip term in the same shape, with no trip through LDS.
         f16v yacc = {0};
-        if (emit && wave < TP) {
-            const float at = sAt[li];
-            const float *hrow = sH + (wave * 32 + li) * NP;
+        if (emit && owns) {                                 // the state registers are the A operand: rows p, contraction over the wave's n
 #pragma unroll
-            for (int kk = 0; kk < N / 2; ++kk) {
-                const int n = 2 * kk + lk;
-                yacc = __builtin_amdgcn_mfma_f32_32x32x2f32(hrow[n], sC[li * NP + n] * at, yacc, 0, 0, 0);
+            for (int tn = 0; tn < TNL; ++tn)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const v4f_t c4 = *reinterpret_cast<const v4f_t *>(sC + li * NP + 32 * (TNL * nh + tn) + 8 * q + 4 * lk);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) yacc = __builtin_amdgcn_mfma_f32_32x32x2f32(hacc[tn][4 * q + e], c4[e], yacc, 0, 0, 0);
+                }
+            if (NSPL > 1 && nh > 0) {
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    *reinterpret_cast<v4f_t *>(sZ + ((nh - 1) * TP + pt) * 1024 + q * 256 + lane * 4) =
+                        v4f_t{yacc[4 * q], yacc[4 * q + 1], yacc[4 * q + 2], yacc[4 * q + 3]};
             }
         }
-        if (emit) __syncthreads();     // M is complete; nobody reads the old state any more
+        // X of the wave's channels, token 2 kk + lk: A operand of X^T M^T, and, weighted, B operand of the state update
+        float xop[Q / 2];
+#pragma unroll
+        for (int kk = 0; kk < Q / 2; ++kk) xop[kk] = sX[(2 * kk + lk) * P + pt * 32 + li];
+        if (emit) __syncthreads();     // M is complete, and the shares of C h^T
 
         // ---- Y^T += X^T M^T, + D X, gate, store ---------------------------------------------------------
-        if (emit && wave < TP) {
+        if (emit && nh == 0) {
             const int t = li;                                   // this lane's token within the chunk
             const bool live = t0 + t < L;
             const int tc = live ? t0 + t : L - 1;
@@ -264,16 +296,23 @@ __global__ __launch_bounds__(256) void prefill_kernel(const PrefillParams p)
             typename QV::Raw zraw[4];
             if (gated) {                                        // requested ahead of the matrix products
 #pragma unroll
-                for (int q = 0; q < 4; ++q) zraw[q] = QV::load(z_b, off(tc, HP, hd * P + wave * 32 + 8 * q + 4 * lk));
+                for (int q = 0; q < 4; ++q) zraw[q] = QV::load(z_b, off(tc, HP, hd * P + pt * 32 + 8 * q + 4 * lk));
             }
 #pragma unroll
-            for (int kk = 0; kk < Q / 2; ++kk) {
-                const int s_ = 2 * kk + lk;
-                yacc = __builtin_amdgcn_mfma_f32_32x32x2f32(sX[s_ * P + wave * 32 + li], sM[li * QP + s_], yacc, 0, 0, 0);
-            }
+            for (int u = 0; u < NSPL - 1; ++u)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const v4f_t z4 = *reinterpret_cast<const v4f_t *>(sZ + (u * TP + pt) * 1024 + q * 256 + lane * 4);
+                    yacc[4 * q] += z4.x; yacc[4 * q + 1] += z4.y; yacc[4 * q + 2] += z4.z; yacc[4 * q + 3] += z4.w;
+                }
+            const float at = sAt[li];
+#pragma unroll
+            for (int v = 0; v < 16; ++v) yacc[v] *= at;
+#pragma unroll
+            for (int kk = 0; kk < Q / 2; ++kk) yacc = __builtin_amdgcn_mfma_f32_32x32x2f32(xop[kk], sM[li * QP + 2 * kk + lk], yacc, 0, 0, 0);
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-                const int pl = wave * 32 + 8 * q + 4 * lk;      // first of the four channels (inside the head)
+                const int pl = pt * 32 + 8 * q + 4 * lk;        // first of the four channels (inside the head)
                 const v4f_t xs = *reinterpret_cast<const v4f_t *>(sX + t * P + pl);
                 float yv[4] = {fmaf(D_h, xs.x, yacc[4 * q + 0]), fmaf(D_h, xs.y, yacc[4 * q + 1]), fmaf(D_h, xs.z, yacc[4 * q + 2]),
                                fmaf(D_h, xs.w, yacc[4 * q + 3])};
@@ -286,45 +325,45 @@ __global__ __launch_bounds__(256) void prefill_kernel(const PrefillParams p)
                 if (live) QV::store(y_b, off(t0 + t, HP, hd * P + pl), QV::encode(yv));
             }
         }
-        // ---- h <- exp(cum_Q) h + (diag(w) X)^T B, tile by tile ---------------------------------------------
-        {
+        // ---- h^T <- exp(cum_Q) h^T + B^T (diag(w) X), in the registers ------------------------------------------
+        if (owns) {
             const float aq = sAt[Q - 1];
-            for (int tile = wave; tile < TP * TN; tile += 4) {
-                const int tp = tile / TN, tn = tile % TN;
-                f16v sacc = {0};
 #pragma unroll
-                for (int kk = 0; kk < Q / 2; ++kk) {
-                    const int s = 2 * kk + lk;
-                    const float ws = sW[s];
-                    sacc = __builtin_amdgcn_mfma_f32_32x32x2f32(sX[s * P + tp * 32 + li] * ws, sB[s * NP + tn * 32 + li], sacc, 0, 0, 0);
-                }
+            for (int kk = 0; kk < Q / 2; ++kk) xop[kk] *= sW[2 * kk + lk];
 #pragma unroll
-                for (int v = 0; v < 16; ++v) {
-                    float *d = sH + (tp * 32 + 8 * (v / 4) + 4 * lk + (v % 4)) * NP + tn * 32 + li;
-                    *d = fmaf(aq, *d, sacc[v]);
-                }
+            for (int tn = 0; tn < TNL; ++tn) {
+#pragma unroll
+                for (int v = 0; v < 16; ++v) hacc[tn][v] *= aq;
+#pragma unroll
+                for (int kk = 0; kk < Q / 2; ++kk)
+                    hacc[tn] = __builtin_amdgcn_mfma_f32_32x32x2f32(sB[(2 * kk + lk) * NP + 32 * (TNL * nh + tn) + li], xop[kk], hacc[tn], 0, 0, 0);
             }
         }
-        __syncthreads();     // the next chunk overwrites X, B, C, M and reads the new state
+        __syncthreads();     // the next chunk overwrites X, B, C, M
     }
 
     if constexpr (SEG) {
         if (!seg.last) {
             if (p.seg_pass == 1) return;                // the next segment has its state already
             // a segment's state on its way to the combining launch
-            for (int idx = tid; idx < P * N / 4; idx += 256) {
-                const float *s = sH + (idx * 4) / N * NP + (idx * 4) % N;
-                *reinterpret_cast<float4 *>(y_b + seg_piece<ES>(idx, P, seg.area, HP, hd)) = make_float4(s[0], s[1], s[2], s[3]);
+            if (owns) {
+#pragma unroll
+                for (int tn = 0; tn < TNL; ++tn)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q)
+                        *seg_at(tn, q) = make_float4(hacc[tn][4 * q + 0], hacc[tn][4 * q + 1], hacc[tn][4 * q + 2], hacc[tn][4 * q + 3]);
             }
             if (c_beg > 0 && tid == 0) *reinterpret_cast<float *>(y_b + seg_piece<ES>(P * N / 4, P, seg.area, HP, hd)) = cum_all * 1.4426950408889634f;
             return;
         }
     }
     // ---- state back in place; the newest W-1 raw inputs into the ring behind conv_head -----------------------
-    for (int idx = tid; idx < P * N / 4; idx += 256) {
-        const int row = (idx * 4) / N, col = (idx * 4) % N;
-        const float *s = sH + row * NP + col;
-        *reinterpret_cast<float4 *>(state + state_off4(p.tiled, row, col, N)) = make_float4(s[0], s[1], s[2], s[3]);
+    if (owns) {
+#pragma unroll
+        for (int tn = 0; tn < TNL; ++tn)
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                *reinterpret_cast<float4 *>(state_at(tn, q)) = make_float4(hacc[tn][4 * q + 0], hacc[tn][4 * q + 1], hacc[tn][4 * q + 2], hacc[tn][4 * q + 3]);
     }
     if (tid < P) {
         for (int tg = (L - (W - 1) > 0 ? L - (W - 1) : 0); tg < L; ++tg)
@@ -389,7 +428,7 @@ __global__ __launch_bounds__(256) void prefill_combine_kernel(const PrefillParam
 template <int P, int N, bool SEG>
 static int launch_pn(const PrefillParams &p, hipStream_t stream)
 {
-    const size_t lds = prefill_lds_floats<P, N>() * sizeof(float);
+    const size_t lds = F32Shape<P, N>::floats * sizeof(float);
     const dim3 grid((unsigned)(p.H * p.batch) * (SEG ? p.seg_count - 1 : 1)), block(256);
     const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&prefill_kernel<P, N, SSMV_F32, SEG>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return (int)e;
@@ -409,11 +448,18 @@ static int launch_p(const PrefillParams &p, hipStream_t stream)
 }
 
 // workgroups that fit a compute unit side by side: one wave per SIMD each, two or three of them by their registers
+template <int P, int N>
+static constexpr int resident()
+{
+    constexpr int by_lds = 160 * 1024 / (F32Shape<P, N>::floats * 4), by_registers = P * N <= 4096 ? 3 : 2;
+    return by_lds < by_registers ? by_lds : by_registers;
+}
 static int resident_f32(int P, int N)
 {
-    const size_t lds = ((size_t)P * (N + 1) + (size_t)kQ * P + 2 * (size_t)kQ * (N + 1) + (size_t)kQ * (kQ + 1) + 4 * kQ) * sizeof(float);
-    const int by_lds = (int)(160 * 1024 / lds), by_registers = P * N <= 2048 ? 3 : 2;
-    return by_lds < by_registers ? by_lds : by_registers;
+    auto pick = [&](int n32, int n64, int n128) { return N == 32 ? n32 : N == 64 ? n64 : n128; };
+    if (P == 32) return pick(resident<32, 32>(), resident<32, 64>(), resident<32, 128>());
+    if (P == 64) return pick(resident<64, 32>(), resident<64, 64>(), resident<64, 128>());
+    return pick(resident<128, 32>(), resident<128, 64>(), resident<128, 128>());
 }
 
 bool prefill_shape_supported(int P, int N)
