@@ -111,3 +111,20 @@ def test_materialize_folds_the_pending_tokens(P, N, G, io, mode, kmax):
         rms = ref.pow(2).mean((2, 3), keepdim=True).sqrt()
         assert ((out - ref).abs() / (ref.abs() + rms + 1e-30)).max() <= 4e-6
     assert len(seen) >= 3 and max(seen) >= min(kmax - 1, 3)
+
+
+def test_default_stream_argument_follows_torch():
+    """No stream given: the current stream of the current device, whatever it is when the call is made, in every thread."""
+    import threading
+    from paper_2408_15237_amd.binding import _stream
+    now = lambda: torch.cuda.current_stream().cuda_stream or None
+    side = torch.cuda.Stream()
+    assert _stream(None) == now()
+    with torch.cuda.stream(side):
+        assert _stream(None) == now() == side.cuda_stream
+        seen = []
+        th = threading.Thread(target=lambda: seen.append((_stream(None), now())))      # a thread starts on the default stream
+        th.start()
+        th.join()
+        assert seen[0][0] == seen[0][1] != side.cuda_stream
+    assert _stream(None) == now() and _stream(0) is None and _stream(side.cuda_stream) == side.cuda_stream
