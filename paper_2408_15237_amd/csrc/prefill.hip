@@ -13,10 +13,10 @@
 // scan; the paper's own prefill uses the hardware-aware scan of its reference [Mamba]).  One workgroup of four
 // waves owns one (sequence, head).  The state stays in the accumulator registers across the chunks, transposed (rows = n,
 // columns = channel): a lane's register of a tile is then directly the A operand of C h^T (its two k slots are rows n and n + 4)
-// and the update accumulates in place; the chunk's X, B, C are in LDS as fp32, X is read once for both of its products.
+// and the update ends in place; the chunk's X, B, C are in LDS as fp32, X is read once for both of its products.
 // (With the state in LDS, read for C h^T and read and written back for the update, a chunk took 256 instead of about 90 LDS
-// instructions per wave.  16 x 512 tokens of 32 heads x 128 x 128: 488 -> 237 us; 8 x 512 of 80 x 64 x 128: 293 -> 236; 32 x 512 of 32 x
-// 128 x 64: 321 -> 302.  The products alone, 80 of 64 cycles each per wave and chunk at 128 x 64, would take 0.6 of that time.)
+// instructions per wave.  16 x 512 tokens of 32 heads x 128 x 128: 488 -> 240 us; 8 x 512 of 80 x 64 x 128: 293 -> 241; 32 x 512 of 32 x
+// 128 x 64: 321 -> 304.  The products alone, 80 of 64 cycles each per wave and chunk at 128 x 64, would take 0.6 of that time.)
 // v_mfma_f32_32x32x2_f32 operands: A[i = lane%32][k = lane/32], B[k = lane/32][j = lane%32]; result register v of
 // a lane is D[8*(v/4) + 4*(lane/32) + v%4][lane%32]; v_mfma_f32_16x16x4_f32 (used for the Q x Q product, one
 // quadrant per wave): A[i = lane%16][k = lane/16], B[k = lane/16][j = lane%16], D[4*(lane/16) + v][lane%16].  Rows of
@@ -332,11 +332,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void p
             for (int kk = 0; kk < Q / 2; ++kk) xop[kk] *= sW[2 * kk + lk];
 #pragma unroll
             for (int tn = 0; tn < TNL; ++tn) {
-#pragma unroll
-                for (int v = 0; v < 16; ++v) hacc[tn][v] *= aq;
+                // the chunk's own sum first, then ONE rounding against the state: accumulated straight into it, its sixteen
+                // partial sums are rounded at the state's size (state error 2.3e-7 instead of 1.3e-7 under a slow decay)
+                f16v sacc = {0};
 #pragma unroll
                 for (int kk = 0; kk < Q / 2; ++kk)
-                    hacc[tn] = __builtin_amdgcn_mfma_f32_32x32x2f32(sB[(2 * kk + lk) * NP + 32 * (TNL * nh + tn) + li], xop[kk], hacc[tn], 0, 0, 0);
+                    sacc = __builtin_amdgcn_mfma_f32_32x32x2f32(sB[(2 * kk + lk) * NP + 32 * (TNL * nh + tn) + li], xop[kk], sacc, 0, 0, 0);
+#pragma unroll
+                for (int v = 0; v < 16; ++v) hacc[tn][v] = fmaf(aq, hacc[tn][v], sacc[v]);
+                if constexpr (TNL >= 4) __builtin_amdgcn_sched_barrier(0);       // one tile's sum at a time: four side by side spill
             }
         }
         __syncthreads();     // the next chunk overwrites X, B, C, M
