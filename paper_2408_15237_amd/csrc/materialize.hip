@@ -4,7 +4,8 @@
 // rows; tiles change into rows through a patch of LDS of the wave's own.  (Out of the tiles in 16-byte pieces, as the vector
 // verify kernel reads them, 32 x 32 x 128 x 64 took 21.8 us, so 10.1; 5 x 80 x 64 x 128: 6.0, 4.3; 1 x 32 x 128 x 64: 3.0, 2.3.)
 // The pending tokens: h <- 2^(A sum dt) h + sum_s w_s x_s (x) B_s with w_s = dt_s 2^(A sum_{u > s} dt_u), all in fp32, taken
-// backwards so that the exponent is a running sum.
+// backwards so that the exponent is a running sum - of A dt, not A times a sum that starts at 0: a head with A = -inf (or A log2 e
+// beyond fp32's range) keeps its newest token with weight dt, as exp(dt A) = 0 of the stepwise form has it.
 #include "ssmv_internal.h"
 
 namespace ssmv {
@@ -62,14 +63,15 @@ __global__ __launch_bounds__(256) void materialize_kernel(const VerifyParams p)
         for (int j = 0; j < NQ; ++j) sB[tid + 256 * j] = bv[j];
         if (tid < 16) sDt[tid] = d;
         __syncthreads();
-        const float A2 = p.A[hd] * 1.4426950408889634f;
+        constexpr float LOG2E = 1.4426950408889634f;
+        const float A = p.A[hd];
         v4f u[NQ];
 #pragma unroll
         for (int q = 0; q < NQ; ++q) u[q] = v4f{0.f, 0.f, 0.f, 0.f};
-        float after = 0.f;                               // sum of the later tokens' dt
+        float after = 0.f;                               // sum of the later tokens' A dt
         for (int s = pd - 1; s >= 0; --s) {
-            const float dt = sDt[s], w = dt * __builtin_amdgcn_exp2f(A2 * after);
-            after += dt;
+            const float dt = sDt[s], w = dt * __builtin_amdgcn_exp2f(after * LOG2E);
+            after = fmaf(A, dt, after);
 #pragma unroll
             for (int q = 0; q < NQ; ++q) {
                 const float wx = w * sX[s * 64 + wave * 16 + row_of(q)];
@@ -78,7 +80,7 @@ __global__ __launch_bounds__(256) void materialize_kernel(const VerifyParams p)
                 for (int e = 0; e < 4; ++e) u[q][e] = fmaf(wx, B4[e], u[q][e]);
             }
         }
-        const float a = __builtin_amdgcn_exp2f(A2 * after);
+        const float a = __builtin_amdgcn_exp2f(after * LOG2E);
 #pragma unroll
         for (int q = 0; q < NQ; ++q)
 #pragma unroll

@@ -113,6 +113,29 @@ def test_materialize_folds_the_pending_tokens(P, N, G, io, mode, kmax):
     assert len(seen) >= 3 and max(seen) >= min(kmax - 1, 3)
 
 
+@pytest.mark.parametrize("io,P", [("f32", 20), ("f32", 64), ("bf16", 64)])
+@pytest.mark.parametrize("pending", [1, 3])
+@pytest.mark.parametrize("A", [-3e38, -float("inf")])
+def test_materialize_of_a_head_that_keeps_only_its_newest_token(A, pending, io, P):
+    """exp(dt A) = 0: the state is dt x B^T of the last pending token, also where A log2 e is beyond fp32's range."""
+    H, N, batch, k = 2, 64, 2, 4
+    dt = torch.bfloat16 if io == "bf16" else torch.float32
+    d = ssmv.make_dims(batch, H, P, N, kmax=k, io=io, snapshot_mode="hj_only")
+    g = torch.Generator(device="cuda").manual_seed(pending)
+    rn = lambda *s: torch.randn(*s, generator=g, device="cuda")
+    As, D, xc, B = torch.tensor([A, A], device="cuda"), rn(H), rn(batch, k, H * P).to(dt), rn(batch, k, 1, N).to(dt)
+    step = (0.1 + torch.rand(batch, k, H, generator=g, device="cuda")).to(dt)
+    cache = ssmv.LayerCache.allocate(d)
+    ssmv.ssmv_cache_reset(d, cache.c, rn(batch, H, P, N), None)
+    ssmv.ssm_verify_multistep(d, cache.c, xc, step, B, rn(batch, k, 1, N).to(dt), As, D, k, torch.empty_like(xc))
+    ssmv.ssm_commit_rollback(d, cache.c, torch.full((batch,), pending, dtype=torch.int32, device="cuda"))
+    out = torch.full((batch, H, P, N), 7.0, device="cuda")
+    ssmv.ssmv_materialize(d, cache.c, As, out)
+    n = pending - 1
+    want = (step[:, n, :, None].double() * xc[:, n].double().view(batch, H, P))[..., None] * B[:, n, 0].double()[:, None, None]
+    assert ((out.double() - want).abs() <= 2.0 ** -22 * want.abs() + 1e-30).all()          # two products, an ulp each
+
+
 def test_default_stream_argument_follows_torch():
     """No stream given: the current stream of the current device, whatever it is when the call is made, in every thread."""
     import threading
