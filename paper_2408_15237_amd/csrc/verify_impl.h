@@ -229,10 +229,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void v
     const size_t oX_win = tok_win * HP + ch0, oX_in = tok_in * HP + ch0;
     const size_t oDt_win = tok_win * H + dth0, oDt_in = tok_in * H + dth0;
     // Lane-varying strides are multiplied with the 24-bit multiplier (full rate; the 32-bit one runs at a quarter):
-    // token indices are < 32 and the host refuses row lengths of 2^22 elements or more.
+    // token indices are < 32 and the host refuses row lengths of 2^22 elements or more.  (The conv ring may have more rows
+    // than that multiplier takes: a full product, below 2^31 by the host's check.)
     auto m24 = [](int a, int b_) { return __mul24(a, b_); };
     const size_t ring_b = (size_t)b * p.ring_len * HP + ch0;            // this sequence's ring rows, this workgroup's channels
     const int ring_mask = p.ring_len - 1;
+    auto ring_row = [&](int r) { return (unsigned)(r & ring_mask) * (unsigned)HP; };
     // optional softplus(dt + dt_bias) ahead of the discretisation (Section 2.2: dt is the positive step)
     const float dtb_h = (EXTRA && !DIAG && p.dt_bias) ? p.dt_bias[hd] : 0.f;
     auto dt_fix = [&](float d, float bias) {
@@ -313,7 +315,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void v
                 const int j = t - (W - 1) + w;           // position relative to the round's first token
                 const bool from_ring = j < 0;
                 r.tap[w] = XV::load(from_ring ? p.ring : p.x_raw,
-                                    (from_ring ? ring_b + m24((conv_head + 1 + j) & ring_mask, HP) : oX_in + m24(j, HP)) + q.i);
+                                    (from_ring ? ring_b + ring_row(conv_head + 1 + j) : oX_in + m24(j, HP)) + q.i);
             }
             r.wv = Vec::load_raw(p.wgt, (size_t)(ch0 + q.i) * W);           // XW channels x W taps = 16 bytes
             r.bias = p.bias ? XV::load(p.bias, ch0 + q.i) : XV::zero();
@@ -350,7 +352,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void v
             for (int w = 0; w < W - 1; ++w) XV::decode(r.tap[w], tap[w]);
             Vec::decode(r.wv, wv);                       // wgt[channel c][tap] sits at [c*W + tap]
             XV::decode(r.bias, bias);
-            XV::store(p.ring, ring_b + m24((conv_head + 1 + t) & ring_mask, HP) + q.i, r.x);
+            XV::store(p.ring, ring_b + ring_row(conv_head + 1 + t) + q.i, r.x);
 #pragma unroll
             for (int e = 0; e < XW; ++e) {
                 float s = bias[e];

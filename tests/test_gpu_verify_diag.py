@@ -1,6 +1,6 @@
 """GPU parity of the quad-per-channel verify kernel of diagonal-A mode (csrc/verify_diag.hip) where its layout could go wrong:
 channel counts around a wave's and a workgroup's share, odd ones (two channels per quad need an even count), draft and pending
-counts around the groups of four, all snapshot modes, and tokens that are not taken."""
+counts around the groups of four, all snapshot modes, tokens that are not taken, and conv rings of more than 4 GiB."""
 import numpy as np
 import pytest
 import torch
@@ -77,3 +77,38 @@ def test_kernel_and_forced_shape_agree():
             ssmv.ssmv_set_tuning(0, 0)
     assert rel_err(res[0][0], res[1][0]) <= TOL["f32"] and rel_err(res[0][1], res[1][1]) <= TOL["f32"]
     assert res[0][2]["pend"].tolist() == res[1][2]["pend"].tolist()
+
+
+@pytest.mark.parametrize("mode,H,P,ring_len,forced", [("diag", 1030, 1, 1 << 20, True), ("diag", 64, 1, 1 << 24, True), ("scalar", 4, 16, 1 << 24, False)])
+def test_ring_of_more_than_4_gib(mode, H, P, ring_len, forced):
+    """The fused conv finds its history and appends its inputs where conv1d_state_update does, also in rows whose byte offset does
+    not fit 32 bits or whose number does not fit the 24-bit multiplier."""
+    k, N, ch = 4, 16, H * P
+    d = ssmv.make_dims(1, H, P, N, kmax=k, ring_len=ring_len, io="f32", a_mode=mode)
+    g = torch.Generator(device="cuda").manual_seed(ring_len)
+    rn = lambda *s: torch.randn(*s, generator=g, device="cuda")
+    A, D, w, h0, x, hist = -torch.exp(rn(*((H, N) if mode == "diag" else (H,)))), rn(H), rn(ch, 4), rn(1, H, P, N), rn(1, k, ch), rn(3, ch)
+    dt, B, C = 0.1 * torch.exp(rn(1, k, H)), rn(1, k, 1, N), rn(1, k, 1, N)
+    ys = []
+    for fused in (False, True):
+        cache = ssmv.LayerCache.allocate(d)
+        ssmv.ssmv_cache_reset(d, cache.c, h0, None)
+        ring = cache.buffers["conv_ring"].view(torch.float32)[:ring_len * ch].view(ring_len, ch)
+        ring[ring_len - 4:ring_len - 1] = hist
+        cache.buffers["conv_head"].view(torch.int32)[0] = ring_len - 2
+        y = torch.empty_like(x)
+        if fused:
+            ssmv.ssmv_set_tuning(*((1, 2) if forced else (0, 0)))
+            try:
+                ssmv.ssm_conv_verify_multistep(d, cache.c, x, w, None, dt, B, C, A, D, k, y)
+            finally:
+                ssmv.ssmv_set_tuning(0, 0)
+        else:
+            xc = torch.empty_like(x)
+            ssmv.conv1d_state_update(d, cache.c, x, w, None, k, xc)
+            ssmv.ssm_verify_multistep(d, cache.c, xc, dt, B, C, A, D, k, y)
+        ys.append(to_host(y))
+        assert torch.equal(ring[ring_len - 1], x[0, 0]) and torch.equal(ring[:3], x[0, 1:])
+        assert torch.equal(ring[ring_len - 4:ring_len - 1], hist) and int(ring.count_nonzero()) == 7 * ch
+        del cache, ring
+    assert rel_err(ys[1], ys[0]) <= TOL["f32"]
