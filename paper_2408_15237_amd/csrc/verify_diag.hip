@@ -124,7 +124,8 @@ void verify_diag_kernel(const int32_t *a_cur, const int32_t *a_pend, const int32
     const bool have = c0 < H;
     const int cc = have ? c0 : H - R;                    // quads past the end read the last channels again and store nothing
     // this sequence's part of every array: uniform bases, behind which all lane offsets fit 32 bits of bytes (the host refuses
-    // rows of 2^22 elements and more; a row index is < 32 and multiplied on the 24-bit multiplier)
+    // rows of 2^22 elements and more; a token's row index is < 16 and multiplied on the 24-bit multiplier).  Not so the conv
+    // ring, whose length the caller chooses: its rows are 64-bit offsets of a full product (fewer than 2^31 elements, host)
     constexpr size_t ES = IO == SSMV_BF16 ? 2 : 4;
     const size_t tok_in = (size_t)b * k, tok_win = (size_t)b * p.win_tokens;
     auto seq = [&](const void *base, size_t rows, int len) { return const_cast<char *>(static_cast<const char *>(base) + rows * len * ES); };
@@ -203,8 +204,9 @@ void verify_diag_kernel(const int32_t *a_cur, const int32_t *a_pend, const int32
     }
     const int ring_mask = p.ring_len - 1, conv_head = (ch_raw + t0) & ring_mask;       // newest raw input fed so far
     char *ring_b = seq(p.ring, (size_t)b * p.ring_len, H);
+    auto ring_row = [&](int r) { return ring_b + (size_t)((unsigned)(r & ring_mask) * (unsigned)H) * ES; };
     CV hist;
-    if constexpr (CONV) hist = CV::load(ring_b, row_at((conv_head - 3 + (int)sub) & ring_mask, H, cc));   // token sub - 4
+    if constexpr (CONV) hist = CV::load(ring_row(conv_head - 3 + (int)sub), cc);                 // token sub - 4
     // B rows and C rows into LDS as fp32 (rows of no token are not read back)
     const char *B_b = seq(p.Bm, tok_in, N), *C_b = seq(p.Cm, tok_in, N);
     auto bc_item = [&](int i, uint4 &raw, int &t, bool &is_c) {
@@ -295,7 +297,7 @@ void verify_diag_kernel(const int32_t *a_cur, const int32_t *a_pend, const int32
                     s[r] = acc;
                 }
                 xc = CV::encode(s);                      // what is fed on is what is stored
-                if (on && have) xr[j].store(ring_b, row_at((conv_head + 1 + t) & ring_mask, H, cc));
+                if (on && have) xr[j].store(ring_row(conv_head + 1 + t), cc);
             }
             if (on && have) {
                 const unsigned o = row_at(slot_out(t), H, cc);

@@ -79,7 +79,8 @@ def test_kernel_and_forced_shape_agree():
     assert res[0][2]["pend"].tolist() == res[1][2]["pend"].tolist()
 
 
-@pytest.mark.parametrize("mode,H,P,ring_len,forced", [("diag", 1030, 1, 1 << 20, True), ("diag", 64, 1, 1 << 24, True), ("scalar", 4, 16, 1 << 24, False)])
+@pytest.mark.parametrize("forced", [False, True])
+@pytest.mark.parametrize("mode,H,P,ring_len", [("diag", 1030, 1, 1 << 20), ("diag", 64, 1, 1 << 24), ("scalar", 4, 16, 1 << 24)])
 def test_ring_of_more_than_4_gib(mode, H, P, ring_len, forced):
     """The fused conv finds its history and appends its inputs where conv1d_state_update does, also in rows whose byte offset does
     not fit 32 bits or whose number does not fit the 24-bit multiplier."""
