@@ -266,13 +266,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void p
         // gate inputs and the skip term in the same shape, with no trip through LDS.
         f16v yacc = {0};
         if (emit && owns) {                                 // the state registers are the A operand: rows p, contraction over the wave's n
+            const float at = sAt[li];                       // on C, not on the sums: these may leave fp32's range where y does not
 #pragma unroll
             for (int tn = 0; tn < TNL; ++tn)
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
                     const v4f_t c4 = *reinterpret_cast<const v4f_t *>(sC + li * NP + 32 * (TNL * nh + tn) + 8 * q + 4 * lk);
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) yacc = __builtin_amdgcn_mfma_f32_32x32x2f32(hacc[tn][4 * q + e], c4[e], yacc, 0, 0, 0);
+                    for (int e = 0; e < 4; ++e) yacc = __builtin_amdgcn_mfma_f32_32x32x2f32(hacc[tn][4 * q + e], c4[e] * at, yacc, 0, 0, 0);
                 }
             if (NSPL > 1 && nh > 0) {
 #pragma unroll
@@ -305,9 +306,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void p
                     const v4f_t z4 = *reinterpret_cast<const v4f_t *>(sZ + (u * TP + pt) * 1024 + q * 256 + lane * 4);
                     yacc[4 * q] += z4.x; yacc[4 * q + 1] += z4.y; yacc[4 * q + 2] += z4.z; yacc[4 * q + 3] += z4.w;
                 }
-            const float at = sAt[li];
-#pragma unroll
-            for (int v = 0; v < 16; ++v) yacc[v] *= at;
 #pragma unroll
             for (int kk = 0; kk < Q / 2; ++kk) yacc = __builtin_amdgcn_mfma_f32_32x32x2f32(xop[kk], sM[li * QP + 2 * kk + lk], yacc, 0, 0, 0);
 #pragma unroll

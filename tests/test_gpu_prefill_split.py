@@ -129,3 +129,21 @@ def test_every_sequence_of_a_ragged_batch_is_taken_once(batch, io):
             assert rel_err(y_h[b, :n], y_ref[0]) <= TOL[io], "sequence %d" % b
         assert np.all(y_h[b, n:] == 7.0) and rel_err(h_g[b:b + 1], ora.h) <= TOL[io], "sequence %d" % b
     assert hip.cache.ints()["pos"].tolist() == lens.tolist()
+
+
+@pytest.mark.parametrize("P,N", SHAPES)
+def test_large_state_under_a_decay(P, N):
+    """fp32: C h^T is beyond fp32's range, exp(cum) C h^T is not."""
+    H, L = 2, 40
+    dims = ssmv.make_dims(1, H, P, N, kmax=4, io="f32")
+    full = lambda v, *s: torch.full(s, v, device="cuda")
+    cache = ssmv.LayerCache.allocate(dims)
+    ssmv.ssmv_cache_reset(dims, cache.c, full(1e25, 1, H, P, N), None)
+    y = full(7.0, 1, L, H * P)
+    ssmv.ssm_prefill_chunked(dims, cache.c, full(1.0, 1, L, H * P), full(0.0, H * P, 4), None, full(40.0, 1, L, H), full(1.0, 1, L, 1, N),
+                             full(1e14, 1, L, 1, N), full(-1.0, H), full(0.0, H), L, y)
+    want = N * 1e39 * np.exp(-40.0 * (1 + np.arange(L)))
+    got = to_host(y)[0]
+    # the exponent carries the rounding of 40 t; where exp leaves the normal range, y is zero or nearly
+    np.testing.assert_allclose(got[:2], np.repeat(want[:2, None], H * P, 1), rtol=2e-5)
+    assert np.all(np.isfinite(got)) and np.all(np.abs(got[3:]) < 1e-6 * want[0])
