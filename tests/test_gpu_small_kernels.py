@@ -23,6 +23,22 @@ def test_first_conflict_at_every_position(k):
     assert np.array_equal(out.cpu().numpy(), oracle.first_conflict(draft, target)) and out.tolist() == list(range(k + 1))
 
 
+@pytest.mark.parametrize("batch,k", [(1, 64), (5, 64), (3, 65), (2, 130), (131, 33), (70, 21), (65, 63), (70000, 1), (700001, 3), (40000, 64), (33000, 40)])
+def test_first_conflict_of_many_sequences(batch, k):
+    """A wave's share of the lanes: sequences that fill it, leave lanes over or are longer; several shares per wave; a last one that
+    is not full."""
+    g = torch.Generator(device="cuda").manual_seed(batch + k)
+    draft = torch.randint(0, 3, (batch, k), dtype=torch.int32, device="cuda", generator=g)
+    target = draft.clone()
+    at = torch.randint(0, k + 1, (batch,), device="cuda", generator=g)
+    behind = torch.arange(k, device="cuda")[None] >= at[:, None]
+    target[behind] = torch.randint(0, 3, (int(behind.sum()),), dtype=torch.int32, device="cuda", generator=g)
+    out = torch.full((batch + 1,), -1, dtype=torch.int32, device="cuda")
+    ssmv.ssmv_first_conflict(draft, target, batch, k, out)
+    want = (draft == target).int().cumprod(1).sum(1).int()
+    assert torch.equal(out[:batch], want) and out[batch] == -1
+
+
 @pytest.mark.parametrize("io", ["bf16", "f32"])
 @pytest.mark.parametrize("rows,groups,vecs", [(1, 1, 1), (3, 5, 7), (9, 3, 63), (5, 2, 64), (5, 2, 65), (3, 3, 80), (7, 1, 128), (2, 3, 129), (3, 1, 256),
                                               (2, 2, 257), (3, 1, 512), (2, 1, 513), (1, 2, 1024), (2050, 9, 3), (4097, 5, 80), (4099, 3, 129)])
