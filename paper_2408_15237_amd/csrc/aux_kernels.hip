@@ -324,13 +324,12 @@ __device__ __forceinline__ float wave_sum(float v)
 }
 
 // Gated RMS norm of a Mamba-2 block: g = y * z * sigmoid(z) (or y without z); out = g * rsqrt(mean_group(g^2) + eps) * w.
-// `gt` threads (64, 128 or 256) per (token row, group), 256 / gt groups of a row per workgroup; a thread takes MV 16-byte
-// vectors of its group in each of ROWS token rows.  Everything is requested before the first wait, the weights too: a small
-// launch is one round trip to memory and a reduction, and behind the reduction the weights were a second round trip.  The
+// `gt` threads (64, 128 or 256) per (token row, group), as many groups of a row per workgroup as fit 256 threads; a thread takes
+// MV 16-byte vectors of its group in each of ROWS token rows.  Everything is requested before the first wait, the weights too: a
+// small launch is one round trip to memory and a reduction, and behind the reduction the weights were a second round trip.  The
 // sum of squares goes through DPP row operations, over the waves of a group through LDS; a group of one wave needs neither
-// LDS nor a barrier.  In a large launch a workgroup takes four rows: the weights are fp32, for bf16 tensors twice the bytes
-// of a row of y, and are then fetched once for the four.
-// (128 x 4096, one group, bf16: 3.03 -> 2.45 us; 3500 x 5120 in groups of 640, bf16: 19.0 -> 14.2 us; with z 23.7 -> 20.7 us.)
+// LDS nor a barrier.  (128 x 4096, one group, bf16, against the weights behind the reduction and shuffles: 2.92 -> 2.33 us on buffers
+// in the L2, 4.34 -> 3.19 rotating over 1 GiB.)
 template <int IO, int MV, int ROWS>
 __global__ __launch_bounds__(256) void gated_rmsnorm_kernel(const void *y, const void *z, const float *weight, int rows, int channels,
                                                             int group, int gt, float eps, void *out)
@@ -338,9 +337,9 @@ __global__ __launch_bounds__(256) void gated_rmsnorm_kernel(const void *y, const
     using Vec = IoVec<IO>;
     constexpr int EV = Vec::EV;
     __shared__ float partial[ROWS][4];
-    const int sub = threadIdx.x / gt, tid = threadIdx.x % gt, nvec = group / EV;
-    const int grp = min(blockIdx.y * (256 / gt) + sub, channels / group - 1);        // the last workgroup of a row may hold fewer groups:
-    const bool have = blockIdx.y * (256 / gt) + sub == grp;                          // the rest repeat its last one and store nothing
+    const int sub = threadIdx.x / gt, tid = threadIdx.x % gt, gpb = blockDim.x / gt, nvec = group / EV;
+    const int grp = min(blockIdx.y * gpb + sub, channels / group - 1);        // the last workgroup of a row may hold fewer groups:
+    const bool have = blockIdx.y * gpb + sub == grp;                          // the rest repeat its last one and store nothing
     const int row0 = blockIdx.x * ROWS;
     // rows and vectors past the end read the last one again
     auto at = [&](int r, int v) { return (size_t)min(row0 + r, rows - 1) * channels + (size_t)grp * group + (size_t)min(v, nvec - 1) * EV; };
@@ -408,27 +407,27 @@ __global__ __launch_bounds__(256) void gated_rmsnorm_kernel(const void *y, const
     }
 }
 
-template <int IO, int MV>
-static void launch_norm_rows(int nrows_wg, int gt, const void *y, const void *z, const float *weight, int rows, int channels, int group, float eps,
-                             void *out, hipStream_t stream)
-{
-    const int gpb = 256 / gt, ngroups = channels / group;
-    const dim3 grid((rows + nrows_wg - 1) / nrows_wg, (ngroups + gpb - 1) / gpb), block(256);
-    if (nrows_wg == 4) hipLaunchKernelGGL((gated_rmsnorm_kernel<IO, MV, 4>), grid, block, 0, stream, y, z, weight, rows, channels, group, gt, eps, out);
-    else hipLaunchKernelGGL((gated_rmsnorm_kernel<IO, MV, 1>), grid, block, 0, stream, y, z, weight, rows, channels, group, gt, eps, out);
-}
-
+// Four rows per workgroup only for groups that leave lanes of their wave idle, in launches of sixteen waves and more per compute
+// unit: more bytes under way per wave, and the weights (fp32, for bf16 tensors twice the bytes of a row of y) fetched once for the
+// four.  A full wave is slower so (bf16 with z, rotating over 500 MB: 16 of 64 lanes, 2048 x 1024 in groups of 128, 7.84 us with
+// one row and 7.27 with four, 32768 rows 87 and 69; 64 lanes, 4096 x 2048 in groups of 512, 12.0 and 13.0; 128 vectors on
+// 64 lanes, 4096 x 1024 in one group, 7.4 and 9.0).
 template <int IO>
 static int launch_norm_io(const void *y, const void *z, const float *weight, int rows, int channels, int group, float eps, void *out, hipStream_t stream)
 {
-    const int nvec = group / IoVec<IO>::EV;
+    const int nvec = group / IoVec<IO>::EV, ngroups = channels / group;
     const int gt = nvec > 256 ? 256 : nvec > 128 ? 128 : 64;           // threads per group: two vectors each beat one and another wave
     const int mv = (nvec + gt - 1) / gt;                                // 1 .. 4
-    const long wgs = (long)rows * ((channels / group + 256 / gt - 1) / (256 / gt));
-    const int nrows_wg = mv <= 2 && gt < 256 && wgs >= 4096 ? 4 : 1;    // four rows while that leaves four workgroups per compute unit
-    if (mv <= 1) launch_norm_rows<IO, 1>(nrows_wg, gt, y, z, weight, rows, channels, group, eps, out, stream);
-    else if (mv <= 2) launch_norm_rows<IO, 2>(nrows_wg, gt, y, z, weight, rows, channels, group, eps, out, stream);
-    else launch_norm_rows<IO, 4>(1, gt, y, z, weight, rows, channels, group, eps, out, stream);
+    const int rows_wg = nvec < 64 && (long)rows * ngroups >= 16384 ? 4 : 1;
+    // groups of a row per workgroup: as many as fit 256 threads, spread evenly, and no threads for groups that there are not
+    // (2048 x 1280 in one group, bf16 with z: 4.6 us with its 128 threads, 6.4 with 128 idle ones beside them)
+    const int tiles = (ngroups + 256 / gt - 1) / (256 / gt), gpb = (ngroups + tiles - 1) / tiles;
+    const dim3 grid((rows + rows_wg - 1) / rows_wg, tiles), block(gt * gpb);
+    auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, block, 0, stream, y, z, weight, rows, channels, group, gt, eps, out); };
+    if (rows_wg == 4) go(gated_rmsnorm_kernel<IO, 1, 4>);
+    else if (mv <= 1) go(gated_rmsnorm_kernel<IO, 1, 1>);
+    else if (mv <= 2) go(gated_rmsnorm_kernel<IO, 2, 1>);
+    else go(gated_rmsnorm_kernel<IO, 4, 1>);
     return (int)hipGetLastError();
 }
 
