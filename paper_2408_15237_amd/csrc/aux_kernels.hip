@@ -239,16 +239,27 @@ __global__ __launch_bounds__(256) void reset_kernel(const ResetParams p, unsigne
     const size_t n = (size_t)p.batch * p.R * p.Cx;
     const size_t e0 = (size_t)i * EV;
     if (e0 < n) {
-        if (!p.conv_init && e0 + EV <= n) {
-            Vec::store_raw(p.ring, e0, make_uint4(0, 0, 0, 0));
+        if (e0 + EV <= n && (!p.conv_init || p.Cx % EV == 0)) {    // a whole vector, of one row of the ring
+            uint4 v = make_uint4(0, 0, 0, 0);
+            if (p.conv_init) {
+                const unsigned br = (unsigned)(e0 / (unsigned)p.Cx), c = (unsigned)(e0 - (size_t)br * p.Cx);
+                const unsigned b = br / (unsigned)p.R, slot = br - b * p.R;
+                if ((int)slot < p.W - 1) v = Vec::load_raw(p.conv_init, ((size_t)b * (p.W - 1) + slot) * p.Cx + c);
+            }
+            Vec::store_raw(p.ring, e0, v);
         } else {
-            for (size_t e = e0; e < e0 + EV && e < n; ++e) {
+            float v[EV];
+#pragma unroll
+            for (int u = 0; u < EV; ++u) {                         // requested together; past the end the last element again
+                const size_t e = e0 + u < n ? e0 + u : n - 1;
                 const unsigned br = (unsigned)(e / (unsigned)p.Cx), c = (unsigned)(e - (size_t)br * p.Cx);
                 const unsigned b = br / (unsigned)p.R, slot = br - b * p.R;
-                float v = 0.f;
-                if (p.conv_init && (int)slot < p.W - 1) v = load_io(p.conv_init, ((size_t)b * (p.W - 1) + slot) * p.Cx + c, IO);
-                store_io(p.ring, e, v, IO);
+                v[u] = 0.f;
+                if (p.conv_init && (int)slot < p.W - 1) v[u] = load_io(p.conv_init, ((size_t)b * (p.W - 1) + slot) * p.Cx + c, IO);
             }
+#pragma unroll
+            for (int u = 0; u < EV; ++u)
+                if (e0 + u < n) store_io(p.ring, e0 + u, v[u], IO);
         }
     }
     if (i < (unsigned)p.batch) {                   // the ring has at least four elements per sequence, but a vector holds eight
