@@ -129,12 +129,12 @@ def test_materialize_folds_the_pending_tokens(P, N, G, io, mode, kmax):
     assert len(seen) >= 3 and max(seen) >= min(kmax - 1, 3)
 
 
-@pytest.mark.parametrize("io,P", [("f32", 20), ("f32", 64), ("bf16", 64)])
+@pytest.mark.parametrize("io,P,N", [("f32", 20, 64), ("f32", 64, 64), ("bf16", 64, 64), ("f32", 70, 128), ("f32", 3, 256), ("bf16", 37, 256), ("bf16", 40, 128)])
 @pytest.mark.parametrize("pending", [1, 3])
 @pytest.mark.parametrize("A", [-3e38, -float("inf")])
-def test_materialize_of_a_head_that_keeps_only_its_newest_token(A, pending, io, P):
+def test_materialize_of_a_head_that_keeps_only_its_newest_token(A, pending, io, P, N):
     """exp(dt A) = 0: the state is dt x B^T of the last pending token, also where A log2 e is beyond fp32's range."""
-    H, N, batch, k = 2, 64, 2, 4
+    H, batch, k = 2, 2, 4
     dt = torch.bfloat16 if io == "bf16" else torch.float32
     d = ssmv.make_dims(batch, H, P, N, kmax=k, io=io, snapshot_mode="hj_only")
     g = torch.Generator(device="cuda").manual_seed(pending)
