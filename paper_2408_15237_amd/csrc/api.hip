@@ -140,11 +140,18 @@ int choose_shape(const ssmv_dims *d, int lds_tokens, int k, bool gated, VerifySh
         return verify_lds_bytes(q, diag) <= 64 * 1024;
     };
     if (autoR || autoW) {
-        // Largest tile that still leaves >= 512 workgroups (two per compute unit) and does not exceed the domain; otherwise
-        // the smallest tile, to spread a small problem over the chip.  What a workgroup spends on staging its tokens does not
-        // depend on its rows, so few rows per workgroup cost more than a chip filled less evenly (fp32, 80 heads x 64 x 128, four
-        // layers of a round: 6 sequences, 960 workgroups of 32 rows 46 us, 1920 of 16 rows 60; 2 sequences, 640 of 16 36.9,
-        // 1280 of 8 38.4, 2560 of 4 38.7; bf16, 80 heads x 32 x 64, 12 sequences, 960 of 32 40.9, 1920 of 16 54.7).
+        // Largest tile that leaves workgroups enough and does not exceed the domain; otherwise the smallest tile, to spread a small
+        // problem over the chip.  What a workgroup spends on staging its tokens hardly depends on its rows, so few rows per
+        // workgroup cost more than a chip filled less evenly, and 1024 workgroups (four per compute unit) are resident at once: a
+        // launch of 1500 takes two turns.  Enough is 512 for tiles of up to 16 rows, 576 for 32, 832 for more, and 1024 for tiles that
+        // waste more than a fifth of their rows, whose lanes keep eight strips of state, or whose threads stage x in more than one
+        // pass of two items (x_load of verify_impl.h) for rows of 32 values and less.  Time with that line over the time with 1024
+        // for all (fp32 unless said, k drafts; repeated over four layers' caches / rotating over 1 GiB of them):
+        //   64 x 128, 32 rows, 6 x 80 heads, k = 4, one snapshot, 960 workgroups: 0.81 / 0.83;  64 x 256, 16 rows, 6 x 24, k = 3, 576: 0.93 / 0.92
+        //   128 x 64, 64 rows, k = 8: 14 x 32 heads, 896: 0.85 / 0.86, but 12 x 32, 768: 0.98 / 1.00, 10 x 32, 640: 1.05 / 1.09
+        //   32 x 64, 32 rows, bf16, 12 x 80 heads, k = 4, 960: 0.72 / 0.75;  128 x 32, 32 rows, 32 x 8, k = 4, 512 workgroups: 0.99 / 1.04
+        //   what keeps the line of 1024: 128 x 64, eight strips, 16 x 32 heads, k = 5, 512: 1.16 / 1.15;  64 x 128, eight strips, 8 x 80,
+        //   k = 4, 640: 1.05 / 1.04;  64 x 32, 64 rows, 8 x 64, k = 7, 512: 1.17 / 1.25;  80 x 32, 64 rows, 4 x 80, k = 4, 640: 1.07 / 1.08
         int bestR = -1, bestW = -1;
         long best_rows = -1;
         for (int r = 8; r >= 1; r /= 2) {
@@ -158,7 +165,10 @@ int choose_shape(const ssmv_dims *d, int lds_tokens, int k, bool gated, VerifySh
                 const long groups = domains * t;
                 const bool wasteful = rw > dom && rw > rpi;     // tile larger than the domain
                 long score;                                                    // ties: more waves, fewer rows per lane
-                if (groups >= 512 && !wasteful) score = 1000000L + 16L * rw + w;   // big tiles first
+                const int lpr = lanes_per_row(N), strips = r * (N / lpr / 4), items = 2 * lpr * (d->io_dtype == SSMV_BF16 ? 2 : 1);
+                const bool heavy = (rw >= 64 && (strips == 8 || (N <= 32 && lds_tokens * r > items))) || 4 * t * rw > 5L * dom;
+                const long enough = heavy ? 1024 : rw > 32 ? 832 : rw > 16 ? 576 : 512;
+                if (groups >= enough && !wasteful) score = 1000000L + 16L * rw + w;   // big tiles first
                 else score = wasteful ? -16L * rw + w : 500000L - 16L * rw + w;     // else the more groups the better
                 if (score > best_rows) { best_rows = score; bestR = r; bestW = w; }
             }
