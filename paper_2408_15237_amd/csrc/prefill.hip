@@ -77,7 +77,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void p
     const int pt = wave % TP, nh = wave / TP;           // the wave's channel tile, and its share of n
     const bool owns = nh < NSPL;
     const int H = p.H, G = p.G;
-    const PrefillItem item = prefill_item(p);
+    const PrefillItem item = prefill_item<SEG>(p);
     const int hd = item.hd, b = item.b;
     const int Ls = p.L;                                 // token stride of the arrays
     const int L = item.L;                               // this sequence's prompt length

@@ -183,7 +183,7 @@ void prefill_bf16_kernel(const PrefillParams p)
     float *sDt = reinterpret_cast<float *>(lds + Ld::oDt) + wave * Q;
     float *sW = reinterpret_cast<float *>(lds + Ld::oW) + wave * Q;
     const int H = p.H, G = p.G;
-    const PrefillItem item = prefill_item(p);
+    const PrefillItem item = prefill_item<SEG>(p);
     const int hd = item.hd, b = item.b;
     const int Ls = p.L;                                 // token stride of the arrays
     const int L = item.L;                               // this sequence's prompt length

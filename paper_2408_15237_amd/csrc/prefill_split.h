@@ -50,33 +50,36 @@ __device__ __forceinline__ Segment segment_of(const PrefillParams &p, int L, int
 }
 
 // Which (sequence, head[, segment slot]) a workgroup takes.  Prompts of one length: the heads of a sequence on one XCD
-// (xcd_contiguous), B and C then come out of its L2.  Prompts of different lengths: consecutive workgroups over all XCDs, the
-// longest prompts first.  Contiguous ranges would give an XCD nothing but one long prompt's heads and another nothing but a
-// short one's, and a long prompt that starts last ends alone.  (Lengths drawn from 1 up, bf16: 32 sequences x 32 heads x
-// 128 x 64, 2048 tokens at most 453-515 -> 313-377 us; 20 x 80 x 64 x 128, 700 at most 238-275 -> 179-205; 5 x 80: 102 -> 80.)
+// (xcd_contiguous), B and C then come out of its L2.  Prompts of different lengths: consecutive workgroups over all XCDs, and where
+// prompts are of more than two chunks and some compute unit gets more than one, the longest first.  Contiguous ranges would give an
+// XCD nothing but one long prompt's heads and another nothing but a short one's, and a long prompt that starts last ends alone.
+// (Lengths drawn from 1 up, bf16: 32 sequences x 32 heads x 128 x 64, 2048 tokens at most 453-515 -> 313-377 us; 20 x 80 x 64 x 128,
+// 700 at most 238-275 -> 179-205; 5 x 80: 102 -> 80.  The ranking costs 0.3 us, one round trip and a count over the batch, which
+// nothing gives back on short prompts and small launches: 20 x 80 x 64 x 128, 64 at most, contiguous 38-41, ranked 38-40, spread
+// only 34-38; 12 x 12 x 128 x 64, 128 at most: 14.1, 14.4, 14.1.)
 struct PrefillItem { int hd, b, L, slot; };
+template <bool SEG>
 __device__ __forceinline__ PrefillItem prefill_item(const PrefillParams &p)
 {
     PrefillItem w;
+    const unsigned item = p.seq_len ? blockIdx.x : xcd_contiguous(blockIdx.x, gridDim.x), q = item / (unsigned)p.H;
+    w.hd = (int)(item - q * p.H);
+    w.slot = SEG ? (int)(q / (unsigned)p.batch) : 0;
+    w.b = (int)(q - w.slot * (unsigned)p.batch);
     if (!p.seq_len) {
-        const unsigned item = xcd_contiguous(blockIdx.x, gridDim.x), q = item / (unsigned)p.H;
-        w.hd = (int)(item - q * p.H);
-        w.slot = (int)(q / (unsigned)p.batch);
-        w.b = (int)(q - w.slot * (unsigned)p.batch);
         w.L = p.L;
         return w;
     }
-    const unsigned q = blockIdx.x / (unsigned)p.H;
-    w.hd = (int)(blockIdx.x - q * p.H);
-    w.slot = (int)(q / (unsigned)p.batch);
-    w.b = (int)(q - w.slot * (unsigned)p.batch);
-    if (p.batch <= 64) {                                 // lane j knows sequence j: the one with w.b longer ones ahead of it
+    if (p.batch <= 64 && p.L > 2 * kPrefillChunk && p.H * p.batch > 256) {
+        // lane j knows sequence j: the one with w.b longer ones ahead of it.
+        // (len, lane) as one number, all different: a rank is a count of greater ones.  Eight at a time: lanes without a sequence
+        // hold numbers below all others
         const int lane = threadIdx.x & 63;
-        const int len = lane < p.batch ? min(max(p.seq_len[lane], 0), p.L) : -1;
+        const int len = lane < p.batch ? min(max(p.seq_len[lane], 0), p.L) : -1, key = len * 64 + (63 - lane);
         int ahead = 0;
-        for (int j = 0; j < p.batch; ++j) {
-            const int other = __builtin_amdgcn_readlane(len, j);
-            ahead += other > len || (other == len && j < lane);
+        for (int j0 = 0; j0 < p.batch; j0 += 8) {
+#pragma unroll
+            for (int j = 0; j < 8; ++j) ahead += __builtin_amdgcn_readlane(key, j0 + j) > key;
         }
         w.b = __builtin_ctzll(__ballot(lane < p.batch && ahead == w.b));
         w.L = __builtin_amdgcn_readlane(len, w.b);

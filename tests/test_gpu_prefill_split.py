@@ -1,6 +1,8 @@
 """GPU parity of prompts that are cut into segments (csrc/prefill_split.h): few (sequence, head) pairs and a prompt long
 enough, so that the launch would leave most of the chip idle.  Every tile shape; lengths at the edges of chunks and
 segments; sequences of one call that are cut into many segments, two, one, or none at all."""
+import dataclasses
+
 import numpy as np
 import pytest
 import torch
@@ -147,3 +149,27 @@ def test_large_state_under_a_decay(P, N):
     # the exponent carries the rounding of 40 t; where exp leaves the normal range, y is zero or nearly
     np.testing.assert_allclose(got[:2], np.repeat(want[:2, None], H * P, 1), rtol=2e-5)
     assert np.all(np.isfinite(got)) and np.all(np.abs(got[3:]) < 1e-6 * want[0])
+
+
+@pytest.mark.parametrize("io", ["bf16", "f32"])
+@pytest.mark.parametrize("batch,H,L", [(3, 86, 65), (52, 5, 70), (57, 5, 100), (63, 5, 70), (64, 5, 70), (65, 5, 70), (64, 4, 70), (64, 5, 64)])
+def test_ragged_batches_in_order_of_length(batch, H, L, io):
+    """Up to 64 sequences of more than two chunks, on more than 256 workgroups, are ranked by length: at the edges of that rule
+    every sequence gives what it gives in a call of its own."""
+    P, N = 32, 32
+    dec, data, lp, tok, bias, conv_init = _inputs(io, P, N, H, 1, batch, L, seed=batch)
+    lens = np.random.default_rng(batch).choice([0, 1, 5, 32, 33, L - 1, L], size=batch).astype(np.int32)
+
+    def run(first, n):
+        part = lambda a: a[first:first + n]
+        hip = HipLayer(dec.scaled(batch=n), dataclasses.replace(lp, h0=part(lp.h0)), conv_init=part(conv_init))
+        y = torch.full((n, L, H * P), 7.0, dtype=torch.bfloat16 if io == "bf16" else torch.float32, device="cuda")
+        _prefill(hip, {k: part(v) for k, v in tok.items()}, bias, io, L, y, to_dev(part(tok["z"]), io), part(lens))
+        return y, _materialize(hip, bias), hip.cache.ints()
+
+    y, h, ints = run(0, batch)
+    assert ints["pos"].tolist() == lens.tolist() and ints["err_flag"] == 0
+    for b in range(batch):
+        y1, h1, _ = run(b, 1)
+        assert torch.equal(y[b:b + 1], y1) and torch.equal(h[b:b + 1], h1), "sequence %d" % b
+        assert bool((y[b, lens[b]:] == 7).all())
