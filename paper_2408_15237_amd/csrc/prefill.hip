@@ -338,7 +338,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void p
                     sacc = __builtin_amdgcn_mfma_f32_32x32x2f32(sB[(2 * kk + lk) * NP + 32 * (TNL * nh + tn) + li], xop[kk], sacc, 0, 0, 0);
 #pragma unroll
                 for (int v = 0; v < 16; ++v) hacc[tn][v] = fmaf(aq, hacc[tn][v], sacc[v]);
-                if constexpr (TNL >= 4) __builtin_amdgcn_sched_barrier(0);       // one tile's sum at a time: four side by side spill
+                if constexpr (TNL >= 4) __builtin_amdgcn_sched_barrier(0);       // one tile's sum at a time (128 x 128 spills 4 registers so, 7 cut)
             }
         }
         __syncthreads();     // the next chunk overwrites X, B, C, M
@@ -469,16 +469,18 @@ bool prefill_shape_supported(int P, int N)
     return (P == 32 || P == 64 || P == 128) && (N == 32 || N == 64 || N == 128);
 }
 
-// Whether and how a prompt is cut.  The unit is one chunk of a workgroup that has its compute unit to itself (1.8 us with
-// bf16 tensors, 128 x 64): with q workgroups on the fullest compute unit a chunk takes 1.5 of that when the unit is full (r
-// workgroups fit; measured 1.48 at 128 x 64, r = 2, and 1.58 at 64 x 64, r = 4), and linearly less below.  A segment's share of
-// the state alone costs 0.6 of a chunk with outputs, the two further launches 5.  More workgroups than fit at once would run
-// as a second round, which always lost (320 heads x 1500 tokens at 128 x 64: 150 us cut in three, 118 us uncut): not cut.
-// 15 % of expected gain are asked for.  Measured with bf16 tensors, uncut and cut (us; one sequence unless said):
-//   128 x 64, 32 heads:  700 tokens 47 -> 32, 1500: 93 -> 40, 3000: 180 -> 48;  5 sequences, 3000: 182 -> 125
-//   64 x 128, 80 heads:  1500 tokens 115 -> 70, 3000: 221 -> 91;   64 x 64, 4 x 80 heads, 1500: 123 -> 81
-// fp32 tensors (a chunk takes 6.6 us there, a state takes half as many rows of y):
-//   128 x 64, 32 heads:  400 tokens 88 -> 47, 1500: 299 -> 68, 3000: 592 -> 108;   64 x 128, 80 heads, 1500: 351 -> 152
+// Whether and how a prompt is cut.  The unit is one chunk of a workgroup that has its compute unit to itself (1.9 us with
+// bf16 tensors, 128 x 64, 5.8 with fp32).  With q workgroups on the fullest compute unit a chunk takes 1.5 of that when the unit is
+// full (r workgroups fit; measured 1.48 at 128 x 64, r = 2, and 1.58 at 64 x 64, r = 4), and linearly less below; small tiles, of which
+// five and more fit, are counted as four (with the line drawn to 1.5 at r = 5 and 8, bf16, 320 heads x 400 tokens were cut: 64 x 32 32.4 ->
+// 35.5 us, 32 x 32 31.8 -> 33.3).  A segment's share of the state alone costs 0.6 (fp32 0.5) of a chunk with outputs, the two
+// further launches 5 (1.5).  More workgroups than fit at once would run as a second round, which always lost (320 heads x 1500 tokens at 128 x
+// 64: 150 us cut in three, 118 us uncut): not cut.  15 % of expected gain are asked for.  Over nine tiles, 4 to 320 heads and 260 to 3000
+// tokens the choice was within 10 % (fp32) and 24 % (bf16, prompts left uncut) of the best of ten cuts, and never 1 % slower than
+// uncut.  Uncut and cut (us; one sequence unless said):
+//   bf16  128 x 64, 32 heads:  700 tokens 47 -> 32, 1500: 94 -> 42, 3000: 183 -> 49;  5 sequences, 3000: 182 -> 125
+//         64 x 128, 80 heads:  1500 tokens 113 -> 69, 3000: 217 -> 93;   64 x 64, 4 x 80 heads, 1500: 122 -> 84
+//   fp32  128 x 64, 32 heads:  400 tokens 81 -> 41, 1500: 278 -> 66, 3000: 548 -> 106;   64 x 128, 80 heads, 1500: 282 -> 129
 static void choose_segments(PrefillParams &p)
 {
     p.seg_chunks = p.seg_count = p.seg_pass = 0;
@@ -490,14 +492,20 @@ static void choose_segments(PrefillParams &p)
     const int n = (p.L + kPrefillChunk - 1) / kPrefillChunk;
     // the last segment may end with a chunk of one token, and has to hold a state in its rows
     const int shortest = (4 * p.N / es + kPrefillChunk - 1 + kPrefillChunk - 1) / kPrefillChunk;
-    auto chunk_time = [&](long wgs) { return r > 1 ? 1.0 + 0.5 * ((wgs + kCUs - 1) / kCUs - 1) / (r - 1) : 1.0; };
+    auto chunk_time = [&](long wgs) { return r > 1 ? 1.0 + 0.5 * ((wgs + kCUs - 1) / kCUs - 1) / ((r < 4 ? r : 4) - 1) : 1.0; };
     double best = 0.85 * n * chunk_time(pairs);
-    for (int l = shortest; 2 * l < n; ++l) {
-        const int ns = segments_of(l, n), first = n - (ns - 1) * l;
-        const long wgs = pairs * (ns - 1);
-        if (wgs > (long)kCUs * r) continue;
-        const double t = ((first > share * l ? first : share * l) + l) * chunk_time(wgs) + launches;
-        if (t < best) { best = t; p.seg_chunks = l; p.seg_count = ns; }
+    const long most = kCUs * r / pairs + 1 < segments_of(shortest, n) ? kCUs * r / pairs + 1 : segments_of(shortest, n);
+    for (int ns = (int)most; ns >= 3; --ns) {
+        // the segment lengths l that make ns segments; the time max(n - (ns - 1) l, share l) + l falls and then rises with l
+        int lo = (n - 1) / ns + 1, hi = (n - 1) / (ns - 1);
+        if (lo < shortest) lo = shortest;
+        if (hi < lo) continue;
+        const int turn = (int)(n / (ns - 1 + share));
+        for (int l = turn; l <= turn + 1; ++l) {
+            const int len = l < lo ? lo : l > hi ? hi : l, first = n - (ns - 1) * len;
+            const double t = ((first > share * len ? first : share * len) + len) * chunk_time(pairs * (ns - 1)) + launches;
+            if (t < best) { best = t; p.seg_chunks = len; p.seg_count = ns; }
+        }
     }
     if (!p.seg_count) return;
     // y carries states between the launches: not if it overlaps anything that is still to be read

@@ -1,7 +1,9 @@
 """GPU parity of prompts that are cut into segments (csrc/prefill_split.h): few (sequence, head) pairs and a prompt long
 enough, so that the launch would leave most of the chip idle.  Every tile shape; lengths at the edges of chunks and
 segments; sequences of one call that are cut into many segments, two, one, or none at all."""
+import ctypes
 import dataclasses
+import re
 
 import numpy as np
 import pytest
@@ -173,3 +175,67 @@ def test_ragged_batches_in_order_of_length(batch, H, L, io):
         y1, h1, _ = run(b, 1)
         assert torch.equal(y[b:b + 1], y1) and torch.equal(h[b:b + 1], h1), "sequence %d" % b
         assert bool((y[b, lens[b]:] == 7).all())
+
+
+def _launches(call):
+    """Kernel launches of a call: the nodes of a graph it is captured into (and that is not run)."""
+    path = next(m.group() for m in (re.search(r"/\S*libamdhip64\S*", line) for line in open("/proc/self/maps")) if m)
+    side, graph, n = torch.cuda.Stream(), torch.cuda.CUDAGraph(keep_graph=True), ctypes.c_size_t()
+    torch.cuda.synchronize()
+    with torch.cuda.stream(side):
+        graph.capture_begin()
+        call()
+        graph.capture_end()
+    assert ctypes.CDLL(path).hipGraphGetNodes(ctypes.c_void_p(graph.raw_cuda_graph()), None, ctypes.byref(n)) == 0
+    return n.value
+
+
+CUT, UNCUT = 3, 2           # two passes and the launch between them, or one and the bookkeeping
+
+
+def _launches_of(io, P, N, H, batch, L, lens=None, in_place=False):
+    dims = ssmv.make_dims(batch, H, P, N, kmax=4, io=io)
+    cache = ssmv.LayerCache.allocate(dims)
+    new = lambda *s: torch.zeros(*s, dtype=torch.bfloat16 if io == "bf16" else torch.float32, device="cuda")
+    x, y, w, dt, B, C, A = new(batch, L, H * P), new(batch, L, H * P), new(H * P, 4), new(batch, L, H), new(batch, L, 1, N), new(batch, L, 1, N), torch.zeros(H, device="cuda")
+    seq_len = None if lens is None else torch.tensor(lens, dtype=torch.int32, device="cuda")
+    return _launches(lambda: ssmv.ssm_prefill_block(dims, cache.c, x_raw=x, conv_wgt=w, dt=dt, Bm=B, Cm=C, A=A, D=A, L=L, y_out=y, z=y if in_place else None,
+                                                    seq_len=seq_len))
+
+
+@pytest.mark.parametrize("io", ["bf16", "f32"])
+def test_which_prompts_are_cut(io):
+    """The prompts of this file that are to be cut are, those that are not to be are not, and lengths of a call's sequences, which the
+    device knows, do not matter."""
+    for P, N in SHAPES:
+        assert _launches_of(io, P, N, 4, 7, 1200) == _launches_of(io, P, N, 4, 7, 1200, lens=[1] * 7) == CUT, (P, N)
+        assert _launches_of(io, P, N, 4, 7, 64) == UNCUT
+    for L in (1024, 1025, 1535):
+        assert _launches_of(io, 64, 64, 2, 2, L) == CUT and _launches_of(io, 64, 64, 2, 2, L, in_place=True) == UNCUT
+    assert _launches_of(io, 128, 64, 2, 2, 1100) == CUT
+    assert _launches_of(io, 32, 32, 1, 70, 1100) == CUT
+    assert _launches_of(io, 128, 64, 80, 4, 1500) == UNCUT            # as many workgroups as fit without
+    if io == "bf16":                                                  # few chunks of a small tile: the passes cost more than they save
+        assert _launches_of(io, 64, 32, 80, 4, 400) == UNCUT and _launches_of(io, 32, 32, 80, 4, 400) == UNCUT
+
+
+@pytest.mark.parametrize("io", ["bf16", "f32"])
+def test_segments_of_more_sequences_than_lanes(io):
+    """A ragged batch of more than 64 sequences, cut: workgroups take the sequences as they come."""
+    P, N, H, batch, L = 32, 32, 1, 70, 1100
+    dec, data, lp, tok, bias, conv_init = _inputs(io, P, N, H, 1, batch, L, seed=41)
+    lens = np.random.default_rng(41).choice([0, 1, 31, 64, 65, 200], size=batch).astype(np.int32)
+    lens[[3, 40, 69]] = L, 700, L - 1
+    hip = HipLayer(dec, lp, conv_init=conv_init)
+    y = torch.full((batch, L, H * P), 7.0, dtype=torch.bfloat16 if io == "bf16" else torch.float32, device="cuda")
+    _prefill(hip, tok, bias, io, L, y, None, lens)
+    y_h, h_g = to_host(y), to_host(_materialize(hip, bias))
+    for b, n in enumerate(int(v) for v in lens):
+        ora = oracle.EagerOracle("scalar", lp.A, lp.D, lp.conv_w, lp.conv_b, lp.h0[b:b + 1], io, dec.conv_act, 1, dt_bias=bias, dt_softplus=True,
+                                 conv_init=conv_init[b:b + 1])
+        if n:
+            y_ref, _, _ = ora.verify(*(tok[m][b:b + 1, :n] for m in ("x", "dt", "B", "C")))
+            ora.commit([n])
+            assert rel_err(y_h[b, :n], y_ref[0]) <= TOL[io], "sequence %d" % b
+        assert np.all(y_h[b, n:] == 7.0) and rel_err(h_g[b:b + 1], ora.h) <= TOL[io], "sequence %d" % b
+    assert hip.cache.ints()["pos"].tolist() == lens.tolist()
