@@ -62,14 +62,18 @@ template <bool SEG>
 __device__ __forceinline__ PrefillItem prefill_item(const PrefillParams &p)
 {
     PrefillItem w;
-    const unsigned item = p.seq_len ? blockIdx.x : xcd_contiguous(blockIdx.x, gridDim.x), q = item / (unsigned)p.H;
-    w.hd = (int)(item - q * p.H);
-    w.slot = SEG ? (int)(q / (unsigned)p.batch) : 0;
-    w.b = (int)(q - w.slot * (unsigned)p.batch);
+    auto take = [&](unsigned item) {
+        const unsigned q = item / (unsigned)p.H;
+        w.hd = (int)(item - q * p.H);
+        w.slot = SEG ? (int)(q / (unsigned)p.batch) : 0;
+        w.b = (int)(q - w.slot * (unsigned)p.batch);
+    };
     if (!p.seq_len) {
+        take(xcd_contiguous(blockIdx.x, gridDim.x));
         w.L = p.L;
         return w;
     }
+    take(blockIdx.x);
     if (p.batch <= 64 && p.L > 2 * kPrefillChunk && p.H * p.batch > 256) {
         // lane j knows sequence j: the one with w.b longer ones ahead of it.
         // (len, lane) as one number, all different: a rank is a count of greater ones.  Eight at a time: lanes without a sequence
