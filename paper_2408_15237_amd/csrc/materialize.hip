@@ -4,7 +4,7 @@
 // rows; tiles change into rows through a patch of LDS of the wave's own.  (Out of the tiles in 16-byte pieces, as the vector
 // verify kernel reads them, 32 x 32 x 128 x 64 took 21.8 us, so 10.1; 5 x 80 x 64 x 128: 6.0, 4.3; 1 x 32 x 128 x 64: 3.0, 2.3.)
 // Row-major slots with N > 64: as many rows as make 4 KiB, so that a launch has workgroups enough and wastes few rows on a headdim
-// that 64 does not divide.  (fp32, 31 x 13 x 70 x 256: 14.1 us with 16 rows, 10.8 so, as the vector verify kernel; 28 x 2 x 128 x 256: 3.8, 3.1.)
+// that 64 does not divide.  (fp32, 31 x 13 x 70 x 256: 14.1 us with 16 rows, 10.9 on the vector verify kernel, 10.1 so; 28 x 2 x 128 x 256: 3.8, 3.8, 3.1.)
 // The pending tokens: h <- 2^(A sum dt) h + sum_s w_s x_s (x) B_s with w_s = dt_s 2^(A sum_{u > s} dt_u), all in fp32, taken
 // backwards so that the exponent is a running sum - of A dt, not A times a sum that starts at 0: a head with A = -inf (or A log2 e
 // beyond fp32's range) keeps its newest token with weight dt, as exp(dt A) = 0 of the stepwise form has it.

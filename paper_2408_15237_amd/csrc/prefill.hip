@@ -15,8 +15,9 @@
 // columns = channel): a lane's register of a tile is then directly the A operand of C h^T (its two k slots are rows n and n + 4)
 // and the update ends in place; the chunk's X, B, C are in LDS as fp32, X is read once for both of its products.
 // (With the state in LDS, read for C h^T and read and written back for the update, a chunk took 256 instead of about 90 LDS
-// instructions per wave.  16 x 512 tokens of 32 heads x 128 x 128: 488 -> 240 us; 8 x 512 of 80 x 64 x 128: 293 -> 241; 32 x 512 of 32 x
-// 128 x 64: 321 -> 304.  The products alone, 80 of 64 cycles each per wave and chunk at 128 x 64, would take 0.6 of that time.)
+// instructions per wave.  16 x 512 tokens of 32 heads x 128 x 128: 473 -> 238 us; 8 x 512 of 80 x 64 x 128: 283 -> 236; 32 x 512 of 32 x
+// 128 x 64: 311 -> 295.  Scaling C by exp(cum_t) ahead of the product and not the sums behind it is 1 to 3 % of that: 229, 233, 291.)
+// (The products alone, 80 of 64 cycles each per wave and chunk at 128 x 64, would take 0.6 of that time.)
 // v_mfma_f32_32x32x2_f32 operands: A[i = lane%32][k = lane/32], B[k = lane/32][j = lane%32]; result register v of
 // a lane is D[8*(v/4) + 4*(lane/32) + v%4][lane%32]; v_mfma_f32_16x16x4_f32 (used for the Q x Q product, one
 // quadrant per wave): A[i = lane%16][k = lane/16], B[k = lane/16][j = lane%16], D[4*(lane/16) + v][lane%16].  Rows of

@@ -12,12 +12,12 @@
 //     four tokens), which is where they are scaled, gated and stored;
 //   * what does not depend on the cache's integers (this call's tokens, taps, A) is requested ahead of them, the rest right
 //     behind: two round trips to memory before the first step.
-// Measured (all layers of a round, conv fused, bf16): one sequence, 8192 channels x 16, k = 8, 24 layers 192 -> 117 us; 24
-// sequences x 5120 channels, ragged k = 6, softplus and SiLU, four layers 60 -> 45 us (500 vector instructions for a wave's 32
+// Measured (all layers of a round, conv fused, bf16): one sequence, 8192 channels x 16, k = 8, 24 layers 193 -> 117 us; 24
+// sequences x 5120 channels, ragged k = 6, softplus and SiLU, four layers 63 -> 47 us (500 vector instructions for a wave's 32
 // channels, where verify_impl.h took 404 for 16).  What is left: at small batch two round trips to memory and the launch itself, at
 // large batch the vector instructions (about half of them exp, softplus and SiLU).
-// (verify_impl.h, which stages the tokens in
-// LDS as fp32 and walks them one at a time, keeps ssmv_materialize and explicitly chosen launch shapes.)
+// (verify_impl.h, which stages the tokens in LDS as fp32 and walks them one at a time, keeps ssmv_materialize of these caches and
+// explicitly chosen launch shapes.)
 #include <type_traits>
 
 #include "verify_impl.h"

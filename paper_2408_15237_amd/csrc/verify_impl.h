@@ -23,6 +23,8 @@
 //     of the row with DPP row operations; the row's first lane adds it to D*x in LDS with a
 //     no-return LDS add, and the workgroup writes y with 16-byte stores at the end.
 //   * Diagonal A: the rounds of a decoder run on verify_diag.hip; here it serves ssmv_materialize and chosen launch shapes.
+//   * ssmv_materialize of scalar caches runs on materialize.hip; here (k = 0, h_out) only with a chosen launch shape, as the
+//     second implementation that the other is tested against.
 //   * The state is read and the snapshots are written with non-temporal accesses: each byte is touched
 //     once per round and a decoder streams the model's weights through the caches before the next one.
 //     (Mixing a temporal and a non-temporal access to one address under an `if` lets the optimiser merge
@@ -161,8 +163,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void v
     const unsigned loff0 = (lrow0 << LOG2N) + sub * 4;
     const int nvalid = rows_dom - (int)(row0 + lrow0);
     // element offset, inside a slot, of strip v of the lane's row r.  Row-major slots: the lane's rows are N apart.  Tiled
-    // slots (scalar mode, state_off4): 16-byte pieces scattered over the tiles - this kernel then only serves the calls
-    // the matrix-core kernel does not take (materialize, an explicitly chosen launch shape).
+    // slots (scalar mode, state_off4): 16-byte pieces scattered over the tiles - this kernel then only serves calls with an
+    // explicitly chosen launch shape.
     const bool tiled = !DIAG && p.tiled;
     // uniform base of the workgroup inside a slot plus a 32-bit lane offset
     const size_t slot_base = tiled ? ((size_t)b * p.H + hd) * p.P * N : (grow << LOG2N);
