@@ -598,7 +598,8 @@ def main():
                 traffic = float(line.split(":")[1])
     roofline = {"bound": "hbm", "achieved": round(achieved, 1), "peak": PEAK_HBM_GBPS, "unit": "GB/s",
                 "frac": round(achieved / PEAK_HBM_GBPS, 4), "traffic": traffic,
-                "kernel": ("verify_mfma_kernel" if matrix_engine and args.rows == 0 and args.waves == 0 else "verify_kernel") +
+                "kernel": ("verify_kernel" if args.rows or args.waves else "verify_mfma_kernel" if matrix_engine else
+                           "verify_diag_kernel" if wl.a_mode == "diag" else "verify_kernel") +
                           (" (conv roll fused, one token appended to the round)" if args.draft else " (conv roll fused)" if fused else ""),
                 "avg_launch_us": round(avg_ms * 1e3, 3),
                 "median_launch_us": round(durs[len(durs) // 2] * 1e3, 3),
