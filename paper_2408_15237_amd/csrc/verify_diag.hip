@@ -124,8 +124,7 @@ void verify_diag_kernel(const int32_t *a_cur, const int32_t *a_pend, const int32
     const bool have = c0 < H;
     const int cc = have ? c0 : H - R;                    // quads past the end read the last channels again and store nothing
     // this sequence's part of every array: uniform bases, behind which all lane offsets fit 32 bits of bytes (the host refuses
-    // rows of 2^22 elements and more; a token's row index is < 16 and multiplied on the 24-bit multiplier).  Not so the conv
-    // ring, whose length the caller chooses: its rows are 64-bit offsets of a full product (fewer than 2^31 elements, host)
+    // rows of 2^22 elements and more, and longer conv rings do not get here: ring_fits), row numbers the 24-bit multiplier
     constexpr size_t ES = IO == SSMV_BF16 ? 2 : 4;
     const size_t tok_in = (size_t)b * k, tok_win = (size_t)b * p.win_tokens;
     auto seq = [&](const void *base, size_t rows, int len) { return const_cast<char *>(static_cast<const char *>(base) + rows * len * ES); };
@@ -204,9 +203,8 @@ void verify_diag_kernel(const int32_t *a_cur, const int32_t *a_pend, const int32
     }
     const int ring_mask = p.ring_len - 1, conv_head = (ch_raw + t0) & ring_mask;       // newest raw input fed so far
     char *ring_b = seq(p.ring, (size_t)b * p.ring_len, H);
-    auto ring_row = [&](int r) { return ring_b + (size_t)((unsigned)(r & ring_mask) * (unsigned)H) * ES; };
     CV hist;
-    if constexpr (CONV) hist = CV::load(ring_row(conv_head - 3 + (int)sub), cc);                 // token sub - 4
+    if constexpr (CONV) hist = CV::load(ring_b, row_at((conv_head - 3 + (int)sub) & ring_mask, H, cc));   // token sub - 4
     // B rows and C rows into LDS as fp32 (rows of no token are not read back)
     const char *B_b = seq(p.Bm, tok_in, N), *C_b = seq(p.Cm, tok_in, N);
     auto bc_item = [&](int i, uint4 &raw, int &t, bool &is_c) {
@@ -297,7 +295,7 @@ void verify_diag_kernel(const int32_t *a_cur, const int32_t *a_pend, const int32
                     s[r] = acc;
                 }
                 xc = CV::encode(s);                      // what is fed on is what is stored
-                if (on && have) xr[j].store(ring_row(conv_head + 1 + t), cc);
+                if (on && have) xr[j].store(ring_b, row_at((conv_head + 1 + t) & ring_mask, H, cc));
             }
             if (on && have) {
                 const unsigned o = row_at(slot_out(t), H, cc);
@@ -418,13 +416,21 @@ int launch_groups(const VerifyParams &p, int waves, hipStream_t stream)
 
 }  // namespace
 
+// The ring's length is the caller's choice, and here a sequence's ring has to lie within 32 bits of bytes and its row
+// numbers within the (signed) 24-bit multiplier.  verify_impl.h takes any: a ring of 4 GiB or 2^23 rows goes there.  (64-bit
+// offsets of a full product here instead: rotating over 600 MB of caches, k up to 4, 3.61 -> 3.83, 3.71 -> 3.92 us.)
+static bool ring_fits(const VerifyParams &p)
+{
+    return !p.x_raw || (p.ring_len <= 1 << 23 && (size_t)p.ring_len * p.H * (p.io == SSMV_BF16 ? 2 : 4) <= (size_t)1 << 32);
+}
+
 // Two channels per quad with bf16 tokens and 16 states (one 4-byte access then serves both): 24 sequences x 5120 channels,
 // ragged k = 6, four layers 45.4 against 50.3 us, one sequence of 8192 channels, k = 8, 24 layers 116.7 against 119.3.  With fp32 tokens
 // or 32 states one channel is faster (51.2 against 51.8, 40.3 against 42.7 us).  Four waves per workgroup share B and C where
 // there are workgroups for every compute unit even so, fewer where the chip would not fill.
 int launch_verify_diag(const VerifyParams &p, VerifyShape shape, hipStream_t stream)
 {
-    if (shape.forced || p.h_out) return launch_verify_any<true>(p, shape, stream);
+    if (shape.forced || p.h_out || !ring_fits(p)) return launch_verify_any<true>(p, shape, stream);
     const bool bf16 = p.io == SSMV_BF16, two = bf16 && p.N == 16 && p.H % 2 == 0;
     const long quads = (long)p.batch * p.H / (two ? 2 : 1);
     const int waves = quads >= 32768 ? 4 : quads >= 8192 ? 2 : 1;

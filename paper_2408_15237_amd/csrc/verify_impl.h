@@ -22,7 +22,8 @@
 //   * y_t[row] = sum_n C_t[n] h[row][n] is EPL FMAs in-lane, then a reduction over the LPR lanes
 //     of the row with DPP row operations; the row's first lane adds it to D*x in LDS with a
 //     no-return LDS add, and the workgroup writes y with 16-byte stores at the end.
-//   * Diagonal A: the rounds of a decoder run on verify_diag.hip; here it serves ssmv_materialize and chosen launch shapes.
+//   * Diagonal A: the rounds of a decoder run on verify_diag.hip; here it serves ssmv_materialize, chosen launch shapes
+//     and conv rings too long for that kernel's 32-bit offsets.
 //   * ssmv_materialize of scalar caches runs on materialize.hip; here (k = 0, h_out) only with a chosen launch shape, as the
 //     second implementation that the other is tested against.
 //   * The state is read and the snapshots are written with non-temporal accesses: each byte is touched
