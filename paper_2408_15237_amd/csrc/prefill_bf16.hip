@@ -18,8 +18,16 @@
 // shape the registers of a lane (its channel, 16 of the 32 n of a tile) are directly the k-slots of the A operand of
 // h C^T, so the state never visits LDS; the result tile comes out as [channel][token], a lane holding runs of four
 // adjacent channels of its token (the wave turns the tile through a patch of LDS of its own into 64-byte rows for the
-// stores).  G^T (32 x 32) is computed by every wave (four products, the matrix pipe has slack); each wave finishes a
-// quarter of its registers into M^T (mask, decay, dt_s, D on the diagonal, head and tail) and shares it through LDS.
+// stores).  G^T comes in 16 x 16 quadrants on v_mfma_f32_16x16x32_bf16: the three that are not above the diagonal go round the
+// waves, each finishes its own into M^T (mask, decay, dt_s, D on the diagonal) and shares it through LDS.
+// What a chunk costs is its instructions, vector ones above all (two waves per SIMD, neither the matrix pipe nor LDS nor memory
+// more than half busy).  So: raw inputs and B leave LDS through the transposing read (read_tr16), four tokens of a channel per lane
+// and instruction, already paired for the conv's dot products; the addend of those is an operand (conv8); G is computed once, not by
+// every wave; lane offsets of all global accesses stay the same over the chunks; SiLU is exp2 and rcp.  With single 16-bit
+// LDS reads, pairs put together by shifts, G in every wave, 64-bit addresses formed per access and a SiLU of expf and a division a
+// wave took 316 vector, 18 matrix and 67 LDS instructions per chunk at 128 x 64, so 221, 15.5 and 42 (605 -> 365 vector ones at
+// 64 x 128 with SiLU).  32 x 2048 tokens of 32 heads x 128 x 64: 348 -> 298 us; 5 ragged x 700 of 80 x 64 x 128 with SiLU, gate and
+// softplus 75.2 -> 61.4; 16 x 1024: 64 heads x 64 x 64 112 -> 105, 64 x 32 x 64 102 -> 83, 64 x 32 x 32 73 -> 58, 32 x 128 x 128 206 -> 172.
 // Operand layout (checked on the hardware): A[i = lane%32][k = 8 (lane/32) + j], B[k = 8 (lane/32) + j][col = lane%32],
 // j = 0..7 the elements of the lane's 16-byte operand; result register v of a lane is row 8 (v/4) + 4 (lane/32) + v%4,
 // column lane%32.  Registers 8 st .. 8 st + 7 of a result tile, used as the operand of step st of a following
@@ -39,7 +47,6 @@ namespace ssmv {
 
 typedef float f16v __attribute__((ext_vector_type(16)));
 typedef __bf16 bf8 __attribute__((ext_vector_type(8)));
-typedef __bf16 bf2 __attribute__((ext_vector_type(2)));
 
 namespace {
 
@@ -62,7 +69,8 @@ struct PfLds {              // byte offsets of the LDS arrays (bf16 unless said)
     static constexpr int YS = 32 * 2 + 16;                 // row stride of a wave's output tile [token][32 channels]
     static constexpr int oY = oMh + kQ * XS;               // [NP][Q][32]  the output tiles, for stores of whole 64-byte rows
     // filled by loads that go from global memory straight into LDS (1 KB per wave and instruction, lane l at byte 16 l):
-    static constexpr int oZ = oY + NP * kQ * YS;           // fp32 [NP][16][64]  h C^T over the second half of n, for the tile's first wave
+    static constexpr int YT = kQ * YS + 64;                // stride of the tiles: a row of all tiles then covers the banks
+    static constexpr int oZ = oY + NP * YT;           // fp32 [NP][16][64]  h C^T over the second half of n, for the tile's first wave
     static constexpr int oXraw = oZ + (NSPL - 1) * NP * 4096;        // [Q][P]  raw conv inputs of the chunk, rows of 2 P bytes
     static constexpr int BCS = kQ * N * 2;                 // one copy of B or C: [Q][N], rows of 2 N bytes, 16-byte pieces swizzled
     // Two copies of B and C (chunks alternate; the next chunk's are requested at the start of this one's arithmetic) where
@@ -72,15 +80,22 @@ struct PfLds {              // byte offsets of the LDS arrays (bf16 unless said)
     static constexpr int BCC = (P >= 128 && N < 128) ? 2 : 1;
     static constexpr int oB = oXraw + kQ * P * 2;
     static constexpr int oC = oB + BCC * BCS;
-    static constexpr int oCar = oC + BCC * BCS;              // fp32 [2][3][P]  the last three raw inputs of a chunk, for the next one's conv
-    static constexpr int oCum = oCar + 2 * 3 * P * 4;      // fp32 [NW][Q]  log2 e times the inclusive prefix of dt*A (a copy per wave)
+    static constexpr int oCar = oC + BCC * BCS;              // [2][P][4]  the last four raw inputs of a chunk, for the next one's conv
+    static constexpr int oCum = oCar + 2 * P * 8;          // fp32 [NW][Q]  log2 e times the inclusive prefix of dt*A (a copy per wave)
     static constexpr int oDt = oCum + NW * kQ * 4;         // fp32 [NW][Q]  dt
     static constexpr int oW = oDt + NW * kQ * 4;           // fp32 [NW][Q]  exp(cum_Q - cum_s) dt_s
     static constexpr int total = oW + NW * kQ * 4;
-    // Rows of B and C are 2 N bytes with no padding (the direct loads fill LDS contiguously), so the 16-byte pieces of row r
-    // sit at piece index (logical index ^ swz(r)): 16 consecutive rows then spread a 16-byte column read over all banks.
+    // The direct loads fill rows without padding, so the 16-byte pieces of row r of x, B and C sit at piece index (logical index ^
+    // key(r)).  A cycle serves 256 bytes: 16 lanes that read one logical piece out of 16 consecutive rows (operands of the
+    // products; B and C only), or 32 lanes of a transposing read, four adjacent pieces out of each of four rows.  So the rows that
+    // fall onto the same banks take different keys, and in the key's upper bits, which move groups of four pieces, if they
+    // are among the same four rows.
     static constexpr int PIECES = N / 8;
-    static __host__ __device__ constexpr int swz(int r) { return PIECES == 16 ? (r & 15) : PIECES == 8 ? ((r ^ (r >> 3)) & 7) : ((r >> 2) & 3); }
+    static __host__ __device__ constexpr int swz(int r)
+    {
+        return PIECES == 16 ? ((r & 3) << 2) | ((r >> 2) & 3) : PIECES == 8 ? ((r & 2) << 1) | ((r & 4) >> 1) | ((r & 8) >> 3) : (r >> 2) & 3;
+    }
+    static __host__ __device__ constexpr int swzx(int r) { return P == 128 ? (r & 3) << 2 : P == 64 ? (r & 2) << 1 : 0; }
 };
 
 typedef __attribute__((address_space(3))) char lds_char_t;
@@ -89,12 +104,50 @@ typedef __attribute__((address_space(3))) char lds_char_t;
 // same in all lanes and travels in M0).  Issued from assembly, so that the compiler does not count these loads: it would
 // otherwise wait for them before the next LDS read that it cannot prove to be disjoint from their target, and at every
 // workgroup barrier.  The kernel waits for them itself (wait_direct_loads) ahead of the barrier that publishes the data.
-__device__ __forceinline__ void load_to_lds16(const void *src, const char *dst)
+// The address is a base that is the same in all lanes plus an unsigned byte offset.
+__device__ __forceinline__ void load_to_lds16(const void *base, uint32_t offset, const char *dst)
 {
     const unsigned lds_addr = (unsigned)(size_t)(lds_char_t *)dst;
-    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(src), "s"(lds_addr) : "memory", "m0");
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(offset), "s"(base), "s"(lds_addr) : "memory", "m0");
 }
 __device__ __forceinline__ void wait_direct_loads() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
+// Transposing LDS read: in every 16 lanes, lane i gets element i % 4 of the 8 bytes at the address of each of the lanes i / 4,
+// 4 + i / 4, 8 + i / 4, 12 + i / 4 (checked on the hardware).  With lane j's address in row j / 4, 8 bytes j % 4 of 32, that is
+// column i of four rows.
+__device__ __forceinline__ uint2 read_tr16(const char *at)
+{
+    typedef short s4 __attribute__((ext_vector_type(4)));
+    typedef __attribute__((address_space(3))) s4 lds_s4;
+    return __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4 *)(lds_char_t *)at));
+}
+
+// Eight outputs of the conv from packed pairs of raw inputs (e: even-aligned, o: odd-aligned): x_(2i) = bias + w01 . o[i] + w23 .
+// o[i + 1], x_(2i+1) = bias + w01 . e[i] + w23 . e[i + 1]; products exact, sums in fp32, the pair (w0, w1) first.  In assembly for the
+// form with an addend of its own: the compiler takes the accumulating one and copies the bias ahead of each (16 of a chunk's
+// 92 instructions for the conv).  A result of a dot product may be read three instructions later at the earliest: s_nop.
+__device__ __forceinline__ void conv8(float (&x)[8], const uint32_t *o, const uint32_t *e, uint32_t w01, uint32_t w23, float bias)
+{
+    asm("v_dot2_f32_bf16 %0, %18, %8, %20\n\t"
+        "v_dot2_f32_bf16 %1, %18, %13, %20\n\t"
+        "v_dot2_f32_bf16 %2, %18, %9, %20\n\t"
+        "v_dot2_f32_bf16 %3, %18, %14, %20\n\t"
+        "v_dot2_f32_bf16 %4, %18, %10, %20\n\t"
+        "v_dot2_f32_bf16 %5, %18, %15, %20\n\t"
+        "v_dot2_f32_bf16 %6, %18, %11, %20\n\t"
+        "v_dot2_f32_bf16 %7, %18, %16, %20\n\t"
+        "v_dot2_f32_bf16 %0, %19, %9, %0\n\t"
+        "v_dot2_f32_bf16 %1, %19, %14, %1\n\t"
+        "v_dot2_f32_bf16 %2, %19, %10, %2\n\t"
+        "v_dot2_f32_bf16 %3, %19, %15, %3\n\t"
+        "v_dot2_f32_bf16 %4, %19, %11, %4\n\t"
+        "v_dot2_f32_bf16 %5, %19, %16, %5\n\t"
+        "v_dot2_f32_bf16 %6, %19, %12, %6\n\t"
+        "v_dot2_f32_bf16 %7, %19, %17, %7\n\t"
+        "s_nop 2"
+        : "=&v"(x[0]), "=&v"(x[1]), "=&v"(x[2]), "=&v"(x[3]), "=&v"(x[4]), "=&v"(x[5]), "=&v"(x[6]), "=&v"(x[7])
+        : "v"(o[0]), "v"(o[1]), "v"(o[2]), "v"(o[3]), "v"(o[4]), "v"(e[0]), "v"(e[1]), "v"(e[2]), "v"(e[3]), "v"(e[4]), "v"(w01), "v"(w23), "v"(bias));
+}
 
 // two fp32 values -> packed bf16 heads and packed bf16 tails (first value in the low half)
 __device__ __forceinline__ void split2(float a, float b, uint32_t &hi, uint32_t &lo)
@@ -110,6 +163,8 @@ __device__ __forceinline__ bf8 as_bf8(uint32_t a, uint32_t b, uint32_t c, uint32
 }
 __device__ __forceinline__ bf8 as_bf8(uint4 u) { return __builtin_bit_cast(bf8, u); }
 
+typedef float f4v __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ f4v mfma16(bf8 a, bf8 b, f4v c) { return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0); }
 __device__ __forceinline__ f16v mfma(bf8 a, bf8 b, f16v c) { return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0); }
 
 // inclusive prefix sums over lanes 0..31 and, separately, over lanes 32..63 (rows of 16 lanes: shifts inside a row,
@@ -167,7 +222,7 @@ void prefill_bf16_kernel(const PrefillParams p)
     extern __shared__ float4 lds_raw[];
     char *lds = reinterpret_cast<char *>(lds_raw);
     char *sX = lds + Ld::oX, *sBh = lds + Ld::oBh, *sBl = lds + Ld::oBl, *sMh = lds + Ld::oMh, *sXraw = lds + Ld::oXraw;
-    uint32_t *sCar = reinterpret_cast<uint32_t *>(lds + Ld::oCar);
+    uint2 *sCar = reinterpret_cast<uint2 *>(lds + Ld::oCar);
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
 #ifdef SSMV_TRACE
@@ -178,7 +233,7 @@ void prefill_bf16_kernel(const PrefillParams p)
     const int wave_u = __builtin_amdgcn_readfirstlane(wave);
     const int pt = Ld::NSPL == 1 ? wave_u : wave_u % Ld::NP;   // the wave's 32-channel tile
     const int nh = Ld::NSPL == 1 ? 0 : wave_u / Ld::NP;        // and its half of n (0 unless the state is split)
-    char *sY = lds + Ld::oY + pt * (Q * Ld::YS);
+    char *sY = lds + Ld::oY + pt * Ld::YT;
     float *sCum = reinterpret_cast<float *>(lds + Ld::oCum) + wave * Q;
     float *sDt = reinterpret_cast<float *>(lds + Ld::oDt) + wave * Q;
     float *sW = reinterpret_cast<float *>(lds + Ld::oW) + wave * Q;
@@ -226,24 +281,24 @@ void prefill_bf16_kernel(const PrefillParams p)
             else if (p.seg_pass == 1) v = *seg_at(tn, q, seg.area);
             hacc[tn][4 * q + 0] = v.x; hacc[tn][4 * q + 1] = v.y; hacc[tn][4 * q + 2] = v.z; hacc[tn][4 * q + 3] = v.w;
         }
-    // Every wave computes G^T whole (rows s, columns t = li) and finishes the 16 / (waves) of its registers that are its
-    // share of M^T: register 4 q + e is token s = 8 q + 4 lh + e.  The causal mask, and the skip term D on the diagonal:
-    constexpr int RW = 4 / Ld::NW;                       // register quads per wave
-    float dadd[4 * RW];
-    bool keep[4 * RW];
+    // G^T and M^T in 16 x 16 quadrants (tokens t of the first or second half of the chunk, s likewise; lane: t = 16 qi + lane % 16,
+    // s = 16 qj + 4 (lane / 16) + v): (0,0), (1,0) and (1,1) go round the waves, the fourth is all s > t and stays zero.
+    // In the diagonal ones the causal mask, and the skip term D where s = t:
+    const int l16 = lane & 15, k4 = lane >> 4;
+    float dadd[4];
+    bool keep[4];
 #pragma unroll
-    for (int r = 0; r < 4 * RW; ++r) {
-        const int s = 8 * (RW * wave + r / 4) + 4 * lh + r % 4;
-        keep[r] = s <= li;
-        dadd[r] = s == li ? D_h : 0.f;
+    for (int v = 0; v < 4; ++v) {
+        keep[v] = 4 * k4 + v <= l16;
+        dadd[v] = 4 * k4 + v == l16 ? D_h : 0.f;
     }
+    if (tid < 32) *reinterpret_cast<uint4 *>(sMh + (tid >> 1) * XS + 32 + (tid & 1) * 16) = make_uint4(0u, 0u, 0u, 0u);
     // this thread's conv channel: weights and bias stay in registers for the whole prompt
     const int pc = tid % P;
     const int sg = P >= 64 ? __builtin_amdgcn_readfirstlane(tid / P) : tid / P;      // uniform over a wave when P >= 64
     const unsigned ch = hd * P + pc;
     // the four taps as two packed pairs (they are bf16 in memory): the conv is two bf16 dot products per token
     const uint2 wraw = *reinterpret_cast<const uint2 *>(reinterpret_cast<const uint16_t *>(p.wgt) + (size_t)ch * W);
-    const bf2 w01 = __builtin_bit_cast(bf2, wraw.x), w23 = __builtin_bit_cast(bf2, wraw.y);
     const float cbias = p.bias ? load_io(p.bias, ch, SSMV_BF16) : 0.f;
     // One base pointer per tensor that is uniform over the workgroup plus an element offset; tokens are clamped into
     // the prompt, so every load is unconditional: a token before the prompt is replaced by the ring history, tokens past
@@ -253,49 +308,77 @@ void prefill_bf16_kernel(const PrefillParams p)
     const uint16_t *B_b = reinterpret_cast<const uint16_t *>(p.Bm) + (size_t)b * Ls * GN + (size_t)g * N;
     const uint16_t *C_b = reinterpret_cast<const uint16_t *>(p.Cm) + (size_t)b * Ls * GN + (size_t)g * N;
     const uint16_t *dt_b = reinterpret_cast<const uint16_t *>(p.dt) + (size_t)b * Ls * H + hd;
-    auto off = [](int token, int stride, int rest) { return (size_t)(unsigned)(__umul24(token, stride) + rest); };
+    auto off = [](int token, int stride, int rest) { return 2u * (__umul24(token, stride) + (unsigned)rest); };     // in bytes
+    // the same for a chunk's first row (uniform)
+    auto chunk_of = [](const void *base, int c, int stride) { return static_cast<const char *>(base) + (size_t)c * Q * stride * 2; };
     auto clampL = [&](int tg) { return tg < 0 ? 0 : (tg < L ? tg : L - 1); };
     auto raw_bits = [&](int tg) { return (uint32_t)(x_b + (size_t)clampL(tg) * HP)[ch]; };    // uniform row pointer, 32-bit lane offset
-    // the W-1 raw inputs ahead of the prompt (newest last)
-    uint32_t hist[W - 1];                               // as bits
+    // the W-1 raw inputs ahead of the first chunk (newest last), where the conv finds those of the chunk before
+    if (tid < P) {
+        uint32_t hist[W - 1];                           // as bits
 #pragma unroll
-    for (int j = 0; j < W - 1; ++j) {
-        if (SEG && c_beg > 0) hist[j] = raw_bits(c_beg * Q - (W - 1) + j);
-        else hist[j] = reinterpret_cast<const uint16_t *>(p.ring)[((size_t)b * p.ring_len + ((conv_head + 1 - (W - 1) + j) & mask)) * HP + ch];
+        for (int j = 0; j < W - 1; ++j) {
+            if (SEG && c_beg > 0) hist[j] = raw_bits(c_beg * Q - (W - 1) + j);
+            else hist[j] = reinterpret_cast<const uint16_t *>(p.ring)[((size_t)b * p.ring_len + ((conv_head + 1 - (W - 1) + j) & mask)) * HP + ch];
+        }
+        sCar[((c_beg + 1) & 1) * P + pc] = make_uint2(hist[0] << 16, hist[1] | (hist[2] << 16));
     }
 
     constexpr int UI = (4 * N + NT - 1) / NT;           // (n, eight tokens) units of the transposed B per thread and chunk
     // The chunk's raw x, B and C rows go from global memory straight into LDS, 1 KB per wave and instruction (lane l's 16
     // bytes land at byte 16 l of the destination): no registers hold them while they are under way, and a chunk costs a
     // wave 4 to 6 load instructions instead of 30.  dt (one value per lane) takes the ordinary way.
-    auto issue_x_loads = [&](int c, uint32_t &dt_bits) {
-        const int t0 = c * Q;
-        auto tok = [&](int row) { return min(t0 + row, L - 1); };
-        constexpr int LR = P / 8;                       // lanes per row of x, 64 / LR rows per instruction, P / 16 instructions
-        constexpr int XPW = 2 / NSPL;                   // of them per wave
+    // Every address is the chunk's first row (uniform) plus a lane offset that stays the same over the chunks; a last chunk that is
+    // not full reads its last token again for the rows behind it.
+    constexpr int LR = P / 8;                           // lanes per row of x, 64 / LR rows per instruction, P / 16 instructions
+    constexpr int XPW = 2 / NSPL;                       // of them per wave
+    constexpr int BPW = (PIECES / 2 + Ld::NW - 1) / Ld::NW;      // PIECES / 2 instructions cover the 32 rows of B, and of C
+    uint32_t ox[XPW], obc[BPW], odt;
+    auto lane_offsets = [&](int last) {                 // last: the chunk's last row that is there
 #pragma unroll
         for (int k = 0; k < XPW; ++k) {
-            const int idx = XPW * wave_u + k;
-            const int row = idx * (64 / LR) + lane / LR, piece = lane % LR;
-            load_to_lds16(x_b + off(tok(row), HP, hd * P + piece * 8), sXraw + idx * 1024);
+            const int row = (XPW * wave_u + k) * (64 / LR) + lane / LR;
+            ox[k] = off(min(row, last), HP, hd * P + ((lane % LR) ^ Ld::swzx(row)) * 8);
         }
-        dt_bits = dt_b[off(tok(li), H, 0)];
+#pragma unroll
+        for (int k = 0; k < BPW; ++k) {
+            const int row = (wave_u + k * Ld::NW) * (64 / PIECES) + lane / PIECES;
+            obc[k] = off(min(row, last), GN, ((lane % PIECES) ^ Ld::swz(row)) * 8);
+        }
+        odt = off(min(li, last), H, 0);
     };
-    auto issue_bc_loads = [&](int c) {
-        const int t0 = c * Q;
-        auto tok = [&](int row) { return min(t0 + row, L - 1); };
+    lane_offsets(Q - 1);
+    auto issue_x_loads = [&](int c, uint32_t &dt_bits) {
+        if (c * Q + Q > L) lane_offsets(L - 1 - c * Q);
+        const char *xc = chunk_of(x_b, c, HP);
+#pragma unroll
+        for (int k = 0; k < XPW; ++k) load_to_lds16(xc, ox[k], sXraw + (XPW * wave_u + k) * 1024);
+        dt_bits = *reinterpret_cast<const uint16_t *>(chunk_of(dt_b, c, H) + odt);
+    };
+    auto issue_bc_loads = [&](int c) {                  // behind issue_x_loads of the same chunk
+        const char *Bc = chunk_of(B_b, c, GN), *Cc = chunk_of(C_b, c, GN);
         char *dB = lds + Ld::oB + (c & (Ld::BCC - 1)) * Ld::BCS, *dC = lds + Ld::oC + (c & (Ld::BCC - 1)) * Ld::BCS;
 #pragma unroll
-        for (int k = 0; k < (PIECES / 2 + Ld::NW - 1) / Ld::NW; ++k) {
-            const int idx = wave_u + k * Ld::NW;        // PIECES / 2 instructions cover the 32 rows
+        for (int k = 0; k < BPW; ++k) {
+            const int idx = wave_u + k * Ld::NW;
             if (idx < PIECES / 2) {
-                const int row = idx * (64 / PIECES) + lane / PIECES, pp = lane % PIECES;
-                const size_t o = off(tok(row), GN, (pp ^ Ld::swz(row)) * 8);
-                load_to_lds16(B_b + o, dB + idx * 1024);
-                if (emit) load_to_lds16(C_b + o, dC + idx * 1024);
+                load_to_lds16(Bc, obc[k], dB + idx * 1024);
+                if (emit) load_to_lds16(Cc, obc[k], dC + idx * 1024);
             }
         }
     };
+    // transposing reads (read_tr16): lane j of 16 is in row j / 4 of four, 8 bytes j % 4 of the 32 of its 16 columns.  Of the raw
+    // x rows from token 0 on, this thread's channel; of the rows of B, per unit, tokens 4 h .. 4 h + 3 of its eight
+    const int trow = l16 >> 2, tpiece = (l16 >> 1) & 1, tbyte = (l16 & 1) * 8;
+    const char *xtr = sXraw + trow * (2 * P) + ((((pc >> 4) * 2 + tpiece) ^ Ld::swzx(trow)) * 16) + tbyte;
+    int btr[UI][2];
+#pragma unroll
+    for (int i = 0; i < UI; ++i)
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int u = tid + i * NT, row = 8 * (u / N) + 4 * h + trow;
+            btr[i][h] = row * (2 * N) + ((((u % N) >> 4) * 2 + tpiece) ^ Ld::swz(row)) * 16 + tbyte;
+        }
     // Per chunk, of this lane's token t = li: log2 e * cum_t and exp(cum_t); and exp(cum_Q) (the same in every lane).
     float cum_t, at_t, aq;
     float cum_all = 0.f;                                // SEG: log2 of the segment's decay
@@ -323,46 +406,40 @@ void prefill_bf16_kernel(const PrefillParams p)
         }
         // ---- conv of this thread's QS tokens, rows [p][token] ----
         {
-            // raw inputs: [token][channel] in LDS; the three ahead of this thread's tokens are the ring history (first chunk),
-            // what the other half's threads left of the previous chunk, or simply earlier rows of this one
-            const uint16_t *xin = reinterpret_cast<const uint16_t *>(sXraw) + pc;
-            uint32_t xb[QS + W - 1];                    // the raw inputs of tokens s0 - 3 .. s0 + QS - 1, as bits
-            if (s0 != 0) {
-#pragma unroll
-                for (int j = 0; j < W - 1; ++j) xb[j] = xin[(s0 - (W - 1) + j) * P];
-            } else if (c == c_beg) {
-#pragma unroll
-                for (int j = 0; j < W - 1; ++j) xb[j] = hist[j];
-            } else {
-#pragma unroll
-                for (int j = 0; j < W - 1; ++j) xb[j] = sCar[(((c - 1) & 1) * 3 + j) * P + pc];
+            // raw inputs, as packed pairs of adjacent tokens of this channel: e[0], e[1] the four tokens ahead of s0 (in the chunk's first
+            // tokens what the chunk before left), then the thread's own; o the pairs in between
+            uint32_t e[QS / 2 + 2], o[QS / 2 + 1];
+            uint2 ahead;
+            if constexpr (P >= 64) {
+                if (s0 != 0) ahead = read_tr16(xtr + (s0 - 4) * (2 * P));
+                else ahead = sCar[((c + 1) & 1) * P + pc];
+            } else {                                    // both kinds of threads in one wave
+                const uint2 here = read_tr16(xtr + max(s0 - 4, 0) * (2 * P)), before = sCar[((c + 1) & 1) * P + pc];
+                ahead = s0 != 0 ? here : before;
             }
+            e[0] = ahead.x;
+            e[1] = ahead.y;
 #pragma unroll
-            for (int j = 0; j < QS; ++j) xb[j + W - 1] = xin[(s0 + j) * P];
-            // x_t = bias + (w0, w1).(r_(t-3), r_(t-2)) + (w2, w3).(r_(t-1), r_t): bf16 products are exact in fp32, the sums
-            // are fp32 (v_dot2c_f32_bf16); adjacent raw inputs are packed once and serve two tokens
-            bf2 pk[QS + 2];
-#pragma unroll
-            for (int i = 0; i < QS + 2; ++i) pk[i] = __builtin_bit_cast(bf2, xb[i] | (xb[i + 1] << 16));
-            float xv[QS];
-#pragma unroll
-            for (int j = 0; j < QS; ++j)
-                xv[j] = __builtin_amdgcn_fdot2_f32_bf16(w23, pk[j + 2], __builtin_amdgcn_fdot2_f32_bf16(w01, pk[j], cbias, false), false);
-            if (s0 + QS == Q) {                         // the chunk's last three raw inputs, for the next chunk
-#pragma unroll
-                for (int j = 0; j < W - 1; ++j) sCar[((c & 1) * 3 + j) * P + pc] = xb[QS + j];
+            for (int j = 0; j < QS / 4; ++j) {
+                const uint2 r = read_tr16(xtr + (s0 + 4 * j) * (2 * P));
+                e[2 + 2 * j] = r.x;
+                e[3 + 2 * j] = r.y;
             }
-            if (silu) {
+            if (s0 + QS == Q) sCar[(c & 1) * P + pc] = make_uint2(e[QS / 2], e[QS / 2 + 1]);     // for the next chunk
 #pragma unroll
-                for (int j = 0; j < QS; ++j) xv[j] = xv[j] / (1.f + expf(-xv[j]));
+            for (int i = 0; i < QS / 2 + 1; ++i) o[i] = __builtin_amdgcn_alignbit(e[i + 1], e[i], 16);
+#pragma unroll
+            for (int v = 0; v < QS / 8; ++v) {
+                float xv[8];
+                conv8(xv, o + 4 * v, e + 1 + 4 * v, wraw.x, wraw.y, cbias);
+                if (silu) {
+#pragma unroll
+                    for (int j = 0; j < 8; ++j) xv[j] = silu_fast(xv[j]);
+                }
+                // the rounding to the storage type
+                *reinterpret_cast<uint4 *>(sX + pc * XS + s0 * 2 + 16 * v) =
+                    make_uint4(pack_bf16x2(xv[0], xv[1]), pack_bf16x2(xv[2], xv[3]), pack_bf16x2(xv[4], xv[5]), pack_bf16x2(xv[6], xv[7]));
             }
-            uint32_t xr[QS / 2];
-#pragma unroll
-            for (int j2 = 0; j2 < QS / 2; ++j2) xr[j2] = pack_bf16x2(xv[2 * j2], xv[2 * j2 + 1]);     // the rounding to the storage type
-            const int o = pc * XS + s0 * 2;
-#pragma unroll
-            for (int v = 0; v < QS / 8; ++v)
-                *reinterpret_cast<uint4 *>(sX + o + 16 * v) = make_uint4(xr[4 * v], xr[4 * v + 1], xr[4 * v + 2], xr[4 * v + 3]);
         }
         // ---- w_s B_s transposed, head and tail: eight tokens of one n per unit ----
 #pragma unroll
@@ -374,15 +451,11 @@ void prefill_bf16_kernel(const PrefillParams p)
                 const float4 w0 = *reinterpret_cast<const float4 *>(sW + 8 * oct), w1 = *reinterpret_cast<const float4 *>(sW + 8 * oct + 4);
                 const float wv[8] = {w0.x, w0.y, w0.z, w0.w, w1.x, w1.y, w1.z, w1.w};
                 uint32_t bh[4], bl[4];
-                // B[token 8 oct + j][n] out of the swizzled rows: the piece index of n, XORed with the row's key (the same
-                // in all lanes), plus what does not depend on j - one instruction per element
-                const int piece16 = (n >> 3) * 16, rest = (n & 7) * 2 + oct * (8 * N * 2);
-                auto b_at = [&](int j) {
-                    const int key16 = Ld::swz(8 * oct + j) * 16;
-                    return Vec::decode1(*reinterpret_cast<const uint16_t *>(sB + ((piece16 ^ key16) + rest) + j * (N * 2)));
-                };
+                const uint2 r0 = read_tr16(sB + btr[i][0]), r1 = read_tr16(sB + btr[i][1]);
+                const uint32_t bb[4] = {r0.x, r0.y, r1.x, r1.y};
 #pragma unroll
-                for (int j2 = 0; j2 < 4; ++j2) split2(wv[2 * j2] * b_at(2 * j2), wv[2 * j2 + 1] * b_at(2 * j2 + 1), bh[j2], bl[j2]);
+                for (int j2 = 0; j2 < 4; ++j2)
+                    split2(wv[2 * j2] * __uint_as_float(bb[j2] << 16), wv[2 * j2 + 1] * __uint_as_float(bb[j2] & 0xffff0000u), bh[j2], bl[j2]);
                 *reinterpret_cast<uint4 *>(sBh + n * XS + oct * 16) = make_uint4(bh[0], bh[1], bh[2], bh[3]);
                 *reinterpret_cast<uint4 *>(sBl + n * XS + oct * 16) = make_uint4(bl[0], bl[1], bl[2], bl[3]);
             }
@@ -394,27 +467,31 @@ void prefill_bf16_kernel(const PrefillParams p)
     // to the issue of the following chunk's loads: loads and stores share one counter and complete in no fixed order
     // among each other, so the wait for the loads at the top of a chunk also waits for every store issued before it -
     // which by then is a whole chunk old instead of a few cycles.
+    // By then every wave's tile of that chunk is complete (the barrier at the chunk's end lies in between), so the rows are
+    // dealt out again: a wave stores whole rows of the head (all its 32-channel tiles side by side: whole cache lines
+    // from one instruction instead of 64-byte halves from two waves at different times) for its share of the tokens.
+    // 4 to 8 % on the 64- and 128-channel heads (3 % slower with the 128 x 128 tile, which keeps the wave's own rows).
+    constexpr bool kWholeRows = NSPL == 1 && Ld::NP > 1 && !(P >= 128 && N >= 128);
+    constexpr int LPT = kWholeRows ? 4 * Ld::NP : 4, TPI = 64 / LPT;      // lanes per token row, tokens per instruction
+    int ytok[2], ylds[2];
+    uint32_t oy[2];
+#pragma unroll
+    for (int r = 0; r < 2; ++r) {
+        const int piece = lane % LPT;
+        ytok[r] = (kWholeRows ? 2 * wave_u + r : r) * TPI + lane / LPT;
+        ylds[r] = Ld::oY + (kWholeRows ? piece >> 2 : pt) * Ld::YT + ytok[r] * Ld::YS + (piece & 3) * 16;
+        oy[r] = off(ytok[r], HP, hd * P + (kWholeRows ? 0 : pt * 32) + piece * 8);
+    }
     auto flush_outputs = [&](int c) {
-        const int t0 = c * Q;
-        // By then every wave's tile of that chunk is complete (the barrier at the chunk's end lies in between), so the rows are
-        // dealt out again: a wave stores whole rows of the head (all its 32-channel tiles side by side: whole cache lines
-        // from one instruction instead of 64-byte halves from two waves at different times) for its share of the tokens.
-        // 4 to 8 % on the 64- and 128-channel heads (3 % slower with the 128 x 128 tile, which keeps the wave's own rows).
-        if constexpr (NSPL == 1 && Ld::NP > 1 && !(P >= 128 && N >= 128)) {
-            constexpr int LPT = 4 * Ld::NP, TPI = 64 / LPT;      // lanes per token row of the head, tokens per instruction
+        char *yc = y_b + (size_t)c * Q * HP * 2;
+        const int live = L - c * Q;
+        if (live >= Q) {
 #pragma unroll
-            for (int r = 0; r < 2; ++r) {
-                const int tt = (2 * wave_u + r) * TPI + lane / LPT, piece = lane % LPT;
-                const uint4 v = *reinterpret_cast<const uint4 *>(lds + Ld::oY + (piece >> 2) * (Q * Ld::YS) + tt * Ld::YS + (piece & 3) * 16);
-                if (t0 + tt < L) Vec::store_raw(y_b, off(t0 + tt, HP, hd * P + piece * 8), v);
-            }
-            return;
-        }
+            for (int r = 0; r < 2; ++r) *reinterpret_cast<uint4 *>(yc + oy[r]) = *reinterpret_cast<const uint4 *>(lds + ylds[r]);
+        } else {
 #pragma unroll
-        for (int r = 0; r < 2; ++r) {
-            const int tt = 16 * r + (lane >> 2), piece = lane & 3;
-            const uint4 v = *reinterpret_cast<const uint4 *>(sY + tt * Ld::YS + piece * 16);
-            if (t0 + tt < L) Vec::store_raw(y_b, off(t0 + tt, HP, hd * P + pt * 32 + piece * 8), v);
+            for (int r = 0; r < 2; ++r)
+                if (ytok[r] < live) *reinterpret_cast<uint4 *>(yc + oy[r]) = *reinterpret_cast<const uint4 *>(lds + ylds[r]);
         }
     };
     const int prow = pt * 32 + li;                      // this lane's channel (inside the head) as an operand row
@@ -443,13 +520,12 @@ void prefill_bf16_kernel(const PrefillParams p)
         __builtin_amdgcn_sched_barrier(0);              // the loads and stores stay here, a chunk of arithmetic ahead of the next wait
 
         const int t = li;                               // this lane's token within the chunk
-        const bool live = t0 + t < L;
         using QV = XVec<SSMV_BF16, 4>;                  // four adjacent channels
         typename QV::Raw zraw[4];
         if (gated && nh == 0 && emit) {                 // requested ahead of the matrix products
-            const int tc = live ? t0 + t : L - 1;
+            const char *zc = chunk_of(z_b, c, HP) + off(min(t, L - 1 - t0), HP, hd * P + pt * 32 + 4 * lh);
 #pragma unroll
-            for (int q = 0; q < 4; ++q) zraw[q] = QV::load(z_b, off(tc, HP, hd * P + pt * 32 + 8 * q + 4 * lh));
+            for (int q = 0; q < 4; ++q) zraw[q] = *reinterpret_cast<const typename QV::Raw *>(zc + 16 * q);
         }
         f16v yacc = {0};
         if (emit) {
@@ -457,46 +533,30 @@ void prefill_bf16_kernel(const PrefillParams p)
             uint4 cop[N / 16];
 #pragma unroll
             for (int st = 0; st < N / 16; ++st) cop[st] = *reinterpret_cast<const uint4 *>(sC + t * (N * 2) + (((2 * st + lh) ^ Ld::swz(t)) * 16));
-            // ---- G^T = B C^T, then this wave's share of M^T: masked, decayed, scaled, D on the diagonal; to LDS ----
-            {
-                f16v gacc = {0};
+            // ---- this wave's quadrants of G^T = B C^T, and of M^T: decayed, scaled, masked, D on the diagonal; to LDS ----
+            auto quadrant = [&](int qi, int qj) {
+                f4v gacc = {0};
+                const int rs = 16 * qj + l16, rt = 16 * qi + l16;
 #pragma unroll
-                for (int st = 0; st < N / 16; ++st)
-                    gacc = mfma(as_bf8(*reinterpret_cast<const uint4 *>(sB + li * (N * 2) + (((2 * st + lh) ^ Ld::swz(li)) * 16))), as_bf8(cop[st]), gacc);
-                // registers 4 q .. 4 q + 3 of G^T -> M^T for tokens s = 8 q + 4 lh + [0, 4); r = the quad's index within the wave's share
-                auto finish = [&](int q, int r, float g0, float g1, float g2, float g3) {
-                    const int s0 = 8 * q + 4 * lh;
-                    const float4 cs = *reinterpret_cast<const float4 *>(sCum + s0), ds = *reinterpret_cast<const float4 *>(sDt + s0);
-                    const float csv[4] = {cs.x, cs.y, cs.z, cs.w}, dsv[4] = {ds.x, ds.y, ds.z, ds.w}, g4[4] = {g0, g1, g2, g3};
-                    float m[4];
+                for (int kk = 0; kk < N / 32; ++kk)
+                    gacc = mfma16(as_bf8(*reinterpret_cast<const uint4 *>(sB + rs * (N * 2) + (((4 * kk + k4) ^ Ld::swz(rs)) * 16))),
+                                  as_bf8(*reinterpret_cast<const uint4 *>(sC + rt * (N * 2) + (((4 * kk + k4) ^ Ld::swz(rt)) * 16))), gacc);
+                const int s0 = 16 * qj + 4 * k4;
+                const float ct = sCum[rt];
+                const float4 cs = *reinterpret_cast<const float4 *>(sCum + s0), ds = *reinterpret_cast<const float4 *>(sDt + s0);
+                const float csv[4] = {cs.x, cs.y, cs.z, cs.w}, dsv[4] = {ds.x, ds.y, ds.z, ds.w};
+                float m[4];
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        const float dec = __builtin_amdgcn_exp2f(cum_t - csv[e]) * dsv[e];      // may overflow where s > t: selected away
-                        m[e] = keep[4 * r + e] ? fmaf(g4[e], dec, dadd[4 * r + e]) : 0.f;
-                    }
-                    *reinterpret_cast<uint2 *>(sMh + t * XS + s0 * 2) = make_uint2(pack_bf16x2(m[0], m[1]), pack_bf16x2(m[2], m[3]));
-                };
-                // the wave's quads: a uniform branch, so that no register is indexed by a variable
-                if constexpr (RW == 4) {
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) finish(r, r, gacc[4 * r], gacc[4 * r + 1], gacc[4 * r + 2], gacc[4 * r + 3]);
-                } else if constexpr (RW == 2) {
-                    if (wave_u == 0) {
-                        finish(0, 0, gacc[0], gacc[1], gacc[2], gacc[3]);
-                        finish(1, 1, gacc[4], gacc[5], gacc[6], gacc[7]);
-                    } else {
-                        finish(2, 0, gacc[8], gacc[9], gacc[10], gacc[11]);
-                        finish(3, 1, gacc[12], gacc[13], gacc[14], gacc[15]);
-                    }
-                } else {
-                    switch (wave_u) {
-                        case 0: finish(0, 0, gacc[0], gacc[1], gacc[2], gacc[3]); break;
-                        case 1: finish(1, 0, gacc[4], gacc[5], gacc[6], gacc[7]); break;
-                        case 2: finish(2, 0, gacc[8], gacc[9], gacc[10], gacc[11]); break;
-                        default: finish(3, 0, gacc[12], gacc[13], gacc[14], gacc[15]); break;
-                    }
+                for (int v = 0; v < 4; ++v) {
+                    const float dec = __builtin_amdgcn_exp2f(ct - csv[v]) * dsv[v];      // may overflow where s > t: selected away
+                    if (qi == qj) m[v] = keep[v] ? fmaf(gacc[v], dec, dadd[v]) : 0.f;
+                    else m[v] = gacc[v] * dec;
                 }
-            }
+                *reinterpret_cast<uint2 *>(sMh + rt * XS + s0 * 2) = make_uint2(pack_bf16x2(m[0], m[1]), pack_bf16x2(m[2], m[3]));
+            };
+            if (wave_u == 0) quadrant(0, 0);
+            if (wave_u == 1 % Ld::NW) quadrant(1, 0);
+            if (wave_u == 2 % Ld::NW) quadrant(1, 1);
             // ---- Y^T = h C^T, scaled by exp(cum_t): the state registers are the A operand ----
 #pragma unroll
             for (int tn = 0; tn < TNL; ++tn)
@@ -558,17 +618,19 @@ void prefill_bf16_kernel(const PrefillParams p)
         }
         // ---- gate, store ----
         if (nh == 0 && emit) {
+            if (gated) {
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                float yv[4] = {yacc[4 * q + 0], yacc[4 * q + 1], yacc[4 * q + 2], yacc[4 * q + 3]};
-                if (gated) {
+                for (int q = 0; q < 4; ++q) {
                     float zf[4];
                     QV::decode(zraw[q], zf);
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) yv[e] *= silu_fast(zf[e]);
+                    for (int e = 0; e < 4; ++e) yacc[4 * q + e] *= silu_fast(zf[e]);
                 }
-                *reinterpret_cast<uint2 *>(sY + t * Ld::YS + (8 * q + 4 * lh) * 2) = QV::encode(yv);
             }
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                *reinterpret_cast<uint2 *>(sY + t * Ld::YS + (8 * q + 4 * lh) * 2) =
+                    make_uint2(pack_bf16x2(yacc[4 * q], yacc[4 * q + 1]), pack_bf16x2(yacc[4 * q + 2], yacc[4 * q + 3]));
         }
         __builtin_amdgcn_wave_barrier();                // the tile waits in the wave's LDS patch: flush_outputs
         wait_direct_loads();                            // this wave's share of the next chunk's inputs has landed ...

@@ -268,3 +268,28 @@ def test_prefill_strong_decay_and_accuracy_of_the_state(io):
         print("A x %g, %s: y error %.3g, state error %.3g" % (scale, io, e_y, e_h))
         assert e_y <= TOL[io]
         assert e_h <= (1e-4 if io == "bf16" else 1e-5), "state after the prompt: %.3g" % e_h
+
+
+@pytest.mark.parametrize("N", [32, 64, 128])
+@pytest.mark.parametrize("P", [32, 64, 128])
+def test_prefill_bf16_tiles_at_the_edges_of_chunks(P, N):
+    """Every tile shape at lengths around a chunk (the conv's four-token blocks, the clamped rows of a last chunk that is not
+    full, the quadrants of its matrix) with a history ahead of the prompt, and a SiLU whose argument runs from -200 to 200: its
+    exponential leaves fp32's range on one side and vanishes on the other.  Tolerance of all bf16 I/O."""
+    from workload import round_to_io
+    rng = np.random.default_rng(81)
+    for L in (1, 3, 4, 15, 16, 17, 31, 32, 33, 36, 63, 65, 83):
+        dec = Workload("edges", "scalar", batch=2, nheads=2, headdim=P, dstate=N, k=4, rounds=1, io="bf16", accept="uniform",
+                       conv_act="silu", seed=82)
+        prompt = generate(dec.scaled(k=L, kmax=L, rounds=1, seed=83 + L))
+        lp, pr = prompt.layers[0], prompt.rounds[0]
+        x = round_to_io(pr.x_raw * np.exp(rng.uniform(-3, 5, size=pr.x_raw.shape)).astype(np.float32), "bf16")
+        conv_init = round_to_io(rng.standard_normal((2, 3, 2 * P)).astype(np.float32), "bf16")
+        hip, ora = HipLayer(dec, lp, conv_init=conv_init), eager_oracle(dec, lp, conv_init=conv_init)
+        y_ref, _, _ = ora.verify(x, pr.dt[0], pr.B[0], pr.C[0])
+        ora.commit(np.full(2, L))
+        y = torch.empty_like(to_dev(x, "bf16"))
+        ssmv.ssm_prefill_chunked(hip.dims, hip.cache.c, to_dev(x, "bf16"), hip.conv_w, hip.conv_b, to_dev(pr.dt[0], "bf16"),
+                                 to_dev(pr.B[0], "bf16"), to_dev(pr.C[0], "bf16"), hip.A, hip.D, L, y)
+        assert rel_err(to_host(y), y_ref) <= TOL["bf16"], "L = %d" % L
+        assert rel_err(to_host(hip.materialize()), ora.h) <= TOL["bf16"], "L = %d: state" % L
