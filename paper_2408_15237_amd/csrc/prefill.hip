@@ -470,41 +470,42 @@ bool prefill_shape_supported(int P, int N)
     return (P == 32 || P == 64 || P == 128) && (N == 32 || N == 64 || N == 128);
 }
 
-// Whether and how a prompt is cut.  The unit is one chunk of a workgroup that has its compute unit to itself (1.9 us with
-// bf16 tensors, 128 x 64, 5.8 with fp32).  With q workgroups on the fullest compute unit a chunk takes 1.5 of that when the unit is
-// full (r workgroups fit; measured 1.48 at 128 x 64, r = 2, and 1.58 at 64 x 64, r = 4), and linearly less below; small tiles, of which
-// five and more fit, are counted as four (with the line drawn to 1.5 at r = 5 and 8, bf16, 320 heads x 400 tokens were cut: 64 x 32 32.4 ->
-// 35.5 us, 32 x 32 31.8 -> 33.3).  A segment's share of the state alone costs 0.6 (fp32 0.5) of a chunk with outputs, the two
-// further launches 5 (1.5).  More workgroups than fit at once would run as a second round, which always lost (320 heads x 1500 tokens at 128 x
-// 64: 150 us cut in three, 118 us uncut): not cut.  15 % of expected gain are asked for.  Over nine tiles, 4 to 320 heads and 260 to 3000
-// tokens the choice was within 10 % (fp32) and 24 % (bf16, prompts left uncut) of the best of ten cuts, and never 1 % slower than
-// uncut.  Uncut and cut (us; one sequence unless said):
-//   bf16  128 x 64, 32 heads:  700 tokens 47 -> 32, 1500: 94 -> 42, 3000: 183 -> 49;  5 sequences, 3000: 182 -> 125
-//         64 x 128, 80 heads:  1500 tokens 113 -> 69, 3000: 217 -> 93;   64 x 64, 4 x 80 heads, 1500: 122 -> 84
+// Whether and how a prompt is cut.  The unit is one chunk of a workgroup that has its compute unit to itself (5.8 us with fp32
+// tensors of 128 x 64, prefill_pipe_chunk_us with bf16).  With q workgroups on the fullest compute unit a chunk takes 1.5 (bf16 1.3) of
+// that when the unit is full (r workgroups fit), and linearly less below; fp32 tiles of which five and more fit are counted as
+// four.  A segment's share of the state alone costs 0.5 of a chunk with outputs.  The two further launches cost 1.5 chunks (fp32); bf16:
+// 8 us, and what the states' four trips through memory take at 4.7 TB/s.  More workgroups than fit at once would run as a second round,
+// which always lost: not cut.  15 % of expected gain are asked for (bf16: 10 %).  Uncut and cut (us; one sequence unless said):
+//   bf16  128 x 64, 32 heads:  700 tokens 29 -> 26, 1500: 54 -> 34, 3000: 100 -> 41;  4 sequences, 3000: 99 -> 85;  8 heads, 1500: 52 -> 24
+//         64 x 128, 80 heads:  1500 tokens 69 -> 52, 3000: 130 -> 78;   64 x 64, 80 heads, 1500: 48 -> 37
 //   fp32  128 x 64, 32 heads:  400 tokens 81 -> 41, 1500: 278 -> 66, 3000: 548 -> 106;   64 x 128, 80 heads, 1500: 282 -> 129
 static void choose_segments(PrefillParams &p)
 {
     p.seg_chunks = p.seg_count = p.seg_pass = 0;
     constexpr int kCUs = 256;
-    const int es = p.io == SSMV_BF16 ? 2 : 4;
-    const int r = es == 2 ? prefill_bf16_resident(p.P, p.N) : resident_f32(p.P, p.N);
-    const double share = es == 2 ? 0.6 : 0.5, launches = es == 2 ? 5.0 : 1.5;
+    const bool bf16 = p.io == SSMV_BF16;
+    if (bf16 && !prefill_pipe_serves(p)) return;
+    const int es = bf16 ? 2 : 4;
+    const int r = bf16 ? prefill_pipe_resident(p.P, p.N) : resident_f32(p.P, p.N);
+    const double unit = bf16 ? prefill_pipe_chunk_us(p.P, p.N) : 1.0, company = bf16 ? 0.3 : 0.5;
+    const double trips = bf16 ? 4.0 * p.P * p.N * sizeof(float) / 4.7e6 : 0.0;       // us per workgroup
     const long pairs = (long)p.batch * p.H;
     const int n = (p.L + kPrefillChunk - 1) / kPrefillChunk;
     // the last segment may end with a chunk of one token, and has to hold a state in its rows
     const int shortest = (4 * p.N / es + kPrefillChunk - 1 + kPrefillChunk - 1) / kPrefillChunk;
-    auto chunk_time = [&](long wgs) { return r > 1 ? 1.0 + 0.5 * ((wgs + kCUs - 1) / kCUs - 1) / ((r < 4 ? r : 4) - 1) : 1.0; };
-    double best = 0.85 * n * chunk_time(pairs);
+    auto chunk_time = [&](long wgs) { return r > 1 ? 1.0 + company * ((wgs + kCUs - 1) / kCUs - 1) / ((r < 4 ? r : 4) - 1) : 1.0; };
+    double best = (bf16 ? 0.9 : 0.85) * n * chunk_time(pairs);
     const long most = kCUs * r / pairs + 1 < segments_of(shortest, n) ? kCUs * r / pairs + 1 : segments_of(shortest, n);
     for (int ns = (int)most; ns >= 3; --ns) {
-        // the segment lengths l that make ns segments; the time max(n - (ns - 1) l, share l) + l falls and then rises with l
+        const double launches = bf16 ? (8.0 + trips * pairs * (ns - 1)) / unit : 1.5;
+        // the segment lengths l that make ns segments; the time max(n - (ns - 1) l, l / 2) + l falls and then rises with l
         int lo = (n - 1) / ns + 1, hi = (n - 1) / (ns - 1);
         if (lo < shortest) lo = shortest;
         if (hi < lo) continue;
-        const int turn = (int)(n / (ns - 1 + share));
+        const int turn = (int)(n / (ns - 0.5));
         for (int l = turn; l <= turn + 1; ++l) {
             const int len = l < lo ? lo : l > hi ? hi : l, first = n - (ns - 1) * len;
-            const double t = ((first > share * len ? first : share * len) + len) * chunk_time(pairs * (ns - 1)) + launches;
+            const double t = ((first > 0.5 * len ? first : 0.5 * len) + len) * chunk_time(pairs * (ns - 1)) + launches;
             if (t < best) { best = t; p.seg_chunks = len; p.seg_count = ns; }
         }
     }
@@ -525,7 +526,7 @@ static void choose_segments(PrefillParams &p)
 
 static int launch_pass(const PrefillParams &p, hipStream_t stream)
 {
-    if (p.io == SSMV_BF16) return launch_prefill_bf16(p, stream);
+    if (p.io == SSMV_BF16) return p.seg_count || prefill_pipe_serves(p) ? launch_prefill_pipe(p, stream) : launch_prefill_bf16(p, stream);
     switch (p.P) {
         case 32: return launch_p<32>(p, stream);
         case 64: return launch_p<64>(p, stream);

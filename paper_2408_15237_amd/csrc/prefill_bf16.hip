@@ -41,20 +41,13 @@
 // LDS rows that the kernel writes itself are padded by 16 bytes: a row stride that is an odd multiple of 16 bytes
 // spreads 16-byte reads of consecutive rows over all banks; the rows of B and C, which the direct loads fill without
 // gaps, have their 16-byte pieces XOR-swizzled instead (by the choice of the global address each lane fetches).
+#include "prefill_bf16_ops.h"
 #include "prefill_split.h"
 
 namespace ssmv {
-
-typedef float f16v __attribute__((ext_vector_type(16)));
-typedef __bf16 bf8 __attribute__((ext_vector_type(8)));
-
 namespace {
 
 constexpr int kQ = kPrefillChunk;
-constexpr float kLog2e = 1.4426950408889634f;
-
-// waves per 32-channel tile: a large state under a narrow head is split over n
-__host__ __device__ constexpr int prefill_nsplit(int P, int N) { return (N >= 128 && P <= 64) ? 2 : 1; }
 
 template <int P, int N>
 struct PfLds {              // byte offsets of the LDS arrays (bf16 unless said)
@@ -76,8 +69,8 @@ struct PfLds {              // byte offsets of the LDS arrays (bf16 unless said)
     // Two copies of B and C (chunks alternate; the next chunk's are requested at the start of this one's arithmetic) where
     // that does not cost a workgroup per CU; else one copy, and the next chunk's B and C are requested only once this
     // chunk's have been read (after the barrier in the middle): narrow heads (few waves per workgroup: 48 KB -> 40 KB
-    // is a fourth workgroup per CU) and N = 128 (90 KB -> 74 KB is a second one).
-    static constexpr int BCC = (P >= 128 && N < 128) ? 2 : 1;
+    // is a fourth workgroup per CU).
+    static constexpr int BCC = P >= 128 ? 2 : 1;
     static constexpr int oB = oXraw + kQ * P * 2;
     static constexpr int oC = oB + BCC * BCS;
     static constexpr int oCar = oC + BCC * BCS;              // [2][P][4]  the last four raw inputs of a chunk, for the next one's conv
@@ -85,106 +78,8 @@ struct PfLds {              // byte offsets of the LDS arrays (bf16 unless said)
     static constexpr int oDt = oCum + NW * kQ * 4;         // fp32 [NW][Q]  dt
     static constexpr int oW = oDt + NW * kQ * 4;           // fp32 [NW][Q]  exp(cum_Q - cum_s) dt_s
     static constexpr int total = oW + NW * kQ * 4;
-    // The direct loads fill rows without padding, so the 16-byte pieces of row r of x, B and C sit at piece index (logical index ^
-    // key(r)).  A cycle serves 256 bytes: 16 lanes that read one logical piece out of 16 consecutive rows (operands of the
-    // products; B and C only), or 32 lanes of a transposing read, four adjacent pieces out of each of four rows.  So the rows that
-    // fall onto the same banks take different keys, and in the key's upper bits, which move groups of four pieces, if they
-    // are among the same four rows.
     static constexpr int PIECES = N / 8;
-    static __host__ __device__ constexpr int swz(int r)
-    {
-        return PIECES == 16 ? ((r & 3) << 2) | ((r >> 2) & 3) : PIECES == 8 ? ((r & 2) << 1) | ((r & 4) >> 1) | ((r & 8) >> 3) : (r >> 2) & 3;
-    }
-    static __host__ __device__ constexpr int swzx(int r) { return P == 128 ? (r & 3) << 2 : P == 64 ? (r & 2) << 1 : 0; }
 };
-
-typedef __attribute__((address_space(3))) char lds_char_t;
-
-// 16 bytes per lane from global memory straight into LDS: lane l's data lands at LDS address `dst` + 16 l (dst is the
-// same in all lanes and travels in M0).  Issued from assembly, so that the compiler does not count these loads: it would
-// otherwise wait for them before the next LDS read that it cannot prove to be disjoint from their target, and at every
-// workgroup barrier.  The kernel waits for them itself (wait_direct_loads) ahead of the barrier that publishes the data.
-// The address is a base that is the same in all lanes plus an unsigned byte offset.
-__device__ __forceinline__ void load_to_lds16(const void *base, uint32_t offset, const char *dst)
-{
-    const unsigned lds_addr = (unsigned)(size_t)(lds_char_t *)dst;
-    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(offset), "s"(base), "s"(lds_addr) : "memory", "m0");
-}
-__device__ __forceinline__ void wait_direct_loads() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
-
-// Transposing LDS read: in every 16 lanes, lane i gets element i % 4 of the 8 bytes at the address of each of the lanes i / 4,
-// 4 + i / 4, 8 + i / 4, 12 + i / 4 (checked on the hardware).  With lane j's address in row j / 4, 8 bytes j % 4 of 32, that is
-// column i of four rows.
-__device__ __forceinline__ uint2 read_tr16(const char *at)
-{
-    typedef short s4 __attribute__((ext_vector_type(4)));
-    typedef __attribute__((address_space(3))) s4 lds_s4;
-    return __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4 *)(lds_char_t *)at));
-}
-
-// Eight outputs of the conv from packed pairs of raw inputs (e: even-aligned, o: odd-aligned): x_(2i) = bias + w01 . o[i] + w23 .
-// o[i + 1], x_(2i+1) = bias + w01 . e[i] + w23 . e[i + 1]; products exact, sums in fp32, the pair (w0, w1) first.  In assembly for the
-// form with an addend of its own: the compiler takes the accumulating one and copies the bias ahead of each (16 of a chunk's
-// 92 instructions for the conv).  A result of a dot product may be read three instructions later at the earliest: s_nop.
-__device__ __forceinline__ void conv8(float (&x)[8], const uint32_t *o, const uint32_t *e, uint32_t w01, uint32_t w23, float bias)
-{
-    asm("v_dot2_f32_bf16 %0, %18, %8, %20\n\t"
-        "v_dot2_f32_bf16 %1, %18, %13, %20\n\t"
-        "v_dot2_f32_bf16 %2, %18, %9, %20\n\t"
-        "v_dot2_f32_bf16 %3, %18, %14, %20\n\t"
-        "v_dot2_f32_bf16 %4, %18, %10, %20\n\t"
-        "v_dot2_f32_bf16 %5, %18, %15, %20\n\t"
-        "v_dot2_f32_bf16 %6, %18, %11, %20\n\t"
-        "v_dot2_f32_bf16 %7, %18, %16, %20\n\t"
-        "v_dot2_f32_bf16 %0, %19, %9, %0\n\t"
-        "v_dot2_f32_bf16 %1, %19, %14, %1\n\t"
-        "v_dot2_f32_bf16 %2, %19, %10, %2\n\t"
-        "v_dot2_f32_bf16 %3, %19, %15, %3\n\t"
-        "v_dot2_f32_bf16 %4, %19, %11, %4\n\t"
-        "v_dot2_f32_bf16 %5, %19, %16, %5\n\t"
-        "v_dot2_f32_bf16 %6, %19, %12, %6\n\t"
-        "v_dot2_f32_bf16 %7, %19, %17, %7\n\t"
-        "s_nop 2"
-        : "=&v"(x[0]), "=&v"(x[1]), "=&v"(x[2]), "=&v"(x[3]), "=&v"(x[4]), "=&v"(x[5]), "=&v"(x[6]), "=&v"(x[7])
-        : "v"(o[0]), "v"(o[1]), "v"(o[2]), "v"(o[3]), "v"(o[4]), "v"(e[0]), "v"(e[1]), "v"(e[2]), "v"(e[3]), "v"(e[4]), "v"(w01), "v"(w23), "v"(bias));
-}
-
-// two fp32 values -> packed bf16 heads and packed bf16 tails (first value in the low half)
-__device__ __forceinline__ void split2(float a, float b, uint32_t &hi, uint32_t &lo)
-{
-    hi = pack_bf16x2(a, b);
-    lo = pack_bf16x2(a - __uint_as_float(hi << 16), b - __uint_as_float(hi & 0xffff0000u));
-}
-
-__device__ __forceinline__ bf8 as_bf8(uint32_t a, uint32_t b, uint32_t c, uint32_t d)
-{
-    const uint4 u = make_uint4(a, b, c, d);
-    return __builtin_bit_cast(bf8, u);
-}
-__device__ __forceinline__ bf8 as_bf8(uint4 u) { return __builtin_bit_cast(bf8, u); }
-
-typedef float f4v __attribute__((ext_vector_type(4)));
-__device__ __forceinline__ f4v mfma16(bf8 a, bf8 b, f4v c) { return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0); }
-__device__ __forceinline__ f16v mfma(bf8 a, bf8 b, f16v c) { return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0); }
-
-// inclusive prefix sums over lanes 0..31 and, separately, over lanes 32..63 (rows of 16 lanes: shifts inside a row,
-// then the first row's total into the second); a lane shifted in from outside its row contributes 0
-template <int CTRL, int ROWS>
-__device__ __forceinline__ float dpp_or_zero(float v)
-{
-    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, ROWS, 0xf, false));
-}
-__device__ __forceinline__ float prefix32(float v)
-{
-    v += dpp_or_zero<0x111, 0xf>(v);     // row_shr:1
-    v += dpp_or_zero<0x112, 0xf>(v);     // row_shr:2
-    v += dpp_or_zero<0x114, 0xf>(v);     // row_shr:4
-    v += dpp_or_zero<0x118, 0xf>(v);     // row_shr:8
-    v += dpp_or_zero<0x142, 0xa>(v);     // row_bcast:15 into rows 1 and 3
-    return v;
-}
-
-__device__ __forceinline__ int swap23(int i) { return (i & ~12) | ((i & 4) << 1) | ((i & 8) >> 1); }
 
 #ifdef SSMV_TRACE
 // Profiling builds only: per workgroup, the shader-clock and the 100 MHz wall-clock ticks the kernel took.
@@ -194,16 +89,12 @@ __device__ long long *pf_trace_buf_ = nullptr;
 }  // namespace
 
 // Two waves per SIMD (256 registers each, and then the compiler keeps the accumulators in ordinary registers: no copies
-// between the two register files around every use); a tile's state of N = 128 in one wave (64 registers per lane) does
-// not fit that.
+// between the two register files around every use).  Tiles of 64 x 64 and 128 x 128 are not built: prefill_pipe.hip takes them all.
 // A state of N = 128 under a narrow head (P <= 64) is split over two waves per 32-channel tile, each with half of n: the
 // second adds its share of h C^T through LDS, both update their own half of the state, and the workgroup has twice the
 // threads for the staging.
-// SEG: the workgroup owns one segment of the prompt instead of all of it (prefill_split.h); in the first pass of such a
-// prompt every segment but the first one only needs its share of the state: no C, no Q x Q product, no outputs, and one
-// barrier less per chunk.
-template <int P, int N, bool SEG>
-__global__ __launch_bounds__(2 * P * prefill_nsplit(P, N)) __attribute__((amdgpu_waves_per_eu((N >= 128 && prefill_nsplit(P, N) == 1) ? 1 : 2)))
+template <int P, int N>
+__global__ __launch_bounds__(2 * P * prefill_nsplit(P, N)) __attribute__((amdgpu_waves_per_eu(2)))
 void prefill_bf16_kernel(const PrefillParams p)
 {
     using Ld = PfLds<P, N>;
@@ -238,34 +129,23 @@ void prefill_bf16_kernel(const PrefillParams p)
     float *sDt = reinterpret_cast<float *>(lds + Ld::oDt) + wave * Q;
     float *sW = reinterpret_cast<float *>(lds + Ld::oW) + wave * Q;
     const int H = p.H, G = p.G;
-    const PrefillItem item = prefill_item<SEG>(p);
+    const PrefillItem item = prefill_item<false>(p);
     const int hd = item.hd, b = item.b;
     const int Ls = p.L;                                 // token stride of the arrays
     const int L = item.L;                               // this sequence's prompt length
     if (L == 0) return;                                 // nothing to feed: state, ring and outputs stay as they are
-    Segment seg = {0, (L + Q - 1) / Q, 0, true, true, true};
-    if constexpr (SEG) {
-        seg = segment_of(p, L, item.slot);
-        if (!seg.work) return;
-    }
-    const int c_beg = SEG ? seg.c0 : 0, c_end = seg.c1; // the chunks of this workgroup
-    const bool emit = !SEG || seg.emit;                 // whether it writes outputs
+    const int n_chunks = (L + Q - 1) / Q;
     const int HP = H * P, GN = G * N;
     const int g = hd / (H / G);
     const int cur = (int)((unsigned)p.cur_slot[b] % 3u);
     const int mask = p.ring_len - 1;
-    // (the last pass of a segmented prompt runs behind the launch that has moved conv_head on already)
-    const int conv_head = (p.conv_head[b] - (SEG && p.seg_pass == 1 ? L : 0)) & mask;
+    const int conv_head = p.conv_head[b] & mask;
     const float A2_h = p.A[hd] * kLog2e, D_h = p.D[hd];
     const float dtb_h = p.dt_bias ? p.dt_bias[hd] : 0.f;
     const bool gated = p.z != nullptr, silu = p.conv_act == SSMV_ACT_SILU;
     float *state = p.state + (size_t)cur * p.slot_stride + ((size_t)b * H + hd) * P * N;
 
     char *y_b = reinterpret_cast<char *>(p.y) + (size_t)b * Ls * HP * 2;
-    // a segment's state between the passes: the lane's float4 number q of tile tn in the rows of y from token `t` on
-    auto seg_at = [&](int tn, int q, int t) {
-        return reinterpret_cast<float4 *>(y_b + seg_piece<2>(((wave_u * TNL + tn) * 4 + q) * 64 + lane, P, t, HP, hd));
-    };
     // state -> accumulator registers, transposed tiles [n][p]: register 4 q + e of tile tn holds
     // h[p = 32 pt + li][n = 32 (TNL nh + tn) + 16 (q/2) + 8 lh + 4 (q%2) + e]
     f16v hacc[TNL];
@@ -276,9 +156,7 @@ void prefill_bf16_kernel(const PrefillParams p)
     for (int tn = 0; tn < TNL; ++tn)
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-            float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (!SEG || c_beg == 0) v = *reinterpret_cast<const float4 *>(state_at(tn, q));
-            else if (p.seg_pass == 1) v = *seg_at(tn, q, seg.area);
+            const float4 v = *reinterpret_cast<const float4 *>(state_at(tn, q));
             hacc[tn][4 * q + 0] = v.x; hacc[tn][4 * q + 1] = v.y; hacc[tn][4 * q + 2] = v.z; hacc[tn][4 * q + 3] = v.w;
         }
     // G^T and M^T in 16 x 16 quadrants (tokens t of the first or second half of the chunk, s likewise; lane: t = 16 qi + lane % 16,
@@ -317,11 +195,9 @@ void prefill_bf16_kernel(const PrefillParams p)
     if (tid < P) {
         uint32_t hist[W - 1];                           // as bits
 #pragma unroll
-        for (int j = 0; j < W - 1; ++j) {
-            if (SEG && c_beg > 0) hist[j] = raw_bits(c_beg * Q - (W - 1) + j);
-            else hist[j] = reinterpret_cast<const uint16_t *>(p.ring)[((size_t)b * p.ring_len + ((conv_head + 1 - (W - 1) + j) & mask)) * HP + ch];
-        }
-        sCar[((c_beg + 1) & 1) * P + pc] = make_uint2(hist[0] << 16, hist[1] | (hist[2] << 16));
+        for (int j = 0; j < W - 1; ++j)
+            hist[j] = reinterpret_cast<const uint16_t *>(p.ring)[((size_t)b * p.ring_len + ((conv_head + 1 - (W - 1) + j) & mask)) * HP + ch];
+        sCar[P + pc] = make_uint2(hist[0] << 16, hist[1] | (hist[2] << 16));
     }
 
     constexpr int UI = (4 * N + NT - 1) / NT;           // (n, eight tokens) units of the transposed B per thread and chunk
@@ -338,12 +214,12 @@ void prefill_bf16_kernel(const PrefillParams p)
 #pragma unroll
         for (int k = 0; k < XPW; ++k) {
             const int row = (XPW * wave_u + k) * (64 / LR) + lane / LR;
-            ox[k] = off(min(row, last), HP, hd * P + ((lane % LR) ^ Ld::swzx(row)) * 8);
+            ox[k] = off(min(row, last), HP, hd * P + ((lane % LR) ^ key_x<P>(row)) * 8);
         }
 #pragma unroll
         for (int k = 0; k < BPW; ++k) {
             const int row = (wave_u + k * Ld::NW) * (64 / PIECES) + lane / PIECES;
-            obc[k] = off(min(row, last), GN, ((lane % PIECES) ^ Ld::swz(row)) * 8);
+            obc[k] = off(min(row, last), GN, ((lane % PIECES) ^ key_bc<N>(row)) * 8);
         }
         odt = off(min(li, last), H, 0);
     };
@@ -363,25 +239,24 @@ void prefill_bf16_kernel(const PrefillParams p)
             const int idx = wave_u + k * Ld::NW;
             if (idx < PIECES / 2) {
                 load_to_lds16(Bc, obc[k], dB + idx * 1024);
-                if (emit) load_to_lds16(Cc, obc[k], dC + idx * 1024);
+                load_to_lds16(Cc, obc[k], dC + idx * 1024);
             }
         }
     };
     // transposing reads (read_tr16): lane j of 16 is in row j / 4 of four, 8 bytes j % 4 of the 32 of its 16 columns.  Of the raw
     // x rows from token 0 on, this thread's channel; of the rows of B, per unit, tokens 4 h .. 4 h + 3 of its eight
     const int trow = l16 >> 2, tpiece = (l16 >> 1) & 1, tbyte = (l16 & 1) * 8;
-    const char *xtr = sXraw + trow * (2 * P) + ((((pc >> 4) * 2 + tpiece) ^ Ld::swzx(trow)) * 16) + tbyte;
+    const char *xtr = sXraw + trow * (2 * P) + ((((pc >> 4) * 2 + tpiece) ^ key_x<P>(trow)) * 16) + tbyte;
     int btr[UI][2];
 #pragma unroll
     for (int i = 0; i < UI; ++i)
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
             const int u = tid + i * NT, row = 8 * (u / N) + 4 * h + trow;
-            btr[i][h] = row * (2 * N) + ((((u % N) >> 4) * 2 + tpiece) ^ Ld::swz(row)) * 16 + tbyte;
+            btr[i][h] = row * (2 * N) + ((((u % N) >> 4) * 2 + tpiece) ^ key_bc<N>(row)) * 16 + tbyte;
         }
     // Per chunk, of this lane's token t = li: log2 e * cum_t and exp(cum_t); and exp(cum_Q) (the same in every lane).
     float cum_t, at_t, aq;
-    float cum_all = 0.f;                                // SEG: log2 of the segment's decay
     auto consume = [&](int c, uint32_t dt_bits) {
         const int t0 = c * Q, s0 = sg * QS;
         const char *sB = lds + Ld::oB + (c & (Ld::BCC - 1)) * Ld::BCS;
@@ -396,7 +271,6 @@ void prefill_bf16_kernel(const PrefillParams p)
             cum_t = v;
             at_t = __builtin_amdgcn_exp2f(v);
             aq = __builtin_amdgcn_exp2f(cq);
-            if constexpr (SEG) cum_all += cq;
             if (lh == 0) {
                 sCum[li] = v;
                 sDt[li] = d;
@@ -470,8 +344,8 @@ void prefill_bf16_kernel(const PrefillParams p)
     // By then every wave's tile of that chunk is complete (the barrier at the chunk's end lies in between), so the rows are
     // dealt out again: a wave stores whole rows of the head (all its 32-channel tiles side by side: whole cache lines
     // from one instruction instead of 64-byte halves from two waves at different times) for its share of the tokens.
-    // 4 to 8 % on the 64- and 128-channel heads (3 % slower with the 128 x 128 tile, which keeps the wave's own rows).
-    constexpr bool kWholeRows = NSPL == 1 && Ld::NP > 1 && !(P >= 128 && N >= 128);
+    // 4 to 8 % on the 64- and 128-channel heads.
+    constexpr bool kWholeRows = NSPL == 1 && Ld::NP > 1;
     constexpr int LPT = kWholeRows ? 4 * Ld::NP : 4, TPI = 64 / LPT;      // lanes per token row, tokens per instruction
     int ytok[2], ylds[2];
     uint32_t oy[2];
@@ -497,50 +371,50 @@ void prefill_bf16_kernel(const PrefillParams p)
     const int prow = pt * 32 + li;                      // this lane's channel (inside the head) as an operand row
     float *sZ = reinterpret_cast<float *>(lds + Ld::oZ) + pt * 1024;
     uint32_t dt_bits;
-    issue_x_loads(c_beg, dt_bits);
-    issue_bc_loads(c_beg);
+    issue_x_loads(0, dt_bits);
+    issue_bc_loads(0);
     wait_direct_loads();
     __syncthreads();
-    for (int c = c_beg; c < c_end; ++c) {
+    for (int c = 0; c < n_chunks; ++c) {
         const int t0 = c * Q;
         const char *sB = lds + Ld::oB + (c & (Ld::BCC - 1)) * Ld::BCS, *sC = lds + Ld::oC + (c & (Ld::BCC - 1)) * Ld::BCS;
         consume(c, dt_bits);
         __syncthreads();
         // the stores ahead of the loads on the wide tiles (2 % there; the other way round on the narrow ones)
         constexpr bool kStoresFirst = P >= 128 && N >= 64;
-        if (kStoresFirst && c > c_beg && nh == 0 && emit) {
+        if (kStoresFirst && c > 0 && nh == 0) {
             flush_outputs(c - 1);
             __builtin_amdgcn_sched_barrier(0);
         }
-        if (c + 1 < c_end) {                            // under way for the whole chunk
+        if (c + 1 < n_chunks) {                            // under way for the whole chunk
             issue_x_loads(c + 1, dt_bits);
             if (Ld::BCC == 2) issue_bc_loads(c + 1);
         }
-        if (!kStoresFirst && c > c_beg && nh == 0 && emit) flush_outputs(c - 1);
+        if (!kStoresFirst && c > 0 && nh == 0) flush_outputs(c - 1);
         __builtin_amdgcn_sched_barrier(0);              // the loads and stores stay here, a chunk of arithmetic ahead of the next wait
 
         const int t = li;                               // this lane's token within the chunk
         using QV = XVec<SSMV_BF16, 4>;                  // four adjacent channels
         typename QV::Raw zraw[4];
-        if (gated && nh == 0 && emit) {                 // requested ahead of the matrix products
+        if (gated && nh == 0) {                 // requested ahead of the matrix products
             const char *zc = chunk_of(z_b, c, HP) + off(min(t, L - 1 - t0), HP, hd * P + pt * 32 + 4 * lh);
 #pragma unroll
             for (int q = 0; q < 4; ++q) zraw[q] = *reinterpret_cast<const typename QV::Raw *>(zc + 16 * q);
         }
         f16v yacc = {0};
-        if (emit) {
+        {
             // C of this lane's token, all of it: the B operand of G^T and of h C^T
             uint4 cop[N / 16];
 #pragma unroll
-            for (int st = 0; st < N / 16; ++st) cop[st] = *reinterpret_cast<const uint4 *>(sC + t * (N * 2) + (((2 * st + lh) ^ Ld::swz(t)) * 16));
+            for (int st = 0; st < N / 16; ++st) cop[st] = *reinterpret_cast<const uint4 *>(sC + t * (N * 2) + (((2 * st + lh) ^ key_bc<N>(t)) * 16));
             // ---- this wave's quadrants of G^T = B C^T, and of M^T: decayed, scaled, masked, D on the diagonal; to LDS ----
             auto quadrant = [&](int qi, int qj) {
                 f4v gacc = {0};
                 const int rs = 16 * qj + l16, rt = 16 * qi + l16;
 #pragma unroll
                 for (int kk = 0; kk < N / 32; ++kk)
-                    gacc = mfma16(as_bf8(*reinterpret_cast<const uint4 *>(sB + rs * (N * 2) + (((4 * kk + k4) ^ Ld::swz(rs)) * 16))),
-                                  as_bf8(*reinterpret_cast<const uint4 *>(sC + rt * (N * 2) + (((4 * kk + k4) ^ Ld::swz(rt)) * 16))), gacc);
+                    gacc = mfma16(as_bf8(*reinterpret_cast<const uint4 *>(sB + rs * (N * 2) + (((4 * kk + k4) ^ key_bc<N>(rs)) * 16))),
+                                  as_bf8(*reinterpret_cast<const uint4 *>(sC + rt * (N * 2) + (((4 * kk + k4) ^ key_bc<N>(rt)) * 16))), gacc);
                 const int s0 = 16 * qj + 4 * k4;
                 const float ct = sCum[rt];
                 const float4 cs = *reinterpret_cast<const float4 *>(sCum + s0), ds = *reinterpret_cast<const float4 *>(sDt + s0);
@@ -570,7 +444,7 @@ void prefill_bf16_kernel(const PrefillParams p)
                     // C for the wave's own tiles: with a split state read again at the wave's offset (a choice between
                     // registers by a variable would put the array into scratch memory)
                     uint4 c4;
-                    if constexpr (NSPL == 2) c4 = *reinterpret_cast<const uint4 *>(sC + t * (N * 2) + (((2 * (2 * (TNL * nh + tn) + st) + lh) ^ Ld::swz(t)) * 16));
+                    if constexpr (NSPL == 2) c4 = *reinterpret_cast<const uint4 *>(sC + t * (N * 2) + (((2 * (2 * (TNL * nh + tn) + st) + lh) ^ key_bc<N>(t)) * 16));
                     else c4 = cop[2 * tn + st];
                     const bf8 cb = as_bf8(c4);
                     yacc = mfma(as_bf8(ah[0], ah[1], ah[2], ah[3]), cb, yacc);
@@ -587,9 +461,9 @@ void prefill_bf16_kernel(const PrefillParams p)
         uint4 xop[2];
 #pragma unroll
         for (int st = 0; st < 2; ++st) xop[st] = *reinterpret_cast<const uint4 *>(sX + prow * XS + (16 * st + 8 * lh) * 2);
-        if (emit) __syncthreads();     // M^T is complete; nobody reads this chunk's B and C rows any more
-        if (Ld::BCC == 1 && c + 1 < c_end) issue_bc_loads(c + 1);
-        if (nh == 0 && emit) {
+        __syncthreads();     // M^T is complete; nobody reads this chunk's B and C rows any more
+        if (Ld::BCC == 1 && c + 1 < n_chunks) issue_bc_loads(c + 1);
+        if (nh == 0) {
             if constexpr (NSPL == 2) {
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
@@ -617,7 +491,7 @@ void prefill_bf16_kernel(const PrefillParams p)
             }
         }
         // ---- gate, store ----
-        if (nh == 0 && emit) {
+        if (nh == 0) {
             if (gated) {
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
@@ -637,20 +511,7 @@ void prefill_bf16_kernel(const PrefillParams p)
         __syncthreads();     // ... and so has everybody's; the next chunk overwrites X, B^T, M
     }
 
-    if (nh == 0 && emit) flush_outputs(c_end - 1);
-    if constexpr (SEG) {
-        if (!seg.last) {
-            if (p.seg_pass == 1) return;                // the next segment has its state already
-            // a segment's state on its way to the combining launch
-#pragma unroll
-            for (int tn = 0; tn < TNL; ++tn)
-#pragma unroll
-                for (int q = 0; q < 4; ++q)
-                    *seg_at(tn, q, seg.area) = make_float4(hacc[tn][4 * q + 0], hacc[tn][4 * q + 1], hacc[tn][4 * q + 2], hacc[tn][4 * q + 3]);
-            if (c_beg > 0 && tid == 0) *reinterpret_cast<float *>(y_b + seg_piece<2>(P * N / 4, P, seg.area, HP, hd)) = cum_all;
-            return;
-        }
-    }
+    if (nh == 0) flush_outputs(n_chunks - 1);
     // ---- state back in place; the newest W-1 raw inputs into the ring behind conv_head -----------------------
 #pragma unroll
     for (int tn = 0; tn < TNL; ++tn)
@@ -670,14 +531,14 @@ void prefill_bf16_kernel(const PrefillParams p)
 #endif
 }
 
-template <int P, int N, bool SEG>
+template <int P, int N>
 static int launch_pn(const PrefillParams &p, hipStream_t stream)
 {
     const size_t lds = PfLds<P, N>::total;
-    const dim3 grid((unsigned)(p.H * p.batch) * (SEG ? p.seg_count - 1 : 1)), block(2 * P * PfLds<P, N>::NSPL);
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&prefill_bf16_kernel<P, N, SEG>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    const dim3 grid((unsigned)(p.H * p.batch)), block(2 * P * PfLds<P, N>::NSPL);
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&prefill_bf16_kernel<P, N>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return (int)e;
-    hipLaunchKernelGGL((prefill_bf16_kernel<P, N, SEG>), grid, block, lds, stream, p);
+    hipLaunchKernelGGL((prefill_bf16_kernel<P, N>), grid, block, lds, stream, p);
     return (int)hipGetLastError();
 }
 
@@ -685,33 +546,18 @@ template <int P>
 static int launch_p(const PrefillParams &p, hipStream_t stream)
 {
     switch (p.N) {
-        case 32: return p.seg_count ? launch_pn<P, 32, true>(p, stream) : launch_pn<P, 32, false>(p, stream);
-        case 64: return p.seg_count ? launch_pn<P, 64, true>(p, stream) : launch_pn<P, 64, false>(p, stream);
-        case 128: return p.seg_count ? launch_pn<P, 128, true>(p, stream) : launch_pn<P, 128, false>(p, stream);
-        default: return (int)hipErrorInvalidConfiguration;
+        case 32: return launch_pn<P, 32>(p, stream);
+        case 64: if constexpr (P != 64) return launch_pn<P, 64>(p, stream); else break;
+        case 128: if constexpr (P != 128) return launch_pn<P, 128>(p, stream); else break;
     }
-}
-
-template <int P, int N>
-static constexpr int resident()
-{
-    // 160 KB of LDS; three waves per SIMD by their registers, one with the 128 x 128 tile
-    constexpr int by_lds = 160 * 1024 / PfLds<P, N>::total, by_waves = (P >= 128 && N >= 128 ? 4 : 12) / PfLds<P, N>::NW;
-    return by_lds < by_waves ? by_lds : by_waves;
-}
-int prefill_bf16_resident(int P, int N)
-{
-    auto pick = [&](int n32, int n64, int n128) { return N == 32 ? n32 : N == 64 ? n64 : n128; };
-    if (P == 32) return pick(resident<32, 32>(), resident<32, 64>(), resident<32, 128>());
-    if (P == 64) return pick(resident<64, 32>(), resident<64, 64>(), resident<64, 128>());
-    return pick(resident<128, 32>(), resident<128, 64>(), resident<128, 128>());
+    return (int)hipErrorInvalidConfiguration;
 }
 
 #ifdef SSMV_TRACE
 int set_trace_prefill(long long *buf) { return (int)hipMemcpyToSymbol(HIP_SYMBOL(pf_trace_buf_), &buf, sizeof(buf)); }
 #endif
 
-// one pass over the prompt; the caller appends the combining or the bookkeeping launch
+// large launches (prefill_pipe_serves); the caller appends the bookkeeping launch
 int launch_prefill_bf16(const PrefillParams &p, hipStream_t stream)
 {
     switch (p.P) {

@@ -293,3 +293,43 @@ def test_prefill_bf16_tiles_at_the_edges_of_chunks(P, N):
                                  to_dev(pr.B[0], "bf16"), to_dev(pr.C[0], "bf16"), hip.A, hip.D, L, y)
         assert rel_err(to_host(y), y_ref) <= TOL["bf16"], "L = %d" % L
         assert rel_err(to_host(hip.materialize()), ora.h) <= TOL["bf16"], "L = %d: state" % L
+
+
+@pytest.mark.parametrize("P,N,H,batch", [(128, 64, 33, 8), (128, 32, 33, 8), (64, 128, 33, 8), (64, 32, 33, 16), (32, 64, 60, 13), (32, 32, 60, 13),
+                                         (32, 128, 33, 16)])
+def test_prefill_large_launches_agree_with_small_ones(P, N, H, batch):
+    """bf16 launches of more (sequence, head) pairs than the pipelined kernel takes (one step past its line) go to the other
+    kernel.  Its first and last sequences, alone, go through the pipelined one, which the tests above hold against the oracle.  Same
+    products in the same order, so the state is the same to fp32 rounding; y to the bf16 bound.  With softplus, SiLU, gate, and
+    prompts of one and of different lengths (below 512 tokens the line is the same)."""
+    g = torch.Generator(device="cuda").manual_seed(91)
+    rnd = lambda *s: torch.randn(*s, generator=g, device="cuda")
+    bf = lambda t: t.to(torch.bfloat16)
+    L, Cx = 75, H * P
+    x, z, dt = bf(rnd(batch, L, Cx)), bf(rnd(batch, L, Cx)), bf(rnd(batch, L, H) - 4)
+    B, C = bf(rnd(batch, L, 1, N) / N ** 0.5), bf(rnd(batch, L, 1, N) / N ** 0.5)
+    w, bias, D, dtb = bf(rnd(Cx, 4) / 2), bf(rnd(Cx) * 0.1), rnd(H), torch.rand(H, generator=g, device="cuda") - 0.5
+    A = -torch.exp(torch.rand(H, generator=g, device="cuda") * 2.7)
+    h0, conv0 = rnd(batch, H, P, N) * 0.1, bf(rnd(batch, 3, Cx))
+    lens = torch.randint(0, L + 1, (batch,), generator=torch.Generator().manual_seed(92), dtype=torch.int32).cuda()
+
+    def run(sel, seq_len):
+        n = len(sel)
+        dims = ssmv.make_dims(n, H, P, N, kmax=4, io="bf16", conv_act="silu")
+        cache = ssmv.LayerCache.allocate(dims)
+        ssmv.ssmv_cache_reset(dims, cache.c, h0[sel].contiguous(), conv0[sel].contiguous())
+        t = [v[sel].contiguous() for v in (x, z, dt, B, C)]
+        y, h = torch.zeros_like(t[0]), torch.empty_like(h0[sel])
+        ssmv.ssm_prefill_block(dims, cache.c, x_raw=t[0], conv_wgt=w, conv_bias=bias, dt=t[2], dt_bias=dtb, dt_softplus=True, Bm=t[3], Cm=t[4],
+                               z=t[1], A=A, D=D, L=L, y_out=y, seq_len=None if seq_len is None else seq_len[sel].contiguous())
+        ssmv.ssmv_materialize_block(dims, cache.c, A, dtb, True, h)
+        ssmv.ssmv_check(cache.c)
+        return y, h, cache.buffers["pos"].clone()
+
+    ends = [0, 1, batch - 1]
+    for seq_len in (None, lens):
+        y, h, pos = run(list(range(batch)), seq_len)
+        y_s, h_s, pos_s = run(ends, seq_len)
+        assert rel_err(to_host(y[ends]), to_host(y_s)) <= TOL["bf16"]
+        assert rel_err(to_host(h[ends]), to_host(h_s)) <= 1e-5
+        assert torch.equal(pos[:batch][ends], pos_s[:3])
