@@ -23,11 +23,10 @@
 // What a chunk costs is its instructions, vector ones above all (two waves per SIMD, neither the matrix pipe nor LDS nor memory
 // more than half busy).  So: raw inputs and B leave LDS through the transposing read (read_tr16), four tokens of a channel per lane
 // and instruction, already paired for the conv's dot products; the addend of those is an operand (conv8); G is computed once, not by
-// every wave; lane offsets of all global accesses stay the same over the chunks; SiLU is exp2 and rcp.  With single 16-bit
-// LDS reads, pairs put together by shifts, G in every wave, 64-bit addresses formed per access and a SiLU of expf and a division a
-// wave took 316 vector, 18 matrix and 67 LDS instructions per chunk at 128 x 64, so 221, 15.5 and 42 (605 -> 365 vector ones at
-// 64 x 128 with SiLU).  32 x 2048 tokens of 32 heads x 128 x 64: 348 -> 298 us; 5 ragged x 700 of 80 x 64 x 128 with SiLU, gate and
-// softplus 75.2 -> 61.4; 16 x 1024: 64 heads x 64 x 64 112 -> 105, 64 x 32 x 64 102 -> 83, 64 x 32 x 32 73 -> 58, 32 x 128 x 128 206 -> 172.
+// every wave; lane offsets of all global accesses stay the same over the chunks.  With single 16-bit
+// LDS reads, pairs put together by shifts, G in every wave and 64-bit addresses formed per access a
+// wave took 316 vector, 18 matrix and 67 LDS instructions per chunk at 128 x 64 (no SiLU), so 221, 15.5 and 42.
+// 32 x 2048 tokens of 32 heads x 128 x 64: 348 -> 298 us; 16 x 1024: 64 heads x 32 x 64 102 -> 83, 64 x 32 x 32 73 -> 58.
 // Operand layout (checked on the hardware): A[i = lane%32][k = 8 (lane/32) + j], B[k = 8 (lane/32) + j][col = lane%32],
 // j = 0..7 the elements of the lane's 16-byte operand; result register v of a lane is row 8 (v/4) + 4 (lane/32) + v%4,
 // column lane%32.  Registers 8 st .. 8 st + 7 of a result tile, used as the operand of step st of a following
@@ -308,7 +307,7 @@ void prefill_bf16_kernel(const PrefillParams p)
                 conv8(xv, o + 4 * v, e + 1 + 4 * v, wraw.x, wraw.y, cbias);
                 if (silu) {
 #pragma unroll
-                    for (int j = 0; j < 8; ++j) xv[j] = silu_fast(xv[j]);
+                    for (int j = 0; j < 8; ++j) xv[j] = conv_silu(xv[j]);
                 }
                 // the rounding to the storage type
                 *reinterpret_cast<uint4 *>(sX + pc * XS + s0 * 2 + 16 * v) =

@@ -87,6 +87,10 @@ __device__ __forceinline__ void conv8(float (&x)[8], const uint32_t *o, const ui
         : "v"(o[0]), "v"(o[1]), "v"(o[2]), "v"(o[3]), "v"(o[4]), "v"(e[0]), "v"(e[1]), "v"(e[2]), "v"(e[3]), "v"(e[4]), "v"(w01), "v"(w23), "v"(bias));
 }
 
+// SiLU of the conv output, by the same expression as in every other kernel's conv: a token's conv output is the same bits whichever
+// call it comes through.  (silu_fast, from exp2 of a rounded product and rcp, is off by 1e-6 at -20 and gives 0 below -87.3.)
+__device__ __forceinline__ float conv_silu(float v) { return v / (1.f + expf(-v)); }
+
 // two fp32 values -> packed bf16 heads and packed bf16 tails (first value in the low half)
 __device__ __forceinline__ void split2(float a, float b, uint32_t &hi, uint32_t &lo)
 {

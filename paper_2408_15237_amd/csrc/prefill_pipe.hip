@@ -183,7 +183,7 @@ void prefill_pipe_kernel(const PrefillParams p)
                 conv8(xv, o + 4 * v, e + 1 + 4 * v, wraw.x, wraw.y, cbias);
                 if (silu) {
 #pragma unroll
-                    for (int j = 0; j < 8; ++j) xv[j] = silu_fast(xv[j]);
+                    for (int j = 0; j < 8; ++j) xv[j] = conv_silu(xv[j]);
                 }
                 // the rounding to the storage type
                 *reinterpret_cast<uint4 *>(to + 16 * v) =

@@ -333,3 +333,29 @@ def test_prefill_large_launches_agree_with_small_ones(P, N, H, batch):
         assert rel_err(to_host(y[ends]), to_host(y_s)) <= TOL["bf16"]
         assert rel_err(to_host(h[ends]), to_host(h_s)) <= 1e-5
         assert torch.equal(pos[:batch][ends], pos_s[:3])
+
+
+@pytest.mark.parametrize("batch", [1, 23])
+def test_conv_silu_of_every_bf16_argument_is_that_of_the_other_calls(batch):
+    """With C = 0, D = 1 and the conv weights (0, 0, 0, 1) a prompt's output is its conv output: SiLU of the raw input, bit for bit what
+    conv1d_state_update gives for it.  Every bf16 number up to 100 in magnitude; one launch for either bf16 kernel."""
+    P, N, H, L, k = 32, 32, 34, 32, 16
+    Cx = H * P
+    bits = torch.arange(0x42C9, dtype=torch.int32)
+    x = torch.cat([bits, bits + 0x8000, torch.zeros(L * Cx - 2 * len(bits), dtype=torch.int32)]).to(torch.int16).view(torch.bfloat16).cuda().view(1, L, Cx)
+    w = torch.zeros(Cx, 4, dtype=torch.bfloat16, device="cuda")
+    w[:, 3] = 1
+    dims = ssmv.make_dims(L // k, H, P, N, kmax=k, io="bf16", conv_act="silu")
+    cache = ssmv.LayerCache.allocate(dims)
+    ssmv.ssmv_cache_reset(dims, cache.c, None, None)
+    want = torch.empty(L // k, k, Cx, dtype=torch.bfloat16, device="cuda")
+    ssmv.conv1d_state_update(dims, cache.c, x.view(L // k, k, Cx), w, None, k, want)
+    dims = ssmv.make_dims(batch, H, P, N, kmax=4, io="bf16", conv_act="silu")
+    cache = ssmv.LayerCache.allocate(dims)
+    ssmv.ssmv_cache_reset(dims, cache.c, None, None)
+    xs = x.expand(batch, -1, -1).contiguous()
+    y, zeros = torch.full_like(xs, 7.0), torch.zeros(batch, L, 1, N, dtype=torch.bfloat16, device="cuda")
+    ssmv.ssm_prefill_chunked(dims, cache.c, xs, w, None, torch.zeros(batch, L, H, dtype=torch.bfloat16, device="cuda"), zeros, zeros,
+                             torch.full((H,), -1.0, device="cuda"), torch.ones(H, device="cuda"), L, y)
+    differ = y != want.view(1, L, Cx)
+    assert not bool(differ.any()), "%d values, the first at x = %r" % (int(differ.sum()), xs[differ][:4].tolist())
