@@ -34,16 +34,18 @@ typedef __attribute__((address_space(3))) char lds_char_t;
 // otherwise wait for them before the next LDS read that it cannot prove to be disjoint from their target, and at every
 // workgroup barrier.  The kernel waits for them itself (wait_direct_loads) ahead of the barrier that publishes the data.
 // The address is a base that is the same in all lanes plus an unsigned byte offset.
+// s_nop: the load may read the base five wait states after a vector instruction wrote it (a scalar spilled to a lane comes back that
+// way), one after M0 was written, and the compiler looks for neither in here.
 __device__ __forceinline__ void load_to_lds16(const void *base, uint32_t offset, const char *dst)
 {
     const unsigned lds_addr = (unsigned)(size_t)(lds_char_t *)dst;
-    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(offset), "s"(base), "s"(lds_addr) : "memory", "m0");
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 4\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(offset), "s"(base), "s"(lds_addr) : "memory", "m0");
 }
 // the same with 16 bits per lane, zero-extended: lane l's word at `dst` + 4 l
 __device__ __forceinline__ void load_to_lds2(const void *base, uint32_t offset, const char *dst)
 {
     const unsigned lds_addr = (unsigned)(size_t)(lds_char_t *)dst;
-    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_ushort %0, %1" ::"v"(offset), "s"(base), "s"(lds_addr) : "memory", "m0");
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 4\n\tglobal_load_lds_ushort %0, %1" ::"v"(offset), "s"(base), "s"(lds_addr) : "memory", "m0");
 }
 // until at most COUNT of the wave's memory accesses are under way
 template <int COUNT>
