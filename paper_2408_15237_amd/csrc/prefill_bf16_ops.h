@@ -34,18 +34,23 @@ typedef __attribute__((address_space(3))) char lds_char_t;
 // otherwise wait for them before the next LDS read that it cannot prove to be disjoint from their target, and at every
 // workgroup barrier.  The kernel waits for them itself (wait_direct_loads) ahead of the barrier that publishes the data.
 // The address is a base that is the same in all lanes plus an unsigned byte offset.
-// s_nop: the load may read the base five wait states after a vector instruction wrote it (a scalar spilled to a lane comes back that
-// way), one after M0 was written, and the compiler looks for neither in here.
+// The base is copied by a scalar instruction: a vector memory access may read a scalar five wait states after a vector instruction wrote
+// it (v_readfirstlane, or v_readlane of a spilled one), for which the compiler does not look in here, but at any time after a scalar
+// instruction did, and that one waits for the vector instruction by itself.  The copy is also the wait state that M0 asks for.
+// (Five wait states by s_nop cost 1 to 2 % of launches that fill the chip: 2048 pairs of 32 x 64, 1024 tokens, 189 us with two, 193 with five,
+// 189 so.)
 __device__ __forceinline__ void load_to_lds16(const void *base, uint32_t offset, const char *dst)
 {
     const unsigned lds_addr = (unsigned)(size_t)(lds_char_t *)dst;
-    asm volatile("s_mov_b32 m0, %2\n\ts_nop 4\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(offset), "s"(base), "s"(lds_addr) : "memory", "m0");
+    const void *copy;
+    asm volatile("s_mov_b32 m0, %3\n\ts_mov_b64 %0, %2\n\tglobal_load_lds_dwordx4 %1, %0" : "=&s"(copy) : "v"(offset), "s"(base), "s"(lds_addr) : "memory", "m0");
 }
 // the same with 16 bits per lane, zero-extended: lane l's word at `dst` + 4 l
 __device__ __forceinline__ void load_to_lds2(const void *base, uint32_t offset, const char *dst)
 {
     const unsigned lds_addr = (unsigned)(size_t)(lds_char_t *)dst;
-    asm volatile("s_mov_b32 m0, %2\n\ts_nop 4\n\tglobal_load_lds_ushort %0, %1" ::"v"(offset), "s"(base), "s"(lds_addr) : "memory", "m0");
+    const void *copy;
+    asm volatile("s_mov_b32 m0, %3\n\ts_mov_b64 %0, %2\n\tglobal_load_lds_ushort %1, %0" : "=&s"(copy) : "v"(offset), "s"(base), "s"(lds_addr) : "memory", "m0");
 }
 // until at most COUNT of the wave's memory accesses are under way
 template <int COUNT>
