@@ -88,7 +88,7 @@ __device__ long long *pf_trace_buf_ = nullptr;
 }  // namespace
 
 // Two waves per SIMD (256 registers each, and then the compiler keeps the accumulators in ordinary registers: no copies
-// between the two register files around every use).  Tiles of 64 x 64 and 128 x 128 are not built: prefill_pipe.hip takes them all.
+// between the two register files around every use).  The tile of 128 x 128 is not built: prefill_pipe.hip takes all of it.
 // A state of N = 128 under a narrow head (P <= 64) is split over two waves per 32-channel tile, each with half of n: the
 // second adds its share of h C^T through LDS, both update their own half of the state, and the workgroup has twice the
 // threads for the staging.
@@ -546,7 +546,7 @@ static int launch_p(const PrefillParams &p, hipStream_t stream)
 {
     switch (p.N) {
         case 32: return launch_pn<P, 32>(p, stream);
-        case 64: if constexpr (P != 64) return launch_pn<P, 64>(p, stream); else break;
+        case 64: return launch_pn<P, 64>(p, stream);
         case 128: if constexpr (P != 128) return launch_pn<P, 128>(p, stream); else break;
     }
     return (int)hipErrorInvalidConfiguration;

@@ -643,20 +643,32 @@ int launch_p(const PrefillParams &p, hipStream_t stream)
 //   64 x 128   256: 70, 54;  384: 82, 92;  512: 84, 94;  1024: 167, 184      64 x 32    512: 57, 43;  768: 60, 70;  1024: 86, 110
 //   32 x 128   512: 99, 90;  768: 103, 133;  1024: 181, 175                  32 x 64    768: 81, 66;  1024: 84, 102
 //   32 x 32    768: 58, 42;  1024: 58, 63
-//   always: 64 x 64  256: 64, 39;  512: 76, 52;  1024: 101, 100;  1280: 170, 129      128 x 128  256: 88, 64;  512: 171, 122;  1024: 341, 239
+//   64 x 64    512: 76, 52;  1024: 101, 100;  1280: 170, 129    128 x 128  256: 88, 64;  512: 171, 122;  1024: 341, 239 (all)
+// A second round starts all over (LDS, the state's way in), which short prompts do not give back (us of the other kernel, of this one):
+// 640 workgroups of 64 x 64, 1 token 10.2, 12.2;  64: 14.1, 15.7;  200: 0.97 of the other's;  768 of 32 x 64, 32: 11.1, 12.6;  128: 1.03;
+// 200: 0.94;  512 of 32 x 128, 33: 13.9, 14.9;  128: 1.02;  200: 0.97.  With 64 x 64 the line depends on whether the other kernel's
+// last round is a full one (four workgroups to a compute unit; this one's times over the other's):
+//   one length  640: 128 tokens 1.02, 200 0.97;  1024: 400 1.05, 1024 0.99;  1280: 64 1.00, 96 0.96, 200 0.90;  1600: 64 1.04, 96 1.01, 200 0.98;
+//               2048: 64 1.04, 200 1.03, 700 0.96
+//   different   640: 128 1.08, 200 0.90;  1024: 200 1.08, 400 0.97;  1280: 200 1.16, 400 1.10, 700 1.00;  2048: 400 1.13, 512 1.11, 700 1.01
 // Prompts of different lengths (drawn from 1 up) are bound by the longest, which is alone at its end: twice as many and less (same
 // lengths at most: 128 x 64  512: 61, 53;  768: 85, 88;  64 x 128  512: 73, 63;  768: 84, 99;  64 x 32  768: 52, 45;  1024: 55, 57;  32 x 64  1024:
 // 80, 61;  32 x 128  768: 92, 89;  1024: 94, 111), if they are long enough for that to outweigh the start of a second round of workgroups
-// (512 workgroups of 128 x 64, 200 tokens each: 26, 31).
+// (512 workgroups of 128 x 64, 200 tokens each: 26, 31).  The host sees only that lengths are given: a call that gives equal ones is taken
+// for one of these (64 x 128, 512 pairs of one length: 84, 94).
 bool prefill_pipe_serves(const PrefillParams &p)
 {
     const long pairs = (long)p.batch * p.H;
     auto pick = [&](int n32, int n64, int n128) { return p.N == 32 ? n32 : p.N == 64 ? n64 : n128; };
-    constexpr int kAll = 1 << 30;
     const bool mixed = p.seq_len && p.L >= 512;
-    if (p.P == 32) return pairs <= (mixed ? pick(1024, 1024, 768) : pick(768, 768, 512));
-    if (p.P == 64) return pairs <= (mixed ? pick(768, kAll, 512) : pick(512, kAll, 256));
-    return pairs <= (mixed ? pick(512, 512, kAll) : pick(256, 256, kAll));
+    if ((p.P == 128 && p.N == 128) || pairs <= 256 * prefill_pipe_resident(p.P, p.N)) return true;
+    if (p.P == 64 && p.N == 64) {
+        if (pairs <= 768) return p.L >= 160;
+        if (pairs <= 1024) return p.L >= (p.seq_len ? 400 : 1024);
+        return p.L >= (p.seq_len ? 700 : 65);
+    }
+    if (p.P == 32) return p.L >= 128 && pairs <= (mixed ? pick(1024, 1024, 768) : pick(768, 768, 512));
+    return mixed && pairs <= (p.P == 64 && p.N == 32 ? 768 : 512);
 }
 
 int prefill_pipe_resident(int P, int N)

@@ -8,6 +8,9 @@ with fp32 state.  Integers (slot, pending count, position, ring head, parity) mu
 """
 from __future__ import annotations
 
+import ctypes
+import re
+
 import numpy as np
 import torch
 
@@ -186,3 +189,31 @@ def run_parity(wl: Workload, data: WorkloadData, layer: int = 0, x_override=None
         worst["y"], worst["xc"] = max(worst["y"], e_y), max(worst["xc"], e_xc)
     ssmv.ssmv_check(hip.cache.c)
     return worst
+
+
+class _KernelNode(ctypes.Structure):                         # hipKernelNodeParams
+    _fields_ = [("block", ctypes.c_uint32 * 3), ("extra", ctypes.c_void_p), ("func", ctypes.c_void_p), ("grid", ctypes.c_uint32 * 3),
+                ("args", ctypes.c_void_p), ("shared", ctypes.c_uint32)]
+
+
+def launches(call):
+    """The kernel launches of a call as (workgroups, threads of a workgroup), in order: the nodes of a graph it is captured into (and
+    that is not run)."""
+    path = next(m.group() for m in (re.search(r"/\S*libamdhip64\S*", line) for line in open("/proc/self/maps")) if m)
+    hip = ctypes.CDLL(path)
+    side, graph, n = torch.cuda.Stream(), torch.cuda.CUDAGraph(keep_graph=True), ctypes.c_size_t()
+    torch.cuda.synchronize()
+    with torch.cuda.stream(side):
+        graph.capture_begin()
+        call()
+        graph.capture_end()
+    raw = ctypes.c_void_p(graph.raw_cuda_graph())
+    assert hip.hipGraphGetNodes(raw, None, ctypes.byref(n)) == 0
+    nodes = (ctypes.c_void_p * n.value)()
+    assert hip.hipGraphGetNodes(raw, nodes, ctypes.byref(n)) == 0
+    out = []
+    for node in nodes:
+        k = _KernelNode()
+        assert hip.hipGraphKernelNodeGetParams(ctypes.c_void_p(node), ctypes.byref(k)) == 0
+        out.append((k.grid[0] * k.grid[1] * k.grid[2], k.block[0] * k.block[1] * k.block[2]))
+    return out
