@@ -1,10 +1,13 @@
-"""bf16 prefill launches of more (sequence, head) pairs than the pipelined kernel (csrc/prefill_pipe.hip) takes: which kernel a call runs."""
+"""bf16 prefill launches of more (sequence, head) pairs than the pipelined kernel (csrc/prefill_pipe.hip) takes: which kernel a call runs,
+and the other one (csrc/prefill_bf16.hip) against the oracle."""
+import numpy as np
 import pytest
 import torch
 
+import oracle
 import paper_2408_15237_amd as ssmv
 
-from _harness import launches
+from _harness import TOL, launches, rel_err, to_host
 
 pytestmark = pytest.mark.gpu
 
@@ -49,3 +52,67 @@ PIPE, OTHER = 0, 1
 def test_which_kernel_a_call_runs(P, N, pairs, L, lens, kernel):
     main = _prefill_launches(P, N, pairs, L, lens)[0]
     assert main == (pairs, _threads(P, N)[kernel])
+
+
+# (headdim, dstate, heads, batch): one step or a few past the lines, at any length up to 300 tokens
+LARGE = [(128, 64, 34, 8), (128, 32, 34, 8), (64, 128, 34, 8), (64, 64, 56, 16), (64, 32, 34, 16), (32, 64, 60, 13), (32, 32, 60, 13), (32, 128, 34, 16)]
+
+
+@pytest.mark.parametrize("block", [False, True], ids=["plain", "block"])
+@pytest.mark.parametrize("P,N,H,batch", LARGE)
+def test_large_launches_against_the_oracle(P, N, H, batch, block):
+    """Two groups of B and C, two prompts one after the other (the second continues the ring and the state of the first), then a
+    decoding round, at lengths around a chunk and at 300 tokens.  block: SiLU, gate, softplus, conv bias, row-major slots, and lengths
+    that differ; plain: none of it, tiled slots where the verify kernel takes the shape.  The oracle runs two heads of either group in three sequences."""
+    G, io, k = 2, torch.bfloat16, 4
+    g = torch.Generator(device="cuda").manual_seed(P + N + block)
+    rnd = lambda *s: torch.randn(*s, generator=g, device="cuda")
+    bf = lambda t: t.to(io)
+    Cx = H * P
+    w, bias, D, dtb = bf(rnd(Cx, 4) / 2), bf(rnd(Cx) * 0.1) if block else None, rnd(H), torch.rand(H, generator=g, device="cuda") - 0.5
+    A = -torch.exp(torch.rand(H, generator=g, device="cuda") * 2.7)
+    heads, seqs = [0, H // 2 - 1, H // 2, H - 1], [0, 1, batch - 1]
+    ch = np.concatenate([np.arange(h * P, (h + 1) * P) for h in heads])
+    act = "silu" if block else "none"
+    dims = ssmv.make_dims(batch, H, P, N, ngroups=G, kmax=k, io="bf16", conv_act=act, engine="vector" if block else "auto")
+    host = lambda t: to_host(t)
+    tokens = lambda n: dict(x=bf(rnd(batch, n, Cx)), dt=bf(rnd(batch, n, H) - 4 if block else torch.nn.functional.softplus(rnd(batch, n, H) - 4)),
+                            B=bf(rnd(batch, n, G, N) / N ** 0.5), C=bf(rnd(batch, n, G, N) / N ** 0.5), z=bf(rnd(batch, n, Cx)) if block else None)
+    for L in (1, 3, 31, 32, 33, 64, 65, 300):
+        h0, conv0 = rnd(batch, H, P, N) * 0.1, bf(rnd(batch, 3, Cx))
+        cache = ssmv.LayerCache.allocate(dims)
+        ssmv.ssmv_cache_reset(dims, cache.c, h0, conv0)
+        oras = [oracle.EagerOracle("scalar", host(A)[heads], host(D)[heads], host(w)[ch], host(bias)[ch] if block else None, host(h0[b:b + 1])[:, heads], "bf16", act, G,
+                                   conv_init=host(conv0[b:b + 1])[:, :, ch], dt_bias=host(dtb)[heads] if block else None, dt_softplus=block) for b in seqs]
+
+        def against_oracle(tok, y, lens, what):
+            for ora, b, n in zip(oras, seqs, lens):
+                if n:
+                    f = lambda t, sel: host(t[b:b + 1, :n])[:, :, sel]
+                    y_ref, _, _ = ora.verify(f(tok["x"], ch), f(tok["dt"], heads), host(tok["B"][b:b + 1, :n]), host(tok["C"][b:b + 1, :n]), z=f(tok["z"], ch) if block else None)
+                    ora.commit([n])
+                    assert rel_err(f(y, ch), y_ref) <= TOL["bf16"], "L = %d, %s, sequence %d" % (L, what, b)
+                assert bool((y[b, n:] == 7).all()), "L = %d, %s, sequence %d: outputs behind its length" % (L, what, b)
+
+        for what in ("first prompt", "second prompt"):
+            tok = tokens(L)
+            lens = torch.randint(0, L + 1, (batch,), generator=torch.Generator().manual_seed(L), dtype=torch.int32) if block else torch.full((batch,), L, dtype=torch.int32)
+            if block:
+                lens[1] = L
+            y = torch.full_like(tok["x"], 7.0)
+            run = lambda: ssmv.ssm_prefill_block(dims, cache.c, x_raw=tok["x"], conv_wgt=w, conv_bias=bias, dt=tok["dt"], dt_bias=dtb if block else None, dt_softplus=block,
+                                                 Bm=tok["B"], Cm=tok["C"], z=tok["z"], A=A, D=D, L=L, y_out=y, seq_len=lens_dev)
+            lens_dev = lens.cuda() if block else None
+            assert launches(run)[0] == (H * batch, _threads(P, N)[OTHER])
+            run()
+            against_oracle(tok, y, [int(lens[b]) for b in seqs], what)
+            h = torch.empty_like(h0)
+            ssmv.ssmv_materialize_block(dims, cache.c, A, dtb if block else None, block, h)
+            for ora, b in zip(oras, seqs):
+                assert rel_err(host(h[b:b + 1])[:, heads], ora.h) <= TOL["bf16"], "L = %d, %s, sequence %d: state" % (L, what, b)
+        tok = tokens(k)
+        y = torch.full_like(tok["x"], 7.0)
+        ssmv.ssm_block_multistep(dims, cache.c, x_raw=tok["x"], conv_wgt=w, conv_bias=bias, dt=tok["dt"], dt_bias=dtb if block else None, dt_softplus=block, Bm=tok["B"],
+                                 Cm=tok["C"], z=tok["z"], A=A, D=D, k=k, y_out=y)
+        against_oracle(tok, y, [k] * len(seqs), "decoding")
+        ssmv.ssmv_check(cache.c)
