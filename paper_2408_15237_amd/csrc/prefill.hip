@@ -470,46 +470,91 @@ bool prefill_shape_supported(int P, int N)
     return (P == 32 || P == 64 || P == 128) && (N == 32 || N == 64 || N == 128);
 }
 
-// Whether and how a prompt is cut.  The unit is one chunk of a workgroup that has its compute unit to itself (5.8 us with fp32
-// tensors of 128 x 64, prefill_pipe_chunk_us with bf16).  With q workgroups on the fullest compute unit a chunk takes 1.5 (bf16 1.3) of
-// that when the unit is full (r workgroups fit), and linearly less below; fp32 tiles of which five and more fit are counted as
-// four.  A segment's share of the state alone costs 0.5 of a chunk with outputs.  The two further launches cost 1.5 chunks (fp32); bf16:
-// 8 us, and what the states' four trips through memory take at 4.7 TB/s.  More workgroups than fit at once would run as a second round,
-// which always lost: not cut.  15 % of expected gain are asked for (bf16: 10 %).  Uncut and cut (us; one sequence unless said):
-//   bf16  128 x 64, 32 heads:  700 tokens 29 -> 26, 1500: 54 -> 34, 3000: 100 -> 41;  4 sequences, 3000: 99 -> 85;  8 heads, 1500: 52 -> 24
-//         64 x 128, 80 heads:  1500 tokens 69 -> 52, 3000: 130 -> 78;   64 x 64, 80 heads, 1500: 48 -> 37
-//   fp32  128 x 64, 32 heads:  400 tokens 81 -> 41, 1500: 278 -> 66, 3000: 548 -> 106;   64 x 128, 80 heads, 1500: 282 -> 129
-static void choose_segments(PrefillParams &p)
+// What a cut costs a kernel.  The unit of time is one chunk of a workgroup that has its compute unit to itself.
+struct CutCosts {
+    int resident;        // workgroups that fit a compute unit side by side
+    double company;      // with all of them there a chunk takes 1 + company, linearly less below; five and more are counted as four
+    double share;        // a chunk of a segment's share of the state alone
+    double launches;     // the two further launches
+    double trip;         // a segment's state through memory, four times
+    double worth;        // asked for: this much of the uncut time at most
+};
+
+// The segments of a prompt, or none.  More workgroups than fit at once would run as a second round, which always lost (320 heads x 1500
+// tokens at 128 x 64: 150 us cut in three, 118 us uncut): not cut.
+static void choose_segments(PrefillParams &p, const CutCosts &k)
 {
-    p.seg_chunks = p.seg_count = p.seg_pass = 0;
     constexpr int kCUs = 256;
-    const bool bf16 = p.io == SSMV_BF16;
-    if (bf16 && !prefill_pipe_serves(p)) return;
-    const int es = bf16 ? 2 : 4;
-    const int r = bf16 ? prefill_pipe_resident(p.P, p.N) : resident_f32(p.P, p.N);
-    const double unit = bf16 ? prefill_pipe_chunk_us(p.P, p.N) : 1.0, company = bf16 ? 0.3 : 0.5;
-    const double trips = bf16 ? 4.0 * p.P * p.N * sizeof(float) / 4.7e6 : 0.0;       // us per workgroup
     const long pairs = (long)p.batch * p.H;
     const int n = (p.L + kPrefillChunk - 1) / kPrefillChunk;
     // the last segment may end with a chunk of one token, and has to hold a state in its rows
-    const int shortest = (4 * p.N / es + kPrefillChunk - 1 + kPrefillChunk - 1) / kPrefillChunk;
-    auto chunk_time = [&](long wgs) { return r > 1 ? 1.0 + company * ((wgs + kCUs - 1) / kCUs - 1) / ((r < 4 ? r : 4) - 1) : 1.0; };
-    double best = (bf16 ? 0.9 : 0.85) * n * chunk_time(pairs);
+    const int shortest = (4 * p.N / (p.io == SSMV_BF16 ? 2 : 4) + kPrefillChunk - 1 + kPrefillChunk - 1) / kPrefillChunk;
+    const int r = k.resident;
+    auto chunk_time = [&](long wgs) { return r > 1 ? 1.0 + k.company * ((wgs + kCUs - 1) / kCUs - 1) / ((r < 4 ? r : 4) - 1) : 1.0; };
+    p.seg_chunks = p.seg_count = 0;
+    double best = k.worth * n * chunk_time(pairs);
     const long most = kCUs * r / pairs + 1 < segments_of(shortest, n) ? kCUs * r / pairs + 1 : segments_of(shortest, n);
     for (int ns = (int)most; ns >= 3; --ns) {
-        const double launches = bf16 ? (8.0 + trips * pairs * (ns - 1)) / unit : 1.5;
-        // the segment lengths l that make ns segments; the time max(n - (ns - 1) l, l / 2) + l falls and then rises with l
+        // the segment lengths l that make ns segments; the time max(n - (ns - 1) l, share l) + l falls and then rises with l
         int lo = (n - 1) / ns + 1, hi = (n - 1) / (ns - 1);
         if (lo < shortest) lo = shortest;
         if (hi < lo) continue;
-        const int turn = (int)(n / (ns - 0.5));
+        const int turn = (int)(n / (ns - 1 + k.share));
         for (int l = turn; l <= turn + 1; ++l) {
             const int len = l < lo ? lo : l > hi ? hi : l, first = n - (ns - 1) * len;
-            const double t = ((first > 0.5 * len ? first : 0.5 * len) + len) * chunk_time(pairs * (ns - 1)) + launches;
+            const double t = ((first > k.share * len ? first : k.share * len) + len) * chunk_time(pairs * (ns - 1)) + k.launches + k.trip * pairs * (ns - 1);
             if (t < best) { best = t; p.seg_chunks = len; p.seg_count = ns; }
         }
     }
-    if (!p.seg_count) return;
+}
+
+// Whether a bf16 prompt that the pipelined kernel would take whole or cut is cut by the other kernel instead.  That one fits more workgroups
+// (prefill_bf16_resident), so that it can cut a prompt into more segments where the pipelined kernel has room for a few or none: worth it
+// from so many tokens on, between two numbers of (sequence, head) pairs.  Lines from times of both at 260 to 4096 tokens, 4 to 512
+// pairs, prompts of one length and of different ones (drawn from 1 up).  The pipelined kernel's choice, this one's (us):
+//   one length  128 x 32  96 pairs, 4096 tokens: 104, 74;  144, 3000: 104, 88     64 x 32  176, 3000: 89, 66
+//               32 x 32  288, 4096: 110, 83                                       32 x 128  384, 4096: 319, 253
+//   different   128 x 32  80, 4096: 95, 60;  96, 1500: 56, 38     64 x 32  176, 4096: 118, 75     32 x 32  288, 4096: 113, 74     32 x 128  96, 3000: 96, 76
+//   outside     128 x 32  192, 4096: 140, 152;  208, 1024: 43, 51   64 x 32  352, 3000: 106, 126    32 x 128  288, 3000, different: 113, 189
+static bool prefill_bf16_cuts(const PrefillParams &p)
+{
+    if (!prefill_bf16_resident(p.P, p.N)) return false;
+    const long pairs = (long)p.batch * p.H;
+    auto between = [&](int tokens, int from, int to) { return p.L >= tokens && pairs >= from && pairs <= to; };
+    if (p.seq_len) {
+        if (p.P == 32) return p.N == 32 ? between(1500, 112, 256) || between(2048, 80, 384) : between(3000, 64, 144);
+        return p.P == 64 ? between(1024, 80, 224) : between(1024, 80, 144) || between(1500, 32, 208);
+    }
+    if (p.P == 32) return p.N == 32 ? between(3000, 112, 448) : between(1500, 288, 384) || between(3000, 80, 192);
+    return p.P == 64 ? between(2048, 144, 256) : between(1500, 48, 176);
+}
+
+// Whether and how a prompt is cut, and by which kernel: the return value says whether by the pipelined one (bf16).
+// Uncut and cut (us; one sequence unless said):
+//   bf16  128 x 64, 32 heads:  700 tokens 29 -> 26, 1500: 54 -> 34, 3000: 100 -> 41;  4 sequences, 3000: 99 -> 85;  8 heads, 1500: 52 -> 24
+//         64 x 128, 80 heads:  1500 tokens 69 -> 52, 3000: 130 -> 78;   64 x 64, 80 heads, 1500: 48 -> 37
+//   fp32  128 x 64, 32 heads:  400 tokens 81 -> 41, 1500: 278 -> 66, 3000: 548 -> 106;   64 x 128, 80 heads, 1500: 282 -> 129
+// bf16 over nine tiles, 4 to 512 pairs and 260 to 4096 tokens of one length: never more than 4 % slower than uncut, 13 % faster on average.  Of
+// prompts of different lengths only the device knows them: one sequence that is far shorter than L pays for the launches (32 heads of
+// 128 x 64, 700 tokens given, one there: 8 -> 11 us).
+static bool cut_prompt(PrefillParams &p)
+{
+    p.seg_chunks = p.seg_count = p.seg_pass = 0;
+    const bool bf16 = p.io == SSMV_BF16;
+    const int es = bf16 ? 2 : 4;
+    bool pipe = bf16 && prefill_pipe_serves(p);
+    if (!bf16) choose_segments(p, {resident_f32(p.P, p.N), 0.5, 0.5, 1.5, 0.0, 0.85});
+    else if (pipe) {
+        if (prefill_bf16_cuts(p)) {
+            choose_segments(p, {prefill_bf16_resident(p.P, p.N), 0.5, 0.6, 5.0, 0.0, 0.85});
+            pipe = !p.seg_count;
+        }
+        if (!p.seg_count) {
+            const double unit = prefill_pipe_chunk_us(p.P, p.N);
+            choose_segments(p, {prefill_pipe_resident(p.P, p.N), 0.3, 0.5, 8.0 / unit, 4.0 * p.P * p.N * sizeof(float) / 4.7e6 / unit, 0.9});
+        }
+    }
+    if (!p.seg_count) return pipe;
     // y carries states between the launches: not if it overlaps anything that is still to be read
     const char *y0 = static_cast<const char *>(p.y), *y1 = y0 + (size_t)p.batch * p.L * p.H * p.P * es;
     auto overlaps = [&](const void *t, size_t bytes) {
@@ -520,13 +565,16 @@ static void choose_segments(PrefillParams &p)
     if (overlaps(p.x_raw, tok * ch * es) || overlaps(p.z, tok * ch * es) || overlaps(p.dt, tok * p.H * es) ||
         overlaps(p.Bm, tok * p.G * p.N * es) || overlaps(p.Cm, tok * p.G * p.N * es) || overlaps(p.wgt, ch * SSMV_CONV_WIDTH * es) ||
         overlaps(p.bias, ch * es) || overlaps(p.A, p.H * sizeof(float)) || overlaps(p.D, p.H * sizeof(float)) ||
-        overlaps(p.dt_bias, p.H * sizeof(float)) || overlaps(p.seq_len, p.batch * sizeof(int32_t)))
+        overlaps(p.dt_bias, p.H * sizeof(float)) || overlaps(p.seq_len, p.batch * sizeof(int32_t))) {
         p.seg_chunks = p.seg_count = 0;
+        return bf16;                                     // uncut, which the pipelined kernel serves or nothing would have been cut
+    }
+    return pipe;
 }
 
-static int launch_pass(const PrefillParams &p, hipStream_t stream)
+static int launch_pass(const PrefillParams &p, bool pipe, hipStream_t stream)
 {
-    if (p.io == SSMV_BF16) return p.seg_count || prefill_pipe_serves(p) ? launch_prefill_pipe(p, stream) : launch_prefill_bf16(p, stream);
+    if (p.io == SSMV_BF16) return pipe ? launch_prefill_pipe(p, stream) : launch_prefill_bf16(p, stream);
     switch (p.P) {
         case 32: return launch_p<32>(p, stream);
         case 64: return launch_p<64>(p, stream);
@@ -538,8 +586,8 @@ static int launch_pass(const PrefillParams &p, hipStream_t stream)
 int launch_prefill(const PrefillParams &p_in, hipStream_t stream)
 {
     PrefillParams p = p_in;
-    choose_segments(p);
-    int rc = launch_pass(p, stream);
+    const bool pipe = cut_prompt(p);
+    int rc = launch_pass(p, pipe, stream);
     if (rc != 0) return rc;
     if (p.seg_count) {
         const dim3 grid(p.P * p.N / 1024, p.H, p.batch);
@@ -547,7 +595,7 @@ int launch_prefill(const PrefillParams &p_in, hipStream_t stream)
         else hipLaunchKernelGGL(prefill_combine_kernel<4>, grid, dim3(256), 0, stream, p);
         if ((rc = (int)hipGetLastError()) != 0) return rc;
         p.seg_pass = 1;
-        return launch_pass(p, stream);
+        return launch_pass(p, pipe, stream);
     }
     hipLaunchKernelGGL(prefill_finish_kernel, dim3((p.batch + 63) / 64), dim3(64), 0, stream, p);
     return (int)hipGetLastError();

@@ -48,6 +48,8 @@ namespace {
 
 constexpr int kQ = kPrefillChunk;
 
+__host__ __device__ constexpr bool cuts(int P, int N) { return N == 32 || (P == 32 && N == 128); }      // see prefill_bf16_resident
+
 template <int P, int N>
 struct PfLds {              // byte offsets of the LDS arrays (bf16 unless said)
     static constexpr int XS = kQ * 2 + 16;                 // row stride of the arrays indexed [..][token]
@@ -92,7 +94,10 @@ __device__ long long *pf_trace_buf_ = nullptr;
 // A state of N = 128 under a narrow head (P <= 64) is split over two waves per 32-channel tile, each with half of n: the
 // second adds its share of h C^T through LDS, both update their own half of the state, and the workgroup has twice the
 // threads for the staging.
-template <int P, int N>
+// SEG: the workgroup owns one segment of the prompt instead of all of it (prefill_split.h); in the first pass of such a
+// prompt every segment but the first one only needs its share of the state: no C, no Q x Q product, no outputs, and one
+// barrier less per chunk.
+template <int P, int N, bool SEG>
 __global__ __launch_bounds__(2 * P * prefill_nsplit(P, N)) __attribute__((amdgpu_waves_per_eu(2)))
 void prefill_bf16_kernel(const PrefillParams p)
 {
@@ -128,23 +133,34 @@ void prefill_bf16_kernel(const PrefillParams p)
     float *sDt = reinterpret_cast<float *>(lds + Ld::oDt) + wave * Q;
     float *sW = reinterpret_cast<float *>(lds + Ld::oW) + wave * Q;
     const int H = p.H, G = p.G;
-    const PrefillItem item = prefill_item<false>(p);
+    const PrefillItem item = prefill_item<SEG>(p);
     const int hd = item.hd, b = item.b;
     const int Ls = p.L;                                 // token stride of the arrays
     const int L = item.L;                               // this sequence's prompt length
     if (L == 0) return;                                 // nothing to feed: state, ring and outputs stay as they are
-    const int n_chunks = (L + Q - 1) / Q;
+    Segment seg = {0, (L + Q - 1) / Q, 0, true, true, true};
+    if constexpr (SEG) {
+        seg = segment_of(p, L, item.slot);
+        if (!seg.work) return;
+    }
+    const int c_beg = SEG ? seg.c0 : 0, c_end = seg.c1; // the chunks of this workgroup
+    const bool emit = !SEG || seg.emit;                 // whether it writes outputs
     const int HP = H * P, GN = G * N;
     const int g = hd / (H / G);
     const int cur = (int)((unsigned)p.cur_slot[b] % 3u);
     const int mask = p.ring_len - 1;
-    const int conv_head = p.conv_head[b] & mask;
+    // (the last pass of a segmented prompt runs behind the launch that has moved conv_head on already)
+    const int conv_head = (p.conv_head[b] - (SEG && p.seg_pass == 1 ? L : 0)) & mask;
     const float A2_h = p.A[hd] * kLog2e, D_h = p.D[hd];
     const float dtb_h = p.dt_bias ? p.dt_bias[hd] : 0.f;
     const bool gated = p.z != nullptr, silu = p.conv_act == SSMV_ACT_SILU;
     float *state = p.state + (size_t)cur * p.slot_stride + ((size_t)b * H + hd) * P * N;
 
     char *y_b = reinterpret_cast<char *>(p.y) + (size_t)b * Ls * HP * 2;
+    // a segment's state between the passes: the lane's float4 number q of tile tn in the rows of y from the segment's area on
+    auto seg_at = [&](int tn, int q) {
+        return reinterpret_cast<float4 *>(y_b + seg_piece<2>(((wave_u * TNL + tn) * 4 + q) * 64 + lane, P, seg.area, HP, hd));
+    };
     // state -> accumulator registers, transposed tiles [n][p]: register 4 q + e of tile tn holds
     // h[p = 32 pt + li][n = 32 (TNL nh + tn) + 16 (q/2) + 8 lh + 4 (q%2) + e]
     f16v hacc[TNL];
@@ -155,7 +171,9 @@ void prefill_bf16_kernel(const PrefillParams p)
     for (int tn = 0; tn < TNL; ++tn)
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-            const float4 v = *reinterpret_cast<const float4 *>(state_at(tn, q));
+            float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (!SEG || c_beg == 0) v = *reinterpret_cast<const float4 *>(state_at(tn, q));
+            else if (p.seg_pass == 1) v = *seg_at(tn, q);
             hacc[tn][4 * q + 0] = v.x; hacc[tn][4 * q + 1] = v.y; hacc[tn][4 * q + 2] = v.z; hacc[tn][4 * q + 3] = v.w;
         }
     // G^T and M^T in 16 x 16 quadrants (tokens t of the first or second half of the chunk, s likewise; lane: t = 16 qi + lane % 16,
@@ -194,9 +212,11 @@ void prefill_bf16_kernel(const PrefillParams p)
     if (tid < P) {
         uint32_t hist[W - 1];                           // as bits
 #pragma unroll
-        for (int j = 0; j < W - 1; ++j)
-            hist[j] = reinterpret_cast<const uint16_t *>(p.ring)[((size_t)b * p.ring_len + ((conv_head + 1 - (W - 1) + j) & mask)) * HP + ch];
-        sCar[P + pc] = make_uint2(hist[0] << 16, hist[1] | (hist[2] << 16));
+        for (int j = 0; j < W - 1; ++j) {
+            if (SEG && c_beg > 0) hist[j] = raw_bits(c_beg * Q - (W - 1) + j);
+            else hist[j] = reinterpret_cast<const uint16_t *>(p.ring)[((size_t)b * p.ring_len + ((conv_head + 1 - (W - 1) + j) & mask)) * HP + ch];
+        }
+        sCar[((c_beg + 1) & 1) * P + pc] = make_uint2(hist[0] << 16, hist[1] | (hist[2] << 16));
     }
 
     constexpr int UI = (4 * N + NT - 1) / NT;           // (n, eight tokens) units of the transposed B per thread and chunk
@@ -238,7 +258,7 @@ void prefill_bf16_kernel(const PrefillParams p)
             const int idx = wave_u + k * Ld::NW;
             if (idx < PIECES / 2) {
                 load_to_lds16(Bc, obc[k], dB + idx * 1024);
-                load_to_lds16(Cc, obc[k], dC + idx * 1024);
+                if (emit) load_to_lds16(Cc, obc[k], dC + idx * 1024);
             }
         }
     };
@@ -256,6 +276,7 @@ void prefill_bf16_kernel(const PrefillParams p)
         }
     // Per chunk, of this lane's token t = li: log2 e * cum_t and exp(cum_t); and exp(cum_Q) (the same in every lane).
     float cum_t, at_t, aq;
+    float cum_all = 0.f;                                // SEG: log2 of the segment's decay
     auto consume = [&](int c, uint32_t dt_bits) {
         const int t0 = c * Q, s0 = sg * QS;
         const char *sB = lds + Ld::oB + (c & (Ld::BCC - 1)) * Ld::BCS;
@@ -270,6 +291,7 @@ void prefill_bf16_kernel(const PrefillParams p)
             cum_t = v;
             at_t = __builtin_amdgcn_exp2f(v);
             aq = __builtin_amdgcn_exp2f(cq);
+            if constexpr (SEG) cum_all += cq;
             if (lh == 0) {
                 sCum[li] = v;
                 sDt[li] = d;
@@ -370,38 +392,38 @@ void prefill_bf16_kernel(const PrefillParams p)
     const int prow = pt * 32 + li;                      // this lane's channel (inside the head) as an operand row
     float *sZ = reinterpret_cast<float *>(lds + Ld::oZ) + pt * 1024;
     uint32_t dt_bits;
-    issue_x_loads(0, dt_bits);
-    issue_bc_loads(0);
+    issue_x_loads(c_beg, dt_bits);
+    issue_bc_loads(c_beg);
     wait_direct_loads();
     __syncthreads();
-    for (int c = 0; c < n_chunks; ++c) {
+    for (int c = c_beg; c < c_end; ++c) {
         const int t0 = c * Q;
         const char *sB = lds + Ld::oB + (c & (Ld::BCC - 1)) * Ld::BCS, *sC = lds + Ld::oC + (c & (Ld::BCC - 1)) * Ld::BCS;
         consume(c, dt_bits);
         __syncthreads();
         // the stores ahead of the loads on the wide tiles (2 % there; the other way round on the narrow ones)
         constexpr bool kStoresFirst = P >= 128 && N >= 64;
-        if (kStoresFirst && c > 0 && nh == 0) {
+        if (kStoresFirst && c > c_beg && nh == 0 && emit) {
             flush_outputs(c - 1);
             __builtin_amdgcn_sched_barrier(0);
         }
-        if (c + 1 < n_chunks) {                            // under way for the whole chunk
+        if (c + 1 < c_end) {                            // under way for the whole chunk
             issue_x_loads(c + 1, dt_bits);
             if (Ld::BCC == 2) issue_bc_loads(c + 1);
         }
-        if (!kStoresFirst && c > 0 && nh == 0) flush_outputs(c - 1);
+        if (!kStoresFirst && c > c_beg && nh == 0 && emit) flush_outputs(c - 1);
         __builtin_amdgcn_sched_barrier(0);              // the loads and stores stay here, a chunk of arithmetic ahead of the next wait
 
         const int t = li;                               // this lane's token within the chunk
         using QV = XVec<SSMV_BF16, 4>;                  // four adjacent channels
         typename QV::Raw zraw[4];
-        if (gated && nh == 0) {                 // requested ahead of the matrix products
+        if (gated && nh == 0 && emit) {                 // requested ahead of the matrix products
             const char *zc = chunk_of(z_b, c, HP) + off(min(t, L - 1 - t0), HP, hd * P + pt * 32 + 4 * lh);
 #pragma unroll
             for (int q = 0; q < 4; ++q) zraw[q] = *reinterpret_cast<const typename QV::Raw *>(zc + 16 * q);
         }
         f16v yacc = {0};
-        {
+        if (emit) {
             // C of this lane's token, all of it: the B operand of G^T and of h C^T
             uint4 cop[N / 16];
 #pragma unroll
@@ -460,9 +482,9 @@ void prefill_bf16_kernel(const PrefillParams p)
         uint4 xop[2];
 #pragma unroll
         for (int st = 0; st < 2; ++st) xop[st] = *reinterpret_cast<const uint4 *>(sX + prow * XS + (16 * st + 8 * lh) * 2);
-        __syncthreads();     // M^T is complete; nobody reads this chunk's B and C rows any more
-        if (Ld::BCC == 1 && c + 1 < n_chunks) issue_bc_loads(c + 1);
-        if (nh == 0) {
+        if (emit) __syncthreads();     // M^T is complete; nobody reads this chunk's B and C rows any more
+        if (Ld::BCC == 1 && c + 1 < c_end) issue_bc_loads(c + 1);
+        if (nh == 0 && emit) {
             if constexpr (NSPL == 2) {
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
@@ -490,7 +512,7 @@ void prefill_bf16_kernel(const PrefillParams p)
             }
         }
         // ---- gate, store ----
-        if (nh == 0) {
+        if (nh == 0 && emit) {
             if (gated) {
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
@@ -510,7 +532,20 @@ void prefill_bf16_kernel(const PrefillParams p)
         __syncthreads();     // ... and so has everybody's; the next chunk overwrites X, B^T, M
     }
 
-    if (nh == 0) flush_outputs(n_chunks - 1);
+    if (nh == 0 && emit) flush_outputs(c_end - 1);
+    if constexpr (SEG) {
+        if (!seg.last) {
+            if (p.seg_pass == 1) return;                // the next segment has its state already
+            // a segment's state on its way to the combining launch
+#pragma unroll
+            for (int tn = 0; tn < TNL; ++tn)
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    *seg_at(tn, q) = make_float4(hacc[tn][4 * q + 0], hacc[tn][4 * q + 1], hacc[tn][4 * q + 2], hacc[tn][4 * q + 3]);
+            if (c_beg > 0 && tid == 0) *reinterpret_cast<float *>(y_b + seg_piece<2>(P * N / 4, P, seg.area, HP, hd)) = cum_all;
+            return;
+        }
+    }
     // ---- state back in place; the newest W-1 raw inputs into the ring behind conv_head -----------------------
 #pragma unroll
     for (int tn = 0; tn < TNL; ++tn)
@@ -530,33 +565,56 @@ void prefill_bf16_kernel(const PrefillParams p)
 #endif
 }
 
-template <int P, int N>
+template <int P, int N, bool SEG>
 static int launch_pn(const PrefillParams &p, hipStream_t stream)
 {
     const size_t lds = PfLds<P, N>::total;
-    const dim3 grid((unsigned)(p.H * p.batch)), block(2 * P * PfLds<P, N>::NSPL);
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&prefill_bf16_kernel<P, N>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    const dim3 grid((unsigned)(p.H * p.batch) * (SEG ? p.seg_count - 1 : 1)), block(2 * P * PfLds<P, N>::NSPL);
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&prefill_bf16_kernel<P, N, SEG>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return (int)e;
-    hipLaunchKernelGGL((prefill_bf16_kernel<P, N>), grid, block, lds, stream, p);
+    hipLaunchKernelGGL((prefill_bf16_kernel<P, N, SEG>), grid, block, lds, stream, p);
     return (int)hipGetLastError();
+}
+
+template <int P, int N>
+static int launch_n(const PrefillParams &p, hipStream_t stream)
+{
+    if constexpr (P == 128 && N == 128) return (int)hipErrorInvalidConfiguration;
+    else if constexpr (cuts(P, N)) return p.seg_count ? launch_pn<P, N, true>(p, stream) : launch_pn<P, N, false>(p, stream);
+    else return p.seg_count ? (int)hipErrorInvalidConfiguration : launch_pn<P, N, false>(p, stream);
 }
 
 template <int P>
 static int launch_p(const PrefillParams &p, hipStream_t stream)
 {
     switch (p.N) {
-        case 32: return launch_pn<P, 32>(p, stream);
-        case 64: return launch_pn<P, 64>(p, stream);
-        case 128: if constexpr (P != 128) return launch_pn<P, 128>(p, stream); else break;
+        case 32: return launch_n<P, 32>(p, stream);
+        case 64: return launch_n<P, 64>(p, stream);
+        case 128: return launch_n<P, 128>(p, stream);
+        default: return (int)hipErrorInvalidConfiguration;
     }
-    return (int)hipErrorInvalidConfiguration;
+}
+
+template <int P, int N>
+static constexpr int resident()
+{
+    constexpr int by_lds = 160 * 1024 / PfLds<P, N>::total, by_waves = 12 / PfLds<P, N>::NW;      // three waves per SIMD by their registers
+    return by_lds < by_waves ? by_lds : by_waves;
+}
+
+// The tiles whose prompts this kernel cuts, under prefill_bf16_cuts: those of which it fits more than twice as many workgroups on a compute
+// unit as the pipelined kernel does (8 to 3, 5 to 2, 3 to 1, 3 to 1), at 1.4 to 2.1 times its time per chunk
+int prefill_bf16_resident(int P, int N)
+{
+    if (!cuts(P, N)) return 0;
+    return P == 64 ? resident<64, 32>() : P == 128 ? resident<128, 32>() : N == 32 ? resident<32, 32>() : resident<32, 128>();
 }
 
 #ifdef SSMV_TRACE
 int set_trace_prefill(long long *buf) { return (int)hipMemcpyToSymbol(HIP_SYMBOL(pf_trace_buf_), &buf, sizeof(buf)); }
 #endif
 
-// large launches (prefill_pipe_serves); the caller appends the bookkeeping launch
+// large launches (prefill_pipe_serves), and a pass over a prompt that is cut; the caller appends the bookkeeping or the combining launch
 int launch_prefill_bf16(const PrefillParams &p, hipStream_t stream)
 {
     switch (p.P) {

@@ -677,8 +677,14 @@ int prefill_pipe_resident(int P, int N)
     return P == 32 ? pick(3, 2, 1) : P == 64 ? pick(2, 2, 1) : 1;
 }
 
-// one workgroup to a compute unit; slope between prompts of 1500 and 3000 tokens
-double prefill_pipe_chunk_us(int P, int N) { return N == 128 ? (P == 128 ? 1.38 : 1.25) : P == 128 ? 1.0 : 0.78; }
+// One workgroup to a compute unit, most units idle; slope between prompts of 1500 and 3000 tokens (64 x 32: 300 and 1024).  With a workgroup on
+// every unit a chunk takes 0.86 to 1.01 (N <= 64) and 1.33 to 1.39 us.  Counted with those, choose_segments cuts more, and prompts of different
+// lengths lose by it (288 pairs of 32 x 32, 1500 tokens at most: 41 whole, 54 cut).
+double prefill_pipe_chunk_us(int P, int N)
+{
+    if (N == 128) return P == 128 ? 1.38 : 1.25;
+    return P == 128 ? 1.0 : P == 64 && N == 32 ? 0.91 : 0.78;
+}
 
 int launch_prefill_pipe(const PrefillParams &p, hipStream_t stream)
 {

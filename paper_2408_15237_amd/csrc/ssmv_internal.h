@@ -157,9 +157,10 @@ bool verify_shape_supported(int N, int R, bool diag);
 
 int launch_conv(const ConvParams &p, hipStream_t stream);
 int launch_prefill(const PrefillParams &p, hipStream_t stream);
-int launch_prefill_bf16(const PrefillParams &p, hipStream_t stream);      // bf16 tensors: the main kernel only, of large launches
-int launch_prefill_pipe(const PrefillParams &p, hipStream_t stream);      // the same of smaller ones, and of prompts that are cut
-bool prefill_pipe_serves(const PrefillParams &p);                         // which of the two
+int launch_prefill_bf16(const PrefillParams &p, hipStream_t stream);      // bf16 tensors: the main kernel only, of large launches and some cut prompts
+int prefill_bf16_resident(int P, int N);                                  // its workgroups that fit a compute unit side by side; 0: it cuts no prompts
+int launch_prefill_pipe(const PrefillParams &p, hipStream_t stream);      // the same of smaller ones, and of the other cut prompts
+bool prefill_pipe_serves(const PrefillParams &p);                         // which of the two, for a prompt that is not cut
 int prefill_pipe_resident(int P, int N);                                  // workgroups of the second that fit a compute unit side by side
 double prefill_pipe_chunk_us(int P, int N);                               // and its time per chunk
 bool prefill_shape_supported(int P, int N);

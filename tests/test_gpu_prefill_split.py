@@ -13,7 +13,7 @@ import oracle
 import paper_2408_15237_amd as ssmv
 from workload import Workload, generate, round_to_io
 
-from _harness import HipLayer, TOL, rel_err, to_dev, to_host
+from _harness import HipLayer, TOL, launches, rel_err, to_dev, to_host
 
 pytestmark = pytest.mark.gpu
 
@@ -239,3 +239,91 @@ def test_segments_of_more_sequences_than_lanes(io):
             assert rel_err(y_h[b, :n], y_ref[0]) <= TOL[io], "sequence %d" % b
         assert np.all(y_h[b, n:] == 7.0) and rel_err(h_g[b:b + 1], ora.h) <= TOL[io], "sequence %d" % b
     assert hip.cache.ints()["pos"].tolist() == lens.tolist()
+
+
+# (headdim, dstate, pairs, tokens, whether lengths are given): the ends of the lines within which the bf16 kernel of the large launches
+# (csrc/prefill_bf16.hip) cuts a prompt, which the pipelined one would cut into fewer segments or leave whole
+OTHER_CUTS = [(32, 32, 112, 3000, False), (32, 32, 448, 3000, False), (32, 32, 112, 1500, True), (32, 32, 256, 1500, True), (32, 32, 80, 2048, True), (32, 32, 384, 2048, True),
+              (32, 128, 288, 1500, False), (32, 128, 384, 1500, False), (32, 128, 80, 3000, False), (32, 128, 192, 3000, False), (32, 128, 64, 3000, True),
+              (32, 128, 144, 3000, True), (64, 32, 144, 2048, False), (64, 32, 256, 2048, False), (64, 32, 80, 1024, True), (64, 32, 224, 1024, True),
+              (128, 32, 48, 1500, False), (128, 32, 176, 1500, False), (128, 32, 80, 1024, True), (128, 32, 144, 1024, True), (128, 32, 32, 1500, True), (128, 32, 208, 1500, True)]
+
+
+@pytest.mark.parametrize("P,N,pairs,L,lens", OTHER_CUTS)
+def test_which_kernel_cuts(P, N, pairs, L, lens):
+    """At the ends of a line the other kernel cuts (its first pass: threads of one wave per 32 channels and half of a large state); a token
+    less, a pair less or more, lengths not given (or given), or y over the gate, and the pipelined kernel takes the prompt."""
+    def first(pairs, L, lens, in_place=False):
+        H = 4 if pairs % 4 == 0 else 1
+        batch = pairs // H
+        dims = ssmv.make_dims(batch, H, P, N, kmax=4, io="bf16")
+        cache = ssmv.LayerCache.allocate(dims)
+        new = lambda *s: torch.zeros(*s, dtype=torch.bfloat16, device="cuda")
+        x, y, w, dt, B, C, A = new(batch, L, H * P), new(batch, L, H * P), new(H * P, 4), new(batch, L, H), new(batch, L, 1, N), new(batch, L, 1, N), torch.zeros(H, device="cuda")
+        seq_len = torch.full((batch,), L, dtype=torch.int32, device="cuda") if lens else None
+        made = launches(lambda: ssmv.ssm_prefill_block(dims, cache.c, x_raw=x, conv_wgt=w, dt=dt, Bm=B, Cm=C, A=A, D=A, L=L, y_out=y, z=y if in_place else None, seq_len=seq_len))
+        return len(made), made[0][1] == (4 * P if N == 128 else 2 * P)
+
+    rule = lambda pairs, L, lens: any((P, N, lens) == (p, n, given) and lo <= pairs <= hi and L >= tokens for p, n, given, tokens, lo, hi in (
+        (32, 32, False, 3000, 112, 448), (32, 32, True, 1500, 112, 256), (32, 32, True, 2048, 80, 384), (32, 128, False, 1500, 288, 384), (32, 128, False, 3000, 80, 192),
+        (32, 128, True, 3000, 64, 144), (64, 32, False, 2048, 144, 256), (64, 32, True, 1024, 80, 224), (128, 32, False, 1500, 48, 176), (128, 32, True, 1024, 80, 144),
+        (128, 32, True, 1500, 32, 208)))
+    assert rule(pairs, L, lens) and first(pairs, L, lens) == (CUT, True)
+    assert first(pairs, L, lens, in_place=True) == (UNCUT, False)
+    for q in ((pairs, L - 1, lens), (pairs - 1, L, lens), (pairs + 1, L, lens), (pairs, L, not lens)):
+        assert first(*q)[1] == rule(*q), q
+
+
+@pytest.mark.parametrize("P,N,pairs,L,lens", OTHER_CUTS[::2])
+def test_segments_of_the_other_kernel_against_the_oracle(P, N, pairs, L, lens):
+    """A cut prompt behind another one (so that state, ring and conv_head are in the middle of something), then a decoding round; with SiLU,
+    gate, softplus and two groups, tiled or row-major slots.  The oracle runs a head of either group in two sequences."""
+    H, G, k, io = 4 if pairs % 16 else 16, 2, 4, torch.bfloat16
+    batch = pairs // H
+    assert H * batch == pairs
+    g = torch.Generator(device="cuda").manual_seed(pairs)
+    rnd = lambda *s: torch.randn(*s, generator=g, device="cuda")
+    bf, Cx = (lambda t: t.to(io)), H * P
+    w, bias, D, dtb = bf(rnd(Cx, 4) / 2), bf(rnd(Cx) * 0.1), rnd(H), torch.rand(H, generator=g, device="cuda") - 0.5
+    A = -torch.exp(torch.rand(H, generator=g, device="cuda") * 2.7)
+    heads, seqs = [1, H - 1], [0, batch - 1]
+    ch = np.concatenate([np.arange(h * P, (h + 1) * P) for h in heads])
+    dims = ssmv.make_dims(batch, H, P, N, ngroups=G, kmax=k, io="bf16", conv_act="silu", engine="vector" if lens else "auto")
+    cache = ssmv.LayerCache.allocate(dims)
+    h0, conv0 = rnd(batch, H, P, N) * 0.1, bf(rnd(batch, 3, Cx))
+    ssmv.ssmv_cache_reset(dims, cache.c, h0, conv0)
+    oras = [oracle.EagerOracle("scalar", to_host(A)[heads], to_host(D)[heads], to_host(w)[ch], to_host(bias)[ch], to_host(h0[b:b + 1])[:, heads], "bf16", "silu", G,
+                               conv_init=to_host(conv0[b:b + 1])[:, :, ch], dt_bias=to_host(dtb)[heads], dt_softplus=True) for b in seqs]
+
+    def compare(tok, y, lens, what):
+        for ora, b in zip(oras, seqs):
+            n = int(lens[b])
+            f = lambda t, sel: to_host(t[b:b + 1, :n])[:, :, sel]
+            y_ref, _, _ = ora.verify(f(tok["x"], ch), f(tok["dt"], heads), to_host(tok["B"][b:b + 1, :n]), to_host(tok["C"][b:b + 1, :n]), z=f(tok["z"], ch))
+            ora.commit([n])
+            assert rel_err(f(y, ch), y_ref) <= TOL["bf16"], "%s, sequence %d" % (what, b)
+            assert bool((y[b, n:] == 7).all()), "%s, sequence %d: outputs behind its length" % (what, b)
+
+    for n, what in ((37, "short prompt"), (L, "cut prompt"), (k, "decoding")):
+        tok = dict(x=bf(rnd(batch, n, Cx)), dt=bf(rnd(batch, n, H) - 4), B=bf(rnd(batch, n, G, N) / N ** 0.5), C=bf(rnd(batch, n, G, N) / N ** 0.5), z=bf(rnd(batch, n, Cx)))
+        y, given, seq_len = torch.full_like(tok["x"], 7.0), torch.full((batch,), n, dtype=torch.int32), None
+        common = dict(x_raw=tok["x"], conv_wgt=w, conv_bias=bias, dt=tok["dt"], dt_bias=dtb, dt_softplus=True, Bm=tok["B"], Cm=tok["C"], z=tok["z"], A=A, D=D, y_out=y)
+        if what == "decoding":
+            ssmv.ssm_block_multistep(dims, cache.c, k=k, **common)
+        else:
+            if lens:
+                given = torch.randint(1, n + 1, (batch,), generator=torch.Generator().manual_seed(n), dtype=torch.int32)
+                given[0], given[-1] = n, n - 33
+                seq_len = given.cuda()
+            run = lambda: ssmv.ssm_prefill_block(dims, cache.c, L=n, seq_len=seq_len, **common)
+            if what == "cut prompt":
+                made = launches(run)
+                assert len(made) == CUT and made[0][1] == (4 * P if N == 128 else 2 * P)
+            run()
+        compare(tok, y, given, what)
+        if what == "cut prompt":
+            h = torch.empty_like(h0)
+            ssmv.ssmv_materialize_block(dims, cache.c, A, dtb, True, h)
+            for ora, b in zip(oras, seqs):
+                assert rel_err(to_host(h[b:b + 1])[:, heads], ora.h) <= TOL["bf16"], "sequence %d: state" % b
+    ssmv.ssmv_check(cache.c)
