@@ -32,8 +32,8 @@
 // column lane%32.  Registers 8 st .. 8 st + 7 of a result tile, used as the operand of step st of a following
 // product, are therefore rows 16 st + 8 (j/4) + 4 (lane/32) + j%4.  Rows of the state tiles (the index n) are stored
 // under the permutation "swap bits 2 and 3" of the row index: then those eight registers hold the CONSECUTIVE indices
-// 16 st + 8 (lane/32) + j, and the other operand of h C^T is one 16-byte LDS read, the same read that G^T needs
-// anyway; likewise X serves M X and the update with one read.
+// 16 st + 8 (lane/32) + j, and the other operand of h C^T is one 16-byte LDS read; X serves M X and the update with
+// one read.
 // The chunk's raw x, B and C rows travel from global memory straight into LDS (no registers, 1 KB per wave and
 // instruction), one chunk ahead: they are requested right after the barrier that ends the staging of chunk c, land
 // during its arithmetic, and the barrier at its end publishes them.
@@ -111,7 +111,6 @@ void prefill_bf16_kernel(const PrefillParams p)
     constexpr int QS = Q * P / NT;       // consecutive tokens one thread convolves per chunk (NT / P threads per channel)
     constexpr int XS = Ld::XS, PIECES = Ld::PIECES;
     using Vec = IoVec<SSMV_BF16>;
-    constexpr int EV = Vec::EV;
     static_assert(P % 32 == 0 && P <= 128 && N % 32 == 0 && W == 4, "tile shapes");
 
     extern __shared__ float4 lds_raw[];
@@ -274,8 +273,8 @@ void prefill_bf16_kernel(const PrefillParams p)
             const int u = tid + i * NT, row = 8 * (u / N) + 4 * h + trow;
             btr[i][h] = row * (2 * N) + ((((u % N) >> 4) * 2 + tpiece) ^ key_bc<N>(row)) * 16 + tbyte;
         }
-    // Per chunk, of this lane's token t = li: log2 e * cum_t and exp(cum_t); and exp(cum_Q) (the same in every lane).
-    float cum_t, at_t, aq;
+    // Per chunk: exp(cum_t) of this lane's token t = li, and exp(cum_Q) (the same in every lane).
+    float at_t, aq;
     float cum_all = 0.f;                                // SEG: log2 of the segment's decay
     auto consume = [&](int c, uint32_t dt_bits) {
         const int t0 = c * Q, s0 = sg * QS;
@@ -288,7 +287,6 @@ void prefill_bf16_kernel(const PrefillParams p)
             float v = d * A2_h;
             v = prefix32(v);
             const float cq = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), Q - 1));
-            cum_t = v;
             at_t = __builtin_amdgcn_exp2f(v);
             aq = __builtin_amdgcn_exp2f(cq);
             if constexpr (SEG) cum_all += cq;
@@ -424,10 +422,10 @@ void prefill_bf16_kernel(const PrefillParams p)
         }
         f16v yacc = {0};
         if (emit) {
-            // C of this lane's token, all of it: the B operand of G^T and of h C^T
-            uint4 cop[N / 16];
+            // C of this lane's token: the B operand of h C^T over the wave's own tiles
+            uint4 cop[2 * TNL];
 #pragma unroll
-            for (int st = 0; st < N / 16; ++st) cop[st] = *reinterpret_cast<const uint4 *>(sC + t * (N * 2) + (((2 * st + lh) ^ key_bc<N>(t)) * 16));
+            for (int st = 0; st < 2 * TNL; ++st) cop[st] = *reinterpret_cast<const uint4 *>(sC + t * (N * 2) + (((2 * (2 * TNL * nh + st) + lh) ^ key_bc<N>(t)) * 16));
             // ---- this wave's quadrants of G^T = B C^T, and of M^T: decayed, scaled, masked, D on the diagonal; to LDS ----
             auto quadrant = [&](int qi, int qj) {
                 f4v gacc = {0};
@@ -462,13 +460,7 @@ void prefill_bf16_kernel(const PrefillParams p)
                     for (int d = 0; d < 4; ++d) {
                         ah[d] = pack_bf16x2(hacc[tn][8 * st + 2 * d], hacc[tn][8 * st + 2 * d + 1]);
                     }
-                    // C for the wave's own tiles: with a split state read again at the wave's offset (a choice between
-                    // registers by a variable would put the array into scratch memory)
-                    uint4 c4;
-                    if constexpr (NSPL == 2) c4 = *reinterpret_cast<const uint4 *>(sC + t * (N * 2) + (((2 * (2 * (TNL * nh + tn) + st) + lh) ^ key_bc<N>(t)) * 16));
-                    else c4 = cop[2 * tn + st];
-                    const bf8 cb = as_bf8(c4);
-                    yacc = mfma(as_bf8(ah[0], ah[1], ah[2], ah[3]), cb, yacc);
+                    yacc = mfma(as_bf8(ah[0], ah[1], ah[2], ah[3]), as_bf8(cop[2 * tn + st]), yacc);
                 }
             if constexpr (NSPL == 2) {
                 if (nh == 1) {                              // the second half of n: hand the sum to the tile's first wave

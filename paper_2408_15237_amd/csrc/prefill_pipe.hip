@@ -32,9 +32,7 @@ struct PipeLds {              // byte offsets of the LDS arrays (bf16 unless sai
     static constexpr int NW = NC + NWT + NCV;
     // chunks that raw inputs are requested ahead of their use: one where two of them take the LDS of a further workgroup (64 x 64) or
     // more than there is (128 x 128)
-    static constexpr int DIST = P >= 128 && N >= 128 || P == 64 && N == 64 ? 1 : 2;
-    // waves per SIMD that the registers have to leave room for: all workgroups that fit by their LDS
-    static constexpr int WPE = P <= 64 && N == 64 ? 4 : NW > 8 ? 3 : 2;
+    static constexpr int DIST = (P >= 128 && N >= 128) || (P == 64 && N == 64) ? 1 : 2;
     static constexpr int XB = DIST + 1, CB = DIST + 2;     // copies of the raw x and B, of C (the consumers read it, a chunk later)
     static constexpr int PX = P * XS, PB = N * XS, PM = kQ * XS;
     static constexpr int oX = 0;                           // [2][P][Q]  conv output x_s
@@ -56,6 +54,12 @@ struct PipeLds {              // byte offsets of the LDS arrays (bf16 unless sai
     static constexpr int oW = oDt + NWT * 2 * kQ * 4;      // fp32 [NWT][2][Q]  exp(cum_Q - cum_s) dt_s
     static constexpr int oAt = oW + NWT * 2 * kQ * 4;      // fp32 [4][Q]  exp(cum_t), for the consumers
     static constexpr int total = oAt + 4 * kQ * 4;
+    // Workgroups that fit a compute unit by their LDS, and the waves per SIMD that the registers have to leave room for then.  The fullest SIMD
+    // counts: a workgroup of six waves puts two on the same ones as the next does (32 x 64 with registers for three waves, which would do if
+    // they were dealt out evenly, 512 workgroups, 1024 tokens: 46 -> 61 us).  32 x 64, 64 x 64 and 64 x 128 spill 1 to 4 registers for
+    // it, outside the chunk loop.
+    static constexpr int fit = 160 * 1024 / total;
+    static constexpr int WPE = fit * ((NW + 3) / 4);
 };
 
 template <int P, int N, bool SEG>
@@ -220,9 +224,8 @@ void prefill_pipe_kernel(const PrefillParams p)
         // first row (uniform) plus a lane offset that stays the same over the chunks; a last chunk that is not full reads its last
         // token again for the rows behind it (they carry dt = 0 and thereby weight 0 everywhere) -------------------------------
         constexpr int BT = N / 16;                       // instructions for the 32 rows of B, and as many for C
-        constexpr bool kBoth = BT % NWT == 0;            // a wave loads rows of both, else the first half of the waves B, the others C
-        constexpr int BPW = kBoth ? BT / NWT : 1;
-        static_assert(kBoth || 2 * BT == NWT, "loads per wave");
+        constexpr int BPW = BT / NWT;
+        static_assert(BT % NWT == 0, "loads per wave");
         uint32_t obc[BPW];
         auto lane_offsets = [&](int last) {              // last: the chunk's last row that is there
 #pragma unroll
@@ -232,7 +235,7 @@ void prefill_pipe_kernel(const PrefillParams p)
             }
         };
         lane_offsets(Q - 1);
-        constexpr int kLoads = kBoth ? 2 * BPW : 1, kLoadsState = kBoth ? BPW : 0;    // of a wave and chunk, at least (dt ahead of them)
+        constexpr int kLoads = 2 * BPW, kLoadsState = BPW;      // of a wave and chunk, at least (dt ahead of them); without outputs
         // dt of a chunk comes with the rows of the one before it: its decay factors are worked out a step ahead of the rest
         auto issue_dt = [&](int c) { if (pw == 0) load_to_lds2(dt_b, off(min(c * Q + li, L - 1), H, 0), sDtr + (c & 3) * 256); };
         auto issue = [&](int c, int tob, int toc) {      // which copies
@@ -243,8 +246,8 @@ void prefill_pipe_kernel(const PrefillParams p)
 #pragma unroll
             for (int k = 0; k < BPW; ++k) {
                 const int idx = (pw + k * NWT) % BT;
-                if (kBoth || pw < BT) load_to_lds16(Bc, obc[k], dB + idx * 1024);
-                if ((kBoth || pw >= BT) && emit) load_to_lds16(Cc, obc[k], dC + idx * 1024);
+                load_to_lds16(Bc, obc[k], dB + idx * 1024);
+                if (emit) load_to_lds16(Cc, obc[k], dC + idx * 1024);
             }
         };
         issue_dt(c_beg);
@@ -264,7 +267,8 @@ void prefill_pipe_kernel(const PrefillParams p)
         if (ptid < 64) *reinterpret_cast<uint4 *>(lds + Ld::oM + (ptid >> 5) * Ld::PM + ((ptid & 31) >> 1) * XS + 32 + (ptid & 1) * 16) = make_uint4(0u, 0u, 0u, 0u);
         // transposing reads (read_tr16): lane j of 16 is in row j / 4 of four, 8 bytes j % 4 of the 32 of its 16 columns: of
         // the rows of B, per unit, tokens 4 h .. 4 h + 3 of its eight
-        constexpr int UI = (4 * N + (64 * NWT) - 1) / (64 * NWT);      // (n, eight tokens) units of the transposed B per thread
+        constexpr int UI = 4 * N / (64 * NWT);           // (n, eight tokens) units of the transposed B per thread
+        static_assert(4 * N % (64 * NWT) == 0, "units per thread");
         const int trow = l16 >> 2, tpiece = (l16 >> 1) & 1, tbyte = (l16 & 1) * 8;
         int btr[UI][2];
 #pragma unroll
@@ -274,7 +278,8 @@ void prefill_pipe_kernel(const PrefillParams p)
                 const int u = ptid + i * (64 * NWT), row = 8 * (u / N) + 4 * h + trow;
                 btr[i][h] = row * (2 * N) + ((((u % N) >> 4) * 2 + tpiece) ^ key_bc<N>(row)) * 16 + tbyte;
             }
-        constexpr int QPW = (3 + NWT - 1) / NWT;         // quadrants (0,0), (1,0), (1,1) of M^T go round the waves
+        // quadrants (0,0), (1,0), (1,1) of M^T go round the waves; of four the last makes one too that it does not store
+        constexpr int QPW = (3 + NWT - 1) / NWT;
         auto qi_of = [&](int i) { return pw + i * NWT >= 1 ? 1 : 0; };
         auto qj_of = [&](int i) { return pw + i * NWT == 2 ? 1 : 0; };
         float cum_all = 0.f;                             // SEG: log2 of the segment's decay
@@ -350,18 +355,15 @@ void prefill_pipe_kernel(const PrefillParams p)
             // ---- w_s B_s transposed, head and tail: eight tokens of one n per unit ----
 #pragma unroll
             for (int i = 0; i < UI; ++i) {
-                const int u = ptid + i * (64 * NWT);
-                if (u < 4 * N) {
-                    const int n = u % N, oct = u / N;
-                    const float wv[8] = {w0[i].x, w0[i].y, w0[i].z, w0[i].w, w1[i].x, w1[i].y, w1[i].z, w1[i].w};
-                    uint32_t bh[4], bl[4];
-                    const uint32_t bb[4] = {br[i][0].x, br[i][0].y, br[i][1].x, br[i][1].y};
+                const int u = ptid + i * (64 * NWT), n = u % N, oct = u / N;
+                const float wv[8] = {w0[i].x, w0[i].y, w0[i].z, w0[i].w, w1[i].x, w1[i].y, w1[i].z, w1[i].w};
+                uint32_t bh[4], bl[4];
+                const uint32_t bb[4] = {br[i][0].x, br[i][0].y, br[i][1].x, br[i][1].y};
 #pragma unroll
-                    for (int j2 = 0; j2 < 4; ++j2)
-                        split2(wv[2 * j2] * __uint_as_float(bb[j2] << 16), wv[2 * j2 + 1] * __uint_as_float(bb[j2] & 0xffff0000u), bh[j2], bl[j2]);
-                    *reinterpret_cast<uint4 *>(sBh + n * XS + oct * 16) = make_uint4(bh[0], bh[1], bh[2], bh[3]);
-                    *reinterpret_cast<uint4 *>(sBl + n * XS + oct * 16) = make_uint4(bl[0], bl[1], bl[2], bl[3]);
-                }
+                for (int j2 = 0; j2 < 4; ++j2)
+                    split2(wv[2 * j2] * __uint_as_float(bb[j2] << 16), wv[2 * j2 + 1] * __uint_as_float(bb[j2] & 0xffff0000u), bh[j2], bl[j2]);
+                *reinterpret_cast<uint4 *>(sBh + n * XS + oct * 16) = make_uint4(bh[0], bh[1], bh[2], bh[3]);
+                *reinterpret_cast<uint4 *>(sBl + n * XS + oct * 16) = make_uint4(bl[0], bl[1], bl[2], bl[3]);
             }
             // ---- this wave's quadrants of M^T: decayed, scaled, masked, D on the diagonal ----
             if (emit) {
@@ -404,11 +406,8 @@ void prefill_pipe_kernel(const PrefillParams p)
         }
         __syncthreads();
         if constexpr (SEG) {
-            if (!seg.last) {
-                if (p.seg_pass == 0 && c_beg > 0 && ptid == 0)
-                    *reinterpret_cast<float *>(y_b + seg_piece<2>(P * N / 4, P, seg.area, HP, hd)) = cum_all;
-                return;
-            }
+            if (!seg.last && p.seg_pass == 0 && c_beg > 0 && ptid == 0)
+                *reinterpret_cast<float *>(y_b + seg_piece<2>(P * N / 4, P, seg.area, HP, hd)) = cum_all;
         }
         return;
     }
@@ -674,7 +673,9 @@ bool prefill_pipe_serves(const PrefillParams &p)
 int prefill_pipe_resident(int P, int N)
 {
     auto pick = [&](int n32, int n64, int n128) { return N == 32 ? n32 : N == 64 ? n64 : n128; };
-    return P == 32 ? pick(3, 2, 1) : P == 64 ? pick(2, 2, 1) : 1;
+    if (P == 32) return pick(PipeLds<32, 32>::fit, PipeLds<32, 64>::fit, PipeLds<32, 128>::fit);
+    if (P == 64) return pick(PipeLds<64, 32>::fit, PipeLds<64, 64>::fit, PipeLds<64, 128>::fit);
+    return pick(PipeLds<128, 32>::fit, PipeLds<128, 64>::fit, PipeLds<128, 128>::fit);
 }
 
 // One workgroup to a compute unit, most units idle; slope between prompts of 1500 and 3000 tokens (64 x 32: 300 and 1024).  With a workgroup on
