@@ -215,9 +215,14 @@ void fill_verify(VerifyParams &p, const ssmv_dims *d, const ssmv_cache *c)
 #ifdef SSMV_TRACE
 // Profiling builds (-DSSMV_TRACE) only, no part of the library's interface: a device buffer of 8 wall-clock stamps per
 // workgroup of the matrix-core verify kernel.
-namespace ssmv { int set_trace_mfma(long long *buf); int set_trace_prefill(long long *buf); }
+namespace ssmv { int set_trace_mfma(long long *buf); int set_trace_prefill_bf16(long long *buf); int set_trace_prefill_pipe(long long *buf); }
 extern "C" int ssmv_debug_set_trace(long long *buf) { return ssmv::set_trace_mfma(buf); }
-extern "C" int ssmv_debug_set_trace_prefill(long long *buf) { return ssmv::set_trace_prefill(buf); }
+// and of 2 tick counts per workgroup of either bf16 prefill kernel
+extern "C" int ssmv_debug_set_trace_prefill(long long *buf)
+{
+    const int rc = ssmv::set_trace_prefill_bf16(buf);
+    return rc ? rc : ssmv::set_trace_prefill_pipe(buf);
+}
 #endif
 
 extern "C" {

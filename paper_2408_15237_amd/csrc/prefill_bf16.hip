@@ -82,11 +82,6 @@ struct PfLds {              // byte offsets of the LDS arrays (bf16 unless said)
     static constexpr int PIECES = N / 8;
 };
 
-#ifdef SSMV_TRACE
-// Profiling builds only: per workgroup, the shader-clock and the 100 MHz wall-clock ticks the kernel took.
-__device__ long long *pf_trace_buf_ = nullptr;
-#endif
-
 }  // namespace
 
 // Two waves per SIMD (256 registers each, and then the compiler keeps the accumulators in ordinary registers: no copies
@@ -119,9 +114,7 @@ void prefill_bf16_kernel(const PrefillParams p)
     uint2 *sCar = reinterpret_cast<uint2 *>(lds + Ld::oCar);
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-#ifdef SSMV_TRACE
-    const long long tr_c0 = clock64(), tr_w0 = wall_clock64();
-#endif
+    SSMV_TRACE_BEGIN();
     const int li = lane & 31, lh = lane >> 5;           // MFMA: row/column index and k half of this lane
     const int lperm = swap23(li);
     const int wave_u = __builtin_amdgcn_readfirstlane(wave);
@@ -527,7 +520,10 @@ void prefill_bf16_kernel(const PrefillParams p)
     if (nh == 0 && emit) flush_outputs(c_end - 1);
     if constexpr (SEG) {
         if (!seg.last) {
-            if (p.seg_pass == 1) return;                // the next segment has its state already
+            if (p.seg_pass == 1) {                      // the next segment has its state already
+                SSMV_TRACE_END(tid == 0);
+                return;
+            }
             // a segment's state on its way to the combining launch
 #pragma unroll
             for (int tn = 0; tn < TNL; ++tn)
@@ -535,6 +531,7 @@ void prefill_bf16_kernel(const PrefillParams p)
                 for (int q = 0; q < 4; ++q)
                     *seg_at(tn, q) = make_float4(hacc[tn][4 * q + 0], hacc[tn][4 * q + 1], hacc[tn][4 * q + 2], hacc[tn][4 * q + 3]);
             if (c_beg > 0 && tid == 0) *reinterpret_cast<float *>(y_b + seg_piece<2>(P * N / 4, P, seg.area, HP, hd)) = cum_all;
+            SSMV_TRACE_END(tid == 0);
             return;
         }
     }
@@ -549,12 +546,7 @@ void prefill_bf16_kernel(const PrefillParams p)
         for (int tg = (L - (W - 1) > 0 ? L - (W - 1) : 0); tg < L; ++tg)
             Vec::store_raw1(p.ring, ((size_t)b * p.ring_len + ((conv_head + 1 + tg) & mask)) * HP + ch, raw_bits(tg));
     }
-#ifdef SSMV_TRACE
-    if (pf_trace_buf_ && tid == 0) {
-        pf_trace_buf_[2 * blockIdx.x] = clock64() - tr_c0;
-        pf_trace_buf_[2 * blockIdx.x + 1] = wall_clock64() - tr_w0;
-    }
-#endif
+    SSMV_TRACE_END(tid == 0);
 }
 
 template <int P, int N, bool SEG>
@@ -603,7 +595,7 @@ int prefill_bf16_resident(int P, int N)
 }
 
 #ifdef SSMV_TRACE
-int set_trace_prefill(long long *buf) { return (int)hipMemcpyToSymbol(HIP_SYMBOL(pf_trace_buf_), &buf, sizeof(buf)); }
+int set_trace_prefill_bf16(long long *buf) { return (int)hipMemcpyToSymbol(HIP_SYMBOL(pf_trace_buf_), &buf, sizeof(buf)); }
 #endif
 
 // large launches (prefill_pipe_serves), and a pass over a prompt that is cut; the caller appends the bookkeeping or the combining launch

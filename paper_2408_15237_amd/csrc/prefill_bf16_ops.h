@@ -135,5 +135,22 @@ __device__ __forceinline__ float prefix32(float v)
 
 __device__ __forceinline__ int swap23(int i) { return (i & ~12) | ((i & 4) << 1) | ((i & 8) >> 1); }
 
+// Profiling builds only: per workgroup that has work, the shader-clock and the 100 MHz wall-clock ticks from its start to its end (the
+// kernel of either file has a buffer pointer of its own; the last launch counts).
+#ifdef SSMV_TRACE
+__device__ long long *pf_trace_buf_ = nullptr;
+#define SSMV_TRACE_BEGIN() const long long tr_c0 = clock64(), tr_w0 = wall_clock64()
+#define SSMV_TRACE_END(one_thread)                                  \
+    do {                                                            \
+        if (pf_trace_buf_ && (one_thread)) {                        \
+            pf_trace_buf_[2 * blockIdx.x] = clock64() - tr_c0;      \
+            pf_trace_buf_[2 * blockIdx.x + 1] = wall_clock64() - tr_w0; \
+        }                                                           \
+    } while (0)
+#else
+#define SSMV_TRACE_BEGIN() (void)0
+#define SSMV_TRACE_END(one_thread) (void)0
+#endif
+
 }  // namespace
 }  // namespace ssmv

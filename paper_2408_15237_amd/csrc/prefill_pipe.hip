@@ -78,6 +78,7 @@ void prefill_pipe_kernel(const PrefillParams p)
     const int tid = threadIdx.x, lane = tid & 63;
     const int li = lane & 31, lh = lane >> 5;            // MFMA: row/column index and k half of this lane
     const int wave_u = __builtin_amdgcn_readfirstlane(tid >> 6);
+    SSMV_TRACE_BEGIN();
     const int H = p.H, G = p.G;
     const PrefillItem item = prefill_item<SEG>(p);
     const int hd = item.hd, b = item.b;
@@ -593,13 +594,17 @@ void prefill_pipe_kernel(const PrefillParams p)
     if (emit) finish(c_end - 1);
     if constexpr (SEG) {
         if (!seg.last) {
-            if (p.seg_pass == 1) return;                 // the next segment has its state already
+            if (p.seg_pass == 1) {                       // the next segment has its state already
+                SSMV_TRACE_END(tid == 0);
+                return;
+            }
             // a segment's state on its way to the combining launch
 #pragma unroll
             for (int tn = 0; tn < TNL; ++tn)
 #pragma unroll
                 for (int q = 0; q < 4; ++q)
                     *seg_at(tn, q) = make_float4(hacc[tn][4 * q + 0], hacc[tn][4 * q + 1], hacc[tn][4 * q + 2], hacc[tn][4 * q + 3]);
+            SSMV_TRACE_END(tid == 0);
             return;
         }
     }
@@ -609,6 +614,7 @@ void prefill_pipe_kernel(const PrefillParams p)
         for (int q = 0; q < 4; ++q)
             *reinterpret_cast<float4 *>(state_at(tn, q)) =
                 make_float4(hacc[tn][4 * q + 0], hacc[tn][4 * q + 1], hacc[tn][4 * q + 2], hacc[tn][4 * q + 3]);
+    SSMV_TRACE_END(tid == 0);
 }
 
 template <int P, int N, bool SEG>
@@ -686,6 +692,10 @@ double prefill_pipe_chunk_us(int P, int N)
     if (N == 128) return P == 128 ? 1.38 : 1.25;
     return P == 128 ? 1.0 : P == 64 && N == 32 ? 0.91 : 0.78;
 }
+
+#ifdef SSMV_TRACE
+int set_trace_prefill_pipe(long long *buf) { return (int)hipMemcpyToSymbol(HIP_SYMBOL(pf_trace_buf_), &buf, sizeof(buf)); }
+#endif
 
 int launch_prefill_pipe(const PrefillParams &p, hipStream_t stream)
 {
