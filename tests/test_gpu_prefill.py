@@ -143,8 +143,8 @@ def test_prefill_flags_a_cache_with_pending_tokens():
 
 
 def test_prefill_full_layer_shape_every_head_of_two_sequences():
-    """The bench's launch shape (cfg3 layer: 32 heads x 128 x 64, bf16 I/O, 2048 prompt tokens) at batch 4; the oracle
-    runs the token-by-token scan over every head of two sequences (eight heads at a time: it keeps every
+    """A full layer (cfg3: 32 heads x 128 x 64, bf16 I/O, 2048 prompt tokens) at batch 4, whose 128 workgroups the pipelined kernel takes (the
+    bench's batch 32 goes to the other one: test_gpu_prefill_large.py); the oracle runs the token-by-token scan over every head of two sequences (eight heads at a time: it keeps every
     intermediate state)."""
     from workload import CONFIGS, round_to_io
     io = "bf16"

@@ -1,5 +1,5 @@
-"""bf16 prefill launches of more (sequence, head) pairs than the pipelined kernel (csrc/prefill_pipe.hip) takes: which kernel a call runs,
-and the other one (csrc/prefill_bf16.hip) against the oracle."""
+"""bf16 prefill launches of more (sequence, head) pairs than fit the chip at once: which kernel a call runs, and both of them against
+the oracle there (csrc/prefill_bf16.hip, csrc/prefill_pipe.hip)."""
 import numpy as np
 import pytest
 import torch
@@ -116,3 +116,45 @@ def test_large_launches_against_the_oracle(P, N, H, batch, block):
                                  Cm=tok["C"], z=tok["z"], A=A, D=D, k=k, y_out=y)
         against_oracle(tok, y, [k] * len(seqs), "decoding")
         ssmv.ssmv_check(cache.c)
+
+
+# (headdim, dstate, heads, batch, tokens, whether lengths differ, kernel)
+@pytest.mark.parametrize("P,N,H,batch,L,lens,kernel", [
+    (128, 64, 32, 32, 2048, False, OTHER),                             # the bench's launch
+    # the pipelined kernel in more than one round: prompts of different lengths, and tiles that it takes at any count
+    (128, 64, 32, 16, 530, True, PIPE), (128, 32, 32, 16, 530, True, PIPE), (64, 128, 32, 16, 530, True, PIPE), (64, 32, 48, 16, 530, True, PIPE),
+    (32, 64, 64, 16, 530, True, PIPE), (32, 32, 64, 16, 530, True, PIPE), (32, 128, 48, 16, 530, True, PIPE), (64, 64, 80, 16, 710, True, PIPE),
+    (64, 64, 64, 20, 100, False, PIPE), (128, 128, 34, 16, 100, False, PIPE)])
+def test_more_rounds_and_long_prompts_against_the_oracle(P, N, H, batch, L, lens, kernel):
+    G, io = 2, torch.bfloat16
+    g = torch.Generator(device="cuda").manual_seed(L + P + N)
+    rnd = lambda *s: torch.randn(*s, generator=g, device="cuda")
+    bf, Cx = (lambda t: t.to(io)), H * P
+    w, D, A = bf(rnd(Cx, 4) / 2), rnd(H), -torch.exp(torch.rand(H, generator=g, device="cuda") * 2.7)
+    x, dt = bf(rnd(batch, L, Cx)), bf(torch.nn.functional.softplus(rnd(batch, L, H) - 4))
+    B, C = bf(rnd(batch, L, G, N) / N ** 0.5), bf(rnd(batch, L, G, N) / N ** 0.5)
+    h0 = rnd(batch, H, P, N) * 0.1
+    dims = ssmv.make_dims(batch, H, P, N, ngroups=G, kmax=4, io="bf16")
+    cache = ssmv.LayerCache.allocate(dims)
+    ssmv.ssmv_cache_reset(dims, cache.c, h0, None)
+    given = torch.full((batch,), L, dtype=torch.int32)
+    if lens:
+        given = torch.randint(0, L + 1, (batch,), generator=torch.Generator().manual_seed(L), dtype=torch.int32)
+        given[3] = L
+    given_dev, y = given.cuda() if lens else None, torch.full_like(x, 7.0)
+    run = lambda: ssmv.ssm_prefill_block(dims, cache.c, x_raw=x, conv_wgt=w, dt=dt, Bm=B, Cm=C, A=A, D=D, L=L, y_out=y, seq_len=given_dev)
+    assert launches(run)[0] == (H * batch, _threads(P, N)[kernel])
+    run()
+    h = torch.empty_like(h0)
+    ssmv.ssmv_materialize(dims, cache.c, A, h)
+    ssmv.ssmv_check(cache.c)
+    heads = [0, H // 2 - 1, H // 2, H - 1]
+    ch = np.concatenate([np.arange(hd * P, (hd + 1) * P) for hd in heads])
+    for b in (3, batch - 1):
+        n = int(given[b])
+        ora = oracle.EagerOracle("scalar", to_host(A)[heads], to_host(D)[heads], to_host(w)[ch], None, to_host(h0[b:b + 1])[:, heads], "bf16", "none", G)
+        f = lambda t, sel: to_host(t[b:b + 1, :n])[:, :, sel]
+        y_ref, _, _ = ora.verify(f(x, ch), f(dt, heads), to_host(B[b:b + 1, :n]), to_host(C[b:b + 1, :n]))
+        ora.commit([n])
+        assert rel_err(f(y, ch), y_ref) <= TOL["bf16"] and bool((y[b, n:] == 7).all()), "sequence %d" % b
+        assert rel_err(to_host(h[b:b + 1])[:, heads], ora.h) <= TOL["bf16"], "sequence %d: state" % b
