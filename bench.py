@@ -225,9 +225,9 @@ def bench_prefill(args):
     tflops = flops / (ms * 1e-3) / 1e12
     gbps = nbytes / (ms * 1e-3) / 1e9
     if wl.io == "bf16":
-        # executed matrix work per chunk and wave, in products of 32x32x16: N/16 (G^T, every wave its own) + N/16 (h C^T, head
-        # only) + 2 (M X, head only) + 2 N/16 (update, head and tail)
-        mfma_flops = (2 + 4 * (N // 16)) * 32768.0 * (P // 32) * math.ceil(L / Q) * B_ * H
+        # executed matrix work per chunk, in products of 32x32x16: per 32 channels N/16 (h C^T, head only) + 2 (M X, head only) + 2 N/16 (update,
+        # head and tail), and once per workgroup three 16x16xN quadrants of G^T
+        mfma_flops = ((2 + 3 * (N // 16)) * (P // 32) + 1.5 * (N // 32)) * 32768.0 * math.ceil(L / Q) * B_ * H
         traffic = None                                  # the counters were read on this shape only
         tpath = os.path.join(ROOT, "profiles", "prefill_bf16_kernel_%s_L%d_pmc.txt" % (wl.name, L))
         if not args.prefill_io and os.path.exists(tpath):
@@ -235,7 +235,7 @@ def bench_prefill(args):
                 if line.startswith("traffic_bytes_per_launch:"):
                     traffic = float(line.split(":")[1])
         roof = {"bound": "hbm", "achieved": round(gbps, 1), "peak": PEAK_HBM_GBPS, "unit": "GB/s", "frac": round(gbps / PEAK_HBM_GBPS, 4),
-                "traffic": traffic, "kernel": "prefill_bf16_kernel (bf16 MFMA, split operand in the state update)", "avg_launch_us": round(ms * 1e3, 1),
+                "traffic": traffic, "kernel": "prefill_bf16_kernel, or prefill_pipe_kernel for launches that fit the chip at once (bf16 MFMA, split operand in the state update)", "avg_launch_us": round(ms * 1e3, 1),
                 "algorithmic_bytes_per_launch": int(nbytes), "algorithmic_flops_per_launch": int(flops),
                 "mfma_executed_tflops": round(mfma_flops / (ms * 1e-3) / 1e12, 1),
                 "mfma_frac_of_bf16_peak": round(mfma_flops / (ms * 1e-3) / 1e12 / PEAK_MFMA_BF16_TFLOPS, 4)}
