@@ -94,9 +94,52 @@ __device__ __forceinline__ void conv8(float (&x)[8], const uint32_t *o, const ui
         : "v"(o[0]), "v"(o[1]), "v"(o[2]), "v"(o[3]), "v"(o[4]), "v"(e[0]), "v"(e[1]), "v"(e[2]), "v"(e[3]), "v"(e[4]), "v"(w01), "v"(w23), "v"(bias));
 }
 
-// SiLU of the conv output, by the same expression as in every other kernel's conv: a token's conv output is the same bits whichever
-// call it comes through.  (silu_fast, from exp2 of a rounded product and rcp, is off by 1e-6 at -20 and gives 0 below -87.3.)
-__device__ __forceinline__ float conv_silu(float v) { return v / (1.f + expf(-v)); }
+// SiLU of eight conv outputs on their way to bf16: the bits of v / (1 + expf(-v)), rounded, which every other kernel's conv takes (a token's
+// conv output is the same whichever call it comes through), for less than half of its instructions.  silu_fast is within 9 fp32 steps
+// of that for every v >= -8 (all of them tried); rounding to bf16 gives the same then unless it is that close to the middle between two bf16
+// numbers.  Such a result, and any v below -8 (silu_fast is off by 18 steps at -20 and gives 0 from -87.3 on), is computed as there: one
+// in 3000 for values of order 1, so every sixth call of a wave.
+// 1024 tokens with SiLU, gate and softplus (us), silu_fast alone, v / (1 + expf(-v)) alone, and so:  256 pairs of 128 x 64 57, 72, 65;  1024: 230, 293,
+// 265;  256 of 64 x 128 58, 71, 63;  256 of 32 x 64 40, 51, 43.
+__device__ __forceinline__ void conv_silu8(float (&v)[8])
+{
+    constexpr uint32_t kSteps = 10, kClose = 2 * kSteps << 16;
+    constexpr float kLowest = -8.f;
+    float f[8], lowest = v[0];
+    uint32_t dist[8], closest = ~0u;                     // dist at most kClose: within kSteps of the middle
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+        f[j] = silu_fast(v[j]);
+        dist[j] = (__float_as_uint(f[j]) + (0x8000u + kSteps)) << 16;
+        closest = min(closest, dist[j]);
+        lowest = fminf(lowest, v[j]);
+    }
+    if (closest <= kClose || lowest < kLowest) {
+        // One value of a lane after the other (two different ones are rare; the rows behind a prompt's end are all the same): the code for it
+        // is there once and short, since the first wave that gets here waits for it to be fetched
+        if (lowest < kLowest) {
+#pragma unroll
+            for (int j = 0; j < 8; ++j) dist[j] = v[j] < kLowest ? 0u : dist[j];
+        }
+        bool left;
+        do {
+            float a = v[7];
+#pragma unroll
+            for (int j = 6; j >= 0; --j) a = dist[j] <= kClose ? v[j] : a;
+            const float exact = a / (1.f + expf(-a));
+            left = false;
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                const bool hard = dist[j] <= kClose, same = __float_as_uint(v[j]) == __float_as_uint(a);
+                f[j] = hard && same ? exact : f[j];
+                dist[j] = same ? ~0u : dist[j];
+                left = left || (hard && !same);
+            }
+        } while (left);
+    }
+#pragma unroll
+    for (int j = 0; j < 8; ++j) v[j] = f[j];
+}
 
 // two fp32 values -> packed bf16 heads and packed bf16 tails (first value in the low half)
 __device__ __forceinline__ void split2(float a, float b, uint32_t &hi, uint32_t &lo)

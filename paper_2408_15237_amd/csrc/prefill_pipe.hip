@@ -186,10 +186,7 @@ void prefill_pipe_kernel(const PrefillParams p)
             for (int v = 0; v < QS / 8; ++v) {
                 float xv[8];
                 conv8(xv, o + 4 * v, e + 1 + 4 * v, wraw.x, wraw.y, cbias);
-                if (silu) {
-#pragma unroll
-                    for (int j = 0; j < 8; ++j) xv[j] = conv_silu(xv[j]);
-                }
+                if (silu) conv_silu8(xv);
                 // the rounding to the storage type
                 *reinterpret_cast<uint4 *>(to + 16 * v) =
                     make_uint4(pack_bf16x2(xv[0], xv[1]), pack_bf16x2(xv[2], xv[3]), pack_bf16x2(xv[4], xv[5]), pack_bf16x2(xv[6], xv[7]));

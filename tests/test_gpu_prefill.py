@@ -336,20 +336,29 @@ def test_prefill_large_launches_agree_with_small_ones(P, N, H, batch):
 
 
 @pytest.mark.parametrize("batch", [1, 23])
-def test_conv_silu_of_every_bf16_argument_is_that_of_the_other_calls(batch):
-    """With C = 0, D = 1 and the conv weights (0, 0, 0, 1) a prompt's output is its conv output: SiLU of the raw input, bit for bit what
-    conv1d_state_update gives for it.  Every bf16 number up to 100 in magnitude; one launch for either bf16 kernel."""
+@pytest.mark.parametrize("arguments", ["bf16", "1/16", "1/4", "5/8"])
+def test_conv_silu_is_that_of_the_other_calls(arguments, batch):
+    """With C = 0 and D = 1 a prompt's output is its conv output: SiLU of the conv sum, bit for bit what conv1d_state_update gives for it,
+    also where that is close to the middle between two bf16 numbers.  Conv sums without a rounding of their own: every bf16 number up to 100 in
+    magnitude (taps 0, 0, 0, 1), or i u + 2^-10 j u with i, j random in -127 .. 127 (taps 0, 0, 2^-10, 1).  One launch for either bf16 kernel."""
     P, N, H, L, k = 32, 32, 34, 32, 16
     Cx = H * P
-    bits = torch.arange(0x42C9, dtype=torch.int32)
-    x = torch.cat([bits, bits + 0x8000, torch.zeros(L * Cx - 2 * len(bits), dtype=torch.int32)]).to(torch.int16).view(torch.bfloat16).cuda().view(1, L, Cx)
     w = torch.zeros(Cx, 4, dtype=torch.bfloat16, device="cuda")
     w[:, 3] = 1
+    if arguments == "bf16":
+        bits = torch.arange(0x42C9, dtype=torch.int32)
+        x = torch.cat([bits, bits + 0x8000, torch.zeros(L * Cx - 2 * len(bits), dtype=torch.int32)]).to(torch.int16).view(torch.bfloat16).cuda().view(1, L, Cx)
+    else:
+        w[:, 2] = 2.0 ** -10
+        num, den = (int(v) for v in arguments.split("/"))
+        x = torch.randint(-127 // num, 127 // num + 1, (1, L, Cx), generator=torch.Generator().manual_seed(den)).mul(num).to(torch.bfloat16).cuda() / den
     dims = ssmv.make_dims(L // k, H, P, N, kmax=k, io="bf16", conv_act="silu")
     cache = ssmv.LayerCache.allocate(dims)
-    ssmv.ssmv_cache_reset(dims, cache.c, None, None)
-    want = torch.empty(L // k, k, Cx, dtype=torch.bfloat16, device="cuda")
-    ssmv.conv1d_state_update(dims, cache.c, x.view(L // k, k, Cx), w, None, k, want)
+    windows = x.view(L // k, k, Cx)
+    history = torch.cat([torch.zeros_like(windows[:1, -3:]), windows[:-1, -3:]]).contiguous()
+    ssmv.ssmv_cache_reset(dims, cache.c, None, history)
+    want = torch.empty_like(windows)
+    ssmv.conv1d_state_update(dims, cache.c, windows, w, None, k, want)
     dims = ssmv.make_dims(batch, H, P, N, kmax=4, io="bf16", conv_act="silu")
     cache = ssmv.LayerCache.allocate(dims)
     ssmv.ssmv_cache_reset(dims, cache.c, None, None)
