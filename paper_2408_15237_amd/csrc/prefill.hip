@@ -550,7 +550,9 @@ static bool cut_prompt(PrefillParams &p)
             pipe = !p.seg_count;
         }
         if (!p.seg_count) {
-            const double unit = prefill_pipe_chunk_us(p.P, p.N);
+            // with SiLU (us)  4 heads of 128 x 64, 550 tokens: 37 uncut, 27 cut;  48 pairs of 128 x 32, 550: 35, 28;  of lengths that differ as many
+            // calls lost by it as gained (96 pairs of 64 x 128, 1024 at most: 54, 64)
+            const double unit = prefill_pipe_chunk_us(p.P, p.N, p.conv_act == SSMV_ACT_SILU && !p.seq_len);
             choose_segments(p, {prefill_pipe_resident(p.P, p.N), 0.3, 0.5, 8.0 / unit, 4.0 * p.P * p.N * sizeof(float) / 4.7e6 / unit, 0.9});
         }
     }

@@ -684,10 +684,12 @@ int prefill_pipe_resident(int P, int N)
 // One workgroup to a compute unit, most units idle; slope between prompts of 1500 and 3000 tokens (64 x 32: 300 and 1024).  With a workgroup on
 // every unit a chunk takes 0.86 to 1.01 (N <= 64) and 1.33 to 1.39 us.  Counted with those, choose_segments cuts more, and prompts of different
 // lengths lose by it (288 pairs of 32 x 32, 1500 tokens at most: 41 whole, 54 cut).
-double prefill_pipe_chunk_us(int P, int N)
+double prefill_pipe_chunk_us(int P, int N, bool silu)
 {
-    if (N == 128) return P == 128 ? 1.38 : 1.25;
-    return P == 128 ? 1.0 : P == 64 && N == 32 ? 0.91 : 0.78;
+    // the conv waves are the longest stage then: 1.1 to 1.6 times (64 x 64, counted with 1.1: 176 pairs, 4096 tokens 175 uncut, 200 cut)
+    const double conv = !silu || (P == 64 && N == 64) ? 1.0 : P == 128 ? 1.5 : P == 64 ? 1.3 : 1.1;
+    if (N == 128) return conv * (P == 128 ? 1.38 : 1.25);
+    return conv * (P == 128 ? 1.0 : P == 64 && N == 32 ? 0.91 : 0.78);
 }
 
 #ifdef SSMV_TRACE

@@ -162,7 +162,7 @@ int prefill_bf16_resident(int P, int N);                                  // its
 int launch_prefill_pipe(const PrefillParams &p, hipStream_t stream);      // the same of smaller ones, and of the other cut prompts
 bool prefill_pipe_serves(const PrefillParams &p);                         // which of the two, for a prompt that is not cut
 int prefill_pipe_resident(int P, int N);                                  // workgroups of the second that fit a compute unit side by side
-double prefill_pipe_chunk_us(int P, int N);                               // and its time per chunk
+double prefill_pipe_chunk_us(int P, int N, bool silu);                               // and its time per chunk
 bool prefill_shape_supported(int P, int N);
 int launch_commit(const CommitParams &p, hipStream_t stream);
 int launch_reset(const ResetParams &p, hipStream_t stream);

@@ -193,8 +193,8 @@ def _launches(call):
 CUT, UNCUT = 3, 2           # two passes and the launch between them, or one and the bookkeeping
 
 
-def _launches_of(io, P, N, H, batch, L, lens=None, in_place=False):
-    dims = ssmv.make_dims(batch, H, P, N, kmax=4, io=io)
+def _launches_of(io, P, N, H, batch, L, lens=None, in_place=False, act="none"):
+    dims = ssmv.make_dims(batch, H, P, N, kmax=4, io=io, conv_act=act)
     cache = ssmv.LayerCache.allocate(dims)
     new = lambda *s: torch.zeros(*s, dtype=torch.bfloat16 if io == "bf16" else torch.float32, device="cuda")
     x, y, w, dt, B, C, A = new(batch, L, H * P), new(batch, L, H * P), new(H * P, 4), new(batch, L, H), new(batch, L, 1, N), new(batch, L, 1, N), torch.zeros(H, device="cuda")
@@ -217,6 +217,12 @@ def test_which_prompts_are_cut(io):
     assert _launches_of(io, 128, 64, 80, 4, 1500) == UNCUT            # as many workgroups as fit without
     if io == "bf16":                                                  # few chunks of a small tile: the passes cost more than they save
         assert _launches_of(io, 64, 32, 80, 4, 400) == UNCUT and _launches_of(io, 32, 32, 80, 4, 400) == UNCUT
+
+
+@pytest.mark.parametrize("P,N,H,batch,L", [(128, 32, 4, 2, 400), (128, 64, 4, 12, 700), (64, 32, 4, 1, 400)])
+def test_a_conv_silu_is_counted(P, N, H, batch, L):
+    """bf16: a chunk takes longer with it, so that cutting pays earlier."""
+    assert _launches_of("bf16", P, N, H, batch, L) == UNCUT and _launches_of("bf16", P, N, H, batch, L, act="silu") == CUT
 
 
 @pytest.mark.parametrize("io", ["bf16", "f32"])
