@@ -26,7 +26,7 @@
 // every wave; lane offsets of all global accesses stay the same over the chunks.  With single 16-bit
 // LDS reads, pairs put together by shifts, G in every wave and 64-bit addresses formed per access a
 // wave took 334 vector, 18 matrix and 67 LDS instructions per chunk at 128 x 64 (no SiLU; counters, start and end of a prompt included), so
-// 239, 15.5 and 42.
+// 237, 15.5 and 42.
 // 32 x 2048 tokens of 32 heads x 128 x 64: 348 -> 298 us; 16 x 1024: 64 heads x 32 x 64 102 -> 83, 64 x 32 x 32 73 -> 58.
 // Operand layout (checked on the hardware): A[i = lane%32][k = 8 (lane/32) + j], B[k = 8 (lane/32) + j][col = lane%32],
 // j = 0..7 the elements of the lane's 16-byte operand; result register v of a lane is row 8 (v/4) + 4 (lane/32) + v%4,
