@@ -158,3 +158,24 @@ def test_more_rounds_and_long_prompts_against_the_oracle(P, N, H, batch, L, lens
         ora.commit([n])
         assert rel_err(f(y, ch), y_ref) <= TOL["bf16"] and bool((y[b, n:] == 7).all()), "sequence %d" % b
         assert rel_err(to_host(h[b:b + 1])[:, heads], ora.h) <= TOL["bf16"], "sequence %d: state" % b
+
+
+@pytest.mark.parametrize("P,N,H,batch", [(128, 64, 34, 8), (64, 128, 34, 8), (64, 64, 56, 16)])
+def test_large_launches_with_outputs_over_the_gate_input(P, N, H, batch):
+    """y in z's buffer gives what it gives in one of its own, bit for bit."""
+    L, io = 100, torch.bfloat16
+    g = torch.Generator(device="cuda").manual_seed(P * N)
+    bf = lambda *s: torch.randn(*s, generator=g, device="cuda").to(io)
+    x, z, dt = bf(batch, L, H * P), bf(batch, L, H * P), torch.nn.functional.softplus(bf(batch, L, H) - 4)
+    B, C, w, A = bf(batch, L, 1, N), bf(batch, L, 1, N), bf(H * P, 4), -torch.rand(H, generator=g, device="cuda")
+    dims = ssmv.make_dims(batch, H, P, N, kmax=4, io="bf16")
+    out = []
+    for y in (torch.empty_like(z), z.clone()):
+        gate = z if not out else y
+        cache = ssmv.LayerCache.allocate(dims)
+        ssmv.ssmv_cache_reset(dims, cache.c, None, None)
+        run = lambda: ssmv.ssm_prefill_block(dims, cache.c, x_raw=x, conv_wgt=w, dt=dt, Bm=B, Cm=C, A=A, D=A, L=L, y_out=y, z=gate)
+        assert launches(run)[0] == (H * batch, _threads(P, N)[OTHER])
+        run()
+        out.append(y)
+    assert torch.equal(out[0], out[1])
