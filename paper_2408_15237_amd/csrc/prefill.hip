@@ -543,15 +543,17 @@ static bool cut_prompt(PrefillParams &p)
     const bool bf16 = p.io == SSMV_BF16;
     const int es = bf16 ? 2 : 4;
     bool pipe = bf16 && prefill_pipe_serves(p);
+    // unit 5.8 us (128 x 64); full compute units 1.5 of it, a share of the state half
     if (!bf16) choose_segments(p, {resident_f32(p.P, p.N), 0.5, 0.5, 1.5, 0.0, 0.85});
     else if (pipe) {
-        if (prefill_bf16_cuts(p)) {
+        if (prefill_bf16_cuts(p)) {                      // unit 1.3 to 2.4 us; of full compute units 1.5 of it, the launches with the states' trips 5
             choose_segments(p, {prefill_bf16_resident(p.P, p.N), 0.5, 0.6, 5.0, 0.0, 0.85});
             pipe = !p.seg_count;
         }
         if (!p.seg_count) {
             // with SiLU (us)  4 heads of 128 x 64, 550 tokens: 37 uncut, 27 cut;  48 pairs of 128 x 32, 550: 35, 28;  of lengths that differ as many
             // calls lost by it as gained (96 pairs of 64 x 128, 1024 at most: 54, 64)
+            // the launches 8 us, the states' trips at 4.7 TB/s
             const double unit = prefill_pipe_chunk_us(p.P, p.N, p.conv_act == SSMV_ACT_SILU && !p.seq_len);
             choose_segments(p, {prefill_pipe_resident(p.P, p.N), 0.3, 0.5, 8.0 / unit, 4.0 * p.P * p.N * sizeof(float) / 4.7e6 / unit, 0.9});
         }
