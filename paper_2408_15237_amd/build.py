@@ -10,7 +10,7 @@ ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 OBJ = os.path.join(PKG, "_build")
 LIB = os.path.join(PKG, "libssmv.so")
-SOURCES = ["api.hip", "aux_kernels.hip", "verify_scalar.hip", "verify_diag.hip", "verify_mfma.hip", "materialize.hip", "prefill.hip", "prefill_bf16.hip", "prefill_pipe.hip"]
+SOURCES = ["api.hip", "aux_kernels.hip", "verify_scalar.hip", "verify_diag.hip", "verify_mfma.hip", "materialize.hip", "prefill.hip", "prefill_f32_pipe.hip", "prefill_bf16.hip", "prefill_pipe.hip"]
 HEADERS = [os.path.join(CSRC, "ssmv_internal.h"), os.path.join(CSRC, "verify_impl.h"), os.path.join(CSRC, "prefill_split.h"), os.path.join(CSRC, "prefill_bf16_ops.h"),
            os.path.join(ROOT, "include", "ssmv.h")]
 

@@ -1,5 +1,5 @@
-// Chunked prefill of a scalar-decay (Mamba-2 style) layer with fp32 tensors (bf16 tensors: prefill_bf16.hip, same
-// evaluation on the bf16 matrix cores): all L prompt tokens through the recurrence of
+// Chunked prefill of a scalar-decay (Mamba-2 style) layer with fp32 tensors, in large launches and where a cut prompt is faster this way
+// (plan_f32; the others: prefill_f32_pipe.hip; bf16 tensors: prefill_bf16.hip, same evaluation on the bf16 matrix cores): all L prompt tokens through the recurrence of
 // Section 2.1 Eq. 1 (with the discretisation of Section 2.2), producing every y_t and leaving the cached state and
 // the conv ring as if the L tokens had been verified and accepted.  This is where the path has a dense
 // contraction, so it runs on the matrix cores (fp32 MFMA: the state and the outputs keep fp32 accuracy).
@@ -482,7 +482,8 @@ struct CutCosts {
 
 // The segments of a prompt, or none.  More workgroups than fit at once would run as a second round, which always lost (320 heads x 1500
 // tokens at 128 x 64: 150 us cut in three, 118 us uncut): not cut.
-static void choose_segments(PrefillParams &p, const CutCosts &k)
+// Returns the time of the cut, in units.
+static double choose_segments(PrefillParams &p, const CutCosts &k)
 {
     constexpr int kCUs = 256;
     const long pairs = (long)p.batch * p.H;
@@ -506,6 +507,7 @@ static void choose_segments(PrefillParams &p, const CutCosts &k)
             if (t < best) { best = t; p.seg_chunks = len; p.seg_count = ns; }
         }
     }
+    return best;
 }
 
 // Whether a bf16 prompt that the pipelined kernel would take whole or cut is cut by the other kernel instead.  That one fits more workgroups
@@ -529,49 +531,99 @@ static bool prefill_bf16_cuts(const PrefillParams &p)
     return p.P == 64 ? between(2048, 144, 256) : between(1500, 48, 176);
 }
 
-// Whether and how a prompt is cut, and by which kernel: the return value says whether by the pipelined one (bf16).
-// Uncut and cut (us; one sequence unless said):
-//   bf16  128 x 64, 32 heads:  700 tokens 29 -> 26, 1500: 54 -> 34, 3000: 100 -> 41;  4 sequences, 3000: 99 -> 85;  8 heads, 1500: 52 -> 24
-//         64 x 128, 80 heads:  1500 tokens 69 -> 52, 3000: 130 -> 78;   64 x 64, 80 heads, 1500: 48 -> 37
-//   fp32  128 x 64, 32 heads:  400 tokens 81 -> 41, 1500: 278 -> 66, 3000: 548 -> 106;   64 x 128, 80 heads, 1500: 282 -> 129
-// bf16 over nine tiles, 4 to 512 pairs and 260 to 4096 tokens of one length: never more than 4 % slower than uncut, 13 % faster on average.  Of
-// prompts of different lengths only the device knows them: one sequence that is far shorter than L pays for the launches (32 heads of
-// 128 x 64, 700 tokens given, one there: 8 -> 11 us).
-static bool cut_prompt(PrefillParams &p)
+// y carries states between the launches of a cut prompt: not if it overlaps anything that is still to be read
+static bool y_is_apart(const PrefillParams &p)
 {
-    p.seg_chunks = p.seg_count = p.seg_pass = 0;
-    const bool bf16 = p.io == SSMV_BF16;
-    const int es = bf16 ? 2 : 4;
-    bool pipe = bf16 && prefill_pipe_serves(p);
-    // unit 5.8 us (128 x 64); full compute units 1.5 of it, a share of the state half
-    if (!bf16) choose_segments(p, {resident_f32(p.P, p.N), 0.5, 0.5, 1.5, 0.0, 0.85});
-    else if (pipe) {
-        if (prefill_bf16_cuts(p)) {                      // unit 1.3 to 2.4 us; of full compute units 1.5 of it, the launches with the states' trips 5
-            choose_segments(p, {prefill_bf16_resident(p.P, p.N), 0.5, 0.6, 5.0, 0.0, 0.85});
-            pipe = !p.seg_count;
-        }
-        if (!p.seg_count) {
-            // with SiLU (us)  4 heads of 128 x 64, 550 tokens: 37 uncut, 27 cut;  48 pairs of 128 x 32, 550: 35, 28;  of lengths that differ as many
-            // calls lost by it as gained (96 pairs of 64 x 128, 1024 at most: 54, 64)
-            // the launches 8 us, the states' trips at 4.7 TB/s
-            const double unit = prefill_pipe_chunk_us(p.P, p.N, p.conv_act == SSMV_ACT_SILU && !p.seq_len);
-            choose_segments(p, {prefill_pipe_resident(p.P, p.N), 0.3, 0.5, 8.0 / unit, 4.0 * p.P * p.N * sizeof(float) / 4.7e6 / unit, 0.9});
-        }
-    }
-    if (!p.seg_count) return pipe;
-    // y carries states between the launches: not if it overlaps anything that is still to be read
+    const int es = p.io == SSMV_BF16 ? 2 : 4;
     const char *y0 = static_cast<const char *>(p.y), *y1 = y0 + (size_t)p.batch * p.L * p.H * p.P * es;
     auto overlaps = [&](const void *t, size_t bytes) {
         const char *a = static_cast<const char *>(t);
         return a && a < y1 && y0 < a + bytes;
     };
     const size_t tok = (size_t)p.batch * p.L, ch = (size_t)p.H * p.P;
-    if (overlaps(p.x_raw, tok * ch * es) || overlaps(p.z, tok * ch * es) || overlaps(p.dt, tok * p.H * es) ||
-        overlaps(p.Bm, tok * p.G * p.N * es) || overlaps(p.Cm, tok * p.G * p.N * es) || overlaps(p.wgt, ch * SSMV_CONV_WIDTH * es) ||
-        overlaps(p.bias, ch * es) || overlaps(p.A, p.H * sizeof(float)) || overlaps(p.D, p.H * sizeof(float)) ||
-        overlaps(p.dt_bias, p.H * sizeof(float)) || overlaps(p.seq_len, p.batch * sizeof(int32_t))) {
-        p.seg_chunks = p.seg_count = 0;
-        return bf16;                                     // uncut, which the pipelined kernel serves or nothing would have been cut
+    return !(overlaps(p.x_raw, tok * ch * es) || overlaps(p.z, tok * ch * es) || overlaps(p.dt, tok * p.H * es) ||
+             overlaps(p.Bm, tok * p.G * p.N * es) || overlaps(p.Cm, tok * p.G * p.N * es) || overlaps(p.wgt, ch * SSMV_CONV_WIDTH * es) ||
+             overlaps(p.bias, ch * es) || overlaps(p.A, p.H * sizeof(float)) || overlaps(p.D, p.H * sizeof(float)) ||
+             overlaps(p.dt_bias, p.H * sizeof(float)) || overlaps(p.seq_len, p.batch * sizeof(int32_t)));
+}
+
+// Whether and how a bf16 prompt is cut, and by which kernel: the return value says whether by the pipelined one.
+// Uncut and cut (us; one sequence unless said):
+//   128 x 64, 32 heads:  700 tokens 29 -> 26, 1500: 54 -> 34, 3000: 100 -> 41;  4 sequences, 3000: 99 -> 85;  8 heads, 1500: 52 -> 24
+//   64 x 128, 80 heads:  1500 tokens 69 -> 52, 3000: 130 -> 78;   64 x 64, 80 heads, 1500: 48 -> 37
+// Over nine tiles, 4 to 512 pairs and 260 to 4096 tokens of one length: never more than 4 % slower than uncut, 13 % faster on average.  Of
+// prompts of different lengths only the device knows them: one sequence that is far shorter than L pays for the launches (32 heads of
+// 128 x 64, 700 tokens given, one there: 8 -> 11 us).
+static bool plan_bf16(PrefillParams &p)
+{
+    p.seg_chunks = p.seg_count = 0;
+    if (!prefill_pipe_serves(p)) return false;
+    if (!y_is_apart(p)) return true;
+    if (prefill_bf16_cuts(p)) {                          // unit 1.3 to 2.4 us; of full compute units 1.5 of it, the launches with the states' trips 5
+        choose_segments(p, {prefill_bf16_resident(p.P, p.N), 0.5, 0.6, 5.0, 0.0, 0.85});
+        if (p.seg_count) return false;
+    }
+    // with SiLU (us)  4 heads of 128 x 64, 550 tokens: 37 uncut, 27 cut;  48 pairs of 128 x 32, 550: 35, 28;  of lengths that differ as many
+    // calls lost by it as gained (96 pairs of 64 x 128, 1024 at most: 54, 64)
+    // the launches 8 us, the states' trips at 4.7 TB/s
+    const double unit = prefill_pipe_chunk_us(p.P, p.N, p.conv_act == SSMV_ACT_SILU && !p.seq_len);
+    choose_segments(p, {prefill_pipe_resident(p.P, p.N), 0.3, 0.5, 8.0 / unit, 4.0 * p.P * p.N * sizeof(float) / 4.7e6 / unit, 0.9});
+    return true;
+}
+
+// fp32: which kernel, into how many parts a head goes (the pipelined kernel only, prefill_f32_pipe.hip), and whether and how the prompt
+// is cut: what a model of the times says is fastest.  The model's figures are the times of both kernels at 512 tokens, 64 to 1024 pairs.
+// Up to the (sequence, head) pairs at which the other kernel has two workgroups on every compute unit the pipelined one is the faster, with
+// as many parts as the chip has room for; in large launches those of its shapes whose products outweigh the start of each round.
+// us with the other kernel alone -> with this choice, one length, one sequence unless said:
+//   128 x 64, 32 heads:   4 sequences, 512 tokens 78 -> 45, 1021: 126 -> 81;  8, 512: 101 -> 74;  12: 144 -> 114;  16, 32: the same
+//   128 x 128, 32 heads:  4 sequences, 512 tokens 116 -> 70;  12: 222 -> 186;  16: 232 (the other; this one 256)
+//   64 x 128, 80 heads:   8 sequences, 512 tokens 237 -> 185;   64 x 64, 80 heads: 2 sequences, 1024 tokens 107 -> 78
+static bool plan_f32(PrefillParams &p)
+{
+    // per chunk (us): the other kernel with a compute unit to itself, what company adds to it (CutCosts), the pipelined kernel
+    struct Times { double unit, company, pipe; };
+    constexpr Times kTimes[3][3] = {{{3.5, 0.21, 1.6}, {4.0, 0.43, 1.85}, {4.7, 0.32, 2.5}},
+                                    {{3.7, 0.60, 2.0}, {4.4, 0.65, 2.20}, {5.9, 0.50, 3.75}},
+                                    {{4.3, 0.50, 2.7}, {5.7, 0.56, 4.10}, {8.5, 0.64, 0.0}}};
+    auto times = [&](int P, int N) { return kTimes[P == 32 ? 0 : P == 64 ? 1 : 2][N == 32 ? 0 : N == 64 ? 1 : 2]; };
+    constexpr double kStart = 6.5, kStartPipe = 7.5, kTurn = 2.0, kLaunches = 14.0;      // of a launch, of a further round of workgroups, of a cut prompt's two further launches
+    constexpr int kCUs = 256;
+    const int n = (p.L + kPrefillChunk - 1) / kPrefillChunk, r = resident_f32(p.P, p.N);
+    const bool may_cut = y_is_apart(p);
+    // of different lengths: the first sequence's and half of the others' chunks, the longest alone at its end
+    const double mean = p.seq_len ? 0.05 + (1.0 + (p.batch - 1) * 0.5 * (n + 1) / n) / p.batch : 1.0;
+    auto rounds = [&](double first, double all) { return mean * all < first ? first : mean * all; };
+    p.seg_chunks = p.seg_count = 0;
+    const PrefillParams whole = p;
+    const Times k = times(p.P, p.N);
+    const long wgs = (long)p.batch * p.H, rest = wgs % (kCUs * r);
+    auto shared = [&](long w) { return r > 1 ? 1.0 + k.company * ((w + kCUs - 1) / kCUs - 1) / (r - 1) : 1.0; };
+    double best = kStart + n * k.unit * rounds(shared(wgs < kCUs * r ? wgs : kCUs * r), wgs / (kCUs * r) * shared(kCUs * r) + (rest ? shared(rest) : 0.0));
+    bool pipe = false;
+    auto better = [&](const PrefillParams &q, double t, bool piped) {
+        if (t < best) { best = t; p = q; pipe = piped; }
+    };
+    if (may_cut) {
+        PrefillParams q = whole;
+        const double t = choose_segments(q, {r, k.company, 0.5, 1.5, 0.0, 0.85});
+        if (q.seg_count) better(q, kStart + t * k.unit, false);
+    }
+    for (int parts = 1; whole.P / parts >= 32; parts *= 2) {
+        PrefillParams q = whole;
+        q.parts = parts;
+        q.H *= parts;
+        q.P /= parts;
+        if (q.P == 128 && q.N == 128) continue;          // never the fastest: its waves lack registers
+        const double unit = times(q.P, q.N).pipe;
+        double turns = (wgs * parts + kCUs - 1) / kCUs;
+        if (p.seq_len && n > 1 && turns > 1.0) turns = 0.5 * (turns + wgs * parts / (double)kCUs);       // the last round starts as workgroups end
+        // (a clock that is lower by 6 % where no compute unit rests)
+        better(q, kStartPipe + n * (turns > 1.0 ? 1.06 : 1.0) * unit * rounds(1.0, turns) + kTurn * (turns - 1.0), true);
+        if (may_cut) {
+            const double t = choose_segments(q, {1, 0.0, 0.6, kLaunches / unit, 4.0 * q.P * q.N * sizeof(float) / 4.7e6 / unit, 0.9});
+            if (q.seg_count) better(q, kStartPipe + t * unit, true);
+        }
     }
     return pipe;
 }
@@ -579,6 +631,7 @@ static bool cut_prompt(PrefillParams &p)
 static int launch_pass(const PrefillParams &p, bool pipe, hipStream_t stream)
 {
     if (p.io == SSMV_BF16) return pipe ? launch_prefill_pipe(p, stream) : launch_prefill_bf16(p, stream);
+    if (pipe) return launch_prefill_f32_pipe(p, stream);
     switch (p.P) {
         case 32: return launch_p<32>(p, stream);
         case 64: return launch_p<64>(p, stream);
@@ -590,7 +643,9 @@ static int launch_pass(const PrefillParams &p, bool pipe, hipStream_t stream)
 int launch_prefill(const PrefillParams &p_in, hipStream_t stream)
 {
     PrefillParams p = p_in;
-    const bool pipe = cut_prompt(p);
+    p.parts = 1;
+    p.seg_pass = 0;
+    const bool pipe = p.io == SSMV_BF16 ? plan_bf16(p) : plan_f32(p);
     int rc = launch_pass(p, pipe, stream);
     if (rc != 0) return rc;
     if (p.seg_count) {

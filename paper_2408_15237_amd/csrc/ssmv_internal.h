@@ -89,6 +89,7 @@ struct PrefillParams {
     int seg_chunks;          // chunks of a segment (the first one of a prompt takes the rest), 0: not cut
     int seg_count;           // segments of the longest prompt
     int seg_pass;            // 0: first pass, 1: last pass
+    int parts;               // H and P are those of this many parts of a head, which share dt, A, D, B and C (prefill_f32_pipe.hip); else 1
 };
 
 struct CacheInts {
@@ -159,6 +160,7 @@ int launch_conv(const ConvParams &p, hipStream_t stream);
 int launch_prefill(const PrefillParams &p, hipStream_t stream);
 int launch_prefill_bf16(const PrefillParams &p, hipStream_t stream);      // bf16 tensors: the main kernel only, of large launches and some cut prompts
 int prefill_bf16_resident(int P, int N);                                  // its workgroups that fit a compute unit side by side; 0: it cuts no prompts
+int launch_prefill_f32_pipe(const PrefillParams &p, hipStream_t stream);  // fp32 tensors, the main kernel only
 int launch_prefill_pipe(const PrefillParams &p, hipStream_t stream);      // the same of smaller ones, and of the other cut prompts
 bool prefill_pipe_serves(const PrefillParams &p);                         // which of the two, for a prompt that is not cut
 int prefill_pipe_resident(int P, int N);                                  // workgroups of the second that fit a compute unit side by side
