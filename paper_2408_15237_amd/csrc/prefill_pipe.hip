@@ -11,6 +11,12 @@
 // Each stage requests everything it reads from LDS at the top of its step: left in place, a read would queue up behind the stores of the
 // part before it, which the compiler cannot tell apart from it.  Raw inputs come straight into LDS, DIST chunks ahead, and are waited
 // for by count.  Outputs leave a step late, as whole rows of the head.
+// Who shares a SIMD with whom, and who goes first: wave w is on SIMD w % 4, and the stage that a step waits for is a chain of short
+// instructions beside others' long ones.  The weight waves have priority, and the conv waves where they have a SiLU; where the state is split
+// the waves of the second half of n, which have no M X, gate and outputs, come first, so that they share with the conv waves.  us, without
+// any of it -> with all: 5 x 80 heads x 64 x 128, lengths up to 700, SiLU, gate, softplus 52 -> 48 (the order of the halves alone: 48.7);  3 x
+// 80 x 64 x 128, 700 tokens 39 -> 36;  2 x 64 x 128 x 128, 1000: 51 -> 49;  4 x 64 x 128 x 32, 1000, SiLU 49.3 -> 44.9;  128 x 64, 1500 tokens,
+// SiLU 39.1 -> 37.7.  Priority for conv waves without a SiLU loses 3 % (128 x 64), for the consumers it does nothing.
 // Which launches are served: prefill_pipe_serves.  A split state (NSPL = 2): both waves of a tile scale their share of h C^T by exp(cum_t),
 // and the second's goes to the first through LDS a step later.
 #include "prefill_bf16_ops.h"
@@ -107,6 +113,7 @@ void prefill_pipe_kernel(const PrefillParams p)
         // (the last pass of a segmented prompt runs behind the launch that has moved conv_head on already)
         const int conv_head = (p.conv_head[b] - (SEG && p.seg_pass == 1 ? L : 0)) & mask;
         const bool silu = p.conv_act == SSMV_ACT_SILU;
+        if (silu) __builtin_amdgcn_s_setprio(2);         // (in the head of this file)
         uint2 *sCar = reinterpret_cast<uint2 *>(lds + Ld::oCar);
         const uint16_t *x_b = reinterpret_cast<const uint16_t *>(p.x_raw) + (size_t)b * Ls * HP;
         constexpr int LR = P / 8;                        // lanes per row of x, 64 / LR rows per instruction, P / 16 instructions
@@ -206,6 +213,7 @@ void prefill_pipe_kernel(const PrefillParams p)
     int cb = 0, ci = DIST % CB;                          // the same of C, which the consumers read a chunk later
     if (wave_u >= NC) {
         // =================================================== weight waves ===================================================
+        __builtin_amdgcn_s_setprio(2);                   // (in the head of this file)
         const int pw = wave_u - NC, ptid = tid - 64 * NC;
         const float A2_h = p.A[hd] * kLog2e, D_h = p.D[hd];
         float dtb_h = p.dt_bias ? p.dt_bias[hd] : 0.f;
@@ -412,7 +420,7 @@ void prefill_pipe_kernel(const PrefillParams p)
 
     // ===================================================== consumers =====================================================
     const int lperm = swap23(li);
-    const int pt = wave_u % NP, nh = wave_u / NP;        // the wave's 32-channel tile, and its share of n (0 unless the state is split)
+    const int pt = wave_u % NP, nh = NSPL - 1 - wave_u / NP;        // the wave's 32-channel tile, and its share of n (0 unless the state is split)
     const bool gated = p.z != nullptr;
     const int cur = (int)((unsigned)p.cur_slot[b] % 3u);
     float *state = p.state + (size_t)cur * p.slot_stride + ((size_t)b * H + hd) * P * N;
