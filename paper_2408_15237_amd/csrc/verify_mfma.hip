@@ -100,7 +100,6 @@ void verify_mfma_kernel(const int32_t *a_cur, const int32_t *a_pend, const int32
     constexpr int XRS = RW + 8;                          // LDS row stride of a raw x row
     constexpr int CX = RW / 8, CB = N / 8;               // 16-byte pieces of an x row, of a B or C row
     constexpr int W = SSMV_CONV_WIDTH;
-    constexpr int BT0 = 256 - 2 * N > 0 ? 256 - 2 * N : 0;   // first thread that builds the weighted B rows
     constexpr int XIT = (3 + 16 + 64 / CX - 1) / (64 / CX);  // load rounds of wave 0 over the raw x rows
     constexpr int BIT = (16 + 64 / CB - 1) / (64 / CB);      // load rounds of waves 1 and 2 over the B and C rows
     static_assert(W == 4, "the conv below is written for four taps");
@@ -318,6 +317,18 @@ void verify_mfma_kernel(const int32_t *a_cur, const int32_t *a_pend, const int32
     __syncthreads();
     dt_raw = sDtRaw[li];
 
+    // ---- wave 0: G^T = B C^T on the matrix core ----------------------------------------------------------------------------
+    v4f G = {0.f, 0.f, 0.f, 0.f};                        // lane: draft t = li, tokens s = 4 g + r
+    if (w == 0) {
+#pragma unroll
+        for (int h = 0; h < NH; ++h) {
+            u4v bs = *reinterpret_cast<const u4v *>(sBr + li * CS + 8 * g + 32 * h), cs_ = *reinterpret_cast<const u4v *>(sC + li * CS + 8 * g + 32 * h);
+            if ((int)li >= T) bs = u4v{0u, 0u, 0u, 0u};
+            if ((int)li >= kb) cs_ = u4v{0u, 0u, 0u, 0u};
+            G = mfma16(as_bf8(bs), as_bf8(cs_), G);
+        }
+    }
+
     // ---- decay factors and weights: every wave, lane li = token li ---------------------------------------------------------
     float dtv = bf16lo(dt_raw);
     if constexpr (EXTRA) {                               // optional softplus(dt + dt_bias) ahead of the discretisation (Section 2.2)
@@ -333,55 +344,60 @@ void verify_mfma_kernel(const int32_t *a_cur, const int32_t *a_pend, const int32
     const float alphaJ = __builtin_amdgcn_exp2f(cumJ), beta = __builtin_amdgcn_exp2f(cumK - cumJ);
     const float cy = lane_get(cum, min(pq + (int)li, 15));   // draft li is token pq + li
     const float alphaY = __builtin_amdgcn_exp2f(cy);
-    if (w == 0 && first_tile) {
+    if (w == 2 && first_tile) {
         if (g == 0 && (int)li >= pq && (int)li < T) winDt_out[oDt_win + (size_t)out_entry(li - pq) * H] = (uint16_t)dt_raw;   // the raw dt: replay transforms it again
-        if (hd == 0 && tid == 0) p.last_k[b] = t0 + kb;
+        if (hd == 0 && l == 0) p.last_k[b] = t0 + kb;
     }
 
-    // ---- x: conv roll, stash, and the [row][token] operand.  An item is two adjacent channels x two adjacent token slots ----
+    // ---- x: conv roll, stash, and the [row][token] operand.  An item is two adjacent channels x two adjacent token slots.  Of a
+    // launch of at most eight tokens (NT = 1) waves 2 and 3 have items, wave 1 the weighted B rows and wave 0 G and M: as
+    // many short chains side by side as there are waves, where waves 0 and 1 had the items as well.  With the reads of an item ahead
+    // of its first use and G ahead of the decays, rounds of one sequence (us): 16 layers of 80 heads x 64 x 128 88.2 -> 80.8;  24 layers of 32
+    // x 128 x 64 with SiLU, softplus and gate 126 -> 118, without 102 -> 101;  8 sequences, deferred advance, 16 layers 98.8 -> 97.0;  large launches
+    // the same (32 sequences 72.2, 72.1) ----
     {
         constexpr int XI = RW * 4 / 256;                 // items per thread
         const uint32_t *sXr32 = reinterpret_cast<const uint32_t *>(sXr);
         uint32_t *sX32 = reinterpret_cast<uint32_t *>(sX);
 #pragma unroll
         for (int it = 0; it < XI; ++it) {
-            const unsigned idx = tid + 256 * it, cp = idx % (RW / 2), u = idx / (RW / 2);
+            const unsigned idx = tid + 256 * it, cp = idx % (RW / 2), u = NT == 1 ? 7 - idx / (RW / 2) : idx / (RW / 2);
             uint32_t outA = 0, outB = 0;                 // channel 2 cp and channel 2 cp + 1: slots 2 u, 2 u + 1
             if ((int)(2 * u) < T) {
-                float wf[2][4], bias_f[2] = {0.f, 0.f};
-                if constexpr (CONV) {
+                const int ta = 2 * (int)u, ja = ta - pq; // the first of the two tokens, and its number among the drafts
+                uint32_t bits[2] = {sXr32[(3 + ta) * (XRS / 2) + cp], sXr32[(4 + ta) * (XRS / 2) + cp]};
+                if (CONV && ja >= -1) {
+                    // width-4 causal depthwise conv, fp32 accumulate in tap order, rounded to the I/O type; the three inputs
+                    // before a draft: earlier drafts, else the ring's history rows.  All that the two tokens read is requested at once
                     const u4v wv = reinterpret_cast<const u4v *>(sWgt)[cp];
-                    wf[0][0] = bf16lo(wv.x); wf[0][1] = bf16hi(wv.x); wf[0][2] = bf16lo(wv.y); wf[0][3] = bf16hi(wv.y);
-                    wf[1][0] = bf16lo(wv.z); wf[1][1] = bf16hi(wv.z); wf[1][2] = bf16lo(wv.w); wf[1][3] = bf16hi(wv.w);
                     const uint32_t bv = reinterpret_cast<const uint32_t *>(sBias)[cp];
-                    bias_f[0] = bf16lo(bv); bias_f[1] = bf16hi(bv);
+                    uint32_t tap[4];
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) tap[i] = sXr32[(ja + i < 3 ? max(ja + i, 0) : ta + i) * (XRS / 2) + cp];
+                    const float wf[2][4] = {{bf16lo(wv.x), bf16hi(wv.x), bf16lo(wv.y), bf16hi(wv.y)}, {bf16lo(wv.z), bf16hi(wv.z), bf16lo(wv.w), bf16hi(wv.w)}};
+#pragma unroll
+                    for (int e = 0; e < 2; ++e) {
+                        float s0 = bf16lo(bv), s1 = bf16hi(bv);
+#pragma unroll
+                        for (int i = 0; i < 3; ++i) {
+                            s0 = fmaf(wf[0][i], bf16lo(tap[e + i]), s0);
+                            s1 = fmaf(wf[1][i], bf16hi(tap[e + i]), s1);
+                        }
+                        s0 = fmaf(wf[0][3], bf16lo(bits[e]), s0);
+                        s1 = fmaf(wf[1][3], bf16hi(bits[e]), s1);
+                        if (p.conv_act == SSMV_ACT_SILU) {
+                            s0 = s0 / (1.f + expf(-s0));
+                            s1 = s1 / (1.f + expf(-s1));
+                        }
+                        if (ja + e >= 0) bits[e] = pack_bf16x2(s0, s1);
+                    }
                 }
 #pragma unroll
                 for (int e = 0; e < 2; ++e) {
-                    const int tt = 2 * (int)u + e, j = tt - pq;
-                    if (tt < T) {
-                        uint32_t bits = sXr32[(3 + tt) * (XRS / 2) + cp];
-                        if (CONV && j >= 0) {
-                            // width-4 causal depthwise conv, fp32 accumulate in tap order, rounded to the I/O type; the
-                            // three inputs before token j: earlier tokens of this call, else the ring's history rows
-                            float s0 = bias_f[0], s1 = bias_f[1];
-#pragma unroll
-                            for (int i = 0; i < 3; ++i) {
-                                const uint32_t tap = sXr32[(j + i < 3 ? j + i : tt + i) * (XRS / 2) + cp];
-                                s0 = fmaf(wf[0][i], bf16lo(tap), s0);
-                                s1 = fmaf(wf[1][i], bf16hi(tap), s1);
-                            }
-                            s0 = fmaf(wf[0][3], bf16lo(bits), s0);
-                            s1 = fmaf(wf[1][3], bf16hi(bits), s1);
-                            if (p.conv_act == SSMV_ACT_SILU) {
-                                s0 = s0 / (1.f + expf(-s0));
-                                s1 = s1 / (1.f + expf(-s1));
-                            }
-                            bits = pack_bf16x2(s0, s1);
-                        }
-                        if (j >= 0) reinterpret_cast<uint32_t *>(winX_out + oX_win + (size_t)out_entry(j) * HP)[cp] = bits;
-                        outA |= (bits & 0xffffu) << (16 * e);
-                        outB |= (bits >> 16) << (16 * e);
+                    if (ta + e < T) {
+                        if (ja + e >= 0) reinterpret_cast<uint32_t *>(winX_out + oX_win + (size_t)out_entry(ja + e) * HP)[cp] = bits[e];
+                        outA |= (bits[e] & 0xffffu) << (16 * e);
+                        outB |= (bits[e] >> 16) << (16 * e);
                     }
                 }
             }
@@ -394,8 +410,10 @@ void verify_mfma_kernel(const int32_t *a_cur, const int32_t *a_pend, const int32
     // this launch forms a snapshot for this sequence: with a deferred advance, and in a call of a replayed round that is not
     // its last, most launches form none ---------------------------------------------------------------------------------
     const bool forms_state = (!EXTRA || p.store_state) && (adv || p.write_hk);
-    if (forms_state && (int)tid >= BT0) {
-        const unsigned bi = tid - BT0, bn = bi % N;
+    // (unit = eight tokens of one n; of a launch of at most eight tokens the second half of the units are zeros)
+    const unsigned bi = N == 128 ? 255u - tid : tid - 64u;
+    if (forms_state && bi < 2 * N) {
+        const unsigned bn = bi % N;
         // the eight tokens of this thread's unit: the same for the whole wave when a wave covers one n range (N >= 64), and
         // then a weight comes out of its lane with a scalar read instead of a trip through the LDS crossbar
         const unsigned bt0 = N >= 64 ? 8 * __builtin_amdgcn_readfirstlane(bi / N) : 8 * (bi / N);
@@ -419,16 +437,8 @@ void verify_mfma_kernel(const int32_t *a_cur, const int32_t *a_pend, const int32
         }
     }
 
-    // ---- wave 0: G^T = B C^T on the matrix core, M^T from it ---------------------------------------------------------------
+    // ---- wave 0: M^T from G^T -------------------------------------------------------------------------------------------------
     if (w == 0) {
-        v4f G = {0.f, 0.f, 0.f, 0.f};                    // lane: draft t = li, tokens s = 4 g + r
-#pragma unroll
-        for (int h = 0; h < NH; ++h) {
-            u4v bs = *reinterpret_cast<const u4v *>(sBr + li * CS + 8 * g + 32 * h), cs_ = *reinterpret_cast<const u4v *>(sC + li * CS + 8 * g + 32 * h);
-            if ((int)li >= T) bs = u4v{0u, 0u, 0u, 0u};
-            if ((int)li >= kb) cs_ = u4v{0u, 0u, 0u, 0u};
-            G = mfma16(as_bf8(bs), as_bf8(cs_), G);
-        }
         const int tty = pq + (int)li;                    // draft li as a token of the launch
         float m[4];
 #pragma unroll
