@@ -591,7 +591,7 @@ static bool plan_f32(PrefillParams &p)
     struct Times { double unit, company, pipe; };
     constexpr Times kTimes[3][3] = {{{3.5, 0.21, 1.6}, {4.0, 0.43, 1.85}, {4.7, 0.32, 2.5}},
                                     {{3.7, 0.60, 2.0}, {4.4, 0.65, 2.20}, {5.9, 0.50, 3.75}},
-                                    {{4.3, 0.50, 2.7}, {5.7, 0.56, 4.10}, {8.5, 0.64, 0.0}}};
+                                    {{4.3, 0.50, 2.95}, {5.7, 0.56, 4.3}, {8.5, 0.64, 0.0}}};
     auto times = [&](int P, int N) { return kTimes[P == 32 ? 0 : P == 64 ? 1 : 2][N == 32 ? 0 : N == 64 ? 1 : 2]; };
     constexpr double kStart = 6.5, kStartPipe = 7.5, kTurn = 2.0, kLaunches = 14.0;      // of a launch, of a further round of workgroups, of a cut prompt's two further launches
     constexpr int kCUs = 256;
