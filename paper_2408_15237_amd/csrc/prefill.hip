@@ -451,7 +451,9 @@ static int launch_p(const PrefillParams &p, hipStream_t stream)
     switch (p.N) {
         case 32: return p.seg_count ? launch_pn<P, 32, true>(p, stream) : launch_pn<P, 32, false>(p, stream);
         case 64: return p.seg_count ? launch_pn<P, 64, true>(p, stream) : launch_pn<P, 64, false>(p, stream);
-        case 128: return p.seg_count ? launch_pn<P, 128, true>(p, stream) : launch_pn<P, 128, false>(p, stream);
+        case 128:
+            if constexpr (P > 32) if (p.seg_count) return launch_pn<P, 128, true>(p, stream);      // (plan_f32)
+            return launch_pn<P, 128, false>(p, stream);
         default: return (int)hipErrorInvalidConfiguration;
     }
 }
@@ -578,57 +580,81 @@ static bool plan_bf16(PrefillParams &p)
 }
 
 // fp32: which kernel, into how many parts a head goes (the pipelined kernel only, prefill_f32_pipe.hip), and whether and how the prompt
-// is cut: what a model of the times says is fastest.  The model's figures are the times of both kernels at 512 tokens, 64 to 1024 pairs.
+// is cut: what a model of the times says is fastest.  The model's figures are the times of both kernels at 512 tokens, 64 to 1024 pairs; those
+// of several rounds of the pipelined one, and of a cut's launches, are the ones whose choices over 2148 measured calls took the least time (nine
+// tiles, 20 to 2048 pairs, 24 to 3000 tokens, with and without SiLU, gate and softplus).  Time of the choice over the other kernel's, whole or cut, mean
+// and slowest: 900 calls of 20 to 1300 pairs, one length 0.83, 1.04, lengths that spread 0.78, 1.08, lengths given and all the same 0.86, 1.27;
+// 1248 calls of 512 to 2048 pairs 0.93, 1.05;  0.91, 1.06;  0.93, 1.21.
 // Up to the (sequence, head) pairs at which the other kernel has two workgroups on every compute unit the pipelined one is the faster, with
 // as many parts as the chip has room for; in large launches those of its shapes whose products outweigh the start of each round.
 // us with the other kernel alone -> with this choice, one length, one sequence unless said:
-//   128 x 64, 32 heads:   4 sequences, 512 tokens 78 -> 45, 1021: 126 -> 81;  8, 512: 101 -> 74;  12: 144 -> 114;  16, 32: the same
+//   128 x 64, 32 heads:   4 sequences, 512 tokens 78 -> 45, 1021: 126 -> 81;  8, 512: 101 -> 74;  12: 144 -> 114
+//                         16, 700: 226 -> 219, with SiLU, gate and softplus 264 -> 231;  32, 2000: 1126 -> 1072, 1347 -> 1167
 //   128 x 128, 32 heads:  4 sequences, 512 tokens 116 -> 70;  12: 222 -> 186;  16: 232 (the other; this one 256)
 //   64 x 128, 80 heads:   8 sequences, 512 tokens 237 -> 185;   64 x 64, 80 heads: 2 sequences, 1024 tokens 107 -> 78
+// A conv SiLU, a gate and a softplus are not in it: they cost the other kernel more than the pipelined one, which has other waves for the
+// first and the last.
+// Lengths that are given are the device's to know: they may spread from 1 up or all be the longest, and what is fast for the one can be slow
+// for the other (22 x 7 x 64 x 32, 2324 tokens, all that long: two parts 306 us, the other kernel 182).  The fastest for lengths that spread is
+// taken of what loses at most kLoss times as much (and kSlack) where all are equal as it gains there.  Without that condition the choice lost up
+// to 69 % on equal lengths (with it 16 x 32 x 128 x 128, 300 tokens, still 178 -> 201 us, for 153 -> 134 spread); at kLoss = 1 it gives up too
+// much on lengths that spread (24 x 30 x 32 x 32, 2364 tokens at most, SiLU: 313 us, 208 at 2).
 static bool plan_f32(PrefillParams &p)
 {
-    // per chunk (us): the other kernel with a compute unit to itself, what company adds to it (CutCosts), the pipelined kernel
-    struct Times { double unit, company, pipe; };
-    constexpr Times kTimes[3][3] = {{{3.5, 0.21, 1.6}, {4.0, 0.43, 1.85}, {4.7, 0.32, 2.5}},
-                                    {{3.7, 0.60, 2.0}, {4.4, 0.65, 2.20}, {5.9, 0.50, 3.75}},
-                                    {{4.3, 0.50, 2.95}, {5.7, 0.56, 4.3}, {8.5, 0.64, 0.0}}};
+    // per chunk (us): the other kernel with a compute unit to itself, what company adds to it (CutCosts), the pipelined kernel in a launch of
+    // one round of workgroups, and in each of several
+    struct Times { double unit, company, pipe, pipe_rounds; };
+    constexpr Times kTimes[3][3] = {{{3.5, 0.21, 1.6, 1.78}, {4.0, 0.43, 1.85, 1.90}, {4.7, 0.32, 2.35, 2.25}},
+                                    {{3.7, 0.60, 2.0, 2.23}, {4.4, 0.65, 2.20, 2.01}, {5.9, 0.50, 3.75, 3.98}},
+                                    {{4.3, 0.50, 2.95, 2.50}, {5.7, 0.56, 3.7, 3.76}, {8.5, 0.64, 0.0, 0.0}}};
     auto times = [&](int P, int N) { return kTimes[P == 32 ? 0 : P == 64 ? 1 : 2][N == 32 ? 0 : N == 64 ? 1 : 2]; };
-    constexpr double kStart = 6.5, kStartPipe = 7.5, kTurn = 2.0, kLaunches = 14.0;      // of a launch, of a further round of workgroups, of a cut prompt's two further launches
+    constexpr double kStart = 6.5, kStartPipe = 7.5, kTurn = 2.0, kLaunches = 8.0;      // of a launch, of a further round of workgroups, of a cut prompt's two further launches
+    // of lengths that spread: several rounds of the pipelined kernel (the last workgroups have the chip to themselves), a prompt that the other
+    // kernel cuts (the long sequences' segments share compute units while others rest)
+    constexpr double kSpread = 1.2, kCutSpread = 1.15;
+    constexpr double kLoss = 2.0, kSlack = 2.5;          // (us: the model is not better than that)
     constexpr int kCUs = 256;
     const int n = (p.L + kPrefillChunk - 1) / kPrefillChunk, r = resident_f32(p.P, p.N);
     const bool may_cut = y_is_apart(p);
-    // of different lengths: the first sequence's and half of the others' chunks, the longest alone at its end
-    const double mean = p.seq_len ? 0.05 + (1.0 + (p.batch - 1) * 0.5 * (n + 1) / n) / p.batch : 1.0;
-    auto rounds = [&](double first, double all) { return mean * all < first ? first : mean * all; };
+    // of lengths that spread: the first sequence's and half of the others' chunks, the longest alone at its end
+    const double half = 0.05 + (1.0 + (p.batch - 1) * 0.5 * (n + 1) / n) / p.batch;
+    auto rounds = [&](double mean, double first, double all) { return mean * all < first ? first : mean * all; };
     p.seg_chunks = p.seg_count = 0;
     const PrefillParams whole = p;
     const Times k = times(p.P, p.N);
     const long wgs = (long)p.batch * p.H, rest = wgs % (kCUs * r);
     auto shared = [&](long w) { return r > 1 ? 1.0 + k.company * ((w + kCUs - 1) / kCUs - 1) / (r - 1) : 1.0; };
-    double best = kStart + n * k.unit * rounds(shared(wgs < kCUs * r ? wgs : kCUs * r), wgs / (kCUs * r) * shared(kCUs * r) + (rest ? shared(rest) : 0.0));
-    bool pipe = false;
-    auto better = [&](const PrefillParams &q, double t, bool piped) {
-        if (t < best) { best = t; p = q; pipe = piped; }
-    };
-    if (may_cut) {
-        PrefillParams q = whole;
-        const double t = choose_segments(q, {r, k.company, 0.5, 1.5, 0.0, 0.85});
-        if (q.seg_count) better(q, kStart + t * k.unit, false);
+    struct Cost { double same, spread; };                // of one length, of lengths that spread
+    // the other kernel, whole or cut
+    const double first = shared(wgs < kCUs * r ? wgs : kCUs * r), all = wgs / (kCUs * r) * shared(kCUs * r) + (rest ? shared(rest) : 0.0);
+    Cost other = {kStart + n * k.unit * rounds(1.0, first, all), kStart + n * k.unit * rounds(half, first, 0.5 * (all + wgs / (double)(kCUs * r) * shared(kCUs * r)))};
+    if (may_cut && !(p.P == 32 && p.N == 128)) {         // (of 32 x 128 the pipelined kernel's is always the faster)
+        const double t = kStart + k.unit * choose_segments(p, {r, k.company < 0.5 ? k.company : 0.5, 0.5, 1.5, 0.0, 0.85});
+        if (p.seg_count) other = {t, kCutSpread * t};
     }
+    bool pipe = false;
+    double best = p.seq_len ? other.spread : other.same;
+    auto better = [&](const PrefillParams &q, Cost t) {
+        const double at = p.seq_len ? t.spread : t.same;
+        const bool safe = !p.seq_len || t.same - other.same - kSlack <= kLoss * (other.spread - t.spread);
+        if (at < best && safe) { best = at; p = q; pipe = true; }
+    };
     for (int parts = 1; whole.P / parts >= 32; parts *= 2) {
         PrefillParams q = whole;
         q.parts = parts;
         q.H *= parts;
         q.P /= parts;
         if (q.P == 128 && q.N == 128) continue;          // never the fastest: its waves lack registers
-        const double unit = times(q.P, q.N).pipe;
-        double turns = (wgs * parts + kCUs - 1) / kCUs;
-        if (p.seq_len && n > 1 && turns > 1.0) turns = 0.5 * (turns + wgs * parts / (double)kCUs);       // the last round starts as workgroups end
-        // (a clock that is lower by 6 % where no compute unit rests)
-        better(q, kStartPipe + n * (turns > 1.0 ? 1.06 : 1.0) * unit * rounds(1.0, turns) + kTurn * (turns - 1.0), true);
+        const double unit = times(q.P, q.N).pipe, turns = (wgs * parts + kCUs - 1) / kCUs;
+        auto time = [&](double mean, double turns) {
+            return kStartPipe + n * (turns > 1.0 ? times(q.P, q.N).pipe_rounds : unit) * rounds(mean, 1.0, turns) + kTurn * (turns - 1.0);
+        };
+        // of lengths that spread a workgroup starts as another ends
+        const double spread = turns > 1.0 ? kSpread * time(half, n > 1 ? wgs * parts / (double)kCUs : turns) : time(half, turns);
+        better(q, {time(1.0, turns), spread});
         if (may_cut) {
-            const double t = choose_segments(q, {1, 0.0, 0.6, kLaunches / unit, 4.0 * q.P * q.N * sizeof(float) / 4.7e6 / unit, 0.9});
-            if (q.seg_count) better(q, kStartPipe + t * unit, true);
+            const double t = kStartPipe + unit * choose_segments(q, {1, 0.0, 0.6, kLaunches / unit, 4.0 * q.P * q.N * sizeof(float) / 4.7e6 / unit, 0.9});
+            if (q.seg_count) better(q, {t, t});
         }
     }
     return pipe;
