@@ -228,17 +228,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void p
         }
     };
 
-    // Of two workgroups on a compute unit the one that stages goes first: its four waves wait for each other, the other's products take the
-    // same time either way.  32 x 512 tokens of 32 x 128 x 64 293 -> 288 us, with SiLU 323 -> 317;  24 x 512 of 32 x 32 x 32 76.5 -> 74; not at
-    // 128 x 32: 206, 211
-    constexpr bool kStagingFirst = !(P == 128 && N == 32);
     Fetch fetch;
     prefetch(c_beg, fetch);
     for (int c = c_beg; c < c_end; ++c) {
         const int t0 = c * Q;
-        if (kStagingFirst) __builtin_amdgcn_s_setprio(1);
         consume(c, fetch);
-        if (kStagingFirst) __builtin_amdgcn_s_setprio(0);
         __syncthreads();
         if (c + 1 < c_end) prefetch(c + 1, fetch);
         __builtin_amdgcn_sched_barrier(0);              // the loads stay here, a whole chunk of arithmetic ahead of their use
