@@ -188,7 +188,6 @@ __global__ __launch_bounds__((64 * F32Pipe<P, N>::NW)) void prefill_f32_pipe_ker
     }
     if (wave >= NC) {
         // =================================================== weight waves ===================================================
-        __builtin_amdgcn_s_setprio(2);                   // their products are a chain behind the consumers' (2 to 4 % at N = 128)
         const int pw = wave - NC, qi = pw >= 1, qj = pw == 2;       // rows t in [16 qi, +16), columns s in [16 qj, +16)
         const int l16 = lane & 15, k4 = lane >> 4;
         const int GN = p.G * N, g = hr / (heads / p.G);
