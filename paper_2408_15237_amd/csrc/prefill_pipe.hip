@@ -12,11 +12,22 @@
 // part before it, which the compiler cannot tell apart from it.  Raw inputs come straight into LDS, DIST chunks ahead, and are waited
 // for by count.  Outputs leave a step late, as whole rows of the head.
 // Who shares a SIMD with whom, and who goes first: wave w is on SIMD w % 4, and the stage that a step waits for is a chain of short
-// instructions beside others' long ones.  The weight waves have priority, and the conv waves where they have a SiLU; where the state is split
-// the waves of the second half of n, which have no M X, gate and outputs, come first, so that they share with the conv waves.  us, without
-// any of it -> with all: 5 x 80 heads x 64 x 128, lengths up to 700, SiLU, gate, softplus 52 -> 48 (the order of the halves alone: 48.7);  3 x
-// 80 x 64 x 128, 700 tokens 39 -> 36;  2 x 64 x 128 x 128, 1000: 51 -> 49;  4 x 64 x 128 x 32, 1000, SiLU 49.3 -> 44.9;  128 x 64, 1500 tokens,
-// SiLU 39.1 -> 37.7.  Priority for conv waves without a SiLU loses 3 % (128 x 64), for the consumers it does nothing.
+// instructions beside others' long ones.  Where the state is split the waves of the second half of n, which have no M X, gate and outputs, come
+// first, so that they share with the conv waves (0.98 of the time at 32 x 128 and 64 x 128).  The weight waves have priority where that pays, the conv waves
+// where they have a SiLU and it does.  Time over that without either, with the halves in the old order; means of 24 calls each, 16 to 210 pairs,
+// 300 to 1985 tokens, one length and spread:
+//             no SiLU, no gate     gate                 SiLU                             SiLU and gate
+//             none  weights        none  weights        none  weights  conv  both        none  weights  conv  both
+//    32 x 64  1.00  1.01           1.00  1.04           1.00  1.00     1.03  1.00        1.00  1.01     1.03  1.02
+//    32 x 128 0.97  0.96           0.96  1.00           0.98  0.98     1.03  0.98        0.96  1.00     1.00  1.00
+//    64 x 64  1.00  0.99           1.00  1.02           1.00  1.01     1.00  1.00        1.00  1.00     1.00  1.00
+//    64 x 128 0.99  0.96           0.99  1.05           0.98  0.99     1.02  0.95        0.95  0.98     0.98  0.97
+//   128 x 64  1.00  0.98           1.00  1.01           1.00  1.00     0.96  0.94        1.00  1.00     0.99  0.97
+//   128 x 128 1.00  0.99           1.00  1.01           1.00  1.00     0.97  1.01        1.00  0.98     0.97  1.00
+//   128 x 32  1.00  0.97           1.00  0.99           1.00  1.00     1.01  0.97        1.00  1.00     1.02  0.97
+//    64 x 32  1.00  1.00           1.00  1.00           1.00  1.00     0.97  0.97        1.00  1.00     0.97  0.97
+//    32 x 32  nothing does anything
+// The worst of weights first with a gate was 1.12 (32 x 64, 6 x 35 pairs, 1985 tokens: 80 -> 89 us).
 // Which launches are served: prefill_pipe_serves.  A split state (NSPL = 2): both waves of a tile scale their share of h C^T by exp(cum_t),
 // and the second's goes to the first through LDS a step later.
 #include "prefill_bf16_ops.h"
@@ -113,7 +124,7 @@ void prefill_pipe_kernel(const PrefillParams p)
         // (the last pass of a segmented prompt runs behind the launch that has moved conv_head on already)
         const int conv_head = (p.conv_head[b] - (SEG && p.seg_pass == 1 ? L : 0)) & mask;
         const bool silu = p.conv_act == SSMV_ACT_SILU;
-        if (silu) __builtin_amdgcn_s_setprio(2);         // (in the head of this file)
+        if (silu && !(P == 32 && N >= 64) && !(P == 64 && N == 128 && p.z)) __builtin_amdgcn_s_setprio(2);      // (in the head of this file)
         uint2 *sCar = reinterpret_cast<uint2 *>(lds + Ld::oCar);
         const uint16_t *x_b = reinterpret_cast<const uint16_t *>(p.x_raw) + (size_t)b * Ls * HP;
         constexpr int LR = P / 8;                        // lanes per row of x, 64 / LR rows per instruction, P / 16 instructions
@@ -213,7 +224,8 @@ void prefill_pipe_kernel(const PrefillParams p)
     int cb = 0, ci = DIST % CB;                          // the same of C, which the consumers read a chunk later
     if (wave_u >= NC) {
         // =================================================== weight waves ===================================================
-        __builtin_amdgcn_s_setprio(2);                   // (in the head of this file)
+        // (in the head of this file; of the wide tiles 32 x 128, 64 x 128 and 128 x 64)
+        if (N == 32 || ((P == 128) != (N == 128) && (!p.z || (P == 128 && p.conv_act == SSMV_ACT_SILU)))) __builtin_amdgcn_s_setprio(2);
         const int pw = wave_u - NC, ptid = tid - 64 * NC;
         const float A2_h = p.A[hd] * kLog2e, D_h = p.D[hd];
         float dtb_h = p.dt_bias ? p.dt_bias[hd] : 0.f;
