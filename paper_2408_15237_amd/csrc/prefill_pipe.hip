@@ -124,7 +124,6 @@ void prefill_pipe_kernel(const PrefillParams p)
         // (the last pass of a segmented prompt runs behind the launch that has moved conv_head on already)
         const int conv_head = (p.conv_head[b] - (SEG && p.seg_pass == 1 ? L : 0)) & mask;
         const bool silu = p.conv_act == SSMV_ACT_SILU;
-        if (silu && !(P == 32 && N >= 64) && !(P == 64 && N == 128 && p.z)) __builtin_amdgcn_s_setprio(2);      // (in the head of this file)
         uint2 *sCar = reinterpret_cast<uint2 *>(lds + Ld::oCar);
         const uint16_t *x_b = reinterpret_cast<const uint16_t *>(p.x_raw) + (size_t)b * Ls * HP;
         constexpr int LR = P / 8;                        // lanes per row of x, 64 / LR rows per instruction, P / 16 instructions
@@ -173,6 +172,8 @@ void prefill_pipe_kernel(const PrefillParams p)
         };
         wait_next(c_beg + 1 < c_end);
         __syncthreads();
+        // (in the head of this file.  Not ahead of the first loads: a branch there waits for conv_head)
+        if (silu && !(P == 32 && N >= 64) && !(P == 64 && (N == 64 || (N == 128 && p.z)))) __builtin_amdgcn_s_setprio(2);
         for (int c = c_beg; c < c_end; ++c) {
             const bool more = c + DIST < c_end;
             if (more) issue(c + DIST, xi);
@@ -224,8 +225,6 @@ void prefill_pipe_kernel(const PrefillParams p)
     int cb = 0, ci = DIST % CB;                          // the same of C, which the consumers read a chunk later
     if (wave_u >= NC) {
         // =================================================== weight waves ===================================================
-        // (in the head of this file; of the wide tiles 32 x 128, 64 x 128 and 128 x 64)
-        if (N == 32 || ((P == 128) != (N == 128) && (!p.z || (P == 128 && p.conv_act == SSMV_ACT_SILU)))) __builtin_amdgcn_s_setprio(2);
         const int pw = wave_u - NC, ptid = tid - 64 * NC;
         const float A2_h = p.A[hd] * kLog2e, D_h = p.D[hd];
         float dtb_h = p.dt_bias ? p.dt_bias[hd] : 0.f;
@@ -410,6 +409,8 @@ void prefill_pipe_kernel(const PrefillParams p)
         asm volatile("" : "+v"(dtb_h));
         wait_next(c_beg + 1 < c_end);
         __syncthreads();
+        // (in the head of this file; of the wide tiles 32 x 128, 64 x 128 and 128 x 64)
+        if (N == 32 || ((P == 128) != (N == 128) && (!p.z || (P == 128 && p.conv_act == SSMV_ACT_SILU)))) __builtin_amdgcn_s_setprio(2);
         decays(c_beg);                                   // (read by this wave only, but for the consumers' share, a barrier later)
         for (int c = c_beg; c < c_end; ++c) {
             const bool more = c + DIST < c_end;
