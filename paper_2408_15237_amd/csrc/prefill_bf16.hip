@@ -381,12 +381,17 @@ void prefill_bf16_kernel(const PrefillParams p)
     };
     const int prow = pt * 32 + li;                      // this lane's channel (inside the head) as an operand row
     float *sZ = reinterpret_cast<float *>(lds + Ld::oZ) + pt * 1024;
-    // Which of two workgroups on a compute unit goes first where one stages and the other multiplies: 1, the staging (all of a 128 x 64
-    // head's waves wait for it); 2, the products (narrow heads: a wave or two stage much for few); 0, whoever is ready.  us without, staging first,
-    // products first:  32 x 32 heads x 128 x 64, 2048 tokens 294, 287, 294, 700 with SiLU, gate, softplus 184, 167, 179;  16 x 48 x 32 x 128, 1000: 102,
-    // 101, 98;  32 x 64 x 32 x 64, 500: 92.0, 88.6, 88.5, with SiLU 110, 108, 107;  32 x 32, SiLU 53, 51, 50;  12 x 80 x 64 x 64, SiLU 60.7, 58.8, 57.9.
-    // Left at 0:  16 x 80 x 64 x 128, 500: 113, 124, 122;  32 x 32 x 128 x 32, 1000: 147, 149, 152;  32 x 48 x 64 x 32, SiLU 171, 189, 173
-    constexpr int kFirst = P == 128 && N == 64 ? 1 : P == 32 || (P == 64 && N == 64) ? 2 : 0;
+    // Of the workgroups on a compute unit the one that stages goes first on two kinds of heads, all of whose waves wait for the staging.  Time over
+    // that without, means of 96 to 1500 tokens with and without SiLU and gate:
+    //   128 x 64   with a gate 0.94 to 1.01 at any number of workgroups.  Without one, where the last round fills more than a workgroup a compute
+    //              unit, 0.97 at 258 and 512 workgroups, 0.98 at 896, 0.99 at 1024, 1536 and 2048; where it does not it loses, 1.01 at 520, 600, 1088 and 1280,
+    //              1.03 at 700 and 768; of lengths that differ from about 640 workgroups on, 1.02 at 520, 0.98 at 900.
+    //              32 x 32 heads, 2048 tokens 294 -> 287 us, 700 with SiLU, gate, softplus 184 -> 167
+    //   32 channels, one length   1100 to 2240 workgroups 0.97 to 0.98 (N = 32), 0.96 to 0.99 (64), 0.99 (128), and never more than 1.01; of lengths that
+    //              differ up to 1.03.  (The products first: the same, but up to 1.03 at N = 128)
+    // Not on the others: staging or products first, means of 24 calls each, 280 to 2048 workgroups, 0.98 to 1.01, single calls up to 1.08.
+    const unsigned wgs = gridDim.x;
+    const bool staging_first = P == 32 ? !p.seq_len : P == 128 && N == 64 && (p.z || (p.seq_len ? wgs >= 640 : (wgs - 1) % 512 >= 256));
     uint32_t dt_bits;
     issue_x_loads(c_beg, dt_bits);
     issue_bc_loads(c_beg);
@@ -395,9 +400,9 @@ void prefill_bf16_kernel(const PrefillParams p)
     for (int c = c_beg; c < c_end; ++c) {
         const int t0 = c * Q;
         const char *sB = lds + Ld::oB + (c & (Ld::BCC - 1)) * Ld::BCS, *sC = lds + Ld::oC + (c & (Ld::BCC - 1)) * Ld::BCS;
-        if (kFirst) __builtin_amdgcn_s_setprio(kFirst == 1);
+        if (staging_first) __builtin_amdgcn_s_setprio(1);
         consume(c, dt_bits);
-        if (kFirst) __builtin_amdgcn_s_setprio(kFirst == 2);
+        if (staging_first) __builtin_amdgcn_s_setprio(0);
         __syncthreads();
         // the stores ahead of the loads on the wide tiles (2 % there; the other way round on the narrow ones)
         constexpr bool kStoresFirst = P >= 128 && N >= 64;
