@@ -409,8 +409,10 @@ void prefill_pipe_kernel(const PrefillParams p)
         asm volatile("" : "+v"(dtb_h));
         wait_next(c_beg + 1 < c_end);
         __syncthreads();
-        // (in the head of this file; of the wide tiles 32 x 128, 64 x 128 and 128 x 64)
-        if (N == 32 || ((P == 128) != (N == 128) && (!p.z || (P == 128 && p.conv_act == SSMV_ACT_SILU)))) __builtin_amdgcn_s_setprio(2);
+        // (in the head of this file)
+        const bool gated = p.z != nullptr, silu = p.conv_act == SSMV_ACT_SILU;
+        const bool first = N == 32 || (N == 128 ? !gated && (P < 128 || !silu) : P == 128 && (!gated || silu));
+        if (first) __builtin_amdgcn_s_setprio(2);
         decays(c_beg);                                   // (read by this wave only, but for the consumers' share, a barrier later)
         for (int c = c_beg; c < c_end; ++c) {
             const bool more = c + DIST < c_end;
