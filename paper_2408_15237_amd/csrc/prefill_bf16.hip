@@ -386,12 +386,12 @@ void prefill_bf16_kernel(const PrefillParams p)
     //   128 x 64   with a gate 0.94 to 1.01 at any number of workgroups.  Without one, where the last round fills more than a workgroup a compute
     //              unit, 0.97 at 258 and 512 workgroups, 0.98 at 896, 0.99 at 1024, 1536 and 2048; where it does not it loses, 1.01 at 520, 600, 1088 and 1280,
     //              1.03 at 700 and 768; of lengths that differ from about 640 workgroups on, 1.02 at 520, 0.98 at 900.
-    //              32 x 32 heads, 2048 tokens 294 -> 287 us, 700 with SiLU, gate, softplus 184 -> 167
+    //              Three chunks 0.99, with SiLU 1.01.  32 x 32 heads, 2048 tokens 294 -> 287 us, 700 with SiLU, gate, softplus 184 -> 167
     //   32 channels, one length   1100 to 2240 workgroups 0.97 to 0.98 (N = 32), 0.96 to 0.99 (64), 0.99 (128), and never more than 1.01; of lengths that
     //              differ up to 1.03.  (The products first: the same, but up to 1.03 at N = 128)
     // Not on the others: staging or products first, means of 24 calls each, 280 to 2048 workgroups, 0.98 to 1.01, single calls up to 1.08.
     const unsigned wgs = gridDim.x;
-    const bool staging_first = P == 32 ? !p.seq_len : P == 128 && N == 64 && (p.z || (p.seq_len ? wgs >= 640 : (wgs - 1) % 512 >= 256));
+    const bool staging_first = P == 32 ? !p.seq_len : P == 128 && N == 64 && p.L > 4 * Q && (p.z || (p.seq_len ? wgs >= 640 : (wgs - 1) % 512 >= 256));
     uint32_t dt_bits;
     issue_x_loads(c_beg, dt_bits);
     issue_bc_loads(c_beg);
