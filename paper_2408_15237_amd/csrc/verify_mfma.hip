@@ -385,7 +385,7 @@ void verify_mfma_kernel(const int32_t *a_cur, const int32_t *a_pend, const int32
                         }
                         s0 = fmaf(wf[0][3], bf16lo(bits[e]), s0);
                         s1 = fmaf(wf[1][3], bf16hi(bits[e]), s1);
-                        if (p.conv_act == SSMV_ACT_SILU && ja + e >= 0 && ta + e < T) {     // (of a draft call one of the two is a draft)
+                        if (p.conv_act == SSMV_ACT_SILU && (kb != 1 || e == (pq & 1))) {     // (of one draft the other token is none)
                             s0 = s0 / (1.f + expf(-s0));
                             s1 = s1 / (1.f + expf(-s1));
                         }
