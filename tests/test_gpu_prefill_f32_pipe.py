@@ -49,8 +49,7 @@ def test_against_the_oracle(P, N, parts, batch, block):
             y, lens_dev = z.clone() if block else torch.full_like(x, 7.0), lens.cuda() if block else None
             run = lambda: ssmv.ssm_prefill_block(dims, cache.c, x_raw=x, conv_wgt=w, conv_bias=bias, dt=dt, dt_bias=dtb if block else None, dt_softplus=block, Bm=B, Cm=C,
                                                  z=y if block else None, A=A, D=D, L=L, y_out=y, seq_len=lens_dev)
-            if L > 64 and not block:
-                assert launches(run)[0] == (H * batch * parts, _threads(P // parts, N))
+            assert launches(run)[0] == (H * batch * parts, _threads(P // parts, N)), "L = %d" % L
             run()
             h = torch.empty_like(h0)
             ssmv.ssmv_materialize_block(dims, cache.c, A, dtb if block else None, block, h)
@@ -66,9 +65,9 @@ def test_against_the_oracle(P, N, parts, batch, block):
         ssmv.ssmv_check(cache.c)
 
 
-@pytest.mark.parametrize("P,N,H,L", [(128, 64, 8, 1500), (64, 64, 20, 1500), (128, 128, 4, 700), (32, 64, 16, 1500)])
-def test_cut_prompts_of_parts(P, N, H, L):
-    """Few pairs and a long prompt: whatever the plan makes of it, with the parts' states between the passes, agrees with the same
+@pytest.mark.parametrize("P,N,H,L,parts,segments", [(128, 64, 8, 1500, 2, 16), (64, 64, 20, 1500, 1, 12), (128, 128, 4, 700, 4, 5), (32, 64, 16, 1500, 1, 16)])
+def test_cut_prompts_of_parts(P, N, H, L, parts, segments):
+    """Few pairs and a long prompt: cut into segments by this kernel, with the parts' states between the passes, it agrees with the same
     prompt fed in two calls, and the outputs do not depend on what was in y."""
     g = torch.Generator(device="cuda").manual_seed(P + N)
     rnd = lambda *s: torch.randn(*s, generator=g, device="cuda")
@@ -82,7 +81,12 @@ def test_cut_prompts_of_parts(P, N, H, L):
         ys = []
         for a, b in zip(cuts, cuts[1:]):
             y = torch.full((1, b - a, H * P), fill, device="cuda")
-            ssmv.ssm_prefill_chunked(dims, cache.c, x[:, a:b].contiguous(), w, None, dt[:, a:b].contiguous(), B[:, a:b].contiguous(), C[:, a:b].contiguous(), A, D, b - a, y)
+            tok = [t[:, a:b].contiguous() for t in (x, dt, B, C)]
+            run = lambda: ssmv.ssm_prefill_chunked(dims, cache.c, tok[0], w, None, tok[1], tok[2], tok[3], A, D, b - a, y)
+            if b - a == L:                                             # the segments but the last, the last one's states put together, all of them again
+                launched = launches(run)
+                assert len(launched) == 3 and launched[0] == (H * parts * (segments - 1), _threads(P // parts, N))
+            run()
             ys.append(y)
         h = torch.empty_like(h0)
         ssmv.ssmv_materialize_block(dims, cache.c, A, None, False, h)
