@@ -242,7 +242,7 @@ def bench_prefill(args):
         dtype = "bf16 products (fp32 operand of the state update split into head and tail), f32 accumulation"
     else:
         roof = {"bound": "mfma", "achieved": round(tflops, 2), "peak": PEAK_MFMA_F32_TFLOPS, "unit": "TFLOP/s",
-                "frac": round(tflops / PEAK_MFMA_F32_TFLOPS, 4), "traffic": None, "kernel": "prefill_kernel (fp32 MFMA)",
+                "frac": round(tflops / PEAK_MFMA_F32_TFLOPS, 4), "traffic": None, "kernel": "prefill_f32_pipe_kernel, or prefill_kernel where that is the faster (fp32 MFMA)",
                 "avg_launch_us": round(ms * 1e3, 1), "algorithmic_flops_per_launch": int(flops), "algorithmic_bytes_per_launch": int(nbytes)}
         dtype = "f32"
     cpu = None

@@ -250,6 +250,9 @@ int ssm_block_multistep(const ssmv_dims *dims, const ssmv_cache *cache, const ss
  * within about 1e-4 (relative) of the exact scan.  The fp32 operands of the products that end in outputs
  * only enter as their bf16 head (2^-9 per term, the size of the outputs' own bf16 rounding): an output is
  * within about 1e-2 of the largest output of its tensor.
+ * Which kernel runs, and how heads and prompts are divided among workgroups, follows from dims, L and which
+ * arguments are given, and with it the order of the sums: the same prompt can differ in its last bits between
+ * calls of another batch or another number of heads.  The same call gives the same bits.
  * dt is the positive step (after softplus, if that is requested); an input that is not finite
  * anywhere in a chunk of 32 tokens can spread over that chunk's outputs.
  *   x_raw, y_out [batch][L][H*P]; dt [batch][L][H]; Bm, Cm [batch][L][G][N]: io_dtype, device;

@@ -1,5 +1,6 @@
-// Chunked prefill for fp32 tensors, as in prefill.hip (same evaluation, same arithmetic, same operand layouts), with the work of a chunk on
-// different waves of the workgroup, side by side, one barrier per chunk:
+// Chunked prefill for fp32 tensors: the evaluation and the operand layouts of prefill.hip, with the work of a chunk on different waves of the
+// workgroup, side by side, one barrier per chunk.  (The sums are taken in another order, and a token's weight in the state comes from a
+// sum of its own instead of the difference of two prefix sums: the last bits of the results are not those of the other kernel.)
 //   consumer waves  own the state (accumulator registers, as there): C h^T, M X, the update, the gate and the outputs, of the chunk that
 //                   the others prepared in the step before;
 //   weight waves    one 16x16 quadrant of M each: B and C come from memory as operands of their product (a lane has the same 16 bytes of
@@ -8,11 +9,13 @@
 //   a decay wave    dt's prefix sums and the decays, a further step ahead;
 //   conv waves      raw x -> X.
 // Two copies of everything that is staged, in the order in which 16-byte reads of it are operands: slot lk of a product's kk-th instruction
-// over the tokens is token 16 lk + kk.  In the other kernel the four waves stage a chunk and then multiply: 5.8 us a chunk alone on a compute
-// unit (128 x 64), 2.2 of them products.  Here 4.1, or 2.2 as two parts on two compute units (1.1 of them products, 0.2 those of G beside
-// them; the rest is the barrier and the LDS round trip behind it, 0.5, and the stages' claims on issue and LDS).
-// 4 x 1021 tokens of 32 heads x 128 x 64, with the ring and the state: 126 -> 81 us.  Where the consumers split n (NSPL > 1) each takes a share of the tokens of M X too, and
-// finishes a share of the tile's channels: the others' sums for these come through LDS, a step later.
+// over the tokens is token 16 lk + kk.  In the other kernel the four waves stage a chunk and then multiply: 5.7 us a chunk alone on a compute
+// unit (128 x 64).  Here 3.7, or 2.2 as two parts on two compute units (the figures that the plan in prefill.hip counts with).  Of a part's chunk
+// the products take 2560 clock cycles of each SIMD and those of G 384 on average, 58 % of the launch below by the counters; the rest is the
+// barrier, the LDS round trips behind it and the two steps that fill the stages.  4 x 1021 tokens of 32 heads x 128 x 64, with the ring and
+// the state: 128 -> 82 us.
+// Where the consumers split n (NSPL > 1) each takes a share of the tokens of M X too, and finishes a share of the tile's channels: the
+// others' sums for these come through LDS, a step later.
 //
 // A head of P channels may be taken as p.parts heads of P / p.parts channels that share dt, A, D, B and C: p.H and p.P are those of the parts.
 #include "prefill_split.h"
@@ -155,7 +158,7 @@ __global__ __launch_bounds__((64 * F32Pipe<P, N>::NW)) void prefill_f32_pipe_ker
             float v = d * A_h;
             // the decay from a token to the chunk's end as a sum of its own: as the difference of two prefix sums it has their rounding,
             // which under a strong decay is large beside what the last tokens add up to (state against 64 bits, 4 x 1021 tokens of 32 heads x
-            // 128 x 64: 1.8e-7 -> 1.2e-7 of the norm)
+            // 128 x 64: 1.1e-7 of the norm; 2.1e-7 to 2.4e-7 in the other kernel, the outputs 5.2e-8 in both)
             float after = __shfl_down(v, 1, 32);
             if (li == Q - 1) after = 0.f;
 #pragma unroll

@@ -350,11 +350,12 @@ void verify_mfma_kernel(const int32_t *a_cur, const int32_t *a_pend, const int32
     }
 
     // ---- x: conv roll, stash, and the [row][token] operand.  An item is two adjacent channels x two adjacent token slots.  Of a
-    // launch of at most eight tokens (NT = 1) waves 2 and 3 have items, wave 1 the weighted B rows and wave 0 G and M: as
-    // many short chains side by side as there are waves, where waves 0 and 1 had the items as well.  With the reads of an item ahead
-    // of its first use and G ahead of the decays, rounds of one sequence (us): 16 layers of 80 heads x 64 x 128 88.2 -> 80.8;  24 layers of 32
-    // x 128 x 64 with SiLU, softplus and gate 126 -> 118, without 102 -> 101;  8 sequences, deferred advance, 16 layers 98.8 -> 97.0;  large launches
-    // the same (32 sequences 72.2, 72.1) ----
+    // launch of at most eight tokens (NT = 1) half of the items and of the weighted B rows hold tokens, wave 0 forms G and M, and the chains go
+    // round so that no wave has more of them than it must: the items with tokens are those of waves 2 and 3 (RW = 64) or one of each wave's
+    // two (RW = 128); the B rows with tokens are wave 1's (N = 32 and 64; there wave 2 writes the zero half) or those of waves 2 and 3
+    // (N = 128; waves 0 and 1 write the zero half).  With that, the reads of an item ahead of its first use and G ahead of the
+    // decays, rounds of one sequence (us): 16 layers of 80 heads x 64 x 128 88.2 -> 80.8;  24 layers of 32 x 128 x 64 with SiLU, softplus and gate
+    // 126 -> 118, without 102 -> 101;  8 sequences, deferred advance, 16 layers 98.8 -> 97.0;  large launches the same (32 sequences 72.2, 72.1) ----
     {
         constexpr int XI = RW * 4 / 256;                 // items per thread
         const uint32_t *sXr32 = reinterpret_cast<const uint32_t *>(sXr);
