@@ -591,8 +591,8 @@ static bool plan_bf16(PrefillParams &p)
 // Lengths that are given are the device's to know: they may spread from 1 up or all be the longest, and what is fast for the one can be slow
 // for the other (22 x 7 x 64 x 32, 2324 tokens, all that long: two parts 306 us, the other kernel 182).  The fastest for lengths that spread is
 // taken of what loses at most kLoss times as much (and kSlack) where all are equal as it gains there.  Without that condition the choice lost up
-// to 69 % on equal lengths (with it 16 x 32 x 128 x 128, 300 tokens, still 178 -> 201 us, for 153 -> 134 spread); at kLoss = 1 it gives up too
-// much on lengths that spread (24 x 30 x 32 x 32, 2364 tokens at most, SiLU: 313 us, 208 at 2).
+// to 69 % on equal lengths; with it up to 27 % (10 x 57 x 32 x 32, 340 tokens, 70 -> 90 us;  16 x 32 x 128 x 128, 2000 tokens, 882 -> 1013, for 715 -> 568
+// where they spread); at kLoss = 1 it gives up too much on lengths that spread (24 x 30 x 32 x 32, 2364 tokens at most, SiLU: 313 us, 208 at 2).
 static bool plan_f32(PrefillParams &p)
 {
     // per chunk (us): the other kernel with a compute unit to itself, what company adds to it (CutCosts), the pipelined kernel in a launch of
